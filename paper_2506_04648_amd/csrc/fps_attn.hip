@@ -49,20 +49,7 @@ struct AttnArgs {
     int out_raster;        // output in raster order (real tokens only) instead of tile order
     int chunk;             // work items per XCD
     int total;             // BH * M * KB
-    uint32_t partial_cls;  // bit c set iff a tile of boundary class c has padding slots
 };
-
-// Second kernel parameter, used by the one-block-per-tile kernels only.  They never name it: they
-// read it through the kernel-argument segment pointer (constant address space), so a wave-uniform
-// index gives scalar loads and the table is never copied to private memory.
-struct MaskTables {
-    // lane_mask[c][4b + r]: bit of lane (n, g) set iff the key that lane holds in accumulator slot
-    // (block b, element r), slot 16b + 4g + r of a one-block tile, is a real token (class c)
-    uint64_t lane_mask[8][32];
-    // 128-slot blocks (32x32 accumulators): see arg_pair_code
-    uint32_t pair_code[8][4];
-};
-constexpr size_t kTablesOffset = (sizeof(AttnArgs) + 7) & ~size_t(7);   // kernarg offset of MaskTables
 
 // Every lambda of the kernels captures the accumulators by reference; left to the inliner's cost
 // model a large one stays a call, which forces everything it captures into private memory.
@@ -124,52 +111,68 @@ __device__ __forceinline__ bool work_item(const AttnArgs& a, int KB, int* bh, in
     return true;
 }
 
-// Tables inside the kernel-argument block, read through the constant address space with a
-// wave-uniform index so that they come in by scalar loads (indexing the by-value argument struct
-// directly can make the compiler spill it to private memory).
-__device__ __forceinline__ uint64_t arg_lane_mask(int cls, int i) {
-    typedef const __attribute__((address_space(4))) uint64_t* ptr_t;
-    const __attribute__((address_space(4))) char* base =
-        (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
-    return ((ptr_t)(base + kTablesOffset + offsetof(MaskTables, lane_mask)))[cls * 32 + i];
-}
-// x where the lane's bit of the wave-uniform mask is set, otherwise y: one v_cndmask with the mask
-// taken straight from scalar registers (no per-lane bit extraction).
-__device__ __forceinline__ float select_lanes(uint64_t lane_mask, float x, float y) {
-    float out;
-    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(out) : "v"(y), "v"(x), "s"(lane_mask));
-    return out;
-}
-
 template <typename G_>
 __device__ __forceinline__ int tile_class(const G_& g, int t, int h, int w) {
     return ((t == g.nT - 1) << 2) | ((h == g.nH - 1) << 1) | (w == g.nW - 1);
 }
 
-// Epilogue shared by both precisions: O = acc * inv_l (times the per-channel V scale if any),
-// padded rows zero, fp32 or bf16, tile or raster order.  A lane holds 4 channels of one row per
-// accumulator, so direct stores would be 8- or 16-byte pieces of many rows; instead each wave
-// transposes its 16-row blocks through a private 16 KB LDS region and writes whole rows
-// (256 or 512 contiguous bytes).  The caller guarantees that no wave still reads the LDS buffers.
-template <int BS>
-__device__ __forceinline__ void store_rows(const AttnArgs& a, int bh, int u, int jq, int KBS, int ucls, int wave,
-                                           int lane, const v4f (&acc)[2][8], const float (&inv)[2],
+// Where the rows of a query block go.  A block holds packed slots of one sub-tile: its first
+// `rows` slots (at most BS) are real tokens, the rest padding.
+struct QueryBlock {
+    RealBox box;
+    int rows;                // real rows of the block (<= 0: padding only)
+    int k0;                  // packed slot of its first row within the sub-tile
+    int slot_base;           // first tiled slot of the sub-tile within its tile
+    size_t tile_lin;         // bh * M + u
+    size_t raster0;          // raster token index of the sub-tile's first token
+    __device__ __forceinline__ void init(const Geom& G, int bh, int u, int cls, int ut, int uh, int uw, int jq,
+                                         int KBS, int BS) {
+        const int sub = KBS == 1 ? jq : jq / KBS;
+        box = real_box(G, cls, sub);
+        k0 = (jq - sub * KBS) * BS;
+        rows = box.n - k0;
+        slot_base = sub * G.QSP;
+        tile_lin = (size_t)bh * G.M + u;
+        raster0 = (((size_t)bh * G.T + (ut * G.Tt + box.o.t0)) * G.H + (uh * G.Th + box.o.h0)) * G.W +
+                  (uw * G.Tw + box.o.w0);
+    }
+    // output row of the block's row r (0 <= r < rows)
+    __device__ __forceinline__ size_t out_row(const AttnArgs& a, int r) const {
+        const Offset d = real_token(box, k0 + r);
+        if (a.out_raster) return raster0 + ((size_t)d.t * a.g.H + d.h) * a.g.W + d.w;
+        return tile_lin * a.g.TSP + slot_base + ((d.t * a.g.Qh + d.h) * a.g.Qw + d.w);
+    }
+};
+
+// A tile-ordered output has rows for padding slots, and they are zero: workgroup jq of a tile clears
+// those among the tile's slots jq*BS .. jq*BS + BS - 1.  NTHR: threads of the workgroup.
+template <int BS, int NTHR>
+__device__ __forceinline__ void zero_padding_rows(const AttnArgs& a, const QueryBlock& qb, int cls) {
+    if (a.out_raster || qb.box.n == a.g.QSP) return;
+    const int row_shift = a.out_f32 ? 5 : 4;                // log2 of the 16-byte chunks of a row
+    uint4* dst = reinterpret_cast<uint4*>(a.out) +
+                 ((qb.tile_lin * a.g.TSP + qb.slot_base + qb.k0) << row_shift);
+    for (int i = threadIdx.x; i < (BS << row_shift); i += NTHR)
+        if (!sub_slot_is_token(a.g, cls, qb.box.o, qb.k0 + (i >> row_shift))) dst[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Epilogue shared by both precisions: O = acc * inv_l (times the per-channel V scale if any), fp32 or
+// bf16, tile or raster order.  A lane holds 4 channels of one row per accumulator, so direct stores
+// would be 8- or 16-byte pieces of many rows; instead each wave transposes its 16-row blocks through
+// a private LDS region and writes whole rows (256 or 512 contiguous bytes).  The caller guarantees
+// that no wave still reads the LDS buffers.  row0: the wave's first row within the query block.
+__device__ __forceinline__ void store_rows(const AttnArgs& a, const QueryBlock& qb, int row0, int lane,
+                                           const v4f (&acc)[2][8], const float (&inv)[2],
                                            uint8_t* wave_lds, const float* ch_scale = nullptr) {
-    const auto& G = a.g;
     const int g = lane >> 4, n = lane & 15;
     const int row_bytes = a.out_f32 ? 512 : 256;
     const int pitch = row_bytes + 16;                      // padding keeps the column writes off one bank
-    const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
-    // the block lies in ONE sub-tile: decode that once, the rows then cost two divisions each
-    const int sub = jq / KBS;
-    const SubTile so = sub_tile_origin(G, sub);
-    const int slot0 = (jq - sub * KBS) * BS;               // the block's first slot within the sub-tile
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qi = 0; qi < 2; ++qi) {
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) {
             const int col = 16 * cb + 4 * g;
-            v4f o = acc[qb][cb] * inv[qb];
+            v4f o = acc[qi][cb] * inv[qi];
             if (ch_scale) o *= *reinterpret_cast<const v4f*>(ch_scale + col);
             if (a.out_f32) {
                 *reinterpret_cast<v4f*>(wave_lds + n * pitch + col * 4) = o;
@@ -187,36 +190,33 @@ __device__ __forceinline__ void store_rows(const AttnArgs& a, int bh, int u, int
         const int rows_per_pass = 64 >> lanes_shift;
         for (int r0 = 0; r0 < 16; r0 += rows_per_pass) {
             const int r = r0 + (lane >> lanes_shift), chunk = lane & ((1 << lanes_shift) - 1);
-            const int in_block = wave * 32 + qb * 16 + r;       // BS: block size
-            int rt = 0, rh = 0, rw = 0;
-            const bool valid = sub_slot_coords(G, so, slot0 + in_block, &rt, &rh, &rw) &&
-                               coords_in_class(G, ucls, rt, rh, rw);
-            uint4 val = *reinterpret_cast<const uint4*>(wave_lds + r * pitch + chunk * 16);
-            size_t row;
-            if (a.out_raster) {
-                if (!valid) continue;
-                row = (((size_t)bh * G.T + (ut * G.Tt + rt)) * G.H + (uh * G.Th + rh)) * G.W + (uw * G.Tw + rw);
-            } else {
-                row = ((size_t)bh * G.M + u) * G.TSP + (size_t)jq * BS + in_block;
-                if (!valid) val = make_uint4(0, 0, 0, 0);
-            }
-            reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(a.out) + row * row_bytes)[chunk] = val;
+            const int row = row0 + qi * 16 + r;
+            const uint4 val = *reinterpret_cast<const uint4*>(wave_lds + r * pitch + chunk * 16);
+            if (row < qb.rows)
+                reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(a.out) + qb.out_row(a, row) * row_bytes)[chunk] = val;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_wave_barrier();                   // the region is reused by the next block
     }
 }
 
-// Walks the key-tile box of Eq. 2 in (t, h, w) order, block by block inside each tile.  Blocks of
-// a last-along-T tile beyond kb_last hold padding only and are skipped.
-struct TileWalk {
-    int t0, h0, w0, h1, w1;
+// One key block: BS packed slots of one sub-tile of a key tile, the first n of them real tokens.
+// Indices count from the head's first tile.
+struct KeyBlock { int blk, group, n; };
+
+// Walks the key-tile box of Eq. 2, block by block inside each tile (32-slot blocks); sub-tiles without a
+// real token do not exist for it.
+template <int BS, bool MB>
+struct KeyWalk {
+    int t0, t1, h0, h1, w0, w1;
     int vt, vh, vw;
-    int jk, kb_cur;                         // block within the tile, blocks to visit in this tile
-    int js, jb, kbs;                        // jk = js * kbs + jb: sub-tile (scale group) and block in it
-    int kb_full, kb_last, last_t;
-    int n;                                  // number of key BLOCKS in the box
-    __device__ __forceinline__ void init(const AttnArgs& a, int KB, int KB_LAST, int KBS, int ut, int uh, int uw) {
+    int s, jb, left;                        // sub-tile, block in it, real tokens of it from this block on
+    SubTile o;                              // the sub-tile's in-tile origin
+    int n;                                  // number of key blocks in the box
+    __device__ __forceinline__ int cls(const Geom& G) const {
+        return ((vt == G.nT - 1) << 2) | ((vh == G.nH - 1) << 1) | (vw == G.nW - 1);
+    }
+    __device__ __forceinline__ void init(const AttnArgs& a, int ut, int uh, int uw) {
         const Geom& G = a.g;
         if (a.edge_shift) {                 // clamp the centre into [r, n-1-r]; an axis not longer than
             // the window has no such centre and is kept whole by the truncation below with u = n/2
@@ -225,47 +225,60 @@ struct TileWalk {
             uw = G.nW > 2 * a.rw + 1 ? min(max(uw, a.rw), G.nW - 1 - a.rw) : G.nW / 2;
         }
         t0 = max(0, ut - a.rt); h0 = max(0, uh - a.rh); w0 = max(0, uw - a.rw);
-        const int t1 = min(G.nT - 1, ut + a.rt);
-        h1 = min(G.nH - 1, uh + a.rh); w1 = min(G.nW - 1, uw + a.rw);
-        kb_full = KB; kb_last = KB_LAST; last_t = G.nT - 1;
-        const int has_last = t1 == last_t;
-        n = (h1 - h0 + 1) * (w1 - w0 + 1) * ((t1 - t0 + 1 - has_last) * KB + has_last * KB_LAST);
-        vt = t0; vh = h0; vw = w0; jk = 0; js = 0; jb = 0; kbs = KBS;
-        kb_cur = vt == last_t ? kb_last : kb_full;
+        t1 = min(G.nT - 1, ut + a.rt); h1 = min(G.nH - 1, uh + a.rh); w1 = min(G.nW - 1, uw + a.rw);
+        n = (t1 - t0 + 1) * (h1 - h0 + 1) * (w1 - w0 + 1);
+        if (MB) {                           // sub-tiles with a real token times their blocks
+            n = (min((t1 + 1) * G.nsT, G.gT) - t0 * G.nsT) * (min((h1 + 1) * G.nsH, G.gH) - h0 * G.nsH) *
+                (min((w1 + 1) * G.nsW, G.gW) - w0 * G.nsW) * G.KBS;
+        }
+        vt = t0; vh = h0; vw = w0;
+        enter_tile(G);
     }
-    __device__ __forceinline__ void next() {
-        if (++jb == kbs) { jb = 0; ++js; }
-        if (++jk < kb_cur) return;
-        jk = 0; js = 0; jb = 0;
-        if (++vw > w1) {
-            vw = w0;
-            if (++vh > h1) { vh = h0; ++vt; kb_cur = vt == last_t ? kb_last : kb_full; }
+    __device__ __forceinline__ void enter_tile(const Geom& G) {
+        s = 0; jb = 0;
+        o = SubTile{0, 0, 0};
+        left = real_tokens(G, cls(G), o);
+    }
+    __device__ __forceinline__ void next(const Geom& G) {
+        if (MB) {
+            left -= BS;
+            if (++jb < G.KBS) return;
+            if (G.NS > 1) {                 // the tile's next sub-tile with a real token
+                while (++s < G.NS) {
+                    o.w0 += G.Qw;
+                    if (o.w0 == G.Tw) {
+                        o.w0 = 0;
+                        o.h0 += G.Qh;
+                        if (o.h0 == G.Th) { o.h0 = 0; o.t0 += G.Qt; }
+                    }
+                    left = real_tokens(G, cls(G), o);
+                    if (left > 0) { jb = 0; return; }
+                }
+            }
+        }
+        if (++vt > t1) {
+            vt = t0;
+            if (++vh > h1) { vh = h0; ++vw; }
+        }
+        enter_tile(G);
+    }
+    __device__ __forceinline__ KeyBlock block(const Geom& G) const {
+        const int tile = (vt * G.nH + vh) * G.nW + vw;
+        KeyBlock b;
+        b.group = MB ? tile * G.NS + s : tile;
+        b.blk = MB ? b.group * G.KBS + jb : tile;
+        b.n = max(0, min(BS, left));
+        return b;
+    }
+    // visited[v] = 1 for every tile of the box (threads of one workgroup)
+    __device__ __forceinline__ void mark(const Geom& G, uint8_t* visited, int nthr) const {
+        const int eh = h1 - h0 + 1, ew = w1 - w0 + 1, total = (t1 - t0 + 1) * eh * ew;
+        for (int i = threadIdx.x; i < total; i += nthr) {
+            const int t = i / (eh * ew), rem = i - t * (eh * ew), h = rem / ew, w = rem - h * ew;
+            visited[((t0 + t) * G.nH + (h0 + h)) * G.nW + (w0 + w)] = 1;
         }
     }
 };
-
-// A query block that holds padding only: its rows of a tile-ordered output are zero, a raster
-// output has no such rows.  BS: block size, NTHR: threads of the workgroup.
-template <int BS, int NTHR>
-__device__ __forceinline__ void zero_block_rows(const AttnArgs& a, int bh, int u, int jq) {
-    if (a.out_raster) return;
-    const int row_bytes = a.out_f32 ? 512 : 256;
-    uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(a.out) +
-                                          (((size_t)bh * a.g.M + u) * a.g.TSP + (size_t)jq * BS) * row_bytes);
-    for (int i = threadIdx.x; i < BS * (row_bytes / 16); i += NTHR) dst[i] = make_uint4(0, 0, 0, 0);
-}
-
-// Validity of the BS slots of block jb of sub-tile js of a tile of class cls as wave-wide ballots:
-// bit i of word h says whether slot 64h + i of the block is a real token.  Evaluated
-// arithmetically, so that tiles of any size need no table.
-template <int BS>
-__device__ __forceinline__ void block_ballots(const Geom& G, int cls, int js, int jb, int lane,
-                                              uint64_t (&bm)[(BS + 63) / 64]) {
-    const SubTile so = sub_tile_origin(G, js);
-#pragma unroll
-    for (int h = 0; h < (BS + 63) / 64; ++h)
-        bm[h] = __ballot(sub_slot_is_token(G, cls, so, jb * BS + 64 * h + lane));
-}
 
 __device__ __forceinline__ v8i make_v8i(const uint4& lo, const uint4& hi) {
     return v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
@@ -325,7 +338,7 @@ __device__ __forceinline__ void dma_chunk_of(int c, const uint8_t* gsrc_wave, ui
 enum { kAnyKeyBlocks = 0, kOneKeyBlock = 1, kManyKeyBlocks = 2 };
 template <int BS, bool VCH, bool MB, int NK>
 __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_fp8_kernel(AttnArgs a, MaskTables) {
+void attn_fp8_kernel(AttnArgs a) {
     constexpr int NB = BS / 16;
     constexpr int NTHR = BS * 2;
     constexpr int CPT = (BS * 8) / NTHR;                   // 16-byte chunks per thread per operand tile
@@ -334,17 +347,17 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[4][TILE_BYTES];   // K even, K odd, V even, V odd
     const Geom& G = a.g;
     const int KB = MB ? G.KB : 1;                          // blocks per tile; 1 is a compile-time fact
-    const int KB_LAST = MB ? G.kb_last : 1;                // ... of a last-along-T tile, without padding-only blocks
     const int KBS = MB ? G.KBS : 1;                        // blocks per quantisation sub-tile (scale group)
     const int NS = MB ? G.NS : 1;                          // sub-tiles per tile
     int bh, u, jq;
     if (!work_item(a, KB, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
     const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
-    if (MB && jq >= (ut == G.nT - 1 ? KB_LAST : KB)) {      // a query block of padding only
-        zero_block_rows<BS, BS * 2>(a, bh, u, jq);
-        return;
-    }
+    const int ucls = tile_class(G, ut, uh, uw);
+    QueryBlock qblk;
+    qblk.init(G, bh, u, ucls, ut, uh, uw, jq, KBS, BS);
+    zero_padding_rows<BS, NTHR>(a, qblk, ucls);
+    if (qblk.rows <= 0) return;                            // a query block of padding only
     const size_t tile0 = (size_t)bh * G.M;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0][0]);   // LDS byte address of buffer 0
 
@@ -372,11 +385,10 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
     }
     const float sqc = load_uniform(a.sq, (tile0 + u) * NS + jq / KBS) * kLog2eOverSqrtD;
 
-    TileWalk w0, w2;                                       // tile i, and the tile whose K is fetched (i+2)
-    w0.init(a, KB, KB_LAST, KBS, ut, uh, uw);
-    w2 = w0;
-    const int ntiles = w0.n;
-    auto tile_of = [&](const TileWalk& w) FPS_INLINE { return (w.vt * G.nH + w.vh) * G.nW + w.vw; };
+    KeyWalk<BS, MB> walk;                                  // the block whose K is fetched (i+2)
+    walk.init(a, ut, uh, uw);
+    const int ntiles = walk.n;
+    if (a.visited && bh == 0 && jq == 0) walk.mark(G, a.visited + (size_t)u * G.M, NTHR);
 
     // chunk c (of CPT) of this thread's share of one operand tile, HBM -> lds[buf]
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);   // the wave index, in a scalar register
@@ -387,8 +399,12 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
 #pragma unroll
         for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
     };
-    auto k_blk = [&](const TileWalk& w) FPS_INLINE { return a.k + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
-    auto v_blk = [&](const TileWalk& w) FPS_INLINE { return a.v + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
+    const uint8_t* const k_head = a.k + tile0 * KB * TILE_BYTES;
+    const uint8_t* const v_head = a.v + tile0 * KB * TILE_BYTES;
+    const float* const sk_head = a.sk + tile0 * NS;
+    const float* const sv_head = a.sv + tile0 * NS;
+    auto k_blk = [&](const KeyBlock& b) FPS_INLINE { return k_head + (size_t)b.blk * TILE_BYTES; };
+    auto v_blk = [&](const KeyBlock& b) FPS_INLINE { return v_head + (size_t)b.blk * TILE_BYTES; };
 
     v4f s[2][NB];
     v8i pb[2];                                             // P^T as packed E4M3, 4 keys per dword
@@ -440,32 +456,15 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
             asm volatile("" : "+v"(acc[qb][cb]));
         }
     };
-    auto mask_scores = [&](int cls, int js, int jb) FPS_INLINE {      // padded keys of a boundary tile: -inf
-        cls = __builtin_amdgcn_readfirstlane(cls);         // wave-uniform by construction
-        if (!((a.partial_cls >> cls) & 1u)) return;
-        if (!MB) {
+    auto mask_scores = [&](int n_real) FPS_INLINE {        // padded keys of a block: -inf
+        if (n_real == BS) return;
+        const uint32_t real = (1u << n_real) - 1u;
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+        for (int b = 0; b < NB; ++b) {
+            const uint32_t bits = ((real >> (16 * b)) & 0xFFFFu) >> (4 * g);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const uint64_t lm = arg_lane_mask(cls, 4 * b + r);   // uniform: one scalar load
-                    s[0][b][r] = select_lanes(lm, s[0][b][r], -INFINITY);
-                    s[1][b][r] = select_lanes(lm, s[1][b][r], -INFINITY);
-                }
-        } else {                                           // block jk of a larger tile
-            uint64_t bm[(BS + 63) / 64];
-            block_ballots<BS>(G, cls, js, jb, lane, bm);
-            bool all = true;
-#pragma unroll
-            for (int h = 0; h < (BS + 63) / 64; ++h) all = all && (bm[h] | (BS >= 64 ? 0ull : ~0xFFFFFFFFull)) == ~0ull;
-            if (all) return;                               // most blocks of a boundary tile are whole
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const uint32_t bits = ((uint32_t)(bm[(16 * b) >> 6] >> ((16 * b) & 63)) & 0xFFFFu) >> (4 * g);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (!((bits >> r) & 1u)) { s[0][b][r] = -INFINITY; s[1][b][r] = -INFINITY; }
-            }
+            for (int r = 0; r < 4; ++r)
+                if (!((bits >> r) & 1u)) { s[0][b][r] = -INFINITY; s[1][b][r] = -INFINITY; }
         }
     };
     auto rescale_acc = [&]() FPS_INLINE {                             // VCH only
@@ -479,17 +478,22 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
     };
 
     // prologue: K(0), K(1) staged; S(0) computed
-    stage(0, k_blk(w2));
-    w2.next();
-    if (ntiles > 1) { stage(1, k_blk(w2)); w2.next(); }
+    KeyBlock cur = walk.block(G), nxt = cur;               // blocks i and i+1
+    stage(0, k_blk(cur));
+    if (ntiles > 1) {
+        walk.next(G);
+        nxt = walk.block(G);
+        stage(1, k_blk(nxt));
+        if (ntiles > 2) walk.next(G);
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < NB; ++b) qk_mfma(load_k(lds[0], b), b);
-    mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
+    mask_scores(cur.n);
 
-    float sc_next = sqc * load_uniform(a.sk, (tile0 + tile_of(w0)) * NS + w0.js);   // scales of the coming block
-    float sv_next = VCH ? 1.f : load_uniform(a.sv, (tile0 + tile_of(w0)) * NS + w0.js);
+    float sc_next = sqc * load_uniform(sk_head, cur.group);   // scales of the coming block
+    float sv_next = VCH ? 1.f : load_uniform(sv_head, cur.group);
     // One iteration.  FIRST: there is no previous tile whose PV is owed.  LAST: there is no next
     // tile whose scores can be started.  Both are compile-time so that the MFMA / VALU interleave
     // of the steady state carries no branches.
@@ -499,10 +503,8 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
         const int par = it & 1;
         const uint8_t* knxt = lds[par ^ 1];                // K(i+1)
         const uint8_t* vprev = lds[2 + (par ^ 1)];         // V(i-1)
-        const int v = tile_of(w0);
         const float sc = sc_next;
         const float svv = sv_next;
-        if (a.visited && bh == 0 && tid == 0 && jq == 0 && w0.jk == 0) a.visited[(size_t)u * G.M + v] = 1;
         __syncthreads();                 // every wave is past QK(i) and PV(i-2); staged tiles are visible
         // the first V operand is requested at once: its LDS latency passes under the scalar work
         // (tile walk, addresses, scale loads) that follows
@@ -512,14 +514,17 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
         // V's between the MFMAs of phase 1 and K's in phase 2, rather than in one burst (the load
         // unit takes them slowly)
         const bool fetch_k = it + 2 < ntiles;
-        const uint8_t* ksrc = fetch_k ? k_blk(w2) : nullptr;
-        const uint8_t* vsrc = v_blk(w0);
-        if (fetch_k) w2.next();
-        w0.next();
+        const uint8_t* ksrc = nullptr;
+        const uint8_t* vsrc = v_blk(cur);
+        KeyBlock ahead = nxt;
+        if (fetch_k) {
+            ahead = walk.block(G);
+            ksrc = k_blk(ahead);
+            if (it + 3 < ntiles) walk.next(G);
+        }
         if (!LAST) {                     // scales of tile i+1, needed next iteration
-            const size_t gn = (tile0 + tile_of(w0)) * NS + w0.js;
-            sc_next = sqc * load_uniform(a.sk, gn);
-            if (!VCH) sv_next = load_uniform(a.sv, gn);
+            sc_next = sqc * load_uniform(sk_head, nxt.group);
+            if (!VCH) sv_next = load_uniform(sv_head, nxt.group);
         }
 
         // ---- phase 1: row maxima of S(i)  |  delayed PV(i-1) --------------------------------
@@ -615,7 +620,9 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
             else     l_run[qb] = __builtin_fmaf(rs[qb], w_cur[qb], l_run[qb]);
             w_prev[qb] = svv * w_cur[qb];
         }
-        if (!LAST) mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
+        if (!LAST) mask_scores(nxt.n);
+        cur = nxt;
+        nxt = ahead;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's share of the staged tiles landed
     };
     using T_ = std::true_type;
@@ -654,8 +661,8 @@ void attn_fp8_kernel(AttnArgs a, MaskTables) {
         inv[qb] = l > 0.f ? 1.0f / l : 0.f;               // l already carries the factor 448
     }
     __syncthreads();                                       // all waves are done with the staged tiles
-    store_rows<BS>(a, bh, u, jq, KBS, tile_class(G, ut, uh, uw), wave, lane, acc, inv,
-                   &lds[0][0] + wave * kStoreRegionBytes, VCH ? a.sv + (size_t)bh * 128 : nullptr);
+    store_rows(a, qblk, wave * 32, lane, acc, inv, &lds[0][0] + wave * kStoreRegionBytes,
+               VCH ? a.sv + (size_t)bh * 128 : nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -691,35 +698,23 @@ __device__ __forceinline__ float keep_if_bit(float x, uint32_t bits, int idx) {
     const uint32_t m = (uint32_t)(-(int)((bits >> idx) & 1u));
     return __uint_as_float((__float_as_uint(x) & m) | (0xFF800000u & ~m));
 }
-// pair_code[c][kb], bits 2r + h: set iff the key that lane half h holds in register r of score block
-// kb, slot 32kb + 8(r/4) + 4h + r%4 of a one-block tile of class c, is a real token
-__device__ __forceinline__ uint32_t arg_pair_code(int cls, int kb) {
-    typedef const __attribute__((address_space(4))) uint32_t* ptr_t;
-    const __attribute__((address_space(4))) char* base =
-        (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
-    return ((ptr_t)(base + kTablesOffset + offsetof(MaskTables, pair_code)))[cls * 4 + kb];
-}
-// the wave-wide lane mask of register r: all of a lane half, or none of it
-__device__ __forceinline__ uint64_t pair_lane_mask(uint32_t code, int r) {
-    const uint32_t c2 = code >> (2 * r);
-    return (uint64_t)(uint32_t)(-(int)(c2 & 1u)) | ((uint64_t)(uint32_t)(-(int)((c2 >> 1) & 1u)) << 32);
+// A key block whose last 32-key sub-block is cut: keys of s from n on (n: real keys of the sub-block)
+// become -inf.
+__device__ __forceinline__ void mask_padding(v16f& s, int n, int h) {
+    const uint32_t bits = ((1u << n) - 1u) >> (4 * h);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = keep_if_bit(s[r], bits, 8 * (r >> 2) + (r & 3));
 }
 
-// Epilogue of the wide kernel: as store_rows, for accumulators of the 32x32 shape.  The wave's 32
+// Epilogue of the wide kernels: as store_rows, for accumulators of the 32x32 shape.  The wave's 32
 // rows go through its LDS region in two passes of 16 rows (rows n < 16 are held by lanes 0..15 and
 // 32..47).
-__device__ __forceinline__ void store_rows_wide(const AttnArgs& a, int bh, int u, int jq, int KBS, int ucls,
-                                                int wave, int lane, const v16f (&acc)[4], float inv,
+__device__ __forceinline__ void store_rows_wide(const AttnArgs& a, const QueryBlock& qb, int row0, int lane,
+                                                const v16f (&acc)[4], float inv,
                                                 uint8_t* wave_lds, const float* ch_scale = nullptr) {
-    constexpr int BS = 128;
-    const auto& G = a.g;
     const int h = lane >> 5, n = lane & 31;
     const int row_bytes = a.out_f32 ? 512 : 256;
     const int pitch = row_bytes + 16;
-    const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
-    const int sub = jq / KBS;
-    const SubTile so = sub_tile_origin(G, sub);
-    const int slot0 = (jq - sub * KBS) * BS;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         if ((n >> 4) == pass) {
@@ -747,29 +742,146 @@ __device__ __forceinline__ void store_rows_wide(const AttnArgs& a, int bh, int u
         const int rows_per_pass = 64 >> lanes_shift;
         for (int r0 = 0; r0 < 16; r0 += rows_per_pass) {
             const int r = r0 + (lane >> lanes_shift), chunk = lane & ((1 << lanes_shift) - 1);
-            const int in_block = wave * 32 + pass * 16 + r;
-            int rt = 0, rh = 0, rw = 0;
-            const bool valid = sub_slot_coords(G, so, slot0 + in_block, &rt, &rh, &rw) &&
-                               coords_in_class(G, ucls, rt, rh, rw);
-            uint4 val = *reinterpret_cast<const uint4*>(wave_lds + r * pitch + chunk * 16);
-            size_t row;
-            if (a.out_raster) {
-                if (!valid) continue;
-                row = (((size_t)bh * G.T + (ut * G.Tt + rt)) * G.H + (uh * G.Th + rh)) * G.W + (uw * G.Tw + rw);
-            } else {
-                row = ((size_t)bh * G.M + u) * G.TSP + (size_t)jq * BS + in_block;
-                if (!valid) val = make_uint4(0, 0, 0, 0);
-            }
-            reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(a.out) + row * row_bytes)[chunk] = val;
+            const int row = row0 + pass * 16 + r;
+            const uint4 val = *reinterpret_cast<const uint4*>(wave_lds + r * pitch + chunk * 16);
+            if (row < qb.rows)
+                reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(a.out) + qb.out_row(a, row) * row_bytes)[chunk] = val;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
 }
 
-template <bool VCH, bool MB, int NK>
+template <int N> using Count = std::integral_constant<int, N>;
+
+// The wide kernels walk the key-tile box of Eq. 2 once per number NB = 4, 3, 2, 1 of 32-key sub-blocks:
+// first every key block of more than 96 real keys, then those of 65 to 96 and so on, each with a main
+// loop compiled for its NB, so that the padding of tiles cut by the grid's edge costs no more than the
+// rest of its last sub-block.  Only O and the row sums live from one walk to the next; loops that hand
+// over to each other in mid-pipeline need more registers than there are (250 to 460 spilled in two
+// such arrangements).  Whole path, against blocks of 128 slots with padding in tile order: 21x30x52 x
+// 12 heads, tile (1,8,16), window 3x3x3: FP8 550 -> 514 us, BF16 741 -> 664 us; tile (6,8,8) 614 -> 522
+// us; 21x45x80 x 40 heads, window 5x3x3: 4.59 -> 4.50 ms, dense BF16 114.6 -> 110.1 ms.
+//
+// The box is walked in units of sub-tiles (scale groups), which a window always takes whole.
+struct KeyBox {
+    int t0, t1, h0, h1, w0, w1;         // first and last key tile of the box, per axis
+    uint32_t classes;                   // bit c: the box has sub-tiles of class c (cut along 4: T, 2: H, 1: W)
+    __device__ __forceinline__ void init(const AttnArgs& a, int ut, int uh, int uw) {
+        const Geom& G = a.g;
+        if (a.edge_shift) {                 // clamp the centre into [r, n-1-r]; an axis not longer than
+            // the window has no such centre and is kept whole by the truncation below with u = n/2
+            ut = G.nT > 2 * a.rt + 1 ? min(max(ut, a.rt), G.nT - 1 - a.rt) : G.nT / 2;
+            uh = G.nH > 2 * a.rh + 1 ? min(max(uh, a.rh), G.nH - 1 - a.rh) : G.nH / 2;
+            uw = G.nW > 2 * a.rw + 1 ? min(max(uw, a.rw), G.nW - 1 - a.rw) : G.nW / 2;
+        }
+        t0 = max(0, ut - a.rt); h0 = max(0, uh - a.rh); w0 = max(0, uw - a.rw);
+        t1 = min(G.nT - 1, ut + a.rt); h1 = min(G.nH - 1, uh + a.rh); w1 = min(G.nW - 1, uw + a.rw);
+        const bool et = has_cut(t1, G.nT, G.cutT, G.Qt), eh = has_cut(h1, G.nH, G.cutH, G.Qh),
+                   ew = has_cut(w1, G.nW, G.cutW, G.Qw);
+        classes = ((has_full(t0, G.nsT, G.gT, et) ? 0x0Fu : 0u) | (et ? 0xF0u : 0u)) &
+                  ((has_full(h0, G.nsH, G.gH, eh) ? 0x33u : 0u) | (eh ? 0xCCu : 0u)) &
+                  ((has_full(w0, G.nsW, G.gW, ew) ? 0x55u : 0u) | (ew ? 0xAAu : 0u));
+    }
+    // the box ends with the axis' last sub-tile, and that one is cut
+    static __device__ __forceinline__ bool has_cut(int last, int n, int cut, int q) { return last == n - 1 && cut < q; }
+    static __device__ __forceinline__ bool has_full(int first, int ns, int g, bool cut) { return !cut || first * ns < g - 1; }
+    // visited[v] = 1 for every tile of the box (threads of one workgroup)
+    __device__ __forceinline__ void mark(const Geom& G, uint8_t* visited, int nthr) const {
+        const int eh = h1 - h0 + 1, ew = w1 - w0 + 1, total = (t1 - t0 + 1) * eh * ew;
+        for (int i = threadIdx.x; i < total; i += nthr) {
+            const int t = i / (eh * ew), rem = i - t * (eh * ew), h = rem / ew, w = rem - h * ew;
+            visited[((t0 + t) * G.nH + (h0 + h)) * G.nW + (w0 + w)] = 1;
+        }
+    }
+};
+
+// One axis of a walk over sub-tiles: `off` is the axis' share of the scale-group index, tile * (step of
+// the next tile) + place in tile * (step of the next sub-tile).
+template <bool MB>
+struct AxisWalk {
+    int i, first, last;                 // sub-tile along the axis
+    int sub, off, off_first;
+    int ns, step, wrap;                 // sub-tiles per tile; off's step within a tile, and to the next tile
+    // the axis' full sub-tiles of the tiles lo .. hi, or (cut_part) only its last one, which is cut
+    __device__ __forceinline__ void init(int lo, int hi, int tiles, int g, bool cut_part, bool has_cut, int ns_, int step_,
+                                         int tile_step) {
+        ns = MB ? ns_ : 1;
+        step = MB ? step_ : tile_step;
+        wrap = tile_step - (ns - 1) * step;
+        const int tile = cut_part ? tiles - 1 : lo;
+        first = cut_part ? g - 1 : lo * ns;
+        last = cut_part ? g - 1 : min((hi + 1) * ns, g) - 1 - (has_cut ? 1 : 0);
+        off_first = tile * tile_step + (MB ? (first - tile * ns) * step : 0);
+        reset();
+    }
+    __device__ __forceinline__ void reset() { i = first; off = off_first; sub = 0; }
+    __device__ __forceinline__ bool advance() {            // false: the axis is exhausted (and reset)
+        if (i == last) { reset(); return false; }
+        ++i;
+        if (!MB) { off += step; return true; }
+        if (++sub == ns) { sub = 0; off += wrap; } else { off += step; }
+        return true;
+    }
+    __device__ __forceinline__ int count() const { return last - first + 1; }
+};
+
+// The key blocks of NB sub-blocks of the box, class by class.
+template <bool MB>
+struct BlockWalk {
+    const Geom& G;
+    const KeyBox& box;
+    uint32_t classes;                   // classes still to come
+    int NB;
+    AxisWalk<MB> t, h, w;
+    int n, jb, jb0, jb1;                // real tokens of a sub-tile of the class; its blocks of NB sub-blocks
+    __device__ __forceinline__ BlockWalk(const Geom& G_, const KeyBox& box_, int nb) : G(G_), box(box_), NB(nb) {}
+    __device__ __forceinline__ void enter(int c) {
+        const bool et = KeyBox::has_cut(box.t1, G.nT, G.cutT, G.Qt), eh = KeyBox::has_cut(box.h1, G.nH, G.cutH, G.Qh),
+                   ew = KeyBox::has_cut(box.w1, G.nW, G.cutW, G.Qw);
+        const int per_tile = MB ? G.NS : 1;
+        t.init(box.t0, box.t1, G.nT, G.gT, c & 4, et, G.nsT, G.nsH * G.nsW, G.nH * G.nW * per_tile);
+        h.init(box.h0, box.h1, G.nH, G.gH, c & 2, eh, G.nsH, G.nsW, G.nW * per_tile);
+        w.init(box.w0, box.w1, G.nW, G.gW, c & 1, ew, G.nsW, 1, per_tile);
+        n = ((c & 4) ? G.cutT : G.Qt) * ((c & 2) ? G.cutH : G.Qh) * ((c & 1) ? G.cutW : G.Qw);
+        jb0 = NB == 4 || !MB ? 0 : n >> 7;
+        jb1 = MB ? (NB == 4 ? (n + 31) >> 7 : jb0 + 1) : 1;
+        jb = jb0;
+    }
+    // sets the walk to its first block; returns the number of blocks
+    __device__ __forceinline__ int begin(uint32_t classes_) {
+        int total = 0;
+        for (uint32_t left = classes_; left; left &= left - 1) {
+            enter(__builtin_ctz(left));
+            total += t.count() * h.count() * w.count() * (jb1 - jb0);
+        }
+        classes = classes_;
+        enter_next();
+        return total;
+    }
+    __device__ __forceinline__ void enter_next() {
+        enter(__builtin_ctz(classes));
+        classes &= classes - 1;
+    }
+    __device__ __forceinline__ void next() {               // not past the last block
+        if (MB) {
+            if (++jb < jb1) return;
+            jb = jb0;
+        }
+        if (!w.advance() && !h.advance() && !t.advance()) enter_next();
+    }
+    __device__ __forceinline__ KeyBlock block() const {
+        KeyBlock b;
+        b.group = t.off + h.off + w.off;
+        b.blk = MB ? b.group * G.KBS + jb : b.group;
+        b.n = MB ? min(128, n - 128 * jb) : n;
+        return b;
+    }
+};
+
+template <bool VCH, bool MB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_fp8_wide_kernel(AttnArgs a, MaskTables) {
+void attn_fp8_wide_kernel(AttnArgs a) {
     constexpr int BS = 128;
     constexpr int NTHR = 256;
     constexpr int CPT = (BS * 8) / NTHR;                   // 16-byte chunks per thread per operand tile (4)
@@ -777,28 +889,87 @@ void attn_fp8_wide_kernel(AttnArgs a, MaskTables) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[4][TILE_BYTES];   // K even, K odd, V even, V odd
     const Geom& G = a.g;
     const int KB = MB ? G.KB : 1;
-    const int KB_LAST = MB ? G.kb_last : 1;
     const int KBS = MB ? G.KBS : 1;
     const int NS = MB ? G.NS : 1;
     int bh, u, jq;
     if (!work_item(a, KB, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
-    if (MB && jq >= (ut == G.nT - 1 ? KB_LAST : KB)) {      // a query block of padding only
-        zero_block_rows<BS, NTHR>(a, bh, u, jq);
-        return;
-    }
+    const int ucls = tile_class(G, ut, uh, uw);
+    QueryBlock qblk;
+    qblk.init(G, bh, u, ucls, ut, uh, uw, jq, KBS, BS);
+    zero_padding_rows<BS, NTHR>(a, qblk, ucls);
+    if (qblk.rows <= 0) return;                            // a query block of padding only
+    // the wave's 32 rows; rotated from tile to tile so that the idle waves of cut tiles fall on
+    // different SIMDs
+    const int row0 = 32 * ((wave_s + u) & 3);
+    const bool idle = row0 >= qblk.rows;
     const size_t tile0 = (size_t)bh * G.M;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0][0]);
+    KeyBox box;
+    box.init(a, ut, uh, uw);
+    if (a.visited && bh == 0 && jq == 0) box.mark(G, a.visited + (size_t)u * G.M, NTHR);
+
+    const uint8_t* const k_head = a.k + tile0 * KB * TILE_BYTES;
+    const uint8_t* const v_head = a.v + tile0 * KB * TILE_BYTES;
+    const float* const sk_head = a.sk + tile0 * NS;
+    const float* const sv_head = a.sv + tile0 * NS;
+    auto k_blk = [&](const KeyBlock& b) FPS_INLINE { return k_head + (size_t)b.blk * TILE_BYTES; };
+    auto v_blk = [&](const KeyBlock& b) FPS_INLINE { return v_head + (size_t)b.blk * TILE_BYTES; };
+    auto stage_chunk = [&](int buf, const uint8_t* src, int c) FPS_INLINE {
+        dma_chunk_of(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * TILE_BYTES + wave_s * (CPT * 1024));
+    };
+    auto stage = [&](int buf, const uint8_t* src) FPS_INLINE {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
+    };
+    int par = 0;                                           // parity of the current block's K and V buffers
+
+    if (idle) {
+        // no real row: this wave only copies its share of the K and V blocks, barrier for barrier
+        for (int nb = 4; nb >= 1; --nb) {
+            const uint32_t classes = G.nb_classes[nb - 1] & box.classes;
+            if (!classes) continue;
+            BlockWalk<MB> walk(G, box, nb);
+            const int nblk = walk.begin(classes);
+            KeyBlock nxt = walk.block();
+            stage(par, k_blk(nxt));
+            stage(2 + par, v_blk(nxt));
+            if (nblk > 1) {
+                walk.next();
+                nxt = walk.block();
+                stage(par ^ 1, k_blk(nxt));
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            for (int i = 0; i + 1 < nblk; ++i) {
+                __syncthreads();
+                const KeyBlock v_next = nxt;
+                if (i + 2 < nblk) {
+                    walk.next();
+                    nxt = walk.block();
+                    stage(par, k_blk(nxt));
+                }
+                stage(2 + (par ^ 1), v_blk(v_next));
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                par ^= 1;
+            }
+            __syncthreads();
+            par ^= 1;
+        }
+        __syncthreads();
+        return;
+    }
 
     v8i qop[2];                                            // Q^T, contraction steps 0 and 1
     float m_run = -INFINITY;
     float l_run = 0.f;                                     // running sum of 448 * P (this lane's keys)
-    float alpha_prev = 1.f;                                // VCH: rescale owed to O before the delayed PV
+    float alpha = 1.f;                                     // VCH: rescale owed to O before the delayed PV
     float m_base = 0.f, w_cur = 1.f, w_prev = 0.f;         // fixed reference and weights: see attn_fp8_kernel
     v16f acc[4];
     {
-        const int row = wave * 32 + n;
+        const int row = row0 + n;
         const uint4* p = reinterpret_cast<const uint4*>(
             a.q + (((tile0 + u) * KB + jq) * BS + row) * 128 + 32 * h);
         qop[0] = make_v8i(p[0], p[1]);
@@ -808,232 +979,241 @@ void attn_fp8_wide_kernel(AttnArgs a, MaskTables) {
     }
     const float sqc = load_uniform(a.sq, (tile0 + u) * NS + jq / KBS) * kLog2eOverSqrtD;
 
-    TileWalk w0, w2;
-    w0.init(a, KB, KB_LAST, KBS, ut, uh, uw);
-    w2 = w0;
-    const int ntiles = w0.n;
-    auto tile_of = [&](const TileWalk& w) FPS_INLINE { return (w.vt * G.nH + w.vh) * G.nW + w.vw; };
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-    auto stage_chunk = [&](int buf, const uint8_t* src, int c) FPS_INLINE {
-        dma_chunk_of(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * TILE_BYTES + wave_s * (CPT * 1024));
-    };
-    auto stage = [&](int buf, const uint8_t* src) FPS_INLINE {
-#pragma unroll
-        for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
-    };
-    auto k_blk = [&](const TileWalk& w) FPS_INLINE { return a.k + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
-    auto v_blk = [&](const TileWalk& w) FPS_INLINE { return a.v + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
+    auto pipeline = [&](auto nb_tag) FPS_INLINE {
+        constexpr int NB = decltype(nb_tag)::value;
+        constexpr int J = NB > 2 ? 2 : 1;                  // contraction steps of the PV product (64 keys each)
+        const uint32_t classes = G.nb_classes[NB - 1] & box.classes;
+        if (!classes) return;
+        BlockWalk<MB> walk(G, box, NB);
+        const int nblk = walk.begin(classes);
 
-    v16f s[4];                                             // S^T, four blocks of 32 keys
-    v8i pb[2];                                             // P^T as packed E4M3: contraction steps 0 and 1
-    pb[0] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-    pb[1] = pb[0];
-
-    // operand `step` (block * 2 + contraction step) of a staged K or V block
-    auto load_op = [&](const uint8_t* buf, int step) FPS_INLINE {
-        const uint4* b4 = reinterpret_cast<const uint4*>(buf);
-        return make_v8i(b4[(step * 2 + 0) * 64 + lane], b4[(step * 2 + 1) * 64 + lane]);
-    };
-    auto qk_mfma = [&](const v8i& kop, int step) FPS_INLINE {
-        const int kb = step >> 1, ks = step & 1;
-        s[kb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop, qop[ks], ks == 0 ? zero16() : s[kb],
-                                                               0, 0, 0, 0, 0, 0);
-    };
-    v16f tq[2];                                            // raw V^T P^T of a channel block, until its fma
-    auto pv_mfma = [&](const v8i& vop, int step) FPS_INLINE {
-        const int db = step >> 1, j = step & 1;
-        if (VCH) acc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vop, pb[j], acc[db], 0, 0, 0, 0, 0, 0);
-        else     tq[db & 1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                     vop, pb[j], j == 0 ? zero16() : tq[db & 1], 0, 0, 0, 0, 0, 0);
-    };
-    // half `half` of O^T(db) += s^V 2^(m - m_base) * raw, pinned where it is written
-    auto pv_accumulate_half = [&](int db, int half) FPS_INLINE {
-        if (VCH) return;
+        v16f s[NB];                                        // S^T, blocks of 32 keys
+        v8i pb[2];                                         // P^T as packed E4M3: contraction steps 0 and 1
+        v16f tq[2];                                        // raw V^T P^T of a channel block, until its fma
+        pb[0] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
+        pb[1] = pb[0];
+        // operand `step` of a staged block -- K: 32-key sub-block * 2 + contraction step; V: 32-channel
+        // block * J + contraction step (keys of sub-blocks 2j and 2j + 1)
+        auto load_k = [&](const uint8_t* buf, int step) FPS_INLINE {
+            const uint4* b4 = reinterpret_cast<const uint4*>(buf);
+            return make_v8i(b4[(step * 2 + 0) * 64 + lane], b4[(step * 2 + 1) * 64 + lane]);
+        };
+        auto load_v = [&](const uint8_t* buf, int step) FPS_INLINE {
+            const int db = step / J, j = step % J;
+            const uint4* b4 = reinterpret_cast<const uint4*>(buf);
+            return make_v8i(b4[((2 * j + 0) * 4 + db) * 64 + lane], b4[((2 * j + 1) * 4 + db) * 64 + lane]);
+        };
+        auto qk_mfma = [&](const v8i& kop, int step) FPS_INLINE {
+            const int kb = step >> 1, ks = step & 1;
+            s[kb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop, qop[ks], ks == 0 ? zero16() : s[kb],
+                                                                   0, 0, 0, 0, 0, 0);
+        };
+        auto pv_mfma = [&](const v8i& vop, int step) FPS_INLINE {
+            const int db = step / J, j = step % J;
+            if (VCH) acc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vop, pb[j], acc[db], 0, 0, 0, 0, 0, 0);
+            else     tq[db & 1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                         vop, pb[j], j == 0 ? zero16() : tq[db & 1], 0, 0, 0, 0, 0, 0);
+        };
+        // half `half` of O^T(db) += s^V 2^(m - m_base) * raw, pinned where it is written
+        auto pv_accumulate_half = [&](int db, int half) FPS_INLINE {
+            if (VCH) return;
 #pragma unroll
-        for (int r = 8 * half; r < 8 * half + 8; ++r) acc[db][r] = __builtin_fmaf(tq[db & 1][r], w_prev, acc[db][r]);
-        asm volatile("" : "+v"(acc[db]));
-    };
-    auto mask_scores = [&](int cls, int js, int jb) FPS_INLINE {      // padded keys of a boundary tile: -inf
-        cls = __builtin_amdgcn_readfirstlane(cls);
-        if (!((a.partial_cls >> cls) & 1u)) return;
-        if (!MB) {
+            for (int r = 8 * half; r < 8 * half + 8; ++r) acc[db][r] = __builtin_fmaf(tq[db & 1][r], w_prev, acc[db][r]);
+            asm volatile("" : "+v"(acc[db]));
+        };
+        // row maximum of half `e` of score block kb
+        auto max_half = [&](float mx, int kb, int e) FPS_INLINE {
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const uint32_t code = arg_pair_code(cls, kb);          // uniform: one scalar load
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    s[kb][r] = select_lanes(pair_lane_mask(code, r), s[kb][r], -INFINITY);
-            }
-        } else {
-            uint64_t bm[2];
-            block_ballots<BS>(G, cls, js, jb, lane, bm);
-            if ((bm[0] & bm[1]) == ~0ull) return;          // most blocks of a boundary tile are whole
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const uint32_t bits = (uint32_t)(bm[kb >> 1] >> (32 * (kb & 1))) >> (4 * h);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[kb][r] = keep_if_bit(s[kb][r], bits, 8 * (r >> 2) + (r & 3));
-            }
-        }
-    };
-    auto rescale_acc = [&]() FPS_INLINE {                             // VCH only
-        if (!VCH) return;
-        if (__any(alpha_prev != 1.0f)) {
-#pragma unroll
-            for (int db = 0; db < 4; ++db) acc[db] *= alpha_prev;
-        }
-    };
-
-    // prologue: K(0), K(1) staged; S(0) computed
-    stage(0, k_blk(w2));
-    w2.next();
-    if (ntiles > 1) { stage(1, k_blk(w2)); w2.next(); }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-#pragma unroll
-    for (int step = 0; step < 8; ++step) qk_mfma(load_op(lds[0], step), step);
-    mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
-
-    float sc_next = sqc * load_uniform(a.sk, (tile0 + tile_of(w0)) * NS + w0.js);
-    float sv_next = VCH ? 1.f : load_uniform(a.sv, (tile0 + tile_of(w0)) * NS + w0.js);
-    auto iteration = [&](auto first_tag, auto last_tag, int it) FPS_INLINE {
-        constexpr bool FIRST = decltype(first_tag)::value;
-        constexpr bool LAST = decltype(last_tag)::value;
-        const int par = it & 1;
-        const uint8_t* knxt = lds[par ^ 1];                // K(i+1)
-        const uint8_t* vprev = lds[2 + (par ^ 1)];         // V(i-1)
-        const int v = tile_of(w0);
-        const float sc = sc_next;
-        const float svv = sv_next;
-        if (a.visited && bh == 0 && tid == 0 && jq == 0 && w0.jk == 0) a.visited[(size_t)u * G.M + v] = 1;
-        __syncthreads();                 // every wave is past QK(i) and PV(i-2); staged tiles are visible
-        v8i op[3];                       // MFMA operands on their way from LDS, two steps ahead
-        if (!FIRST) { op[0] = load_op(vprev, 0); op[1] = load_op(vprev, 1); }
-        const bool fetch_k = it + 2 < ntiles;
-        const uint8_t* ksrc = fetch_k ? k_blk(w2) : nullptr;
-        const uint8_t* vsrc = v_blk(w0);
-        if (fetch_k) w2.next();
-        w0.next();
-        if (!LAST) {                     // scales of tile i+1, needed next iteration
-            const size_t gn = (tile0 + tile_of(w0)) * NS + w0.js;
-            sc_next = sqc * load_uniform(a.sk, gn);
-            if (!VCH) sv_next = load_uniform(a.sv, gn);
-        }
-
-        // ---- phase 1: row maximum of S(i)  |  delayed PV(i-1) --------------------------------
-        // step k: half the fma of the block whose second MFMA was issued two or three steps earlier
-        // (a 16-pass result may be read 18 issue slots after its instruction), the MFMA of channel
-        // block k/2, contraction step k%2, and an eighth of the row maximum
-        if (!FIRST) rescale_acc();
-        float mx = __builtin_fmaxf(__builtin_fmaxf(s[0][0], s[0][1]), __builtin_fmaxf(s[0][2], s[0][3]));
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            if (!FIRST) {
-                if (k + 2 < 8) op[(k + 2) % 3] = load_op(vprev, k + 2);
-                if (k >= 3) pv_accumulate_half((k - 3) >> 1, (k - 3) & 1);   // before tq[..] is refilled
-                pv_mfma(op[k % 3], k);
-            }
-#pragma unroll
-            for (int r = (k == 0 ? 4 : 8 * (k & 1)); r < 8 * (k & 1) + 8; r += 2)
-                mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[k >> 1][r]), s[k >> 1][r + 1]);
+            for (int r = 8 * e; r < 8 * e + 8; r += 2)
+                mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[kb][r]), s[kb][r + 1]);
             asm volatile("" : "+v"(mx));
-            if (k < CPT) stage_chunk(2 + par, vsrc, k);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (!FIRST) pv_accumulate_half(2, 1);
-        if (!LAST) { op[0] = load_op(knxt, 0); op[1] = load_op(knxt, 1); }   // K(i+1): visible since the barrier
-        mx = max_over_row_pair(mx);
-        const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(mx * sc));
-        if (VCH) {
-            alpha_prev = fast_exp2(m_run - m_new);
-        } else {
-            if (FIRST) m_base = m_new;
-            w_cur = fast_exp2(m_new - m_base);
-        }
-        m_run = m_new;
-        const float cm = kLog2Of448 - m_new;   // 448 * 2^(S' - m) = 2^(S' + (log2(448) - m))
-        if (!VCH && !FIRST && __any(m_run - m_base > kMaxDrift)) {
-            const float down = fast_exp2(m_base - m_run);
+            return mx;
+        };
+        float cm = 0.f;
+        // the weights of half `e` of score block kb and their FP8 codes
+        auto weights_half = [&](int kb, int e, float sc, float& rs) FPS_INLINE {
 #pragma unroll
-            for (int db = 0; db < 4; ++db) acc[db] *= down;
-            l_run *= down;
-            w_prev *= down;              // the last channel block's fma is still owed (steps 0, 1 below)
-            m_base = m_run;
-            w_cur = 1.0f;
+            for (int q2 = 0; q2 < 2; ++q2) {
+                float p[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    p[r] = fast_exp2(__builtin_fmaf(s[kb][8 * e + 4 * q2 + r], sc, cm));
+                    rs += p[r];
+                }
+                int pw = pb[kb >> 1][4 * (kb & 1) + 2 * e + q2];
+                pw = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], pw, false);
+                pw = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], pw, true);
+                asm volatile("" : "+v"(pw), "+v"(rs));     // keep the pass where it is written
+                pb[kb >> 1][4 * (kb & 1) + 2 * e + q2] = pw;
+            }
+        };
+        // the row reference of the block whose row maximum mx was taken
+        auto new_reference = [&](float mx, float sc) FPS_INLINE {
+            mx = max_over_row_pair(mx);
+            const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(mx * sc));
+            if (VCH) {
+                alpha = fast_exp2(m_run - m_new);
+            } else {
+                m_base = m_run == -INFINITY ? m_new : m_base;          // the item's first block
+                w_cur = fast_exp2(m_new - m_base);
+            }
+            m_run = m_new;
+            cm = kLog2Of448 - m_new;       // 448 * 2^(S' - m) = 2^(S' + (log2(448) - m))
+            if (!VCH && __any(m_run - m_base > kMaxDrift)) {
+                const float down = fast_exp2(m_base - m_run);
+#pragma unroll
+                for (int db = 0; db < 4; ++db) acc[db] *= down;
+                l_run *= down;
+                w_prev *= down;            // the last channel block's fma is still owed
+                m_base = m_run;
+                w_cur = 1.0f;
+            }
+        };
+
+        // prologue: K(0), V(0), K(1) staged; S(0) and its row reference
+        KeyBlock nxt = walk.block();
+        const int n0 = nxt.n;
+        stage(par, k_blk(nxt));
+        stage(2 + par, v_blk(nxt));
+        float sc = sqc * load_uniform(sk_head, nxt.group);
+        float svv = VCH ? 1.f : load_uniform(sv_head, nxt.group);
+        if (nblk > 1) {
+            walk.next();
+            nxt = walk.block();
+            stage(par ^ 1, k_blk(nxt));
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+#pragma unroll
+        for (int step = 0; step < 2 * NB; ++step) qk_mfma(load_k(lds[par], step), step);
+        if (n0 < 32 * NB) mask_padding(s[NB - 1], n0 - 32 * (NB - 1), h);
+        {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int k = 0; k < 2 * NB; ++k) mx = max_half(mx, k >> 1, k & 1);
+            w_prev = 0.f;
+            new_reference(mx, sc);
+        }
+        if (!VCH) tq[1] = zero16();
+
+        // iteration i: P(i) | S(i+1) = K(i+1) Q^T, then row maximum of S(i+1) | O += s^V (V^T P^T)(i)
+        for (int i = 0; i + 1 < nblk; ++i) {
+            const uint8_t* knxt = lds[par ^ 1];            // K(i+1)
+            const uint8_t* vcur = lds[2 + par];            // V(i)
+            __syncthreads();             // every wave is past QK(i) and PV(i-1); staged blocks are visible
+            v8i op[3];                   // MFMA operands on their way from LDS, two steps ahead
+            op[0] = load_k(knxt, 0);
+            op[1] = load_k(knxt, 1);
+            const int n_next = nxt.n;
+            const uint8_t* vsrc = v_blk(nxt);
+            const float sc_next = sqc * load_uniform(sk_head, nxt.group);
+            const float sv_next = VCH ? 1.f : load_uniform(sv_head, nxt.group);
+            const bool fetch_k = i + 2 < nblk;
+            const uint8_t* ksrc = nullptr;
+            if (fetch_k) {
+                walk.next();
+                nxt = walk.block();
+                ksrc = k_blk(nxt);
+            }
+
+            // ---- P(i) and its FP8 codes  |  QK(i+1) ------------------------------------------
+            // step t: the exponentials of half a score block (block t/2, registers 8(t%2)..+7); the
+            // MFMAs that refill a block follow one block behind, so steps 0, 1 have none (they take
+            // the fma still owed to the last channel block of PV(i-1)) and the last two nothing else
+            float rs = 0.f;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 2 * NB + 2; ++t) {
+                if (t >= 2) {
+                    if (t < 2 * NB) op[t % 3] = load_k(knxt, t);       // operand of step t + 2
+                    qk_mfma(op[(t - 2) % 3], t - 2);
+                }
+                if (t < 2) pv_accumulate_half(3, t);                   // PV(i-1)'s last block
+                if (t < 2 * NB) weights_half(t >> 1, t & 1, sc, rs);
+                if (t < CPT && fetch_k) stage_chunk(par, ksrc, t);     // K(i) was consumed last iteration
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (VCH) l_run = l_run * alpha + rs;
+            else     l_run = __builtin_fmaf(rs, w_cur, l_run);
+            w_prev = svv * w_cur;
+            sc = sc_next;
+            svv = sv_next;
+            op[0] = load_v(vcur, 0);
+            op[1] = load_v(vcur, 1);
+            if (n_next < 32 * NB) mask_padding(s[NB - 1], n_next - 32 * (NB - 1), h);
+            if (VCH && __any(alpha != 1.0f)) {
+#pragma unroll
+                for (int db = 0; db < 4; ++db) acc[db] *= alpha;
+            }
+
+            // ---- row maximum of S(i+1)  |  PV(i) ---------------------------------------------
+            // step k: the MFMA of channel block k/J, contraction step k%J, a 16-key half of the row
+            // maximum, and the fma of a channel block whose last MFMA was issued two or three steps
+            // earlier (a 16-pass result may be read 18 issue slots after its instruction)
+            float mx = __builtin_fmaxf(__builtin_fmaxf(s[0][0], s[0][1]), __builtin_fmaxf(s[0][2], s[0][3]));
+#pragma unroll
+            for (int k = 0; k < 4 * J; ++k) {
+                if (k + 2 < 4 * J) op[(k + 2) % 3] = load_v(vcur, k + 2);
+                if (J == 2) {                              // before tq[..] is refilled
+                    if (k >= 3) pv_accumulate_half((k - 3) >> 1, (k - 3) & 1);
+                } else if (k >= 2) {
+                    pv_accumulate_half(k - 2, 0);
+                    pv_accumulate_half(k - 2, 1);
+                }
+                pv_mfma(op[k % 3], k);
+                if (k < 2 * NB) {
+                    if (k == 0) {
+                        mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][4]), s[0][5]);
+                        mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][6]), s[0][7]);
+                        asm volatile("" : "+v"(mx));
+                    } else {
+                        mx = max_half(mx, k >> 1, k & 1);
+                    }
+                }
+                if (k < CPT) stage_chunk(2 + (par ^ 1), vsrc, k);      // V(i-1) was consumed last iteration
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (J == 1) pv_accumulate_half(2, 0);
+            pv_accumulate_half(2, 1);
+            new_reference(mx, sc);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's share of the staged blocks landed
+            par ^= 1;
         }
 
-        // ---- phase 2: P(i) and its FP8 codes  |  early QK(i+1) ------------------------------
-        // step t: the exponentials of half a score block (block t/2, registers 8(t%2)..+7); the
-        // MFMAs that refill a block follow one block behind, so steps 0, 1 have none (they take the
-        // fma still owed to the last channel block of PV(i-1)) and steps 8, 9 nothing else
+        // the last block's P and PV
+        __syncthreads();
+        pv_accumulate_half(3, 0);
+        pv_accumulate_half(3, 1);
         float rs = 0.f;
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int t = 0; t < 10; ++t) {
-            if (!LAST && t >= 2) {
-                if (t < 8) op[t % 3] = load_op(knxt, t);               // operand of step t + 2
-                qk_mfma(op[(t - 2) % 3], t - 2);
-            }
-            if (!FIRST && t < 2) pv_accumulate_half(3, t);             // PV(i-1)'s last block
-            if (t < 8) {
-                const int kb = t >> 1, e = t & 1;
-#pragma unroll
-                for (int q2 = 0; q2 < 2; ++q2) {
-                    float p[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        p[r] = fast_exp2(__builtin_fmaf(s[kb][8 * e + 4 * q2 + r], sc, cm));
-                        rs += p[r];
-                    }
-                    int pw = pb[kb >> 1][4 * (kb & 1) + 2 * e + q2];
-                    pw = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], pw, false);
-                    pw = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], pw, true);
-                    asm volatile("" : "+v"(pw), "+v"(rs));  // keep the pass where it is written
-                    pb[kb >> 1][4 * (kb & 1) + 2 * e + q2] = pw;
-                }
-            }
-            if (t < CPT && fetch_k) stage_chunk(par, ksrc, t);   // K(i) was consumed last iteration
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (VCH) l_run = l_run * alpha_prev + rs;
+        for (int t = 0; t < 2 * NB; ++t) weights_half(t >> 1, t & 1, sc, rs);
+        if (VCH) l_run = l_run * alpha + rs;
         else     l_run = __builtin_fmaf(rs, w_cur, l_run);
         w_prev = svv * w_cur;
-        if (!LAST) mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's share of the staged tiles landed
-    };
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    if constexpr (NK == kOneKeyBlock) {
-        iteration(T_{}, T_{}, 0);
-    } else if constexpr (NK == kManyKeyBlocks) {
-        iteration(T_{}, F_{}, 0);
-        for (int it = 1; it + 1 < ntiles; ++it) iteration(F_{}, F_{}, it);
-        iteration(F_{}, T_{}, ntiles - 1);
-    } else if (ntiles == 1) {
-        iteration(T_{}, T_{}, 0);
-    } else {
-        iteration(T_{}, F_{}, 0);
-        for (int it = 1; it + 1 < ntiles; ++it) iteration(F_{}, F_{}, it);
-        iteration(F_{}, T_{}, ntiles - 1);
-    }
-    // epilogue: the last tile's PV
-    __syncthreads();
-    rescale_acc();
-    {
-        const uint8_t* vlast = lds[2 + ((ntiles - 1) & 1)];
+        if (VCH && __any(alpha != 1.0f)) {
+#pragma unroll
+            for (int db = 0; db < 4; ++db) acc[db] *= alpha;
+        }
 #pragma unroll
         for (int db = 0; db < 4; ++db) {
-            pv_mfma(load_op(vlast, 2 * db), 2 * db);
-            pv_mfma(load_op(vlast, 2 * db + 1), 2 * db + 1);
-            pv_accumulate_half(db, 0);
-            pv_accumulate_half(db, 1);
+#pragma unroll
+            for (int j = 0; j < J; ++j) pv_mfma(load_v(lds[2 + par], db * J + j), db * J + j);
+            if (db > 0) { pv_accumulate_half(db - 1, 0); pv_accumulate_half(db - 1, 1); }
         }
-    }
+        pv_accumulate_half(3, 0);
+        pv_accumulate_half(3, 1);
+        par ^= 1;
+    };
+    pipeline(Count<4>{});
+    pipeline(Count<3>{});
+    pipeline(Count<2>{});
+    pipeline(Count<1>{});
+
     const float l = sum_over_row_pair(l_run);
     const float inv = l > 0.f ? 1.0f / l : 0.f;            // l already carries the factor 448
     __syncthreads();                                       // all waves are done with the staged tiles
-    store_rows_wide(a, bh, u, jq, KBS, tile_class(G, ut, uh, uw), wave, lane, acc, inv,
-                    &lds[0][0] + wave * kStoreRegionBytes, VCH ? a.sv + (size_t)bh * 128 : nullptr);
+    store_rows_wide(a, qblk, row0, lane, acc, inv, &lds[0][0] + wave * kStoreRegionBytes,
+                    VCH ? a.sv + (size_t)bh * 128 : nullptr);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1048,7 +1228,7 @@ union Bf16x8 { uint4 u; v8bf v; v8h h; };
 
 template <int BS, bool MB, int NK>
 __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_bf16_kernel(AttnArgs a, MaskTables) {
+void attn_bf16_kernel(AttnArgs a) {
     constexpr int NB = BS / 16;
     constexpr int NKK = BS / 32;
     constexpr int NTHR = BS * 2;
@@ -1057,17 +1237,17 @@ void attn_bf16_kernel(AttnArgs a, MaskTables) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][TILE_BYTES];   // K, V
     const Geom& G = a.g;
     const int KB = MB ? G.KB : 1;                          // blocks per tile; 1 is a compile-time fact
-    const int KB_LAST = MB ? G.kb_last : 1;                // ... of a last-along-T tile, without padding-only blocks
     const int KBS = MB ? G.KBS : 1;                        // blocks per quantisation sub-tile (scale group)
     const int NS = MB ? G.NS : 1;                          // sub-tiles per tile
     int bh, u, jq;
     if (!work_item(a, KB, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
     const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
-    if (MB && jq >= (ut == G.nT - 1 ? KB_LAST : KB)) {      // a query block of padding only
-        zero_block_rows<BS, BS * 2>(a, bh, u, jq);
-        return;
-    }
+    const int ucls = tile_class(G, ut, uh, uw);
+    QueryBlock qblk;
+    qblk.init(G, bh, u, ucls, ut, uh, uw, jq, KBS, BS);
+    zero_padding_rows<BS, NTHR>(a, qblk, ucls);
+    if (qblk.rows <= 0) return;                            // a query block of padding only
     const size_t tile0 = (size_t)bh * G.M;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0][0]);
 
@@ -1091,18 +1271,19 @@ void attn_bf16_kernel(AttnArgs a, MaskTables) {
     }
     const float sc = kLog2eOverSqrtD;
 
-    TileWalk w0, w1;                                       // tile i and tile i+1
-    w0.init(a, KB, KB_LAST, KBS, ut, uh, uw);
-    w1 = w0;
-    w1.next();
-    const int ntiles = w0.n;
-    auto tile_of = [&](const TileWalk& w) FPS_INLINE { return (w.vt * G.nH + w.vh) * G.nW + w.vw; };
+    KeyWalk<BS, MB> walk;                                  // block i+1
+    walk.init(a, ut, uh, uw);
+    const int ntiles = walk.n;
+    if (a.visited && bh == 0 && jq == 0) walk.mark(G, a.visited + (size_t)u * G.M, NTHR);
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);   // the wave index, in a scalar register
     auto stage_chunk = [&](int buf, const uint8_t* src, int c) FPS_INLINE {   // wave w copies bytes [w, w+1) * CPT KB
         dma_chunk_of(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * TILE_BYTES + wave_s * (CPT * 1024));
     };
-    auto k_blk = [&](const TileWalk& w) FPS_INLINE { return a.k + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
-    auto v_blk = [&](const TileWalk& w) FPS_INLINE { return a.v + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
+    const uint8_t* const k_head = a.k + tile0 * KB * TILE_BYTES;
+    const uint8_t* const v_head = a.v + tile0 * KB * TILE_BYTES;
+    const float* const sv_head = a.sv + tile0 * NS;
+    auto k_blk = [&](const KeyBlock& b) FPS_INLINE { return k_head + (size_t)b.blk * TILE_BYTES; };
+    auto v_blk = [&](const KeyBlock& b) FPS_INLINE { return v_head + (size_t)b.blk * TILE_BYTES; };
     const uint4* ldsK4 = reinterpret_cast<const uint4*>(lds[0]);
     const uint4* ldsV4 = reinterpret_cast<const uint4*>(lds[1]);
 
@@ -1143,51 +1324,35 @@ void attn_bf16_kernel(AttnArgs a, MaskTables) {
             asm volatile("" : "+v"(acc[qb][cb]));
         }
     };
-    auto mask_scores = [&](int cls, int js, int jb) FPS_INLINE {      // padded keys of a boundary tile: -inf
-        cls = __builtin_amdgcn_readfirstlane(cls);         // wave-uniform by construction
-        if (!((a.partial_cls >> cls) & 1u)) return;
-        if (!MB) {
+    auto mask_scores = [&](int n_real) FPS_INLINE {        // padded keys of a block: -inf
+        if (n_real == BS) return;
+        const uint32_t real = (1u << n_real) - 1u;
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+        for (int b = 0; b < NB; ++b) {
+            const uint32_t bits = ((real >> (16 * b)) & 0xFFFFu) >> (4 * g);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const uint64_t lm = arg_lane_mask(cls, 4 * b + r);   // uniform: one scalar load
-                    s[0][b][r] = select_lanes(lm, s[0][b][r], -INFINITY);
-                    s[1][b][r] = select_lanes(lm, s[1][b][r], -INFINITY);
-                }
-        } else {                                           // block jk of a larger tile
-            uint64_t bm[(BS + 63) / 64];
-            block_ballots<BS>(G, cls, js, jb, lane, bm);
-            bool all = true;
-#pragma unroll
-            for (int h = 0; h < (BS + 63) / 64; ++h) all = all && (bm[h] | (BS >= 64 ? 0ull : ~0xFFFFFFFFull)) == ~0ull;
-            if (all) return;                               // most blocks of a boundary tile are whole
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const uint32_t bits = ((uint32_t)(bm[(16 * b) >> 6] >> ((16 * b) & 63)) & 0xFFFFu) >> (4 * g);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (!((bits >> r) & 1u)) { s[0][b][r] = -INFINITY; s[1][b][r] = -INFINITY; }
-            }
+            for (int r = 0; r < 4; ++r)
+                if (!((bits >> r) & 1u)) { s[0][b][r] = -INFINITY; s[1][b][r] = -INFINITY; }
         }
     };
     // prologue: K(0) staged, S(0) computed
+    KeyBlock cur = walk.block(G), nxt = cur;               // blocks i and i+1
+    int it_done = 0;
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) stage_chunk(0, k_blk(w0), c);
+    for (int c = 0; c < CPT; ++c) stage_chunk(0, k_blk(cur), c);
+    if (ntiles > 1) { walk.next(G); nxt = walk.block(G); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
     for (int b = 0; b < NB; ++b) qk_block(b);
-    mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
+    mask_scores(cur.n);
 
     auto iteration = [&](auto first_tag, auto last_tag) FPS_INLINE {
         constexpr bool FIRST = decltype(first_tag)::value;
         constexpr bool LAST = decltype(last_tag)::value;
-        const int v = tile_of(w0);
-        const float svv = load_uniform(a.sv, (tile0 + v) * NS + w0.js);
-        if (a.visited && bh == 0 && tid == 0 && jq == 0 && w0.jk == 0) a.visited[(size_t)u * G.M + v] = 1;
-        const uint8_t* ksrc = LAST ? nullptr : k_blk(w1);
-        const uint8_t* vsrc = v_blk(w0);
+        const float svv = load_uniform(sv_head, cur.group);
+        const uint8_t* ksrc = LAST ? nullptr : k_blk(nxt);
+        const uint8_t* vsrc = v_blk(cur);
         __syncthreads();                 // every wave has finished QK(i): the K buffer is free; V(i-1) visible
 
         // ---- phase 1: row maxima of S(i)  |  delayed PV(i-1)  |  K(i+1) streams in ------------
@@ -1323,9 +1488,10 @@ void attn_bf16_kernel(AttnArgs a, MaskTables) {
             l_run[qb] = __builtin_fmaf(rs[qb], w_cur[qb], l_run[qb]);
             w_prev[qb] = svv * w_cur[qb];
         }
-        w0.next();
-        w1.next();
-        if (!LAST) mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
+        if (!LAST) mask_scores(nxt.n);
+        cur = nxt;
+        ++it_done;
+        if (it_done + 1 < ntiles) { walk.next(G); nxt = walk.block(G); }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // V(i): this thread's share landed
     };
     using T_ = std::true_type;
@@ -1362,8 +1528,7 @@ void attn_bf16_kernel(AttnArgs a, MaskTables) {
         inv[qb] = l > 0.f ? 1.0f / l : 0.f;
     }
     __syncthreads();                                       // all waves are done with the staged tiles
-    store_rows<BS>(a, bh, u, jq, KBS, tile_class(G, ut, uh, uw), wave, lane, acc, inv,
-                   &lds[0][0] + wave * kStoreRegionBytes);
+    store_rows(a, qblk, wave * 32, lane, acc, inv, &lds[0][0] + wave * kStoreRegionBytes);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1376,9 +1541,9 @@ void attn_bf16_kernel(AttnArgs a, MaskTables) {
 // O is rescaled (exactly) only when that grows, and a tile below it has the difference folded into
 // the exponent of its weights before they are rounded to fp16.
 // ---------------------------------------------------------------------------------------------
-template <bool MB, int NK>
+template <bool MB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_bf16_wide_kernel(AttnArgs a, MaskTables) {
+void attn_bf16_wide_kernel(AttnArgs a) {
     constexpr int BS = 128;
     constexpr int NTHR = 256;
     constexpr int TILE_BYTES = BS * 256;
@@ -1386,27 +1551,78 @@ void attn_bf16_wide_kernel(AttnArgs a, MaskTables) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2][TILE_BYTES];   // K, V
     const Geom& G = a.g;
     const int KB = MB ? G.KB : 1;
-    const int KB_LAST = MB ? G.kb_last : 1;
     const int KBS = MB ? G.KBS : 1;
     const int NS = MB ? G.NS : 1;
     int bh, u, jq;
     if (!work_item(a, KB, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
-    if (MB && jq >= (ut == G.nT - 1 ? KB_LAST : KB)) {      // a query block of padding only
-        zero_block_rows<BS, NTHR>(a, bh, u, jq);
-        return;
-    }
+    const int ucls = tile_class(G, ut, uh, uw);
+    QueryBlock qblk;
+    qblk.init(G, bh, u, ucls, ut, uh, uw, jq, KBS, BS);
+    zero_padding_rows<BS, NTHR>(a, qblk, ucls);
+    if (qblk.rows <= 0) return;                            // a query block of padding only
+    const int row0 = 32 * ((wave_s + u) & 3);              // as in attn_fp8_wide_kernel
+    const bool idle = row0 >= qblk.rows;
     const size_t tile0 = (size_t)bh * G.M;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0][0]);
+    KeyBox box;
+    box.init(a, ut, uh, uw);
+    if (a.visited && bh == 0 && jq == 0) box.mark(G, a.visited + (size_t)u * G.M, NTHR);
+
+    const uint8_t* const k_head = a.k + tile0 * KB * TILE_BYTES;
+    const uint8_t* const v_head = a.v + tile0 * KB * TILE_BYTES;
+    const float* const sv_head = a.sv + tile0 * NS;
+    auto k_blk = [&](const KeyBlock& b) FPS_INLINE { return k_head + (size_t)b.blk * TILE_BYTES; };
+    auto v_blk = [&](const KeyBlock& b) FPS_INLINE { return v_head + (size_t)b.blk * TILE_BYTES; };
+    auto stage_chunk = [&](int buf, const uint8_t* src, int c) FPS_INLINE {
+        dma_chunk_of(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * TILE_BYTES + wave_s * (CPT * 1024));
+    };
+    auto stage = [&](int buf, const uint8_t* src) FPS_INLINE {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
+    };
+
+    if (idle) {
+        // no real row: this wave only copies its share of the K and V blocks, barrier for barrier
+        for (int nb = 4; nb >= 1; --nb) {
+            const uint32_t classes = G.nb_classes[nb - 1] & box.classes;
+            if (!classes) continue;
+            BlockWalk<MB> walk(G, box, nb);
+            const int nblk = walk.begin(classes);
+            KeyBlock cur = walk.block(), nxt = cur;
+            stage(0, k_blk(cur));
+            if (nblk > 1) { walk.next(); nxt = walk.block(); }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();                               // K(0) visible
+            __syncthreads();                               // QK(0) done
+            if (nblk > 1) stage(0, k_blk(nxt));
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            for (int i = 0; i < nblk; ++i) {
+                stage(1, v_blk(cur));
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();                           // QK(i+1) done; V(i) visible
+                cur = nxt;
+                if (i + 2 < nblk) {
+                    walk.next();
+                    nxt = walk.block();
+                    stage(0, k_blk(nxt));
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();                           // PV(i) done; K(i+2) visible
+            }
+        }
+        return;
+    }
 
     Bf16x8 qop[8];                                         // Q^T, contraction steps of 16 channels
     float m_run = -INFINITY, l_run = 0.f;                  // row reference; sum of 2^14 P relative to it
     float e_ref = 0.f;                                     // the largest weight exponent E met so far
-    float alpha_acc = 1.f;                                 // rescale owed to O before the delayed PV
     v16f acc[4];
     {
-        const int row = wave * 32 + n;
+        const int row = row0 + n;
         const uint4* p = reinterpret_cast<const uint4*>(a.q + (((tile0 + u) * KB + jq) * BS + row) * 256);
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) qop[ks].u = p[2 * ks + h];
@@ -1414,248 +1630,242 @@ void attn_bf16_wide_kernel(AttnArgs a, MaskTables) {
         for (int db = 0; db < 4; ++db) acc[db] = zero16();
     }
     const float sc = kLog2eOverSqrtD;
-
-    TileWalk w0, w1;                                       // tile i and tile i+1
-    w0.init(a, KB, KB_LAST, KBS, ut, uh, uw);
-    w1 = w0;
-    w1.next();
-    const int ntiles = w0.n;
-    auto tile_of = [&](const TileWalk& w) FPS_INLINE { return (w.vt * G.nH + w.vh) * G.nW + w.vw; };
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-    auto stage_chunk = [&](int buf, const uint8_t* src, int c) FPS_INLINE {
-        dma_chunk_of(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * TILE_BYTES + wave_s * (CPT * 1024));
-    };
-    auto k_blk = [&](const TileWalk& w) FPS_INLINE { return a.k + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
-    auto v_blk = [&](const TileWalk& w) FPS_INLINE { return a.v + ((tile0 + tile_of(w)) * KB + w.jk) * TILE_BYTES; };
     const uint4* ldsK4 = reinterpret_cast<const uint4*>(lds[0]);
     const uint4* ldsV4 = reinterpret_cast<const uint4*>(lds[1]);
 
-    v16f s[4];                                             // S^T, four blocks of 32 keys
-    Bf16x8 pop[8];                                         // P^T in fp16: contraction steps of 16 keys
-    Bf16x8 ring[4];                                        // MFMA operands on their way from LDS
+    auto pipeline = [&](auto nb_tag) FPS_INLINE {
+        constexpr int NB = decltype(nb_tag)::value;
+        const uint32_t classes = G.nb_classes[NB - 1] & box.classes;
+        if (!classes) return;
+        BlockWalk<MB> walk(G, box, NB);
+        const int nblk = walk.begin(classes);
 
-    auto mask_scores = [&](int cls, int js, int jb) FPS_INLINE {      // padded keys of a boundary tile: -inf
-        cls = __builtin_amdgcn_readfirstlane(cls);
-        if (!((a.partial_cls >> cls) & 1u)) return;
-        if (!MB) {
+        v16f s[NB];                                        // S^T, blocks of 32 keys
+        Bf16x8 pop[2 * NB];                                // P^T in fp16: contraction steps of 16 keys
+        Bf16x8 ring[4];                                    // MFMA operands on their way from LDS
+        float alpha_acc = 1.f;                             // rescale owed to O before the block's PV
+        float alpha_l = 1.f, below = 0.f, cm = 0.f;
+
+        // operand j of the K block: key block j/8, contraction step j%8
+        auto k_operand = [&](int j) FPS_INLINE { return ldsK4[j * 64 + lane]; };
+        auto qk_step = [&](int j) FPS_INLINE {
+            const int kb = j >> 3, ks = j & 7;
+            s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j & 3].v, qop[ks].v, ks == 0 ? zero16() : s[kb], 0, 0, 0);
+        };
+        // PV instructions alternate between two channel blocks, so that consecutive ones do not depend
+        // on each other: instruction j -> channel block 2(j / 4NB) + j%2, contraction step (j % 4NB)/2
+        auto pv_db = [](int j) { return 2 * (j / (4 * NB)) + (j & 1); };
+        auto pv_kk = [](int j) { return (j % (4 * NB)) >> 1; };
+        auto v_operand = [&](int j) FPS_INLINE { return ldsV4[(pv_kk(j) * 4 + pv_db(j)) * 64 + lane]; };
+        auto pv_step = [&](int j) FPS_INLINE {
+            acc[pv_db(j)] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[j & 3].h, pop[pv_kk(j)].h, acc[pv_db(j)], 0, 0, 0);
+        };
+        // a pair of weights (registers 2i, 2i + 1 of score block kb) in fp16
+        auto weights_pair = [&](int kb, int i, float& rs) FPS_INLINE {
+            const float p0 = fast_exp2(__builtin_fmaf(s[kb][2 * i], sc, cm));
+            const float p1 = fast_exp2(__builtin_fmaf(s[kb][2 * i + 1], sc, cm));
+            rs += p0;
+            rs += p1;
+            uint32_t wd = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{p0, p1}, v2h));
+            asm volatile("" : "+v"(wd), "+v"(rs));         // keep the pass in place
+            reinterpret_cast<uint32_t*>(&pop[2 * kb + (i >> 2)].u)[i & 3] = wd;
+        };
+        // the row reference and weight exponents of the block whose row maximum mx was taken; svv: its
+        // V scale, 2^e exactly
+        auto new_reference = [&](float mx, float svv) FPS_INLINE {
+            const float e_v = (float)((int)((__float_as_uint(svv) >> 23) & 0xFFu) - 127);
+            mx = max_over_row_pair(mx);
+            const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(mx * sc));
+            const float e_new = e_v + m_new;
+            const float e_top = m_run == -INFINITY ? e_new : __builtin_fmaxf(e_ref, e_new);
+            alpha_l = fast_exp2(m_run - m_new);            // 0 on the first block (m_run = -inf)
+            alpha_acc = m_run == -INFINITY ? 1.0f : fast_exp2(e_ref - e_top);
+            m_run = m_new;
+            // <= 0: this block's weight relative to O's scale; 64 binades down every fp16 weight is zero
+            below = __builtin_fmaxf(e_new - e_top, -64.0f);
+            e_ref = e_top;
+            // 2^14 * 2^(S' - m) * 2^below: the factor 2^14 keeps small weights in fp16's normal range
+            // and cancels against the row sum, which is taken of the same values
+            cm = kFp16PScaleLog2 - m_new + below;
+        };
+
+        // prologue: S(0) and its row reference, then K(1) on its way
+        KeyBlock cur = walk.block(), nxt = cur;
+        stage(0, k_blk(cur));
+        float svv = load_uniform(sv_head, cur.group);
+        if (nblk > 1) { walk.next(); nxt = walk.block(); }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
 #pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const uint32_t code = arg_pair_code(cls, kb);
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    s[kb][r] = select_lanes(pair_lane_mask(code, r), s[kb][r], -INFINITY);
-            }
-        } else {
-            uint64_t bm[2];
-            block_ballots<BS>(G, cls, js, jb, lane, bm);
-            if ((bm[0] & bm[1]) == ~0ull) return;
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-                const uint32_t bits = (uint32_t)(bm[kb >> 1] >> (32 * (kb & 1))) >> (4 * h);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[kb][r] = keep_if_bit(s[kb][r], bits, 8 * (r >> 2) + (r & 3));
-            }
+        for (int j = 0; j < 8 * NB; ++j) {
+            ring[j & 3].u = k_operand(j);
+            qk_step(j);
         }
-    };
-    // operand j of the K block: key block j/8, contraction step j%8
-    auto k_operand = [&](int j) FPS_INLINE { return ldsK4[j * 64 + lane]; };
-    auto qk_step = [&](int j) FPS_INLINE {
-        const int kb = j >> 3, ks = j & 7;
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ring[j & 3].v, qop[ks].v, ks == 0 ? zero16() : s[kb], 0, 0, 0);
-    };
-    // PV instructions alternate between two channel blocks, so that consecutive ones do not depend
-    // on each other: instruction j -> channel block 2(j/16) + j%2, contraction step (j%16)/2
-    auto pv_db = [](int j) { return 2 * (j >> 4) + (j & 1); };
-    auto pv_kk = [](int j) { return (j & 15) >> 1; };
-    auto v_operand = [&](int j) FPS_INLINE { return ldsV4[(pv_db(j) * 8 + pv_kk(j)) * 64 + lane]; };
-    auto pv_step = [&](int j) FPS_INLINE {
-        acc[pv_db(j)] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[j & 3].h, pop[pv_kk(j)].h, acc[pv_db(j)], 0, 0, 0);
-    };
-
-    // prologue: K(0) staged, S(0) computed
+        if (cur.n < 32 * NB) mask_padding(s[NB - 1], cur.n - 32 * (NB - 1), h);
+        {
+            float mx = -INFINITY;
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) stage_chunk(0, k_blk(w0), c);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
+            for (int k = 0; k < 8 * NB; ++k)
+                mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[k >> 3][2 * (k & 7)]), s[k >> 3][2 * (k & 7) + 1]);
+            new_reference(mx, svv);
+        }
+        __syncthreads();                                   // every wave has finished QK(0): the K buffer is free
+        if (nblk > 1) stage(0, k_blk(nxt));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+
+        // iteration i: P(i) | S(i+1) = K(i+1) Q^T | V(i) streams in, then row maximum of S(i+1) |
+        // O += V^T P^T (i) | K(i+2) streams in
+        for (int i = 0; i + 1 < nblk; ++i) {
+            const uint8_t* vsrc = v_blk(cur);
+            const int n_next = nxt.n;
+            const float svv_next = load_uniform(sv_head, nxt.group);
+            cur = nxt;
+            const bool fetch_k = i + 2 < nblk;
+            if (fetch_k) { walk.next(); nxt = walk.block(); }
+            const uint8_t* ksrc = k_blk(nxt);
+
+            // step (kb, ks): a pair of weights of score block kb beside the MFMA (kb - 1, ks) that
+            // refills the block whose weights were taken one block earlier
+            float rs = 0.f;
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
-        ring[j & 3].u = k_operand(j);
-        qk_step(j);
-    }
-    mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
+            for (int j = 0; j < 3; ++j) ring[j].u = k_operand(j);
+#pragma unroll
+            for (int kb = 0; kb <= NB; ++kb) {
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) {
+                    const int j = (kb - 1) * 8 + ks;
+                    if (kb >= 1) {
+                        if (j + 3 < 8 * NB) ring[(j + 3) & 3].u = k_operand(j + 3);
+                        qk_step(j);
+                    }
+                    if (kb < NB) weights_pair(kb, ks, rs);
+                    if (kb * 8 + ks < CPT) stage_chunk(1, vsrc, kb * 8 + ks);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            // the row sum was taken of weights scaled by 2^below
+            l_run = __builtin_fmaf(rs, fast_exp2(-below), l_run * alpha_l);
+            if (n_next < 32 * NB) mask_padding(s[NB - 1], n_next - 32 * (NB - 1), h);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // V(i): this thread's share landed
+            __syncthreads();             // every wave has finished QK(i+1): the K buffer is free; V(i) visible
 
-    auto iteration = [&](auto first_tag, auto last_tag) FPS_INLINE {
-        constexpr bool FIRST = decltype(first_tag)::value;
-        constexpr bool LAST = decltype(last_tag)::value;
-        const int v = tile_of(w0);
-        const float svv = load_uniform(a.sv, (tile0 + v) * NS + w0.js);        // 2^e exactly
-        const float e_v = (float)((int)((__float_as_uint(svv) >> 23) & 0xFFu) - 127);
-        if (a.visited && bh == 0 && tid == 0 && jq == 0 && w0.jk == 0) a.visited[(size_t)u * G.M + v] = 1;
-        const uint8_t* ksrc = LAST ? nullptr : k_blk(w1);
-        const uint8_t* vsrc = v_blk(w0);
-        __syncthreads();                 // every wave has finished QK(i): the K buffer is free; V(i-1) visible
+            if (__any(alpha_acc != 1.0f)) {
+#pragma unroll
+                for (int db = 0; db < 4; ++db) acc[db] *= alpha_acc;
+            }
+            float mx = __builtin_fmaxf(__builtin_fmaxf(s[0][0], s[0][1]), __builtin_fmaxf(s[0][2], s[0][3]));
+#pragma unroll
+            for (int j = 0; j < 3; ++j) ring[j].u = v_operand(j);
+#pragma unroll
+            for (int j = 0; j < 8 * NB; ++j) {             // one MFMA and one max3 per step
+                if (j + 3 < 8 * NB) ring[(j + 3) & 3].u = v_operand(j + 3);
+                pv_step(j);
+                if (j >= 2) {
+                    mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[j >> 3][2 * (j & 7)]), s[j >> 3][2 * (j & 7) + 1]);
+                    asm volatile("" : "+v"(mx));
+                }
+                constexpr int every = NB > 1 ? 2 : 1;      // K's copies ride in the first half
+                if (fetch_k && j % every == 0 && j / every < CPT) stage_chunk(0, ksrc, j / every);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            svv = svv_next;
+            new_reference(mx, svv);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // K(i+2): this thread's share landed
+            __syncthreads();             // every wave has finished PV(i): the V buffer is free; K(i+2) visible
+        }
 
-        // ---- phase 1: row maximum of S(i)  |  delayed PV(i-1)  |  K(i+1) streams in ------------
-        if (!FIRST && __any(alpha_acc != 1.0f)) {
+        // the last block's P and PV
+        stage(1, v_blk(cur));
+        float rs = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8 * NB; ++k) weights_pair(k >> 3, k & 7, rs);
+        l_run = __builtin_fmaf(rs, fast_exp2(-below), l_run * alpha_l);
+        if (__any(alpha_acc != 1.0f)) {
 #pragma unroll
             for (int db = 0; db < 4; ++db) acc[db] *= alpha_acc;
         }
-        float mx = __builtin_fmaxf(__builtin_fmaxf(s[0][0], s[0][1]), __builtin_fmaxf(s[0][2], s[0][3]));
-        if (!FIRST) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < 3; ++j) ring[j].u = v_operand(j);
+        for (int j = 0; j < 8 * NB; ++j) {
+            ring[j & 3].u = v_operand(j);
+            pv_step(j);
         }
-#pragma unroll
-        for (int j = 0; j < 32; ++j) {                     // one MFMA and one max3 per step
-            if (!FIRST) {
-                if (j + 3 < 32) ring[(j + 3) & 3].u = v_operand(j + 3);
-                pv_step(j);
-            }
-            if (j >= 2) {
-                mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[j >> 3][2 * (j & 7)]), s[j >> 3][2 * (j & 7) + 1]);
-                asm volatile("" : "+v"(mx));
-            }
-            if (!LAST && (j & 1) == 0 && j < 2 * CPT) stage_chunk(0, ksrc, j >> 1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        mx = max_over_row_pair(mx);
-        const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(mx * sc));
-        const float alpha_l = fast_exp2(m_run - m_new);    // 0 on the first tile (m_run = -inf)
-        m_run = m_new;
-        const float e_new = e_v + m_new;
-        const float e_top = FIRST ? e_new : __builtin_fmaxf(e_ref, e_new);
-        alpha_acc = FIRST ? 1.0f : fast_exp2(e_ref - e_top);
-        // <= 0: this tile's weight relative to O's scale; 64 binades down every fp16 weight is zero
-        const float below = __builtin_fmaxf(e_new - e_top, -64.0f);
-        e_ref = e_top;
-        // 2^14 * 2^(S' - m) * 2^below: the factor 2^14 keeps small weights in fp16's normal range and
-        // cancels against the row sum, which is taken of the same values
-        const float cm = kFp16PScaleLog2 - m_new + below;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // K(i+1): this thread's share landed
-        __syncthreads();                 // every wave has finished PV(i-1): the V buffer is free; K(i+1) visible
-
-        // ---- phase 2: P(i) in fp16  |  early QK(i+1)  |  V(i) streams in -----------------------
-        // step (kb, ks): a pair of weights of score block kb beside the MFMA (kb - 1, ks) that
-        // refills the block whose weights were taken one block earlier
-        float rs = 0.f;
-        if (!LAST) {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) ring[j].u = k_operand(j);
-        }
-#pragma unroll
-        for (int kb = 0; kb <= 4; ++kb) {
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                const int j = (kb - 1) * 8 + ks;
-                if (!LAST && kb >= 1) {
-                    if (j + 3 < 32) ring[(j + 3) & 3].u = k_operand(j + 3);
-                    qk_step(j);
-                }
-                if (kb < 4) {
-                    const float p0 = fast_exp2(__builtin_fmaf(s[kb][2 * ks], sc, cm));
-                    const float p1 = fast_exp2(__builtin_fmaf(s[kb][2 * ks + 1], sc, cm));
-                    rs += p0;
-                    rs += p1;
-                    uint32_t wd = __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{p0, p1}, v2h));
-                    asm volatile("" : "+v"(wd), "+v"(rs));  // keep the pass in place
-                    reinterpret_cast<uint32_t*>(&pop[2 * kb + (ks >> 2)].u)[ks & 3] = wd;
-                }
-                if (kb * 8 + ks < CPT) stage_chunk(1, vsrc, kb * 8 + ks);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        // the row sum was taken of weights scaled by 2^below
-        l_run = __builtin_fmaf(rs, fast_exp2(-below), l_run * alpha_l);
-        w0.next();
-        w1.next();
-        if (!LAST) mask_scores(tile_class(G, w0.vt, w0.vh, w0.vw), w0.js, w0.jb);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // V(i): this thread's share landed
+        __syncthreads();                                   // both buffers are free
     };
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    if constexpr (NK == kOneKeyBlock) {
-        iteration(T_{}, T_{});
-    } else if constexpr (NK == kManyKeyBlocks) {
-        iteration(T_{}, F_{});
-        for (int it = 1; it + 1 < ntiles; ++it) iteration(F_{}, F_{});
-        iteration(F_{}, T_{});
-    } else if (ntiles == 1) {
-        iteration(T_{}, T_{});
-    } else {
-        iteration(T_{}, F_{});
-        for (int it = 1; it + 1 < ntiles; ++it) iteration(F_{}, F_{});
-        iteration(F_{}, T_{});
-    }
-    // epilogue: the last tile's PV
-    __syncthreads();
-    if (__any(alpha_acc != 1.0f)) {
-#pragma unroll
-        for (int db = 0; db < 4; ++db) acc[db] *= alpha_acc;
-    }
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-        ring[j & 3].u = v_operand(j);
-        pv_step(j);
-    }
+    pipeline(Count<4>{});
+    pipeline(Count<3>{});
+    pipeline(Count<2>{});
+    pipeline(Count<1>{});
+
     const float l = sum_over_row_pair(l_run);
     const float inv = l > 0.f ? fast_exp2(e_ref - m_run) / l : 0.f;
-    __syncthreads();                                       // all waves are done with the staged tiles
-    store_rows_wide(a, bh, u, jq, KBS, tile_class(G, ut, uh, uw), wave, lane, acc, inv,
-                    &lds[0][0] + wave * kStoreRegionBytes);
+    store_rows_wide(a, qblk, row0, lane, acc, inv, &lds[0][0] + wave * kStoreRegionBytes);
 }
 
-// Debug: raw E4M3 score accumulators sum_c q_ic * k_jc of one tile pair, produced by the same MFMA
-// instruction and operand layouts as attn_fp8_kernel; out[i*BS + j], query-major.
+// Debug: raw E4M3 score accumulators sum_c q_ic * k_jc of pairs of slot blocks, produced by the same
+// MFMA instruction as the attention kernel; out[query slot][key slot] in the tile's slot order, zero for
+// padding slots.  The rows are gathered one by one, since packed operands hold a tile's real tokens
+// in another order (real_box).
+// Byte offset of 16-byte chunk c16 (channels 16 c16 ..) of slot `slot` of tile class cls inside the
+// tile's packed Q (K: is_k) tensor; -1 for a padding slot.
 template <int BS>
-__global__ __launch_bounds__(BS * 2) void scores_fp8_kernel(const uint8_t* __restrict__ q_tile,
-                                                            const uint8_t* __restrict__ k_tile,
-                                                            float* __restrict__ out_tile, int out_pitch) {
-    constexpr int NB = BS / 16;
-    // workgroup (x, y) = (key block, query block) of the tile pair
-    const uint8_t* q = q_tile + (size_t)blockIdx.y * BS * 128;
-    const uint8_t* k = k_tile + (size_t)blockIdx.x * BS * 128;
-    float* out = out_tile + (size_t)blockIdx.y * BS * out_pitch + (size_t)blockIdx.x * BS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, n = lane & 15;
-    const uint4* k4 = reinterpret_cast<const uint4*>(k);
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        const int row = wave * 32 + qb * 16 + n;
-        const uint4* p = reinterpret_cast<const uint4*>(q + row * 128 + 32 * g);
-        const uint4 lo = p[0], hi = p[1];
-        const v8i qop = v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-        for (int b = 0; b < NB; ++b) {
-            const uint4 klo = k4[(b * 2 + 0) * 64 + lane], khi = k4[(b * 2 + 1) * 64 + lane];
-            const v8i kop = v8i{(int)klo.x, (int)klo.y, (int)klo.z, (int)klo.w, (int)khi.x, (int)khi.y, (int)khi.z, (int)khi.w};
-            const v4f s = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                kop, qop, v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0, 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) out[(size_t)row * out_pitch + 16 * b + 4 * g + r] = s[r];
-        }
+__device__ __forceinline__ int packed_row_chunk(const Geom& G, int cls, int slot, int c16, bool is_k) {
+    const int sub = slot / G.QSP;
+    const RealBox box = real_box(G, cls, sub);
+    int rt, rh, rw;
+    if (!sub_slot_coords(G, box.o, slot - sub * G.QSP, &rt, &rh, &rw) || !coords_in_class(G, cls, rt, rh, rw)) return -1;
+    const int k = sub * G.QSP + packed_slot(box, rt, rh, rw);
+    if (!is_k) return k * 128 + c16 * 16;
+    if (BS == 128) {
+        const int ks = c16 >> 2, h = (c16 >> 1) & 1, e = c16 & 1;
+        return (k & ~31) * 128 + ((ks * 2 + e) * 64 + 32 * h + (k & 31)) * 16;
     }
+    const int gg = c16 >> 1, h = c16 & 1;
+    return (k & ~15) * 128 + (h * 64 + gg * 16 + (k & 15)) * 16;
+}
+__device__ __forceinline__ v8i gather_operand(const uint8_t* base, int off_lo, int off_hi) {
+    const uint4 z = make_uint4(0, 0, 0, 0);
+    return make_v8i(off_lo < 0 ? z : *reinterpret_cast<const uint4*>(base + off_lo),
+                    off_hi < 0 ? z : *reinterpret_cast<const uint4*>(base + off_hi));
 }
 
-// The same for 128-slot blocks: the 32x32x64 instruction and operand layouts of attn_fp8_wide_kernel.
-__global__ __launch_bounds__(256) void scores_fp8_wide_kernel(const uint8_t* __restrict__ q_tile,
-                                                              const uint8_t* __restrict__ k_tile,
-                                                              float* __restrict__ out_tile, int out_pitch) {
-    const uint8_t* q = q_tile + (size_t)blockIdx.y * 128 * 128;
-    const uint8_t* k = k_tile + (size_t)blockIdx.x * 128 * 128;
-    float* out = out_tile + (size_t)blockIdx.y * 128 * out_pitch + (size_t)blockIdx.x * 128;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
-    const uint4* k4 = reinterpret_cast<const uint4*>(k);
-    const int row = wave * 32 + n;
-    const uint4* p = reinterpret_cast<const uint4*>(q + row * 128 + 32 * h);
-    const v8i qop[2] = {make_v8i(p[0], p[1]), make_v8i(p[4], p[5])};
-    for (int kb = 0; kb < 4; ++kb) {
+// one wave per 32 x 32 slots: workgroup (x, y) = (32-slot key group, 32-slot query group) of the pair
+template <int BS>
+__global__ __launch_bounds__(64) void scores_fp8_kernel(const uint8_t* __restrict__ q_tile, int q_cls, int q_slot0,
+                                                        const uint8_t* __restrict__ k_tile, int k_cls, int k_slot0,
+                                                        float* __restrict__ out, int out_pitch, Geom G) {
+    const int lane = threadIdx.x;
+    const int qs = q_slot0 + 32 * blockIdx.y, ks0 = k_slot0 + 32 * blockIdx.x;
+    float* o = out + (size_t)(32 * blockIdx.y) * out_pitch + 32 * blockIdx.x;
+    if (BS == 128) {                                       // 32x32x64: lane 32h + n
+        const int h = lane >> 5, n = lane & 31;
         v16f s = zero16();
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            const v8i kop = make_v8i(k4[((kb * 2 + ks) * 2 + 0) * 64 + lane], k4[((kb * 2 + ks) * 2 + 1) * 64 + lane]);
-            s = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop, qop[ks], s, 0, 0, 0, 0, 0, 0);
+            const int c16 = 4 * ks + 2 * h;                // channels 64ks + 32h ..
+            const v8i qop = gather_operand(q_tile, packed_row_chunk<BS>(G, q_cls, qs + n, c16, false),
+                                           packed_row_chunk<BS>(G, q_cls, qs + n, c16 + 1, false));
+            const v8i kop = gather_operand(k_tile, packed_row_chunk<BS>(G, k_cls, ks0 + n, c16, true),
+                                           packed_row_chunk<BS>(G, k_cls, ks0 + n, c16 + 1, true));
+            s = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kop, qop, s, 0, 0, 0, 0, 0, 0);
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            out[(size_t)row * out_pitch + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3)] = s[r];
+        for (int r = 0; r < 16; ++r) o[(size_t)n * out_pitch + 8 * (r >> 2) + 4 * h + (r & 3)] = s[r];
+    } else {                                               // 16x16x128: lane 16g + n
+        const int g = lane >> 4, n = lane & 15;
+        for (int qb = 0; qb < 2; ++qb)
+            for (int b = 0; b < 2; ++b) {
+                const v8i qop = gather_operand(q_tile, packed_row_chunk<BS>(G, q_cls, qs + 16 * qb + n, 2 * g, false),
+                                               packed_row_chunk<BS>(G, q_cls, qs + 16 * qb + n, 2 * g + 1, false));
+                const v8i kop = gather_operand(k_tile, packed_row_chunk<BS>(G, k_cls, ks0 + 16 * b + n, 2 * g, true),
+                                               packed_row_chunk<BS>(G, k_cls, ks0 + 16 * b + n, 2 * g + 1, true));
+                const v4f s = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                    kop, qop, v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[(size_t)(16 * qb + n) * out_pitch + 16 * b + 4 * g + r] = s[r];
+            }
     }
 }
 
@@ -1683,28 +1893,30 @@ int launch_mfma_rate(int workgroups, int iters, float* sink, hipStream_t st) {
     return e == hipSuccess ? FPS_OK : hip_fail(e, "mfma rate launch");
 }
 
-int launch_scores_fp8(const Geom& g, const void* q, const void* k, int bh, int u, int v, float* out,
-                      hipStream_t st) {
-    // every (query block, key block) pair of the tile pair; out is [TSP][TSP], query-major
+// slots slot_q .. of tile u against slots slot_k .. of tile v, `slots` of each
+static int launch_scores(const Geom& g, const void* q, const void* k, int bh, int u, int slot_q, int v, int slot_k,
+                         int slots, float* out, hipStream_t st) {
     const size_t tile_bytes = (size_t)g.TSP * 128;
     const uint8_t* qp = (const uint8_t*)q + ((size_t)bh * g.M + u) * tile_bytes;
     const uint8_t* kp = (const uint8_t*)k + ((size_t)bh * g.M + v) * tile_bytes;
-    const dim3 grid(g.KB, g.KB);
-    if (g.BS == 128) scores_fp8_wide_kernel<<<grid, 256, 0, st>>>(qp, kp, out, g.TSP);
-    else             scores_fp8_kernel<32><<<grid, 64, 0, st>>>(qp, kp, out, g.TSP);
+    auto cls = [&g](int t) {
+        return ((t / (g.nW * g.nH) == g.nT - 1) << 2) | (((t / g.nW) % g.nH == g.nH - 1) << 1) | (t % g.nW == g.nW - 1);
+    };
+    const dim3 grid(slots / 32, slots / 32);
+    if (g.BS == 128) scores_fp8_kernel<128><<<grid, 64, 0, st>>>(qp, cls(u), slot_q, kp, cls(v), slot_k, out, slots, g);
+    else             scores_fp8_kernel<32><<<grid, 64, 0, st>>>(qp, cls(u), slot_q, kp, cls(v), slot_k, out, slots, g);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FPS_OK : hip_fail(e, "debug scores launch");
 }
 
+int launch_scores_fp8(const Geom& g, const void* q, const void* k, int bh, int u, int v, float* out,
+                      hipStream_t st) {
+    return launch_scores(g, q, k, bh, u, 0, v, 0, g.TSP, out, st);
+}
+
 int launch_scores_block_fp8(const Geom& g, const void* q, const void* k, int bh, int u, int jq, int v,
                             int jk, float* out, hipStream_t st) {
-    const size_t blk_bytes = (size_t)g.BS * 128;
-    const uint8_t* qp = (const uint8_t*)q + (((size_t)bh * g.M + u) * g.KB + jq) * blk_bytes;
-    const uint8_t* kp = (const uint8_t*)k + (((size_t)bh * g.M + v) * g.KB + jk) * blk_bytes;
-    if (g.BS == 128) scores_fp8_wide_kernel<<<dim3(1, 1), 256, 0, st>>>(qp, kp, out, g.BS);
-    else             scores_fp8_kernel<32><<<dim3(1, 1), 64, 0, st>>>(qp, kp, out, g.BS);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? FPS_OK : hip_fail(e, "debug block scores launch");
+    return launch_scores(g, q, k, bh, u, jq * g.BS, v, jk * g.BS, g.BS, out, st);
 }
 
 int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, const void* k,
@@ -1721,78 +1933,46 @@ int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, c
     a.out_raster = out_raster;
     a.total = g.BH * g.M * g.KB;
     a.chunk = (a.total + 7) / 8;
-    a.partial_cls = 0;
-    for (int c = 0; c < 8; ++c)
-        if (g.TS != g.TSP || ((c & 4) && g.lastT < g.Tt) || ((c & 2) && g.lastH < g.Th) ||
-            ((c & 1) && g.lastW < g.Tw))
-            a.partial_cls |= 1u << c;
-    MaskTables t;
-    memset(&t, 0, sizeof(t));
-    if (g.KB == 1) {
-        for (int c = 0; c < 8; ++c) {
-            bool ok[128];
-            for (int r = 0; r < 128; ++r) ok[r] = r < g.BS && slot_is_token(g, c, r);
-            for (int i = 0; i < 32; ++i) {
-                uint64_t m = 0;
-                const int b = i >> 2, r = i & 3;
-                for (int lane = 0; lane < 64; ++lane)
-                    if (ok[16 * b + 4 * (lane >> 4) + r]) m |= 1ull << lane;
-                t.lane_mask[c][i] = m;
-            }
-            for (int kb = 0; kb < 4; ++kb)
-                for (int r = 0; r < 16; ++r)
-                    for (int h = 0; h < 2; ++h)
-                        if (ok[32 * kb + 8 * (r >> 2) + 4 * h + (r & 3)]) t.pair_code[c][kb] |= 1u << (2 * r + h);
-        }
-    }
     const int grid = a.chunk * 8;
     const bool multi = g.KB > 1;
     const bool vch = vscale == FPS_VSCALE_CHANNEL;
-    // one-block tiles: every work item walks as many key blocks as its window has tiles, and a corner
-    // tile of the grid has the fewest -- one exactly when no axis has both a radius and a neighbour
-    const int corner = (a.rt < g.nT ? a.rt + 1 : g.nT) * (a.rh < g.nH ? a.rh + 1 : g.nH) *
-                       (a.rw < g.nW ? a.rw + 1 : g.nW);
-    const bool one = corner == 1;
-    // tiles of several blocks: a lower bound on the key blocks of any item
-    const bool many = (long long)corner * (g.KB < g.kb_last ? g.KB : g.kb_last) >= 2;
-#define FPS_LAUNCH_FP8(KERNEL_, THREADS_)                                                          \
-    do {                                                                                           \
-        if (multi && many) {                                                                       \
-            if (vch) KERNEL_(true, true, kManyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);         \
-            else     KERNEL_(false, true, kManyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);        \
-        } else if (multi) {                                                                        \
-            if (vch) KERNEL_(true, true, kAnyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);          \
-            else     KERNEL_(false, true, kAnyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);         \
-        } else if (one) {                                                                          \
-            if (vch) KERNEL_(true, false, kOneKeyBlock)<<<grid, THREADS_, 0, st>>>(a, t);          \
-            else     KERNEL_(false, false, kOneKeyBlock)<<<grid, THREADS_, 0, st>>>(a, t);         \
-        } else {                                                                                   \
-            if (vch) KERNEL_(true, false, kManyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);        \
-            else     KERNEL_(false, false, kManyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);       \
-        }                                                                                          \
-    } while (0)
-#define FPS_FP8_WIDE(VCH_, MB_, NK_) attn_fp8_wide_kernel<VCH_, MB_, NK_>
-#define FPS_FP8_SMALL(VCH_, MB_, NK_) attn_fp8_kernel<32, VCH_, MB_, NK_>
-#define FPS_LAUNCH_BF16(KERNEL_, THREADS_)                                                         \
-    do {                                                                                           \
-        if (multi && many) KERNEL_(true, kManyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);         \
-        else if (multi) KERNEL_(true, kAnyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);             \
-        else if (one) KERNEL_(false, kOneKeyBlock)<<<grid, THREADS_, 0, st>>>(a, t);               \
-        else          KERNEL_(false, kManyKeyBlocks)<<<grid, THREADS_, 0, st>>>(a, t);             \
-    } while (0)
-#define FPS_BF16_WIDE(MB_, NK_) attn_bf16_wide_kernel<MB_, NK_>
-#define FPS_BF16_SMALL(MB_, NK_) attn_bf16_kernel<32, MB_, NK_>
-    if (prec == FPS_PREC_FP8) {
-        if (g.BS == 128) FPS_LAUNCH_FP8(FPS_FP8_WIDE, 256); else FPS_LAUNCH_FP8(FPS_FP8_SMALL, 64);
+    if (g.BS == 128) {
+        if (prec == FPS_PREC_BF16) {
+            if (multi) attn_bf16_wide_kernel<true><<<grid, 256, 0, st>>>(a);
+            else       attn_bf16_wide_kernel<false><<<grid, 256, 0, st>>>(a);
+        } else if (vch) {
+            if (multi) attn_fp8_wide_kernel<true, true><<<grid, 256, 0, st>>>(a);
+            else       attn_fp8_wide_kernel<true, false><<<grid, 256, 0, st>>>(a);
+        } else {
+            if (multi) attn_fp8_wide_kernel<false, true><<<grid, 256, 0, st>>>(a);
+            else       attn_fp8_wide_kernel<false, false><<<grid, 256, 0, st>>>(a);
+        }
     } else {
-        if (g.BS == 128) FPS_LAUNCH_BF16(FPS_BF16_WIDE, 256); else FPS_LAUNCH_BF16(FPS_BF16_SMALL, 64);
-    }
-#undef FPS_LAUNCH_FP8
-#undef FPS_FP8_WIDE
-#undef FPS_FP8_SMALL
-#undef FPS_LAUNCH_BF16
-#undef FPS_BF16_WIDE
+        // one-block tiles: every work item walks as many key blocks as its window has tiles, and a
+        // corner tile of the grid has the fewest -- one exactly when no axis has both a radius and a
+        // neighbour; tiles of several blocks: a lower bound on the key blocks of any item
+        const int corner = (a.rt < g.nT ? a.rt + 1 : g.nT) * (a.rh < g.nH ? a.rh + 1 : g.nH) *
+                           (a.rw < g.nW ? a.rw + 1 : g.nW);
+        const bool one = corner == 1;
+        const bool many = corner * g.KBS >= 2;
+#define FPS_LAUNCH_SMALL(KERNEL_)                                                                  \
+        do {                                                                                       \
+            if (multi && many) KERNEL_(true, kManyKeyBlocks)<<<grid, 64, 0, st>>>(a);              \
+            else if (multi) KERNEL_(true, kAnyKeyBlocks)<<<grid, 64, 0, st>>>(a);                  \
+            else if (one) KERNEL_(false, kOneKeyBlock)<<<grid, 64, 0, st>>>(a);                    \
+            else          KERNEL_(false, kManyKeyBlocks)<<<grid, 64, 0, st>>>(a);                  \
+        } while (0)
+#define FPS_BF16_SMALL(MB_, NK_) attn_bf16_kernel<32, MB_, NK_>
+#define FPS_FP8_SMALL(MB_, NK_) attn_fp8_kernel<32, false, MB_, NK_>
+#define FPS_FP8_SMALL_VCH(MB_, NK_) attn_fp8_kernel<32, true, MB_, NK_>
+        if (prec == FPS_PREC_BF16) FPS_LAUNCH_SMALL(FPS_BF16_SMALL);
+        else if (vch) FPS_LAUNCH_SMALL(FPS_FP8_SMALL_VCH);
+        else FPS_LAUNCH_SMALL(FPS_FP8_SMALL);
+#undef FPS_LAUNCH_SMALL
 #undef FPS_BF16_SMALL
+#undef FPS_FP8_SMALL
+#undef FPS_FP8_SMALL_VCH
+    }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FPS_OK : hip_fail(e, "attention launch");
 }

@@ -4,12 +4,14 @@
 
 namespace fps {
 
-// Where a block of BS slots sits: its head, the grid origin of its SUB-TILE and its first slot
+// Where a block of BS packed slots sits: its tile, the real box of its SUB-TILE and its first slot
 // within the sub-tile.  Computed once per workgroup (the divisions are by run-time values).
 struct BlockOrigin {
-    long long bh;
-    int t0, h0, w0;      // grid coordinates of the sub-tile's first token
-    int slot0;           // first in-sub-tile slot of the block
+    RealBox box;
+    long long tile_lin;  // bh * M + u
+    int slot_base;       // first tiled slot of the sub-tile within its tile
+    long long raster0;   // raster token index of the sub-tile's first token
+    int slot0;           // first in-sub-tile packed slot of the block
 };
 __device__ __forceinline__ BlockOrigin block_origin(const Geom& g, int blk) {
     BlockOrigin o;
@@ -20,27 +22,24 @@ __device__ __forceinline__ BlockOrigin block_origin(const Geom& g, int blk) {
     const int u = tile_lin - bh * g.M;
     const int ut = u / (g.nW * g.nH), rem = u - ut * (g.nW * g.nH);
     const int uh = rem / g.nW, uw = rem - uh * g.nW;
-    const int st = s / (g.nsH * g.nsW), srem = s - st * (g.nsH * g.nsW);
-    const int sh = srem / g.nsW, sw = srem - sh * g.nsW;
-    o.bh = bh;
-    o.t0 = ut * g.Tt + st * g.Qt; o.h0 = uh * g.Th + sh * g.Qh; o.w0 = uw * g.Tw + sw * g.Qw;
+    o.box = real_box(g, ((ut == g.nT - 1) << 2) | ((uh == g.nH - 1) << 1) | (uw == g.nW - 1), s);
+    o.tile_lin = tile_lin;
+    o.slot_base = s * g.QSP;
+    o.raster0 = (((long long)bh * g.T + ut * g.Tt + o.box.o.t0) * g.H + uh * g.Th + o.box.o.h0) * g.W +
+                uw * g.Tw + o.box.o.w0;
     return o;
 }
 
-// The 16 uint4 (256 bytes) of the bf16 row of the token in slot r of block `blk`.  TILED input:
-// blocks are contiguous.  RASTER input: the token's (t,h,w) is recovered from the sub-tile origin
-// and the in-sub-tile slot; padding slots return nullptr.
+// The 16 uint4 (256 bytes) of the bf16 row of the token in packed slot r of the block with origin o,
+// in a TILED or RASTER input; nullptr for padding.
 template <bool RASTER>
-__device__ __forceinline__ const uint4* token_row(const uint4* x, const Geom& g, const BlockOrigin& o,
-                                                  int blk, int r) {
-    if (!RASTER) return x + ((long long)blk * g.BS + r) * 16;
-    const int slot = o.slot0 + r;
-    if (slot >= g.QS) return nullptr;                    // slots past the sub-tile's tokens are padding
-    const int rt = div_by_recip(slot, g.inv_qplane), rem = slot - rt * (g.Qh * g.Qw);
-    const int rh = div_by_recip(rem, g.inv_qw), rw = rem - rh * g.Qw;
-    const int t = o.t0 + rt, h = o.h0 + rh, w = o.w0 + rw;
-    if (t >= g.T || h >= g.H || w >= g.W) return nullptr;
-    return x + ((((o.bh * g.T + t) * g.H + h) * (long long)g.W + w) * 16);
+__device__ __forceinline__ const uint4* token_row(const uint4* x, const Geom& g, const BlockOrigin& o, int r) {
+    const int k = o.slot0 + r;
+    if (k >= o.box.n) return nullptr;
+    const Offset d = real_token(o.box, k);
+    const long long row = RASTER ? o.raster0 + ((long long)d.t * g.H + d.h) * g.W + d.w
+                                 : o.tile_lin * g.TSP + o.slot_base + (d.t * g.Qh + d.h) * g.Qw + d.w;
+    return x + row * 16;
 }
 
 // max of the 15-bit magnitude patterns of 8 bf16 values (|x| of bf16 orders like that integer),
@@ -105,7 +104,7 @@ __global__ __launch_bounds__(256) void block_amax_kernel(const uint4* __restrict
     uint32_t m = 0;
     const BlockOrigin org = block_origin(g, blockIdx.x);
     for (int c = threadIdx.x; c < g.BS * 16; c += 256) {
-        const uint4* row = token_row<RASTER>(x, g, org, blockIdx.x, c >> 4);
+        const uint4* row = token_row<RASTER>(x, g, org, c >> 4);
         if (row) m = amax_bits16(row[c & 15], m);
     }
     m = block_max_256(m, red);

@@ -87,13 +87,14 @@ int check_shape(const fps_shape* s, Geom* g) {
     g->lastT = s->T - (nT - 1) * s->Tt;
     g->lastH = s->H - (nH - 1) * s->Th;
     g->lastW = s->W - (nW - 1) * s->Tw;
-    // sub-tile layers along t that hold a real plane of a last-along-T tile; within the last such
-    // layer the padding-only blocks form a suffix only if the layer is a single sub-tile
-    const int layers = (g->lastT + qt - 1) / qt;
-    if (g->nsH * g->nsW == 1)
-        g->kb_last = (layers - 1) * kbs + ((g->lastT - (layers - 1) * qt) * qh * qw + bs - 1) / bs;
-    else
-        g->kb_last = layers * g->nsH * g->nsW * kbs;
+    g->gT = (s->T + qt - 1) / qt; g->gH = (s->H + qh - 1) / qh; g->gW = (s->W + qw - 1) / qw;
+    g->cutT = s->T - (g->gT - 1) * qt; g->cutH = s->H - (g->gH - 1) * qh; g->cutW = s->W - (g->gW - 1) * qw;
+    for (int nb = 0; nb < 4; ++nb) g->nb_classes[nb] = 0;
+    for (int c = 0; c < 8; ++c) {
+        const int n = ((c & 4) ? g->cutT : qt) * ((c & 2) ? g->cutH : qh) * ((c & 1) ? g->cutW : qw);
+        if (n >= 128) g->nb_classes[3] |= 1u << c;
+        if (n % 128) g->nb_classes[(n % 128 + 31) / 32 - 1] |= 1u << c;
+    }
     return FPS_OK;
 }
 

@@ -31,9 +31,13 @@ struct Geom {
     // Real planes / rows / columns of the LAST tile along each axis (all others are full).  A
     // tile's boundary class is c = 4*(last along T) + 2*(last along H) + (last along W).
     int lastT, lastH, lastW;
-    // Leading blocks of a last-along-T tile that can hold a real token: the blocks after them
-    // are padding only and are never computed.
-    int kb_last;
+    // The grid in sub-tiles that hold a real token: counts per axis, and for the last one along an
+    // axis its real extent, its tile and its place in the tile.
+    int gT, gH, gW;
+    int cutT, cutH, cutW;
+    // Bit c of nb_classes[nb - 1]: sub-tiles cut along the axes of c (4: T, 2: H, 1: W) have a key
+    // block of nb 32-key sub-blocks (BS = 128).
+    uint32_t nb_classes[4];
 };
 
 // n / d for 0 <= n < 2^21, given inv_d = 1.0f / d correctly rounded.  Exact: (n + 1/2) / d is at
@@ -75,10 +79,45 @@ __host__ __device__ inline bool sub_slot_is_token(const Geom& g, int c, const Su
     return sub_slot_coords(g, o, rr, &rt, &rh, &rw) && coords_in_class(g, c, rt, rh, rw);
 }
 
-// slot r (0 .. TSP-1) of a tile of boundary class c holds a real token
-__host__ __device__ inline bool slot_is_token(const Geom& g, int c, int r) {
-    const int s = r / g.QSP;
-    return sub_slot_is_token(g, c, sub_tile_origin(g, s), r - s * g.QSP);
+// Packed operands hold the REAL tokens of a sub-tile first, in raster order of the sub-tile's real
+// box (the sub-tile cut at the grid's edge), then padding: packed slot k < n of a sub-tile of real
+// extent (et, eh, ew), n = et*eh*ew, is its token (k / (eh*ew), k / ew % eh, k % ew).  The padding
+// of a cut tile is thus one run at the end, whole matrix-instruction blocks of which are never
+// computed, instead of being spread over every block (a tile cut along W has padding in every row).
+// Tiled tensors keep the order of fps.h; for a sub-tile that is not cut the two orders agree.
+struct RealBox {
+    SubTile o;               // in-tile origin of the sub-tile
+    int eh, ew, plane, n;    // real rows and columns, eh*ew, real tokens (0 if none)
+    float inv_plane, inv_w;  // for div_by_recip
+};
+__host__ __device__ inline int real_tokens(const Geom& g, int c, const SubTile& o) {
+    const int et = ((c & 4) ? g.lastT : g.Tt) - o.t0, eh = ((c & 2) ? g.lastH : g.Th) - o.h0,
+              ew = ((c & 1) ? g.lastW : g.Tw) - o.w0;
+    if (et <= 0 || eh <= 0 || ew <= 0) return 0;
+    return (et < g.Qt ? et : g.Qt) * (eh < g.Qh ? eh : g.Qh) * (ew < g.Qw ? ew : g.Qw);
+}
+__host__ __device__ inline RealBox real_box(const Geom& g, int c, int s) {
+    RealBox b;
+    b.o = sub_tile_origin(g, s);
+    const int eh = ((c & 2) ? g.lastH : g.Th) - b.o.h0, ew = ((c & 1) ? g.lastW : g.Tw) - b.o.w0;
+    b.n = real_tokens(g, c, b.o);
+    b.eh = b.n ? (eh < g.Qh ? eh : g.Qh) : 1;
+    b.ew = b.n ? (ew < g.Qw ? ew : g.Qw) : 1;
+    b.plane = b.eh * b.ew;
+    b.inv_plane = 1.0f / (float)b.plane;
+    b.inv_w = 1.0f / (float)b.ew;
+    return b;
+}
+// offset of real token k of the box from the sub-tile's origin
+struct Offset { int t, h, w; };
+__host__ __device__ inline Offset real_token(const RealBox& b, int k) {
+    const int t = div_by_recip(k, b.inv_plane), rem = k - t * b.plane;
+    const int h = div_by_recip(rem, b.inv_w);
+    return Offset{t, h, rem - h * b.ew};
+}
+// packed slot within the sub-tile of in-tile coordinates inside its box (inverse of real_token)
+__host__ __device__ inline int packed_slot(const RealBox& b, int rt, int rh, int rw) {
+    return (rt - b.o.t0) * b.plane + (rh - b.o.h0) * b.ew + (rw - b.o.w0);
 }
 
 void set_error(const char* fmt, ...);

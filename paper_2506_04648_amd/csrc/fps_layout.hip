@@ -1,13 +1,15 @@
 // Layout kernels of libfps: raster <-> tile order (Sec. 3.2 step (1)), the BF16 operand packing,
 // and the debug unpacking of packed E4M3 tensors.  All of them are pure data movement.
 //
-// Packed operand layouts, per block of BS = 128 or 32 slots (a tile is one or several blocks).
+// Packed operand layouts, per block of BS = 128 or 32 packed slots (a tile is one or several blocks;
+// packed slots hold the real tokens of a sub-tile first, see real_box in fps_internal.h).  K and V
+// of a 128-slot block are four consecutive 32-key sub-blocks.
 // E4M3, BS = 128 -- operands of v_mfma_f32_32x32x64_f8f6f4; lane = 32h + n, n the row of the 32-row
 // operand block, h the half of the 64 contraction slots of one step:
 //   Q : row-major [token][128]                                              (BS*128 bytes)
 //   K : 16-byte chunk (((kb*2 + ks)*2 + e)*64 + lane) = K[32kb + n][64ks + 32h + 16e + 0..15]
-//   V : 16-byte chunk (((db*2 + j)*2 + e)*64 + lane), byte jj = V[key][32db + n] with
-//       key = 32(2j + e) + 8(jj/4) + 4h + jj%4
+//   V : 16-byte chunk ((kb*4 + db)*64 + lane), byte jj = V[key][32db + n] with
+//       key = 32kb + 8(jj/4) + 4h + jj%4
 //   The accumulator of S^T = K Q^T for key block kb holds, in lane (n,h) and register r, query n and
 //   key 32kb + 8(r/4) + 4h + r%4; the 32 weights of key blocks 2j and 2j+1 of a lane are therefore,
 //   unchanged, its 32 contraction slots of step j of the PV product O^T = V^T P^T.
@@ -18,7 +20,7 @@
 // BF16, BS = 128 -- operands of the 32x32x16 instructions; lane = 32h + n:
 //   Q : row-major [token][128]                                              (BS*256 bytes)
 //   K : 16-byte chunk ((kb*8 + ks)*64 + lane) = K[32kb + n][16ks + 8h + 0..7]
-//   V : 16-byte chunk ((db*8 + kk)*64 + lane), element el = V[key][32db + n] with
+//   V : 16-byte chunk ((kk*4 + db)*64 + lane), element el = V[key][32db + n] with
 //       key = 32(kk/2) + 8(2(kk%2) + el/4) + 4h + el%4 (the key order of the 32x32 accumulator),
 //       stored as fp16 after an exact power-of-two scaling per scale group (see pack_bf16_kernel)
 // BF16, BS = 32 -- 16x16x32 instructions; lane = 16g + n:
@@ -98,7 +100,7 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
     constexpr int kChunks = BS * 16;
     const BlockOrigin org = block_origin(g, blockIdx.x);
     auto load = [&](int c) {                               // chunk c = 8 channels (c & 15) of slot c >> 4
-        const uint4* row = token_row<RASTER>(in, g, org, blockIdx.x, c >> 4);
+        const uint4* row = token_row<RASTER>(in, g, org, c >> 4);
         return row ? row[c & 15] : make_uint4(0, 0, 0, 0);
     };
     if (role == FPS_ROLE_Q) {
@@ -140,7 +142,7 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
         const int lane = c & 63;
         union { uint4 v; _Float16 h[8]; } o;
         if (BS == 128) {
-            const int kk = (c >> 6) & 7, db = c >> 9, hh = lane >> 5, n = lane & 31;
+            const int kk = c >> 8, db = (c >> 6) & 3, hh = lane >> 5, n = lane & 31;
 #pragma unroll
             for (int el = 0; el < 8; ++el) {
                 const int key = 32 * (kk >> 1) + 8 * (2 * (kk & 1) + (el >> 2)) + 4 * hh + (el & 3);
@@ -160,17 +162,28 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
 }
 
 // ---- debug unpack of E4M3 tensors ---------------------------------------------------------------
+// one workgroup per block of BS slots of the tile-ordered output; padding slots become zero
 template <int BS>
 __global__ __launch_bounds__(256) void unpack_q8_kernel(const uint8_t* __restrict__ in,
-                                                        uint8_t* __restrict__ out, int role) {
-    const long long blk = blockIdx.x;
-    const uint8_t* src = in + blk * (BS * 128);
-    uint8_t* dst = out + blk * (BS * 128);
+                                                        uint8_t* __restrict__ out, int role, Geom g) {
+    const int blk = blockIdx.x, group = blk / g.KBS;
+    const int slot0 = (blk - group * g.KBS) * BS, s = group % g.NS, u = (group / g.NS) % g.M;
+    const int uw = u % g.nW, uh = (u / g.nW) % g.nH, ut = u / (g.nW * g.nH);
+    const int cls = ((ut == g.nT - 1) << 2) | ((uh == g.nH - 1) << 1) | (uw == g.nW - 1);
+    const RealBox box = real_box(g, cls, s);
+    const uint8_t* src = in + (long long)group * g.QSP * 128;      // the sub-tile's packed blocks
+    uint8_t* dst = out + (long long)blk * (BS * 128);
     for (int i = threadIdx.x; i < BS * 128; i += 256) {
-        const int j = i >> 7, c = i & 127;                 // token, channel of the row-major output
+        const int c = i & 127;                             // channel
+        int rt, rh, rw;
+        if (!sub_slot_coords(g, box.o, slot0 + (i >> 7), &rt, &rh, &rw) || !coords_in_class(g, cls, rt, rh, rw)) {
+            dst[i] = 0;
+            continue;
+        }
+        const int k = packed_slot(box, rt, rh, rw), j = k & (BS - 1);   // packed slot, within its block
         int off;
         if (role == FPS_ROLE_Q) {
-            off = i;
+            off = j * 128 + c;
         } else if (role == FPS_ROLE_K) {
             if (BS == 128) {
                 const int kb = j >> 5, n = j & 31, ks = c >> 6, h = (c >> 5) & 1, e = (c >> 4) & 1;
@@ -182,13 +195,13 @@ __global__ __launch_bounds__(256) void unpack_q8_kernel(const uint8_t* __restric
         } else if (BS == 128) {                            // inverse of the wide key order
             const int db = c >> 5, n = c & 31;
             const int kb = j >> 5, rem = j & 31, h = (rem >> 2) & 1, jj = 4 * (rem >> 3) + (rem & 3);
-            off = (((db * 2 + (kb >> 1)) * 2 + (kb & 1)) * 64 + 32 * h + n) * 16 + jj;
+            off = ((kb * 4 + db) * 64 + 32 * h + n) * 16 + jj;
         } else {
             const int cb = c >> 4, n = c & 15;
-            const int gg = (j >> 2) & 3, s = 4 * (j >> 4) + (j & 3);   // inverse of key_of_slot
-            off = (cb * 64 + gg * 16 + n) * 8 + s;
+            const int gg = (j >> 2) & 3, s4 = 4 * (j >> 4) + (j & 3);  // inverse of key_of_slot
+            off = (cb * 64 + gg * 16 + n) * 8 + s4;
         }
-        dst[i] = src[off];
+        dst[i] = src[(long long)(k - j) * 128 + off];
     }
 }
 
@@ -248,8 +261,8 @@ int launch_pack_bf16(const Geom& g, const void* x, int raster, int role, void* x
 
 int launch_unpack_q8(const Geom& g, const void* xq, int role, uint8_t* out, hipStream_t st) {
     const int blocks = g.BH * g.M * g.KB;
-    if (g.BS == 128) unpack_q8_kernel<128><<<blocks, 256, 0, st>>>((const uint8_t*)xq, out, role);
-    else             unpack_q8_kernel<32><<<blocks, 256, 0, st>>>((const uint8_t*)xq, out, role);
+    if (g.BS == 128) unpack_q8_kernel<128><<<blocks, 256, 0, st>>>((const uint8_t*)xq, out, role, g);
+    else             unpack_q8_kernel<32><<<blocks, 256, 0, st>>>((const uint8_t*)xq, out, role, g);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FPS_OK : hip_fail(e, "unpack_q8 launch");
 }

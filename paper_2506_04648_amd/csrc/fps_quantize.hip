@@ -7,11 +7,9 @@
 namespace fps {
 
 __device__ __forceinline__ int key_of_slot_q(int g, int s) { return 16 * (s >> 2) + 4 * g + (s & 3); }
-// 128-slot blocks (32x32x64 MFMA): the key behind byte jj of 16-byte half e of contraction step j in
-// lane half h -- where the accumulator of S^T = K Q^T left that key's weight
-__device__ __forceinline__ int key_of_slot_wide(int j, int e, int h, int jj) {
-    return 32 * (2 * j + e) + 8 * (jj >> 2) + 4 * h + (jj & 3);
-}
+// 128-slot blocks (32x32x64 MFMA): the key, within its 32-key sub-block, behind byte jj of the
+// 16-byte chunk of lane half h -- where the accumulator of S^T = K Q^T left that key's weight
+__device__ __forceinline__ int key_of_slot_wide(int h, int jj) { return 8 * (jj >> 2) + 4 * h + (jj & 3); }
 
 // Quotient x/s prepared for the hardware's round-to-nearest-even conversion so that the final code
 // equals the rounding of the EXACT quotient: the correctly rounded float quotient can land exactly
@@ -83,12 +81,12 @@ template <int BS>
 __device__ __forceinline__ void write_v_block(const uint8_t* stage, uint4* dst, int tid) {
     if (BS == 128) {
         for (int c = tid; c < BS * 8; c += 256) {
-            const int lane = c & 63, e = (c >> 6) & 1, j = (c >> 7) & 1, db = c >> 8;
+            const int lane = c & 63, db = (c >> 6) & 3, kb = c >> 8;
             const int h = lane >> 5, n = lane & 31;
             union { uint4 v; uint8_t b[16]; } o;
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj)
-                o.b[jj] = stage[key_of_slot_wide(j, e, h, jj) * 128 + 32 * db + n];
+                o.b[jj] = stage[(32 * kb + key_of_slot_wide(h, jj)) * 128 + 32 * db + n];
             dst[c] = o.v;
         }
     } else {
@@ -130,7 +128,7 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const uint4* __rest
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const int unit = tid + 256 * i;          // token = unit >> 3, 16-channel group = unit & 7
-            const uint4* row = token_row<RASTER>(x, g, org, first + kb, unit >> 3);
+            const uint4* row = token_row<RASTER>(x, g, org, unit >> 3);
             lo[kb][i] = make_uint4(0, 0, 0, 0);
             hi[kb][i] = lo[kb][i];
             if (row) { lo[kb][i] = row[2 * (unit & 7)]; hi[kb][i] = row[2 * (unit & 7) + 1]; }
@@ -194,7 +192,7 @@ __global__ __launch_bounds__(256) void channel_amax_kernel(const uint4* __restri
     uint32_t m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const BlockOrigin org = block_origin(g, blockIdx.x);
     for (int r = tid >> 4; r < g.BS; r += 16) {
-        const uint4* row = token_row<RASTER>(x, g, org, blockIdx.x, r);
+        const uint4* row = token_row<RASTER>(x, g, org, r);
         if (!row) continue;
         const uint4 v = row[c8];
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -229,7 +227,7 @@ __global__ __launch_bounds__(256) void quantize_channels_kernel(const uint4* __r
     const BlockOrigin org = block_origin(g, blockIdx.x);
     for (int unit = tid; unit < BS * 8; unit += 256) {       // 16 channels of one token
         const int r = unit >> 3, c16 = unit & 7;
-        const uint4* row = token_row<RASTER>(x, g, org, blockIdx.x, r);
+        const uint4* row = token_row<RASTER>(x, g, org, r);
         uint4 lo = make_uint4(0, 0, 0, 0), hi = lo;
         if (row) { lo = row[2 * c16]; hi = row[2 * c16 + 1]; }
         const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};

@@ -313,6 +313,27 @@ def test_attention_small_shapes(prec, grid, tile, window):
         gu.assert_parity(st, f"{grid} {tile} {window} head {h}")
 
 
+@pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
+@pytest.mark.parametrize("tile,rest", [((1, 1, 128), r) for r in (1, 31, 32, 33, 64, 65, 96, 97, 127)] +
+                         [((1, 2, 128), r) for r in (1, 48, 63, 64, 65, 127)])
+def test_cut_tiles_at_the_edges_of_sub_blocks(prec, tile, rest):
+    """A tile cut by the grid's edge holds its real tokens first and is walked by 32-key sub-blocks:
+    every count of them, one token to either side of each boundary, with one and two blocks a tile,
+    for keys and for query rows, in both output layouts."""
+    import torch
+    say("cut tiles", prec, tile, rest)
+    w = dataclasses.replace(synth.TINY, grid=(2, 2 * tile[1] + 1, 128 + rest), tile=tile, window=(3, 3, 3), heads=1,
+                            n_outlier=3, config_id=31)
+    run = gu.GpuRun(w)
+    out = run.attn(prec)
+    st = gu.compare_head(run, out, 0, prec, w.window)
+    say("  ", st)
+    gu.assert_parity(st, f"{tile} rest {rest}")
+    assert torch.equal(run.attn(prec, raster_out=True), fps.tile_unorder(run.shape, out))
+    if prec == fps.PREC_FP8:
+        _check_quantize(run, [0], f"cut {tile} {rest}")
+
+
 @pytest.mark.parametrize("grid,tile,window", [((4, 16, 16), (2, 4, 4), (1, 3, 3)),
                                               ((2, 13, 40), (1, 8, 16), (3, 3, 3)),
                                               ((3, 13, 20), (2, 8, 16), (3, 3, 3))])
