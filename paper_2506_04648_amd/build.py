@@ -7,7 +7,8 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
-SOURCES = ("fps_host.cpp", "fps_layout.hip", "fps_quantize.hip", "fps_attn.hip", "fps_issue_mix.hip")
+SOURCES = ("fps_host.cpp", "fps_layout.hip", "fps_quantize.hip", "fps_attn.hip",
+           "fps_attn_fp8.hip", "fps_attn_bf16.hip", "fps_issue_mix.hip")
 OUT = os.path.join(_HERE, "libfps.so")
 
 
@@ -23,6 +24,7 @@ def build_lib(verbose: bool = False) -> str:
            # no NaN ever enters the kernels (inputs are finite, masked scores are -inf, never inf-inf):
            # lets fmax/fmin compile without the canonicalising v_max(x,x) in front of every operand
            "-fno-honor-nans",
+           "-parallel-jobs=8",
            "-o", OUT] + os.environ.get("FPS_EXTRA_HIPCC_FLAGS", "").split() \
           + [os.path.join(CSRC, s) for s in SOURCES]
     res = subprocess.run(cmd, capture_output=True, text=True)

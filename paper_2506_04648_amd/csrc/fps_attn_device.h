@@ -1,0 +1,418 @@
+// Sliding-tile attention forward (Eq. 2-3, Sec. 3.2 aggregation; Algorithm 1 steps 4-5): what the FP8
+// and the BF16 kernel share.
+//
+// A work item is one query block of a tile: W sub-blocks of 32 packed slots, one wave each.  The kernel
+// walks the box of key tiles given by Eq. 2 -- tile pairs outside the box are never scheduled -- in key
+// blocks of at most SB sub-blocks of 32 keys, staged through LDS.  A key block lies in one scale
+// group (a tile, or a quantisation sub-tile):
+//   SB = 4, W = 4        groups of more than 96 tokens; a group is one or several 128-slot blocks
+//   SB = 1, 2, 3         groups of at most 32, 64, 96 tokens, one block each.  W = SB where the tile is
+//                        one group, so that a workgroup is one tile and walks its window exactly; a tile
+//                        of several groups gives its workgroups four of its sub-blocks, or SB where it
+//                        has no multiple of four.  (On 16x16 instructions, one wave and 32 keys at a
+//                        time, the whole path took 1552 instead of 957 us for tile (3,4,4), window 3x5x7 on
+//                        21x30x52 x 12 heads, and 3949 instead of 2664 us for 64-token sub-tiles of (2,8,16)
+//                        tiles, window 3x3x3, x 24 heads.)
+// MB = true: a tile is several key blocks.
+//
+// Scores are produced transposed, S^T = K Q^T, on the 32x32 matrix instructions, so that a lane's
+// accumulator holds one query row and a fixed set of keys: lane (n, h) = lane & 31, lane >> 5 holds
+// query n; of a 32-key sub-block the keys 8(r/4) + 4h + r%4, r = 0..15; of a 32-channel output block
+// the channels of the same pattern.  The other lane of the row is lane n + 32.  After the softmax
+// those registers are, unchanged, the second operand of the PV product O^T = V^T P^T (see the packed
+// layouts in fps_layout.hip).
+//
+// Softmax is online in base 2 with an integer row reference m (ceil of the running row maximum):
+// P = 2^(S' - m) <= 1, rescaling by 2^(m_old - m_new) is exact, and the E4M3 rounding of 448*P
+// does not depend on the order in which key tiles arrive (apart from values in the subnormal
+// range of the format).  The denominator accumulates the unrounded P.
+#pragma once
+#include "fps_internal.h"
+
+#include <type_traits>
+
+namespace fps {
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+struct AttnArgs {
+    const uint8_t* q;
+    const uint8_t* k;
+    const uint8_t* v;
+    const float* sq;
+    const float* sk;
+    const float* sv;
+    void* out;
+    uint8_t* visited;
+    Geom g;
+    int rt, rh, rw;        // window radii in tiles
+    int edge_shift;        // 1: clamp the window centre into the grid instead of truncating
+    int out_f32;
+    int out_raster;        // output in raster order (real tokens only) instead of tile order
+    int qblocks;           // query blocks (work items) of a tile
+    int chunk;             // work items per XCD
+    int total;             // BH * M * qblocks
+};
+
+// Every lambda of the kernels captures the accumulators by reference; left to the inliner's cost
+// model a large one stays a call, which forces everything it captures into private memory.
+#define FPS_INLINE __attribute__((always_inline))
+
+constexpr float kLog2eOverSqrtD = 0.12751743f;   // log2(e) / sqrt(128)
+constexpr float kLog2Of448 = 8.8073549f;          // log2(448)
+constexpr float kFp16PScaleLog2 = 14.0f;          // BF16 mode holds 2^14 * P in fp16
+constexpr float kMaxDrift = 64.0f;                // largest m - m_base before O and l are moved to a new reference
+constexpr int kStoreRegionBytes = 16 * (512 + 16);  // per-wave LDS region of the output transpose
+
+// Scales are read-only for the whole launch and indexed uniformly: reading them through the constant
+// address space lets the compiler use scalar loads, which do not queue behind the vector-memory
+// traffic that stages the K/V tiles.
+typedef const __attribute__((address_space(4))) float* const_f32_ptr;
+__device__ __forceinline__ float load_uniform(const float* p, size_t i) {
+    return ((const_f32_ptr)(uintptr_t)p)[i];
+}
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// two floats -> two bf16 (round to nearest even) in one dword; gfx950 converts in hardware
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{lo, hi}, v2bf));
+}
+
+// Work item of this workgroup: query block jq of tile u of head bh.  Workgroups are dealt round-robin to
+// the 8 XCDs by the hardware; giving XCD x the contiguous range [x*chunk, (x+1)*chunk) of items keeps
+// the key tiles of neighbouring query tiles of one head in that XCD's L2.
+__device__ __forceinline__ bool work_item(const AttnArgs& a, int* bh, int* u, int* jq) {
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int wi = xcd * a.chunk + slot;
+    if (slot >= a.chunk || wi >= a.total) return false;
+    const int tile_lin = wi / a.qblocks;
+    *jq = wi - tile_lin * a.qblocks;
+    *bh = tile_lin / a.g.M;
+    *u = tile_lin - *bh * a.g.M;
+    return true;
+}
+
+template <typename G_>
+__device__ __forceinline__ int tile_class(const G_& g, int t, int h, int w) {
+    return ((t == g.nT - 1) << 2) | ((h == g.nH - 1) << 1) | (w == g.nW - 1);
+}
+
+__device__ __forceinline__ v16f zero16() {
+    v16f z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    return z;
+}
+// Reductions over the two lanes n, n + 32 that hold one query row: gfx950 swaps halves of 32 lanes
+// between two registers at VALU speed.
+__device__ __forceinline__ float max_over_row_pair(float t) {          // lanes n and n + 32
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+    return __builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum_over_row_pair(float t) {
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// x if bit `idx` of the lane's word `bits` is set, otherwise -inf: two vector instructions (a
+// sign-extended one-bit field, a bitwise select) and no compare, so a run of them needs no scalar
+// registers for compare results
+__device__ __forceinline__ float keep_if_bit(float x, uint32_t bits, int idx) {
+    const uint32_t m = (uint32_t)(-(int)((bits >> idx) & 1u));
+    return __uint_as_float((__float_as_uint(x) & m) | (0xFF800000u & ~m));
+}
+// A key block whose last 16-key half is cut: of registers 8e .. 8e+7 of s, which hold the half, those of
+// its keys from n on become -inf.
+__device__ __forceinline__ void mask_cut_half(v16f& s, int e, int n, int h) {
+    const uint32_t bits = ((1u << n) - 1u) >> (4 * h);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) s[8 * e + r] = keep_if_bit(s[8 * e + r], bits, 8 * (r >> 2) + (r & 3));
+}
+
+// The 32 query rows of a wave: packed slots k0 .. k0 + 31 of one scale group, of which the first `rows`
+// (at most 32; none if <= 0) are real tokens.
+struct QueryRows {
+    RealBox box;
+    int k0, rows;
+    int group;               // the scale group within the tile
+    int slot_base;           // first tiled slot of the group within its tile
+    size_t tile_lin;         // bh * M + u
+    size_t raster0;          // raster token index of the group's first token
+    // sub-block qs of the tile; sbg: sub-blocks per group
+    __device__ __forceinline__ void init(const Geom& G, int bh, int u, int cls, int ut, int uh, int uw, int qs, int sbg) {
+        group = qs / sbg;
+        box = real_box(G, cls, group);
+        k0 = 32 * (qs - group * sbg);
+        rows = box.n - k0;
+        slot_base = group * G.QSP;
+        tile_lin = (size_t)bh * G.M + u;
+        raster0 = (((size_t)bh * G.T + (ut * G.Tt + box.o.t0)) * G.H + (uh * G.Th + box.o.h0)) * G.W +
+                  (uw * G.Tw + box.o.w0);
+    }
+    // output row of row r (0 <= r < rows)
+    __device__ __forceinline__ size_t out_row(const AttnArgs& a, int r) const {
+        const Offset d = real_token(box, k0 + r);
+        if (a.out_raster) return raster0 + ((size_t)d.t * a.g.H + d.h) * a.g.W + d.w;
+        return tile_lin * a.g.TSP + slot_base + ((d.t * a.g.Qh + d.h) * a.g.Qw + d.w);
+    }
+};
+
+// A tile-ordered output has rows for padding slots, and they are zero: each wave clears those among its
+// 32 slots.
+__device__ __forceinline__ void zero_padding_rows(const AttnArgs& a, const QueryRows& q, int cls, int lane) {
+    if (a.out_raster || q.box.n == a.g.QSP) return;
+    const int row_shift = a.out_f32 ? 5 : 4;                // log2 of the 16-byte chunks of a row
+    uint4* dst = reinterpret_cast<uint4*>(a.out) + ((q.tile_lin * a.g.TSP + q.slot_base + q.k0) << row_shift);
+    for (int i = lane; i < (32 << row_shift); i += 64)
+        if (!sub_slot_is_token(a.g, cls, q.box.o, q.k0 + (i >> row_shift))) dst[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Some wave of query block jq has a real row.
+template <int SB, int W, bool MB>
+__device__ __forceinline__ bool any_real_row(const Geom& G, int cls, int jq, int sbg) {
+    if (!MB) return true;                                  // the block is the tile
+    for (int w = 0; w < W; ++w) {
+        const int qs = jq * W + w, group = qs / sbg;
+        if (real_tokens(G, cls, sub_tile_origin(G, group)) > 32 * (qs - group * sbg)) return true;
+    }
+    return false;
+}
+
+// Epilogue: O = acc * inv (times the per-channel V scale if any), fp32 or bf16, tile or raster order.  A
+// lane holds 4 channels of one row per accumulator quarter, so direct stores would be 8- or 16-byte
+// pieces of many rows; instead each wave transposes its rows through a private LDS region, 16 rows a
+// pass (rows n < 16 are held by lanes 0..15 and 32..47), and writes whole rows (256 or 512 contiguous
+// bytes).  The caller guarantees that no wave still reads the LDS buffers.
+__device__ __forceinline__ void store_rows(const AttnArgs& a, const QueryRows& q, int lane, const v16f (&acc)[4],
+                                           float inv, uint8_t* wave_lds, const float* ch_scale = nullptr) {
+    const int h = lane >> 5, n = lane & 31;
+    const int row_bytes = a.out_f32 ? 512 : 256;
+    const int pitch = row_bytes + 16;                      // padding keeps the column writes off one bank
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        if ((n >> 4) == pass) {
+            const int rr = n & 15;
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const int col = 32 * db + 8 * q4 + 4 * h;
+                    v4f o = v4f{acc[db][4 * q4], acc[db][4 * q4 + 1], acc[db][4 * q4 + 2], acc[db][4 * q4 + 3]} * inv;
+                    if (ch_scale) o *= *reinterpret_cast<const v4f*>(ch_scale + col);
+                    if (a.out_f32) {
+                        *reinterpret_cast<v4f*>(wave_lds + rr * pitch + col * 4) = o;
+                    } else {
+                        uint2 pk;
+                        pk.x = pack_bf16x2(o[0], o[1]);
+                        pk.y = pack_bf16x2(o[2], o[3]);
+                        *reinterpret_cast<uint2*>(wave_lds + rr * pitch + col * 2) = pk;
+                    }
+                }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int lanes_shift = a.out_f32 ? 5 : 4;
+        const int rows_per_pass = 64 >> lanes_shift;
+        for (int r0 = 0; r0 < 16; r0 += rows_per_pass) {
+            const int r = r0 + (lane >> lanes_shift), chunk = lane & ((1 << lanes_shift) - 1);
+            const int row = pass * 16 + r;
+            const uint4 val = *reinterpret_cast<const uint4*>(wave_lds + r * pitch + chunk * 16);
+            if (row < q.rows)
+                reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(a.out) + q.out_row(a, row) * row_bytes)[chunk] = val;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+__device__ __forceinline__ v8i make_v8i(const uint4& lo, const uint4& hi) {
+    return v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+}
+
+// Linear HBM -> LDS copy of one 16-byte chunk per lane, done by the load unit itself: lane i of the
+// wave deposits its chunk at lds_wave_base + 16 i.  Written as inline assembly so that the
+// compiler's wait-count bookkeeping does not serialise it against LDS reads of OTHER buffers; the
+// kernel waits for it explicitly (s_waitcnt vmcnt(0)) before the barrier that publishes the tile.
+// gsrc is a wave-uniform base (kept in scalar registers), lane_off the lane's byte offset from it.
+// OFF (0, 1024, 2048 or 3072) is the instruction's immediate offset: the hardware adds it to the
+// global address AND to the LDS address, so the four 1 KB pieces of a wave's 4 KB share of a tile
+// need one scalar base each side.
+template <int OFF>
+__device__ __forceinline__ void dma_chunk(const void* gsrc, uint32_t lane_off, uint32_t lds_wave_base) {
+    // both are wave-uniform by construction; say so where the compiler cannot prove it
+    const uint64_t p = reinterpret_cast<uint64_t>(gsrc);
+    gsrc = reinterpret_cast<const void*>(
+        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
+        ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32));
+    lds_wave_base = __builtin_amdgcn_readfirstlane(lds_wave_base);
+    asm volatile("s_mov_b32 m0, %2\n\t"
+                 "s_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:%3"
+                 :
+                 : "v"(lane_off), "s"(gsrc), "s"(lds_wave_base), "n"(OFF)
+                 : "memory", "m0");
+}
+// chunk c of a wave's contiguous share: base moves every four chunks, the rest rides in the offset
+__device__ __forceinline__ void dma_chunk_of(int c, const uint8_t* gsrc_wave, uint32_t lane_off, uint32_t lds_wave) {
+    const uint8_t* gs = gsrc_wave + (c >> 2) * 4096;
+    const uint32_t ld = lds_wave + (c >> 2) * 4096;
+    switch (c & 3) {
+        case 0: dma_chunk<0>(gs, lane_off, ld); break;
+        case 1: dma_chunk<1024>(gs, lane_off, ld); break;
+        case 2: dma_chunk<2048>(gs, lane_off, ld); break;
+        default: dma_chunk<3072>(gs, lane_off, ld); break;
+    }
+}
+
+template <int N> using Count = std::integral_constant<int, N>;
+
+// The kernels walk the key-tile box once per number NH = 2*SB .. 1 of 16-key halves: first every key
+// block that fills its slots, then those of fewer halves, each with a main loop compiled for its NH
+// (score and PV products by 32-key sub-blocks, row maxima and exponentials by halves), so that the
+// padding of tiles cut by the grid's edge, or of tiles that do not fill their blocks, costs no more
+// than the rest of its last half or sub-block.  Only O and the row sums live from one walk to the
+// next; loops that hand over to each other in mid-pipeline need more registers than there are (250
+// to 460 spilled in two such arrangements).  Whole path, walks by sub-blocks against blocks of 128
+// slots with padding in tile order: 21x30x52 x 12 heads, tile (1,8,16), window 3x3x3: FP8 550 -> 514
+// us, BF16 741 -> 664 us; tile (6,8,8) 614 -> 522 us; 21x45x80 x 40 heads, window 5x3x3: 4.59 -> 4.50
+// ms, dense BF16 114.6 -> 110.1 ms.
+//
+// The box is walked in units of scale groups, which a window always takes whole.
+struct KeyBox {
+    int t0, t1, h0, h1, w0, w1;         // first and last key tile of the box, per axis
+    uint32_t classes;                   // bit c: the box has sub-tiles of class c (cut along 4: T, 2: H, 1: W)
+    __device__ __forceinline__ void init(const AttnArgs& a, int ut, int uh, int uw) {
+        const Geom& G = a.g;
+        if (a.edge_shift) {                 // clamp the centre into [r, n-1-r]; an axis not longer than
+            // the window has no such centre and is kept whole by the truncation below with u = n/2
+            ut = G.nT > 2 * a.rt + 1 ? min(max(ut, a.rt), G.nT - 1 - a.rt) : G.nT / 2;
+            uh = G.nH > 2 * a.rh + 1 ? min(max(uh, a.rh), G.nH - 1 - a.rh) : G.nH / 2;
+            uw = G.nW > 2 * a.rw + 1 ? min(max(uw, a.rw), G.nW - 1 - a.rw) : G.nW / 2;
+        }
+        t0 = max(0, ut - a.rt); h0 = max(0, uh - a.rh); w0 = max(0, uw - a.rw);
+        t1 = min(G.nT - 1, ut + a.rt); h1 = min(G.nH - 1, uh + a.rh); w1 = min(G.nW - 1, uw + a.rw);
+        const bool et = has_cut(t1, G.nT, G.cutT, G.Qt), eh = has_cut(h1, G.nH, G.cutH, G.Qh),
+                   ew = has_cut(w1, G.nW, G.cutW, G.Qw);
+        classes = ((has_full(t0, G.nsT, G.gT, et) ? 0x0Fu : 0u) | (et ? 0xF0u : 0u)) &
+                  ((has_full(h0, G.nsH, G.gH, eh) ? 0x33u : 0u) | (eh ? 0xCCu : 0u)) &
+                  ((has_full(w0, G.nsW, G.gW, ew) ? 0x55u : 0u) | (ew ? 0xAAu : 0u));
+    }
+    // the box ends with the axis' last sub-tile, and that one is cut
+    static __device__ __forceinline__ bool has_cut(int last, int n, int cut, int q) { return last == n - 1 && cut < q; }
+    static __device__ __forceinline__ bool has_full(int first, int ns, int g, bool cut) { return !cut || first * ns < g - 1; }
+    // visited[v] = 1 for every tile of the box (threads of one workgroup)
+    __device__ __forceinline__ void mark(const Geom& G, uint8_t* visited, int nthr) const {
+        const int eh = h1 - h0 + 1, ew = w1 - w0 + 1, total = (t1 - t0 + 1) * eh * ew;
+        for (int i = threadIdx.x; i < total; i += nthr) {
+            const int t = i / (eh * ew), rem = i - t * (eh * ew), h = rem / ew, w = rem - h * ew;
+            visited[((t0 + t) * G.nH + (h0 + h)) * G.nW + (w0 + w)] = 1;
+        }
+    }
+};
+
+// One axis of a walk over sub-tiles: `off` is the axis' share of the scale-group index, tile * (step of
+// the next tile) + place in tile * (step of the next sub-tile).
+template <bool MB>
+struct AxisWalk {
+    int i, first, last;                 // sub-tile along the axis
+    int sub, off, off_first;
+    int ns, step, wrap;                 // sub-tiles per tile; off's step within a tile, and to the next tile
+    // the axis' full sub-tiles of the tiles lo .. hi, or (cut_part) only its last one, which is cut
+    __device__ __forceinline__ void init(int lo, int hi, int tiles, int g, bool cut_part, bool has_cut, int ns_, int step_,
+                                         int tile_step) {
+        ns = MB ? ns_ : 1;
+        step = MB ? step_ : tile_step;
+        wrap = tile_step - (ns - 1) * step;
+        const int tile = cut_part ? tiles - 1 : lo;
+        first = cut_part ? g - 1 : lo * ns;
+        last = cut_part ? g - 1 : min((hi + 1) * ns, g) - 1 - (has_cut ? 1 : 0);
+        off_first = tile * tile_step + (MB ? (first - tile * ns) * step : 0);
+        reset();
+    }
+    __device__ __forceinline__ void reset() { i = first; off = off_first; sub = 0; }
+    __device__ __forceinline__ bool advance() {            // false: the axis is exhausted (and reset)
+        if (i == last) { reset(); return false; }
+        ++i;
+        if (!MB) { off += step; return true; }
+        if (++sub == ns) { sub = 0; off += wrap; } else { off += step; }
+        return true;
+    }
+    __device__ __forceinline__ int count() const { return last - first + 1; }
+};
+
+// One key block: packed slots of one scale group, the first n of them real tokens.  Indices count from
+// the head's first tile.
+struct KeyBlock { int blk, group, n; };
+
+// The key blocks of NH 16-key halves of the box, class by class.
+template <bool MB>
+struct BlockWalk {
+    const Geom& G;
+    const KeyBox& box;
+    uint32_t classes;                   // classes still to come
+    int NH;
+    AxisWalk<MB> t, h, w;
+    int n, jb, jb0, jb1;                // real tokens of a sub-tile of the class; its blocks of NH halves
+    __device__ __forceinline__ BlockWalk(const Geom& G_, const KeyBox& box_, int nh) : G(G_), box(box_), NH(nh) {}
+    __device__ __forceinline__ void enter(int c) {
+        const bool et = KeyBox::has_cut(box.t1, G.nT, G.cutT, G.Qt), eh = KeyBox::has_cut(box.h1, G.nH, G.cutH, G.Qh),
+                   ew = KeyBox::has_cut(box.w1, G.nW, G.cutW, G.Qw);
+        const int per_tile = MB ? G.NS : 1;
+        t.init(box.t0, box.t1, G.nT, G.gT, c & 4, et, G.nsT, G.nsH * G.nsW, G.nH * G.nW * per_tile);
+        h.init(box.h0, box.h1, G.nH, G.gH, c & 2, eh, G.nsH, G.nsW, G.nW * per_tile);
+        w.init(box.w0, box.w1, G.nW, G.gW, c & 1, ew, G.nsW, 1, per_tile);
+        n = ((c & 4) ? G.cutT : G.Qt) * ((c & 2) ? G.cutH : G.Qh) * ((c & 1) ? G.cutW : G.Qw);
+        jb0 = NH == 8 || !MB ? 0 : n >> 7;                 // 128-slot blocks; smaller groups have one
+        jb1 = MB ? (NH == 8 ? (n + 15) >> 7 : jb0 + 1) : 1;
+        jb = jb0;
+    }
+    // sets the walk to its first block; returns the number of blocks
+    __device__ __forceinline__ int begin(uint32_t classes_) {
+        int total = 0;
+        for (uint32_t left = classes_; left; left &= left - 1) {
+            enter(__builtin_ctz(left));
+            total += t.count() * h.count() * w.count() * (jb1 - jb0);
+        }
+        classes = classes_;
+        enter_next();
+        return total;
+    }
+    __device__ __forceinline__ void enter_next() {
+        enter(__builtin_ctz(classes));
+        classes &= classes - 1;
+    }
+    __device__ __forceinline__ void next() {               // not past the last block
+        if (MB) {
+            if (++jb < jb1) return;
+            jb = jb0;
+        }
+        if (!w.advance() && !h.advance() && !t.advance()) enter_next();
+    }
+    __device__ __forceinline__ KeyBlock block() const {
+        KeyBlock b;
+        b.group = t.off + h.off + w.off;
+        b.blk = MB ? b.group * G.KBG + jb : b.group;
+        b.n = MB ? min(128, n - 128 * jb) : n;
+        return b;
+    }
+};
+
+// Kernel launchers of the two precisions; grid: workgroups
+void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st);
+void launch_attn_bf16(const AttnArgs& a, int grid, hipStream_t st);
+// waves of a workgroup (= sub-blocks of a query block)
+inline int query_waves(const Geom& g) {
+    const int sb = g.BS == 128 ? 4 : g.KBS, tsb = g.TSP / 32;
+    return sb == 4 || (g.NS > 1 && tsb % 4 == 0) ? 4 : sb;
+}
+
+}  // namespace fps

@@ -89,11 +89,12 @@ int check_shape(const fps_shape* s, Geom* g) {
     g->lastW = s->W - (nW - 1) * s->Tw;
     g->gT = (s->T + qt - 1) / qt; g->gH = (s->H + qh - 1) / qh; g->gW = (s->W + qw - 1) / qw;
     g->cutT = s->T - (g->gT - 1) * qt; g->cutH = s->H - (g->gH - 1) * qh; g->cutW = s->W - (g->gW - 1) * qw;
-    for (int nb = 0; nb < 4; ++nb) g->nb_classes[nb] = 0;
+    g->KBG = bs == 128 ? kbs : 1;
+    for (int nh = 0; nh < 8; ++nh) g->nh_classes[nh] = 0;
     for (int c = 0; c < 8; ++c) {
         const int n = ((c & 4) ? g->cutT : qt) * ((c & 2) ? g->cutH : qh) * ((c & 1) ? g->cutW : qw);
-        if (n >= 128) g->nb_classes[3] |= 1u << c;
-        if (n % 128) g->nb_classes[(n % 128 + 31) / 32 - 1] |= 1u << c;
+        if (n >= 128) g->nh_classes[7] |= 1u << c;
+        if (n % 128) g->nh_classes[(n % 128 + 15) / 16 - 1] |= 1u << c;
     }
     return FPS_OK;
 }

@@ -35,9 +35,12 @@ struct Geom {
     // axis its real extent, its tile and its place in the tile.
     int gT, gH, gW;
     int cutT, cutH, cutW;
-    // Bit c of nb_classes[nb - 1]: sub-tiles cut along the axes of c (4: T, 2: H, 1: W) have a key
-    // block of nb 32-key sub-blocks (BS = 128).
-    uint32_t nb_classes[4];
+    // Key blocks of the attention kernels: KBG 128-slot blocks per sub-tile if BS = 128, otherwise the
+    // sub-tile itself (at most 96 slots).
+    int KBG;
+    // Bit c of nh_classes[nh - 1]: sub-tiles cut along the axes of c (4: T, 2: H, 1: W) have a key
+    // block whose real tokens fill nh 16-key halves.
+    uint32_t nh_classes[8];
 };
 
 // n / d for 0 <= n < 2^21, given inv_d = 1.0f / d correctly rounded.  Exact: (n + 1/2) / d is at

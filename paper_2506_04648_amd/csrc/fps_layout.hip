@@ -1,40 +1,26 @@
 // Layout kernels of libfps: raster <-> tile order (Sec. 3.2 step (1)), the BF16 operand packing,
 // and the debug unpacking of packed E4M3 tensors.  All of them are pure data movement.
 //
-// Packed operand layouts, per block of BS = 128 or 32 packed slots (a tile is one or several blocks;
-// packed slots hold the real tokens of a sub-tile first, see real_box in fps_internal.h).  K and V
-// of a 128-slot block are four consecutive 32-key sub-blocks.
-// E4M3, BS = 128 -- operands of v_mfma_f32_32x32x64_f8f6f4; lane = 32h + n, n the row of the 32-row
-// operand block, h the half of the 64 contraction slots of one step:
-//   Q : row-major [token][128]                                              (BS*128 bytes)
-//   K : 16-byte chunk (((kb*2 + ks)*2 + e)*64 + lane) = K[32kb + n][64ks + 32h + 16e + 0..15]
-//   V : 16-byte chunk ((kb*4 + db)*64 + lane), byte jj = V[key][32db + n] with
-//       key = 32kb + 8(jj/4) + 4h + jj%4
-//   The accumulator of S^T = K Q^T for key block kb holds, in lane (n,h) and register r, query n and
-//   key 32kb + 8(r/4) + 4h + r%4; the 32 weights of key blocks 2j and 2j+1 of a lane are therefore,
-//   unchanged, its 32 contraction slots of step j of the PV product O^T = V^T P^T.
-// E4M3, BS = 32 -- operands of the 16x16 instructions; lane = 16g + n:
-//   Q : row-major [token][128]
-//   K : 16-byte chunk ((b*2 + h)*64 + lane) = K[16b + n][32g + 16h + 0..15]
-//   V :  8-byte chunk (cb*64 + lane), byte j = V[key(g,j)][16cb + n], key(g,s) = 16*(s/4) + 4g + s%4
-// BF16, BS = 128 -- operands of the 32x32x16 instructions; lane = 32h + n:
-//   Q : row-major [token][128]                                              (BS*256 bytes)
-//   K : 16-byte chunk ((kb*8 + ks)*64 + lane) = K[32kb + n][16ks + 8h + 0..7]
+// Packed operand layouts, per sub-block of 32 packed slots (a block of BS = 128 or 32 slots is four of them
+// or one, a tile one or several blocks; packed slots hold the real tokens of a scale group first, see
+// real_box in fps_internal.h); lane = 32h + n.
+// E4M3 -- operands of v_mfma_f32_32x32x64_f8f6f4, h the half of the 64 contraction slots of one step:
+//   Q : row-major [token][128]                                              (4 KB)
+//   K : 16-byte chunk ((ks*2 + e)*64 + lane) = K[n][64ks + 32h + 16e + 0..15]
+//   V : 16-byte chunk (db*64 + lane), byte jj = V[key][32db + n] with key = 8(jj/4) + 4h + jj%4
+//   The accumulator of S^T = K Q^T for a sub-block holds, in lane (n,h) and register r, query n and key
+//   8(r/4) + 4h + r%4; the 32 weights of two sub-blocks of a lane are therefore, unchanged, its 32
+//   contraction slots of one step of the PV product O^T = V^T P^T, and 8 of them those of a
+//   32x32x16 step.
+// BF16 -- operands of the 32x32x16 instructions:
+//   Q : row-major [token][128]                                              (8 KB)
+//   K : 16-byte chunk (ks*64 + lane) = K[n][16ks + 8h + 0..7]
 //   V : 16-byte chunk ((kk*4 + db)*64 + lane), element el = V[key][32db + n] with
-//       key = 32(kk/2) + 8(2(kk%2) + el/4) + 4h + el%4 (the key order of the 32x32 accumulator),
-//       stored as fp16 after an exact power-of-two scaling per scale group (see pack_bf16_kernel)
-// BF16, BS = 32 -- 16x16x32 instructions; lane = 16g + n:
-//   Q : row-major [token][128]
-//   K : 16-byte chunk ((b*4 + ks)*64 + lane) = K[16b + n][32ks + 8g + 0..7]
-//   V : 16-byte chunk ((kk*8 + cb)*64 + lane), element e -> V[32kk + key(g,e)][16cb + n], fp16 as above
-// key(g,s) is the key that slot s of lane group g holds after a 16x16 MFMA wrote S^T = K Q^T: the
-// accumulator of lane (n,g) for key block b has keys 16b + 4g + 0..3, so P^T can be fed back as
-// the second operand of the PV product without any cross-lane movement.
+//       key = 16kk + 8(el/4) + 4h + el%4 (the key order of the accumulator), stored as fp16 after an
+//       exact power-of-two scaling per scale group (see pack_bf16_kernel)
 #include "fps_device_common.h"
 
 namespace fps {
-
-__device__ __forceinline__ int key_of_slot(int g, int s) { return 16 * (s >> 2) + 4 * g + (s & 3); }
 
 // ---- raster -> tiled (bf16, 16-byte chunks of 8 channels) -------------------------------------
 __global__ void tile_order_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, Geom g,
@@ -110,13 +96,8 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
     if (role == FPS_ROLE_K) {
         for (int c = threadIdx.x; c < kChunks; c += 256) {
             const int j = c >> 4, c8 = c & 15;             // row, 8-channel chunk
-            if (BS == 128) {                               // 32x32x16 operand: lane 32h + n, step ks
-                const int kb = j >> 5, n = j & 31, ks = c8 >> 1, h = c8 & 1;
-                dst[(kb * 8 + ks) * 64 + 32 * h + n] = load(c);
-            } else {
-                const int b = j >> 4, n = j & 15, ks = c8 >> 2, gg = c8 & 3;
-                dst[(b * 4 + ks) * 64 + gg * 16 + n] = load(c);
-            }
+            const int sb = j >> 5, n = j & 31, ks = c8 >> 1, h = c8 & 1;   // 32x32x16 operand: lane 32h + n, step ks
+            dst[(sb * 8 + ks) * 64 + 32 * h + n] = load(c);
         }
         return;
     }
@@ -141,21 +122,11 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
     for (int c = threadIdx.x; c < kChunks; c += 256) {
         const int lane = c & 63;
         union { uint4 v; _Float16 h[8]; } o;
-        if (BS == 128) {
-            const int kk = c >> 8, db = (c >> 6) & 3, hh = lane >> 5, n = lane & 31;
+        const int kk = c >> 8, db = (c >> 6) & 3, hh = lane >> 5, n = lane & 31;
 #pragma unroll
-            for (int el = 0; el < 8; ++el) {
-                const int key = 32 * (kk >> 1) + 8 * (2 * (kk & 1) + (el >> 2)) + 4 * hh + (el & 3);
-                const uint32_t bits = tile[key * 128 + 32 * db + n];
-                o.h[el] = (_Float16)(__uint_as_float(bits << 16) * down);
-            }
-        } else {
-            const int cb = (c >> 6) & 7, kk = c >> 9, gg = lane >> 4, n = lane & 15;
-#pragma unroll
-            for (int el = 0; el < 8; ++el) {
-                const uint32_t bits = tile[(32 * kk + key_of_slot(gg, el)) * 128 + 16 * cb + n];
-                o.h[el] = (_Float16)(__uint_as_float(bits << 16) * down);
-            }
+        for (int el = 0; el < 8; ++el) {
+            const uint32_t bits = tile[(16 * kk + 8 * (el >> 2) + 4 * hh + (el & 3)) * 128 + 32 * db + n];
+            o.h[el] = (_Float16)(__uint_as_float(bits << 16) * down);
         }
         dst[c] = o.v;
     }
@@ -185,21 +156,11 @@ __global__ __launch_bounds__(256) void unpack_q8_kernel(const uint8_t* __restric
         if (role == FPS_ROLE_Q) {
             off = j * 128 + c;
         } else if (role == FPS_ROLE_K) {
-            if (BS == 128) {
-                const int kb = j >> 5, n = j & 31, ks = c >> 6, h = (c >> 5) & 1, e = (c >> 4) & 1;
-                off = (((kb * 2 + ks) * 2 + e) * 64 + 32 * h + n) * 16 + (c & 15);
-            } else {
-                const int b = j >> 4, n = j & 15, gg = c >> 5, h = (c >> 4) & 1;
-                off = ((b * 2 + h) * 64 + gg * 16 + n) * 16 + (c & 15);
-            }
-        } else if (BS == 128) {                            // inverse of the wide key order
-            const int db = c >> 5, n = c & 31;
-            const int kb = j >> 5, rem = j & 31, h = (rem >> 2) & 1, jj = 4 * (rem >> 3) + (rem & 3);
-            off = ((kb * 4 + db) * 64 + 32 * h + n) * 16 + jj;
-        } else {
-            const int cb = c >> 4, n = c & 15;
-            const int gg = (j >> 2) & 3, s4 = 4 * (j >> 4) + (j & 3);  // inverse of key_of_slot
-            off = (cb * 64 + gg * 16 + n) * 8 + s4;
+            const int sb = j >> 5, n = j & 31, ks = c >> 6, h = (c >> 5) & 1, e = (c >> 4) & 1;
+            off = (((sb * 2 + ks) * 2 + e) * 64 + 32 * h + n) * 16 + (c & 15);
+        } else {                                           // inverse of the accumulator's key order
+            const int sb = j >> 5, rem = j & 31, h = (rem >> 2) & 1, jj = 4 * (rem >> 3) + (rem & 3);
+            off = ((sb * 4 + (c >> 5)) * 64 + 32 * h + (c & 31)) * 16 + jj;
         }
         dst[i] = src[(long long)(k - j) * 128 + off];
     }

@@ -6,10 +6,9 @@
 
 namespace fps {
 
-__device__ __forceinline__ int key_of_slot_q(int g, int s) { return 16 * (s >> 2) + 4 * g + (s & 3); }
-// 128-slot blocks (32x32x64 MFMA): the key, within its 32-key sub-block, behind byte jj of the
-// 16-byte chunk of lane half h -- where the accumulator of S^T = K Q^T left that key's weight
-__device__ __forceinline__ int key_of_slot_wide(int h, int jj) { return 8 * (jj >> 2) + 4 * h + (jj & 3); }
+// The key, within its 32-key sub-block, behind byte jj of the 16-byte chunk of lane half h -- where the
+// accumulator of S^T = K Q^T left that key's weight
+__device__ __forceinline__ int key_of_slot(int h, int jj) { return 8 * (jj >> 2) + 4 * h + (jj & 3); }
 
 // Quotient x/s prepared for the hardware's round-to-nearest-even conversion so that the final code
 // equals the rounding of the EXACT quotient: the correctly rounded float quotient can land exactly
@@ -79,27 +78,14 @@ __device__ __forceinline__ uint4 encode16(const uint4& lo, const uint4& hi, floa
 // V block in LDS (row-major codes [token][128]) -> key-contiguous packed layout in HBM
 template <int BS>
 __device__ __forceinline__ void write_v_block(const uint8_t* stage, uint4* dst, int tid) {
-    if (BS == 128) {
-        for (int c = tid; c < BS * 8; c += 256) {
-            const int lane = c & 63, db = (c >> 6) & 3, kb = c >> 8;
-            const int h = lane >> 5, n = lane & 31;
-            union { uint4 v; uint8_t b[16]; } o;
+    for (int c = tid; c < BS * 8; c += 256) {
+        const int lane = c & 63, db = (c >> 6) & 3, kb = c >> 8;
+        const int h = lane >> 5, n = lane & 31;
+        union { uint4 v; uint8_t b[16]; } o;
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj)
-                o.b[jj] = stage[(32 * kb + key_of_slot_wide(h, jj)) * 128 + 32 * db + n];
-            dst[c] = o.v;
-        }
-    } else {
-        uint2* dst8 = reinterpret_cast<uint2*>(dst);
-        for (int c = tid; c < BS * 16; c += 256) {
-            const int lane = c & 63, cb = c >> 6;
-            const int gg = lane >> 4, n = lane & 15;
-            union { uint2 v; uint8_t e[8]; } o;
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj)
-                o.e[jj] = stage[key_of_slot_q(gg, jj) * 128 + 16 * cb + n];
-            dst8[c] = o.v;
-        }
+        for (int jj = 0; jj < 16; ++jj)
+            o.b[jj] = stage[(32 * kb + key_of_slot(h, jj)) * 128 + 32 * db + n];
+        dst[c] = o.v;
     }
 }
 
@@ -158,13 +144,9 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const uint4* __rest
             if (role == FPS_ROLE_Q) {
                 dst[unit] = codes;
             } else if (role == FPS_ROLE_K) {
-                if (BS == 128) {                     // 32x32x64 operand: lane 32h + n, k-step ks, 16-byte half e
-                    const int kb = j >> 5, n = j & 31, ks = c16 >> 2, h = (c16 >> 1) & 1, e = c16 & 1;
-                    dst[((kb * 2 + ks) * 2 + e) * 64 + 32 * h + n] = codes;
-                } else {
-                    const int b = j >> 4, n = j & 15, gg = c16 >> 1, h = c16 & 1;
-                    dst[(b * 2 + h) * 64 + gg * 16 + n] = codes;
-                }
+                // 32x32x64 operand: lane 32h + n, k-step ks, 16-byte half e
+                const int sb = j >> 5, n = j & 31, ks = c16 >> 2, h = (c16 >> 1) & 1, e = c16 & 1;
+                dst[((sb * 2 + ks) * 2 + e) * 64 + 32 * h + n] = codes;
             } else {
                 reinterpret_cast<uint4*>(stage)[unit] = codes;
             }

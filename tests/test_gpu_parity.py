@@ -334,6 +334,39 @@ def test_cut_tiles_at_the_edges_of_sub_blocks(prec, tile, rest):
         _check_quantize(run, [0], f"cut {tile} {rest}")
 
 
+SMALL_GROUP_CASES = [                            # tile, sub-tile; key blocks of 1, 2 or 3 sub-blocks
+    ((1, 1, 1), None), ((1, 1, 17), None), ((2, 4, 4), None),                     # one wave a workgroup
+    ((1, 3, 11), None), ((3, 4, 4), None), ((1, 8, 8), None),                     # two
+    ((1, 5, 13), None), ((1, 5, 16), None), ((2, 3, 16), None),                   # three: 65, 80, 96 tokens
+    ((2, 4, 8), (1, 4, 4)), ((1, 4, 12), (1, 4, 4)),              # 4 and 3 sub-tiles of 16: four waves, one
+    ((2, 8, 8), (2, 4, 8)), ((3, 6, 8), (1, 6, 8)),               # 2 and 3 sub-tiles of 64 and 48: four, two
+    ((2, 10, 16), (1, 5, 16)), ((1, 10, 16), (1, 5, 16)),         # 4 and 2 sub-tiles of 80: four, three
+]
+
+
+@pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
+@pytest.mark.parametrize("tile,qtile", SMALL_GROUP_CASES)
+def test_small_scale_groups_for_every_workgroup_shape(prec, tile, qtile):
+    """Scale groups of at most 96 tokens: every number of sub-blocks and waves, with tiles cut along
+    h and w (so that groups hold fewer tokens, or none) and a window that leaves tiles out."""
+    import torch
+    say("small groups", prec, tile, qtile)
+    grid = (2 * tile[0], max(1, 3 * tile[1] - tile[1] // 2), max(1, 4 * tile[2] - (2 * tile[2]) // 3))
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=(3, 3, 3), heads=2, n_outlier=3, config_id=33)
+    run = gu.GpuRun(w, qtile=qtile)
+    out, vis = run.attn(prec, visited=True)
+    assert np.array_equal(vis.cpu().numpy().astype(bool), fo.tile_mask(run.g, w.window))
+    st = gu.compare_head(run, out, 1, prec, w.window)
+    say("  ", st)
+    gu.assert_parity(st, f"{tile} {qtile}")
+    assert torch.equal(run.attn(prec, raster_out=True), fps.tile_unorder(run.shape, out))
+    if prec == fps.PREC_FP8:
+        _check_quantize(run, range(2), f"small groups {tile} {qtile}")
+        out = run.attn(prec, vscale=fps.VSCALE_CHANNEL)
+        st = gu.compare_head(run, out, 1, prec, w.window, vscale=fps.VSCALE_CHANNEL)
+        gu.assert_parity(st, f"{tile} {qtile} per-channel V")
+
+
 @pytest.mark.parametrize("grid,tile,window", [((4, 16, 16), (2, 4, 4), (1, 3, 3)),
                                               ((2, 13, 40), (1, 8, 16), (3, 3, 3)),
                                               ((3, 13, 20), (2, 8, 16), (3, 3, 3))])
