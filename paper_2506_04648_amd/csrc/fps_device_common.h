@@ -61,8 +61,9 @@ __device__ __forceinline__ uint32_t amax_bits16(const uint4& v, uint32_t m) {
     return p > m ? p : m;
 }
 
-// workgroup-wide max of m over 256 threads (red: 4 words of LDS); every thread gets the result
-__device__ __forceinline__ uint32_t block_max_256(uint32_t m, uint32_t* red) {
+// workgroup-wide max of m over WAVES waves (red: WAVES words of LDS); every thread gets the result
+template <int WAVES>
+__device__ __forceinline__ uint32_t workgroup_max(uint32_t m, uint32_t* red) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const uint32_t o = (uint32_t)__shfl_xor((int)m, off);
@@ -72,7 +73,7 @@ __device__ __forceinline__ uint32_t block_max_256(uint32_t m, uint32_t* red) {
     __syncthreads();
     m = red[0];
 #pragma unroll
-    for (int i = 1; i < 4; ++i) m = red[i] > m ? red[i] : m;
+    for (int i = 1; i < WAVES; ++i) m = red[i] > m ? red[i] : m;
     return m;
 }
 
@@ -107,7 +108,7 @@ __global__ __launch_bounds__(256) void block_amax_kernel(const uint4* __restrict
         const uint4* row = token_row<RASTER>(x, g, org, c >> 4);
         if (row) m = amax_bits16(row[c & 15], m);
     }
-    m = block_max_256(m, red);
+    m = workgroup_max<4>(m, red);
     if (threadIdx.x == 0) atomicMax(&amax_bits[blockIdx.x / g.KBS], m << 16);
 }
 

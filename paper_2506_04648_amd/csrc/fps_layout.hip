@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
         amax = tile_amax[blk / g.KBS];
         __syncthreads();
     } else {
-        mb = block_max_256(mb, red);                       // also orders the LDS writes above
+        mb = workgroup_max<4>(mb, red);                       // also orders the LDS writes above
         amax = __uint_as_float(mb << 16);
     }
     const int e = pow2_exponent_for_fp16(amax);

@@ -1,7 +1,10 @@
 // Per-group amax -> scale -> E4M3 encode (Sec. 3.2, Eq. 4-5; Algorithm 1 step 2), writing the
 // packed operand layouts described in fps_layout.hip.  A scale group is a 3D tile, or a
-// quantisation sub-tile of it.  One workgroup of 256 threads per block of BS slots; the pass is
-// HBM-bound (2 bytes read, 1 byte written per element).
+// quantisation sub-tile of it.  The pass is HBM-bound (2 bytes read, 1 byte written per element) as long as
+// the encoding takes few instructions and little code: a test for ties per element, with the exact
+// quotient unrolled behind it, was 18 instructions per element and 29 to 85 KB of code to fetch, against
+// now 7 and 5 to 11 KB.  Three tensors of 720p 629 -> 602 us (5.8 TB/s), of 480p (12 heads x 32760 tokens) 143 ->
+// 101 us, in tiles of three blocks 221 -> 113 us, of 5 heads x 4255 tokens 54 -> 20 us.
 #include "fps_device_common.h"
 
 namespace fps {
@@ -39,46 +42,79 @@ __device__ __forceinline__ float quotient_for_rne(float x, float s) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Same result as quotient_for_rne(x, s), cheaper on the common path: x * (1/s) is within three
-// float ulps of the exact quotient, so the rounding can only differ when an E4M3 midpoint lies
-// within a few ulps of the product; only then (and in the subnormal range of the format, where
-// the grid is absolute) the exact routine runs.  rs = 1/s, correctly rounded.
-// The product is formed as fma(x, 1/s, tiny): a zero input (padding, common) then gives `tiny`,
-// which encodes as 0 like the exact path would, without taking that path; for non-zero inputs the
-// addend is far below an ulp.  No clamp is needed on the common path: |x| <= amax makes the
-// product at most 448 (1 + 2^-22), far below the next rounding boundary (464).
-__device__ __forceinline__ float quotient_fast(float x, float s, float rs) {
-    const float q = __builtin_fmaf(x, rs, 1.3e-30f);
-    const uint32_t qb = __float_as_uint(q);
-    const uint32_t low = (qb & 0xFFFFFu) - (0x80000u - 4u);          // distance to a midpoint pattern
-    const bool near_mid = low <= 8u;
-    // 2^-90 <= |q| < 2^-6 (below 2^-90, which includes `tiny`, the code is 0 either way)
-    const bool subnormal = ((qb << 1) - 0x25000000u) < (0x79000000u - 0x25000000u);
-    if (__builtin_expect(near_mid || subnormal, 0)) return quotient_for_rne(x, s);
-    return q;
+// How the elements of a scale s = RN(amax / 448) are divided by it: multiply by rs = 1/s, round the
+// product to 17 significant bits, move it `nudge` float ulps away from (or towards) zero.
+//
+// Why that rounds to the code of the EXACT quotient x / s.  x and amax have 8 significant bits, X and A
+// as integers, and the quotient is (1 + delta) times the ideal 448 x / amax = 7 X 2^j / A, delta the
+// rounding error of s (|delta| <= 2^-24).  A rounding boundary of E4M3 is M 2^i with M < 32 odd (also in its
+// subnormal range), and |7 X 2^j / A - M 2^i| is zero or at least 1/(A M) > 2^-13 of it.  So an
+// ideal quotient off the boundaries stays on its side through all of these roundings (2^-17 together);
+// one ON a boundary comes out of the rounding to 17 bits as the boundary itself, and the exact
+// quotient lies beside it in the direction of delta, which is the same for the whole scale group: exactly
+// on it (a tie, for the conversion to settle) if 448 s = amax.  Ties of the ideal quotient are
+// common: 6 % of the 16-channel units of normal data hold one.
+//
+// The product is formed as fma(x, rs, kTiny): a zero of either sign (padding, common) then gives code 0; for
+// other inputs the addend is far below an ulp of anything that does not round to zero.  No clamp is
+// needed: |x| <= amax makes the product at most 448 (1 + 2^-18), far below the next boundary (464).
+struct Divisor {
+    float rs;
+    int nudge;
+};
+constexpr float kTiny = 1.3e-30f;
+__device__ __forceinline__ Divisor divisor_of(float s, float amax) {
+    const float rest = __builtin_fmaf(-448.0f, s, amax);   // its sign is exact
+    return Divisor{1.0f / s, rest > 0.0f ? 16 : rest < 0.0f ? -16 : 0};
+}
+// a scale below the normal range has lost bits of amax / 448, and its reciprocal may be infinite: the
+// exact quotients are taken
+__device__ __forceinline__ bool is_divisor(float s) { return __float_as_uint(s) >= 0x00800000u; }
+
+__device__ __forceinline__ float divide(float x, const Divisor& d) {
+    const uint32_t q = __float_as_uint(__builtin_fmaf(x, d.rs, kTiny));
+    return __uint_as_float(((q + 0x40u) & ~0x7Fu) + (uint32_t)d.nudge);
 }
 
-// 16 bf16 (two uint4) -> 16 E4M3 codes (one uint4)
-__device__ __forceinline__ uint4 encode16(const uint4& lo, const uint4& hi, float s) {
+// 16 bf16 (two uint4) -> 16 E4M3 codes (one uint4); scale(i), divisor(i): of element i.  One copy of the
+// exact quotient in a loop: code that has to be fetched is what a launch of few workgroups waits for.
+template <typename D, typename S>
+__device__ __forceinline__ uint4 encode16(const uint4& lo, const uint4& hi, bool usable, D&& divisor, S&& scale) {
     const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    const float rs = 1.0f / s;
     uint32_t o[4];
+    if (__builtin_expect(usable, 1)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int r = 0;
-        r = __builtin_amdgcn_cvt_pk_fp8_f32(quotient_fast(bf16_lo(w[2 * i]), s, rs),
-                                            quotient_fast(bf16_hi(w[2 * i]), s, rs), r, false);
-        r = __builtin_amdgcn_cvt_pk_fp8_f32(quotient_fast(bf16_lo(w[2 * i + 1]), s, rs),
-                                            quotient_fast(bf16_hi(w[2 * i + 1]), s, rs), r, true);
-        o[i] = (uint32_t)r;
+        for (int i = 0; i < 4; ++i) {
+            int r = __builtin_amdgcn_cvt_pk_fp8_f32(divide(bf16_lo(w[2 * i]), divisor(4 * i)),
+                                                    divide(bf16_hi(w[2 * i]), divisor(4 * i + 1)), 0, false);
+            r = __builtin_amdgcn_cvt_pk_fp8_f32(divide(bf16_lo(w[2 * i + 1]), divisor(4 * i + 2)),
+                                                divide(bf16_hi(w[2 * i + 1]), divisor(4 * i + 3)), r, true);
+            o[i] = (uint32_t)r;
+        }
+    } else {
+        uint4 a = lo, b = hi;
+        o[0] = o[1] = o[2] = o[3] = 0u;
+#pragma unroll 1
+        for (int i = 0; i < 16; i += 2) {
+            const int pair = __builtin_amdgcn_cvt_pk_fp8_f32(quotient_for_rne(bf16_lo(a.x), scale(i)),
+                                                             quotient_for_rne(bf16_hi(a.x), scale(i + 1)), 0, false);
+            a = make_uint4(a.y, a.z, a.w, b.x);
+            b = make_uint4(b.y, b.z, b.w, 0u);
+            // the codes move in from the top, two at a time
+            o[0] = (o[0] >> 16) | (o[1] << 16);
+            o[1] = (o[1] >> 16) | (o[2] << 16);
+            o[2] = (o[2] >> 16) | (o[3] << 16);
+            o[3] = (o[3] >> 16) | ((uint32_t)pair << 16);
+        }
     }
     return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// V block in LDS (row-major codes [token][128]) -> key-contiguous packed layout in HBM
-template <int BS>
+// V block in LDS (row-major codes [token][128]) -> key-contiguous packed layout in HBM, by THREADS threads
+template <int BS, int THREADS>
 __device__ __forceinline__ void write_v_block(const uint8_t* stage, uint4* dst, int tid) {
-    for (int c = tid; c < BS * 8; c += 256) {
+#pragma unroll
+    for (int c = tid; c < BS * 8; c += THREADS) {
         const int lane = c & 63, db = (c >> 6) & 3, kb = c >> 8;
         const int h = lane >> 5, n = lane & 31;
         union { uint4 v; uint8_t b[16]; } o;
@@ -89,73 +125,72 @@ __device__ __forceinline__ void write_v_block(const uint8_t* stage, uint4* dst, 
     }
 }
 
-// One workgroup of 256 threads per NB consecutive blocks of BS slots.  A scale group of up to three
-// blocks is handled by one workgroup in a single pass over HBM (NB = blocks per group): all its
-// blocks are held in registers while the amax is reduced, then encoded.  Larger groups take their
-// amax from block_amax_kernel (tile_amax != nullptr, NB = 1) and this kernel only encodes.
+// THREADS threads per block of BS slots; a workgroup is one scale group of up to three blocks (NB), in a
+// single pass over HBM: the whole group is held in registers while the amax is reduced, then encoded.
+// Larger groups take their amax from block_amax_kernel (tile_amax != nullptr, NB = 1) and this kernel
+// only encodes.
 // RASTER: x is the raster tensor [BH,T,H,W,128] and the block's tokens are gathered from it (padded
 // slots read as zero), which fuses the tile ordering of Sec. 3.2 step (1) into this pass.
-template <int BS, bool RASTER, int NB>
-__global__ __launch_bounds__(256) void quantize_tiles_kernel(const uint4* __restrict__ x,
-                                                             uint8_t* __restrict__ xq,
-                                                             float* __restrict__ scales, int role,
-                                                             Geom g, const float* __restrict__ tile_amax) {
-    constexpr int U = BS / 32;                      // 32-byte units (16 channels of one token) per thread
-    __shared__ uint32_t red[4];
-    __shared__ __attribute__((aligned(16))) uint8_t stage[BS * 128];
-    const int first = blockIdx.x * NB;              // first block of this workgroup
-    const int tid = threadIdx.x;
+template <int BS, int THREADS, bool RASTER, int NB>
+__global__ __launch_bounds__(THREADS * NB) void quantize_tiles_kernel(const uint4* __restrict__ x,
+                                                                      uint8_t* __restrict__ xq,
+                                                                      float* __restrict__ scales, int role,
+                                                                      Geom g, const float* __restrict__ tile_amax) {
+    constexpr int U = BS * 8 / THREADS;             // 32-byte units (16 channels of one token) per thread
+    constexpr int WAVES = THREADS * NB / 64;
+    __shared__ uint32_t red[WAVES];
+    __shared__ __attribute__((aligned(16))) uint8_t stage[NB * BS * 128];
+    const int kb = NB > 1 ? (int)threadIdx.x / THREADS : 0, tid = threadIdx.x - kb * THREADS;
+    const int blk = blockIdx.x * NB + kb;
+    const BlockOrigin org = block_origin(g, blockIdx.x * NB);
 
-    uint4 lo[NB][U], hi[NB][U];
+    uint4 lo[U], hi[U];
     uint32_t mb = 0;
 #pragma unroll
-    for (int kb = 0; kb < NB; ++kb) {
-        const BlockOrigin org = block_origin(g, first + kb);
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-            const int unit = tid + 256 * i;          // token = unit >> 3, 16-channel group = unit & 7
-            const uint4* row = token_row<RASTER>(x, g, org, unit >> 3);
-            lo[kb][i] = make_uint4(0, 0, 0, 0);
-            hi[kb][i] = lo[kb][i];
-            if (row) { lo[kb][i] = row[2 * (unit & 7)]; hi[kb][i] = row[2 * (unit & 7) + 1]; }
-            mb = amax_pairs16(lo[kb][i], mb);
-            mb = amax_pairs16(hi[kb][i], mb);
-        }
+    for (int i = 0; i < U; ++i) {
+        const int unit = tid + THREADS * i;          // token = unit >> 3, 16-channel group = unit & 7
+        const uint4* row = token_row<RASTER>(x, g, org, kb * BS + (unit >> 3));
+        lo[i] = make_uint4(0, 0, 0, 0);
+        hi[i] = lo[i];
+        if (row) { lo[i] = row[2 * (unit & 7)]; hi[i] = row[2 * (unit & 7) + 1]; }
     }
-    mb = amax_of_pairs(mb);
     float amax;
     if (tile_amax) {
-        amax = tile_amax[first / g.KBS];
+        amax = tile_amax[blockIdx.x / g.KBS];
     } else {
-        mb = block_max_256(mb, red);
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            mb = amax_pairs16(lo[i], mb);
+            mb = amax_pairs16(hi[i], mb);
+        }
+        mb = workgroup_max<WAVES>(amax_of_pairs(mb), red);
         amax = __uint_as_float(mb << 16);
     }
     const float s = (amax == 0.0f) ? 1.0f : amax / 448.0f;   // Eq. 4 (correctly rounded division)
-    if (!tile_amax && tid == 0) scales[blockIdx.x] = s;       // the workgroup is the whole group
+    if (!tile_amax && threadIdx.x == 0) scales[blockIdx.x] = s;   // the workgroup is the whole group
 
+    const Divisor div = divisor_of(s, amax);
+    const bool usable = is_divisor(s);
+    uint4* dst = reinterpret_cast<uint4*>(xq + (long long)blk * (BS * 128));
+    uint8_t* const staged = stage + kb * (BS * 128);
 #pragma unroll
-    for (int kb = 0; kb < NB; ++kb) {
-        uint4* dst = reinterpret_cast<uint4*>(xq + (long long)(first + kb) * (BS * 128));
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-            const int unit = tid + 256 * i;
-            const uint4 codes = encode16(lo[kb][i], hi[kb][i], s);
-            const int j = unit >> 3, c16 = unit & 7;
-            if (role == FPS_ROLE_Q) {
-                dst[unit] = codes;
-            } else if (role == FPS_ROLE_K) {
-                // 32x32x64 operand: lane 32h + n, k-step ks, 16-byte half e
-                const int sb = j >> 5, n = j & 31, ks = c16 >> 2, h = (c16 >> 1) & 1, e = c16 & 1;
-                dst[((sb * 2 + ks) * 2 + e) * 64 + 32 * h + n] = codes;
-            } else {
-                reinterpret_cast<uint4*>(stage)[unit] = codes;
-            }
+    for (int i = 0; i < U; ++i) {
+        const int unit = tid + THREADS * i;
+        const uint4 codes = encode16(lo[i], hi[i], usable, [&](int) { return div; }, [&](int) { return s; });
+        const int j = unit >> 3, c16 = unit & 7;
+        if (role == FPS_ROLE_Q) {
+            dst[unit] = codes;
+        } else if (role == FPS_ROLE_K) {
+            // 32x32x64 operand: lane 32h + n, k-step ks, 16-byte half e
+            const int sb = j >> 5, n = j & 31, ks = c16 >> 2, h = (c16 >> 1) & 1, e = c16 & 1;
+            dst[((sb * 2 + ks) * 2 + e) * 64 + 32 * h + n] = codes;
+        } else {
+            reinterpret_cast<uint4*>(staged)[unit] = codes;
         }
-        if (role == FPS_ROLE_V) {                    // uniform branch: role is a kernel argument
-            __syncthreads();
-            write_v_block<BS>(stage, dst, tid);
-            if (kb + 1 < NB) __syncthreads();        // the staging buffer is reused by the next block
-        }
+    }
+    if (role == FPS_ROLE_V) {                        // uniform branch: role is a kernel argument
+        __syncthreads();
+        write_v_block<BS, THREADS>(staged, dst, tid);
     }
 }
 
@@ -198,36 +233,40 @@ __global__ __launch_bounds__(256) void quantize_channels_kernel(const uint4* __r
                                                                 const float* __restrict__ amax, Geom g) {
     __shared__ __attribute__((aligned(16))) uint8_t stage[BS * 128];
     __shared__ float sc[128];
-    const int tid = threadIdx.x;
+    __shared__ Divisor div[128];
+    const int tid = threadIdx.x, c16 = tid & 7;
     const long long blk = blockIdx.x;
     const long long bh = blk / ((long long)g.M * g.KB);
+    const BlockOrigin org = block_origin(g, blockIdx.x);
+    constexpr int U = BS / 32;
+    uint4 lo[U], hi[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {                            // 16 channels of one token
+        const uint4* row = token_row<RASTER>(x, g, org, (tid >> 3) + 32 * i);
+        lo[i] = make_uint4(0, 0, 0, 0);
+        hi[i] = lo[i];
+        if (row) { lo[i] = row[2 * c16]; hi[i] = row[2 * c16 + 1]; }
+    }
     if (tid < 128) {
         const float a = amax[bh * 128 + tid];
-        sc[tid] = a == 0.0f ? 1.0f : a / 448.0f;
+        const float s = a == 0.0f ? 1.0f : a / 448.0f;
+        sc[tid] = s;
+        div[tid] = divisor_of(s, a);
     }
     __syncthreads();
-    const BlockOrigin org = block_origin(g, blockIdx.x);
-    for (int unit = tid; unit < BS * 8; unit += 256) {       // 16 channels of one token
-        const int r = unit >> 3, c16 = unit & 7;
-        const uint4* row = token_row<RASTER>(x, g, org, r);
-        uint4 lo = make_uint4(0, 0, 0, 0), hi = lo;
-        if (row) { lo = row[2 * c16]; hi = row[2 * c16 + 1]; }
-        const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        uint32_t o[4];
+    Divisor d[16];                                           // of the thread's 16 channels
+    bool usable = true;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float* s4 = &sc[c16 * 16 + 4 * i];
-            int rr = 0;
-            rr = __builtin_amdgcn_cvt_pk_fp8_f32(quotient_for_rne(bf16_lo(w[2 * i]), s4[0]),
-                                                 quotient_for_rne(bf16_hi(w[2 * i]), s4[1]), rr, false);
-            rr = __builtin_amdgcn_cvt_pk_fp8_f32(quotient_for_rne(bf16_lo(w[2 * i + 1]), s4[2]),
-                                                 quotient_for_rne(bf16_hi(w[2 * i + 1]), s4[3]), rr, true);
-            o[i] = (uint32_t)rr;
-        }
-        reinterpret_cast<uint4*>(stage)[unit] = make_uint4(o[0], o[1], o[2], o[3]);
+    for (int i = 0; i < 16; ++i) {
+        d[i] = div[c16 * 16 + i];
+        usable = usable && is_divisor(sc[c16 * 16 + i]);
     }
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+        reinterpret_cast<uint4*>(stage)[tid + 256 * i] =
+            encode16(lo[i], hi[i], usable, [&](int k) { return d[k]; }, [&](int k) { return sc[c16 * 16 + k]; });
     __syncthreads();
-    write_v_block<BS>(stage, reinterpret_cast<uint4*>(xq + blk * (BS * 128)), tid);
+    write_v_block<BS, 256>(stage, reinterpret_cast<uint4*>(xq + blk * (BS * 128)), tid);
 }
 
 static int launch_quantize_channels(const Geom& g, const void* x, int raster, void* xq, float* scales,
@@ -250,11 +289,19 @@ static int launch_quantize_channels(const Geom& g, const void* x, int raster, vo
     return e == hipSuccess ? FPS_OK : hip_fail(e, "quantize_channels launch");
 }
 
+// Threads per block of slots.  More loads in flight per thread keep the memory system busier at large sizes,
+// more threads shorten a small launch: 3 tensors of 720p (40 heads x 75600 tokens, 25200 blocks) take 602
+// us with 256 threads and 680 us with 512; of 5 heads x 4255 tokens, 20 and 19 us.  In 32-slot blocks
+// (21x30x52 tokens x 12 heads in tiles of 48) 139, 109 and 106 us with 256, 128 and 64 threads, the
+// smallest launches alike.
+template <int BS> constexpr int kQuantThreads = BS == 128 ? 256 : 128;
+
 template <int BS, int NB>
 static void launch_quantize_nb(const Geom& g, const uint4* xi, int raster, int role, uint8_t* xo, float* scales,
                                const float* tile_amax, int grid, hipStream_t st) {
-    if (raster) quantize_tiles_kernel<BS, true, NB><<<grid, 256, 0, st>>>(xi, xo, scales, role, g, tile_amax);
-    else        quantize_tiles_kernel<BS, false, NB><<<grid, 256, 0, st>>>(xi, xo, scales, role, g, tile_amax);
+    constexpr int TH = kQuantThreads<BS>;
+    if (raster) quantize_tiles_kernel<BS, TH, true, NB><<<grid, TH * NB, 0, st>>>(xi, xo, scales, role, g, tile_amax);
+    else        quantize_tiles_kernel<BS, TH, false, NB><<<grid, TH * NB, 0, st>>>(xi, xo, scales, role, g, tile_amax);
 }
 
 int launch_quantize(const Geom& g, const void* x, int raster, int role, int vscale, void* xq,

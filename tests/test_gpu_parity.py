@@ -182,6 +182,33 @@ def test_quantize_special_values():
     assert torch.all(sc == 1.0) and torch.all(xq == 0)
 
 
+@pytest.mark.parametrize("exponent", [0, 100, -120])     # at -120 the scales are subnormal numbers
+@pytest.mark.parametrize("vscale", [fps.VSCALE_TILE, fps.VSCALE_CHANNEL])
+def test_codes_for_every_significand_of_amax(vscale, exponent):
+    """One scale group per 8-bit significand of amax, random significands and 19 binades of values in
+    each: every way in which a quotient can lie on or next to a rounding boundary."""
+    say("quantize significands", vscale, exponent)
+    rng = np.random.default_rng(12)
+    g = fo.Geometry(1, 8, 16 * 128, 1, 8, 16)                # 128 tiles of 128 tokens, 128 channels
+    shape = fps.make_shape(1, (1, 8, 16 * 128), (1, 8, 16))
+    # axis 1 of the groups: the values of one scale (a tile's, or 16384 tokens of a channel)
+    amax = (np.arange(128, 256) * 2.0 ** (exponent - 7))[:, None]
+    x = rng.integers(128, 256, size=(128, 128 * 128)) * 2.0 ** (exponent - 7 - rng.integers(0, 19, size=(128, 128 * 128)))
+    x = np.minimum(x, amax) * rng.choice([-1.0, 1.0], size=x.shape)
+    x[:, :1] = amax
+    x = x.reshape(g.L_padded, 128) if vscale == fps.VSCALE_TILE else np.ascontiguousarray(x.T)
+    xb = synth.round_to_bf16(x.astype(np.float32))
+    tiled = gu.to_device_bf16(xb[None, None])
+    quantize = fo.quantize_tiles if vscale == fps.VSCALE_TILE else lambda v, _: fo.quantize_channels(v)
+    wc, ws = quantize(xb.astype(np.float64), g)
+    for role in (0, 1, 2) if vscale == fps.VSCALE_TILE else (2,):
+        xq, sc = fps.quantize_tiles(shape, tiled, role, vscale=vscale)
+        codes = fps.debug_unpack_q8(shape, xq, role)[0, 0].cpu().numpy()
+        assert np.array_equal(sc[0, 0].cpu().numpy(), ws)
+        zero_sign = ((codes ^ wc) == 0x80) & ((wc & 0x7F) == 0)
+        assert int(((codes != wc) & ~zero_sign).sum()) == 0, role
+
+
 # ---- the matrix instruction's accumulation accuracy -------------------------------------------
 def test_score_accumulation_error_model(tiny):
     """Raw E4M3 scores of single tile pairs against the exact integer dot products: the layout is
