@@ -109,7 +109,8 @@ int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, c
     a.out_raster = out_raster;
     a.qblocks = g.TSP / (32 * query_waves(g));
     a.total = g.BH * g.M * a.qblocks;
-    a.chunk = (a.total + 7) / 8;
+    a.rotate = g.nW * a.qblocks % 2 == 0;
+    a.chunk = ((a.total + 7) / 8 + 3) / 4 * 4;
     const int grid = a.chunk * 8;
     if (prec == FPS_PREC_FP8) launch_attn_fp8(a, vscale == FPS_VSCALE_CHANNEL, grid, st);
     else                      launch_attn_bf16(a, grid, st);

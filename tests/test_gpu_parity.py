@@ -341,6 +341,22 @@ def test_attention_small_shapes(prec, grid, tile, window):
 
 
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
+@pytest.mark.parametrize("heads,grid,tile", [(1, (1, 8, 20), (1, 8, 16)),      # 2 work items: fewer than a group of four
+                                             (3, (3, 9, 60), (1, 8, 16)),      # 72 items, 4 a row: 9 per XCD, rounded to 12
+                                             (2, (2, 9, 40), (2, 8, 16)),      # 2 per tile, 6 a row
+                                             (3, (3, 5, 22), (2, 4, 4))])      # one-wave workgroups, 6 a row
+def test_every_item_of_an_even_row_is_computed(prec, heads, grid, tile):
+    """Rows of an even number of work items are dealt in a turning order: each item once."""
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=(3, 3, 3), heads=heads, n_outlier=3, config_id=16)
+    run = gu.GpuRun(w)
+    out = run.attn(prec)
+    for h in range(heads):
+        st = gu.compare_head(run, out, h, prec, w.window)
+        say("  head", h, st)
+        gu.assert_parity(st, f"{grid} {tile} head {h}")
+
+
+@pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
 @pytest.mark.parametrize("tile,rest", [((1, 1, 128), r) for r in (1, 31, 32, 33, 64, 65, 96, 97, 127)] +
                          [((1, 2, 128), r) for r in (1, 48, 63, 64, 65, 127)])
 def test_cut_tiles_at_the_edges_of_sub_blocks(prec, tile, rest):
