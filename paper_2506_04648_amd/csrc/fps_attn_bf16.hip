@@ -14,15 +14,17 @@ namespace fps {
 
 union Bf16x8 { uint4 u; v8bf v; v8h h; };
 
-template <int SB, int W, bool MB>
-__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int SB, int W, bool MB, int KS>
+__global__ __launch_bounds__(KS * W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bf16_kernel(AttnArgs a) {
-    constexpr int NTHR = W * 64;
+    constexpr int NTHR = KS * W * 64;
     constexpr int CPT = SB * 8 / W;                        // 16-byte chunks per thread per operand block
     constexpr int BLOCK_BYTES = SB * 8192;
     static_assert(CPT >= 1 && CPT <= 8 && CPT * W == SB * 8, "every wave copies the same share of a block");
-    constexpr int LDS_BYTES = 2 * BLOCK_BYTES > W * kStoreRegionBytes ? 2 * BLOCK_BYTES : W * kStoreRegionBytes;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];   // K, V; then the output transpose
+    constexpr int GROUP_BYTES = 2 * BLOCK_BYTES;           // K, V
+    constexpr int LDS_BYTES = KS * GROUP_BYTES > SplitMerge<W, KS>::kBytes ? KS * GROUP_BYTES : SplitMerge<W, KS>::kBytes;
+    // the groups' blocks; afterwards their sums and the output transpose
+    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
     const Geom& G = a.g;
     const int NS = MB ? G.NS : 1;
     const int KBG = MB && SB == 4 ? G.KBG : 1;             // key blocks of a scale group
@@ -30,18 +32,19 @@ void attn_bf16_kernel(AttnArgs a) {
     int bh, u, jq;
     if (!work_item(a, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave) % W, kg = KS > 1 ? __builtin_amdgcn_readfirstlane(wave) / W : 0;
     const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
     const int ucls = tile_class(G, ut, uh, uw);
-    // the wave's sub-block of query rows; rotated from tile to tile so that the idle waves of cut tiles
-    // fall on different SIMDs
-    const int qs = jq * W + (W == 4 ? (wave_s + u) & 3 : wave_s);
+    // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
+    // waves of cut tiles fall on different SIMDs
+    const int row_block = W == 4 ? (wave_s + kg + u) & 3 : wave_s;
+    const int qs = jq * W + row_block;
     QueryRows rows;
     rows.init(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
     zero_padding_rows(a, rows, ucls, lane);
     if (!any_real_row<SB, W, MB>(G, ucls, jq, KBG * SB)) return;
     const size_t tile0 = (size_t)bh * G.M;
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0]);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0]) + kg * GROUP_BYTES;
     KeyBox box;
     box.init(a, ut, uh, uw);
     if (a.visited && bh == 0 && jq == 0) box.mark(G, a.visited + (size_t)u * G.M, NTHR);
@@ -59,16 +62,34 @@ void attn_bf16_kernel(AttnArgs a) {
         for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
     };
 
+    // Of a walk of `total` blocks, those of this wave group.  Group 0 never has fewer than another; what a group
+    // has fewer barriers than group 0 (two a block, three a walk) it makes up for at the end, as every barrier
+    // is one of the whole workgroup.  (Made up for within the walk, they cost 110 spilled registers.)
+    int owed = 0;
+    auto blocks_of_group = [&](int total) FPS_INLINE {
+        if (KS == 1) return total;
+        const int nblk = (total - kg + KS - 1) / KS;
+        owed += 2 * ((total + KS - 1) / KS - nblk) + (nblk == 0 ? 3 : 0);
+        return nblk;
+    };
+    auto make_up = [&]() FPS_INLINE {
+        if (KS > 1)
+            for (; owed > 0; --owed) __syncthreads();
+    };
+
     if (rows.rows <= 0) {
         // no real row: this wave only copies its share of the K and V blocks, barrier for barrier
         for (int nh = 2 * SB; nh >= 1; --nh) {
             const uint32_t classes = G.nh_classes[nh - 1] & box.classes;
             if (!classes) continue;
             BlockWalk<MB> walk(G, box, nh);
-            const int nblk = walk.begin(classes);
+            const int total = walk.begin(classes);
+            const int nblk = blocks_of_group(total);
+            if (nblk == 0) continue;
+            walk.skip(kg);
             KeyBlock cur = walk.block(), nxt = cur;
             stage(0, k_blk(cur));
-            if (nblk > 1) { walk.next(); nxt = walk.block(); }
+            if (nblk > 1) { walk.skip(KS); nxt = walk.block(); }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();                               // K(0) visible
             __syncthreads();                               // QK(0) done
@@ -81,7 +102,7 @@ void attn_bf16_kernel(AttnArgs a) {
                 __syncthreads();                           // QK(i+1) done; V(i) visible
                 cur = nxt;
                 if (i + 2 < nblk) {
-                    walk.next();
+                    walk.skip(KS);
                     nxt = walk.block();
                     stage(0, k_blk(nxt));
                 }
@@ -89,6 +110,8 @@ void attn_bf16_kernel(AttnArgs a) {
                 __syncthreads();                           // PV(i) done; K(i+2) visible
             }
         }
+        make_up();
+        if (KS > 1) __syncthreads();
         return;
     }
 
@@ -104,8 +127,8 @@ void attn_bf16_kernel(AttnArgs a) {
         for (int db = 0; db < 4; ++db) acc[db] = zero16();
     }
     const float sc = kLog2eOverSqrtD;
-    const uint4* ldsK4 = reinterpret_cast<const uint4*>(lds);
-    const uint4* ldsV4 = reinterpret_cast<const uint4*>(lds + BLOCK_BYTES);
+    const uint4* ldsK4 = reinterpret_cast<const uint4*>(lds + kg * GROUP_BYTES);
+    const uint4* ldsV4 = reinterpret_cast<const uint4*>(lds + kg * GROUP_BYTES + BLOCK_BYTES);
 
     auto pipeline = [&](auto nh_tag) FPS_INLINE {
         constexpr int NH = decltype(nh_tag)::value;        // 16-key halves
@@ -113,7 +136,10 @@ void attn_bf16_kernel(AttnArgs a) {
         const uint32_t classes = G.nh_classes[NH - 1] & box.classes;
         if (!classes) return;
         BlockWalk<MB> walk(G, box, NH);
-        const int nblk = walk.begin(classes);
+        const int total = walk.begin(classes);
+        const int nblk = blocks_of_group(total);
+        if (nblk == 0) return;
+        walk.skip(kg);
 
         v16f s[NB];                                        // S^T, blocks of 32 keys
         Bf16x8 pop[NH];                                // P^T in fp16: contraction steps of 16 keys
@@ -168,7 +194,7 @@ void attn_bf16_kernel(AttnArgs a) {
         KeyBlock cur = walk.block(), nxt = cur;
         stage(0, k_blk(cur));
         float svv = load_uniform(sv_head, cur.group);
-        if (nblk > 1) { walk.next(); nxt = walk.block(); }
+        if (nblk > 1) { walk.skip(KS); nxt = walk.block(); }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
 #pragma unroll
@@ -197,7 +223,7 @@ void attn_bf16_kernel(AttnArgs a) {
             const float svv_next = load_uniform(sv_head, nxt.group);
             cur = nxt;
             const bool fetch_k = i + 2 < nblk;
-            if (fetch_k) { walk.next(); nxt = walk.block(); }
+            if (fetch_k) { walk.skip(KS); nxt = walk.block(); }
             const uint8_t* ksrc = k_blk(nxt);
 
             // step (kb, ks): a pair of weights of score block kb beside the MFMA (kb - 1, ks) that
@@ -279,14 +305,34 @@ void attn_bf16_kernel(AttnArgs a) {
     pipeline(Count<2>{});
     pipeline(Count<1>{});
 
+    make_up();
+    if constexpr (KS > 1) {                                // every wave is done with the buffers
+        // O of a group is relative to 2^e_ref, l to 2^m_run: moving both to the largest is exact
+        const SplitMerge<W, KS> merge{lds, row_block, lane};
+        // without a block: O and l are zero and their references the lowest
+        float ref = m_run == -INFINITY ? -INFINITY : e_ref;
+        if (kg > 0) merge.leave(kg, acc, ref, l_run, m_run);
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll 1
+        for (int g = 1; g < KS; ++g) {
+            const v4f o = merge.numbers(g);
+            const float top = __builtin_fmaxf(ref, o[0]), m_top = __builtin_fmaxf(m_run, o[2]);   // finite: group 0 has a block
+            merge.add(g, acc, fast_exp2(ref - top), fast_exp2(o[0] - top));
+            l_run = __builtin_fmaf(o[1], fast_exp2(o[2] - m_top), l_run * fast_exp2(m_run - m_top));
+            ref = top;
+            m_run = m_top;
+        }
+        e_ref = ref;
+    }
     const float l = sum_over_row_pair(l_run);
     const float inv = l > 0.f ? fast_exp2(e_ref - m_run) / l : 0.f;
-    store_rows(a, rows, lane, acc, inv, lds + wave * kStoreRegionBytes);
+    store_rows(a, rows, lane, acc, inv, lds + row_block * kStoreRegionBytes);
 }
 
-template <int SB, int W, bool MB>
+template <int SB, int W, bool MB, int KS = 1>
 static void launch(const AttnArgs& a, int grid, hipStream_t st) {
-    attn_bf16_kernel<SB, W, MB><<<grid, W * 64, 0, st>>>(a);
+    attn_bf16_kernel<SB, W, MB, KS><<<grid, KS * W * 64, 0, st>>>(a);
 }
 
 void launch_attn_bf16(const AttnArgs& a, int grid, hipStream_t st) {
@@ -294,23 +340,43 @@ void launch_attn_bf16(const AttnArgs& a, int grid, hipStream_t st) {
     const bool four = query_waves(g) == 4;
     switch (g.BS == 128 ? 4 : g.KBS) {
         case 4:
-            if (g.KB > 1) launch<4, 4, true>(a, grid, st);
-            else          launch<4, 4, false>(a, grid, st);
+            if (g.KB > 1) {
+                if (split_keys(a, 2)) launch<4, 4, true, 2>(a, grid, st);
+                else                  launch<4, 4, true>(a, grid, st);
+            } else {
+                if (split_keys(a, 2)) launch<4, 4, false, 2>(a, grid, st);
+                else                  launch<4, 4, false>(a, grid, st);
+            }
             break;
         case 3:
-            if (g.NS == 1) launch<3, 3, false>(a, grid, st);
-            else if (four) launch<3, 4, true>(a, grid, st);
-            else           launch<3, 3, true>(a, grid, st);
+            if (g.NS == 1) {
+                if (split_keys(a, 2)) launch<3, 3, false, 2>(a, grid, st);
+                else                  launch<3, 3, false>(a, grid, st);
+            } else if (four) {
+                launch<3, 4, true>(a, grid, st);
+            } else {
+                launch<3, 3, true>(a, grid, st);
+            }
             break;
         case 2:
-            if (g.NS == 1) launch<2, 2, false>(a, grid, st);
-            else if (four) launch<2, 4, true>(a, grid, st);
-            else           launch<2, 2, true>(a, grid, st);
+            if (g.NS == 1) {
+                if (split_keys(a, 4)) launch<2, 2, false, 4>(a, grid, st);
+                else                  launch<2, 2, false>(a, grid, st);
+            } else if (four) {
+                launch<2, 4, true>(a, grid, st);
+            } else {
+                launch<2, 2, true>(a, grid, st);
+            }
             break;
         default:
-            if (g.NS == 1) launch<1, 1, false>(a, grid, st);
-            else if (four) launch<1, 4, true>(a, grid, st);
-            else           launch<1, 1, true>(a, grid, st);
+            if (g.NS == 1) {
+                if (split_keys(a, 4)) launch<1, 1, false, 4>(a, grid, st);
+                else                  launch<1, 1, false>(a, grid, st);
+            } else if (four) {
+                launch<1, 4, true>(a, grid, st);
+            } else {
+                launch<1, 1, true>(a, grid, st);
+            }
             break;
     }
 }

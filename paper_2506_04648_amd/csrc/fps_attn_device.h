@@ -14,6 +14,9 @@
 //                        21x30x52 x 12 heads, and 3949 instead of 2664 us for 64-token sub-tiles of (2,8,16)
 //                        tiles, window 3x3x3, x 24 heads.)
 // MB = true: a tile is several key blocks.
+// KS = 2 or 4 (launches that would leave the chip half empty): KS times W waves; wave group kg takes the
+// blocks kg, kg + KS, .. of every walk, with buffers of its own, and group 0 adds up the groups' O and row
+// sums at the end.
 //
 // Scores are produced transposed, S^T = K Q^T, on the 32x32 matrix instructions, so that a lane's
 // accumulator holds one query row and a fixed set of keys: lane (n, h) = lane & 31, lane >> 5 holds
@@ -403,6 +406,10 @@ struct BlockWalk {
         jb1 = MB ? (NH == 8 ? (n + 15) >> 7 : jb0 + 1) : 1;
         jb = jb0;
     }
+    // n blocks ahead, not past the last one
+    __device__ __forceinline__ void skip(int n_blocks) {
+        for (int i = 0; i < n_blocks; ++i) next();
+    }
     // sets the walk to its first block; returns the number of blocks
     __device__ __forceinline__ int begin(uint32_t classes_) {
         int total = 0;
@@ -434,13 +441,66 @@ struct BlockWalk {
     }
 };
 
-// Kernel launchers of the two precisions; grid: workgroups
-void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st);
-void launch_attn_bf16(const AttnArgs& a, int grid, hipStream_t st);
+// Key split (KS > 1): where the wave groups 1 .. KS - 1 leave O and up to three numbers per lane for group 0.  In LDS,
+// behind the regions of the output transpose.
+template <int W, int KS>
+struct SplitMerge {
+    static constexpr int kWaveBytes = 64 * (64 + 4) * 4;
+    static constexpr int kBytes = W * kStoreRegionBytes + (KS - 1) * W * kWaveBytes;
+    uint8_t* lds;
+    int row_block, lane;                // the 32 query rows of the work item that the wave has
+    __device__ __forceinline__ uint4* region(int kg) const {
+        return reinterpret_cast<uint4*>(lds + W * kStoreRegionBytes + ((kg - 1) * W + row_block) * kWaveBytes);
+    }
+    __device__ __forceinline__ void leave(int kg, const v16f (&acc)[4], float x, float y, float z = 0.f) const {
+        uint4* r = region(kg);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const v4f v = v4f{acc[i >> 2][4 * (i & 3)], acc[i >> 2][4 * (i & 3) + 1], acc[i >> 2][4 * (i & 3) + 2],
+                              acc[i >> 2][4 * (i & 3) + 3]};
+            *reinterpret_cast<v4f*>(r + i * 64 + lane) = v;
+        }
+        reinterpret_cast<v4f*>(r + 16 * 64)[lane] = v4f{x, y, z, 0.f};
+    }
+    __device__ __forceinline__ v4f numbers(int kg) const {
+        return reinterpret_cast<const v4f*>(region(kg) + 16 * 64)[lane];
+    }
+    // acc = acc * mine + theirs * factor
+    __device__ __forceinline__ void add(int kg, v16f (&acc)[4], float mine, float factor) const {
+        const uint4* r = region(kg);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const v4f v = *reinterpret_cast<const v4f*>(r + i * 64 + lane);
+            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few loads ahead, not all: no registers for them
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[i >> 2][4 * (i & 3) + j] = __builtin_fmaf(v[j], factor, acc[i >> 2][4 * (i & 3) + j] * mine);
+        }
+    }
+};
+
 // waves of a workgroup (= sub-blocks of a query block)
 inline int query_waves(const Geom& g) {
     const int sb = g.BS == 128 ? 4 : g.KBS, tsb = g.TSP / 32;
     return sb == 4 || (g.NS > 1 && tsb % 4 == 0) ? 4 : sb;
 }
 
+// Key blocks of the largest walk box of a window, counting full tiles.
+inline int window_blocks(const AttnArgs& a) {
+    auto span = [](int n, int r) { return n < 2 * r + 1 ? n : 2 * r + 1; };
+    const long long tiles = (long long)span(a.g.nT, a.rt) * span(a.g.nH, a.rh) * span(a.g.nW, a.rw);
+    return (int)(tiles * a.g.NS * a.g.KBG > 1 << 20 ? 1 << 20 : tiles * a.g.NS * a.g.KBG);
+}
+// The keys of a work item are split over `ks` wave groups where the launch's waves are few enough to be
+// all resident at once with that (8 waves of these kernels' registers per CU, 256 CUs) and the walk is
+// long enough to pay for adding up.  A wave alone on its SIMD takes 1.6 us a 128-key block, two that share one 2.3
+// us for two.  Attention, split against not: 225 items of up to 27 blocks 45.2 -> 37.9 us (two groups), 64
+// one-wave items of up to 9 blocks 11.6 -> 10.3 us (four groups).
+inline bool split_keys(const AttnArgs& a, int ks) {
+    return (long long)a.total * query_waves(a.g) * ks <= 8 * 256 && window_blocks(a) >= 2 * ks;
+}
+
+// Kernel launchers of the two precisions; grid: workgroups
+void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st);
+void launch_attn_bf16(const AttnArgs& a, int grid, hipStream_t st);
 }  // namespace fps

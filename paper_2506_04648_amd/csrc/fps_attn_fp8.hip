@@ -22,15 +22,16 @@
 
 namespace fps {
 
-template <int SB, int W, bool VCH, bool MB>
-__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int SB, int W, bool VCH, bool MB, int KS>
+__global__ __launch_bounds__(KS * W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fp8_kernel(AttnArgs a) {
-    constexpr int NTHR = W * 64;
+    constexpr int NTHR = KS * W * 64;
     constexpr int CPT = SB * 4 / W;                        // 16-byte chunks per thread per operand block
     constexpr int BLOCK_BYTES = SB * 4096;
     static_assert(CPT >= 1 && CPT <= 4 && CPT * W == SB * 4, "every wave copies the same share of a block");
-    constexpr int LDS_BYTES = 4 * BLOCK_BYTES > W * kStoreRegionBytes ? 4 * BLOCK_BYTES : W * kStoreRegionBytes;
-    // K even, K odd, V even, V odd; the output transpose uses it afterwards
+    constexpr int GROUP_BYTES = 4 * BLOCK_BYTES;           // K even, K odd, V even, V odd
+    constexpr int LDS_BYTES = KS * GROUP_BYTES > SplitMerge<W, KS>::kBytes ? KS * GROUP_BYTES : SplitMerge<W, KS>::kBytes;
+    // the groups' blocks; afterwards their sums and the output transpose
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
     const Geom& G = a.g;
     const int NS = MB ? G.NS : 1;
@@ -39,18 +40,19 @@ void attn_fp8_kernel(AttnArgs a) {
     int bh, u, jq;
     if (!work_item(a, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
-    const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+    const int wave_s = __builtin_amdgcn_readfirstlane(wave) % W, kg = KS > 1 ? __builtin_amdgcn_readfirstlane(wave) / W : 0;
     const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
     const int ucls = tile_class(G, ut, uh, uw);
-    // the wave's sub-block of query rows; rotated from tile to tile so that the idle waves of cut tiles
-    // fall on different SIMDs
-    const int qs = jq * W + (W == 4 ? (wave_s + u) & 3 : wave_s);
+    // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
+    // waves of cut tiles fall on different SIMDs
+    const int row_block = W == 4 ? (wave_s + kg + u) & 3 : wave_s;
+    const int qs = jq * W + row_block;
     QueryRows rows;
     rows.init(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
     zero_padding_rows(a, rows, ucls, lane);
     if (!any_real_row<SB, W, MB>(G, ucls, jq, KBG * SB)) return;
     const size_t tile0 = (size_t)bh * G.M;
-    const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0]);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0]) + kg * GROUP_BYTES;
     KeyBox box;
     box.init(a, ut, uh, uw);
     if (a.visited && bh == 0 && jq == 0) box.mark(G, a.visited + (size_t)u * G.M, NTHR);
@@ -68,8 +70,23 @@ void attn_fp8_kernel(AttnArgs a) {
 #pragma unroll
         for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
     };
-    auto lds_block = [&](int buf) FPS_INLINE { return lds + buf * BLOCK_BYTES; };
+    auto lds_block = [&](int buf) FPS_INLINE { return lds + kg * GROUP_BYTES + buf * BLOCK_BYTES; };
     int par = 0;                                           // parity of the current block's K and V buffers
+
+    // Of a walk of `total` blocks, those of this wave group.  Group 0 never has fewer than another; what a group
+    // has fewer barriers than group 0 (one a block, one a walk) it makes up for at the end, as every barrier
+    // is one of the whole workgroup.  (Made up for within the walk, they cost 110 spilled registers.)
+    int owed = 0;
+    auto blocks_of_group = [&](int total) FPS_INLINE {
+        if (KS == 1) return total;
+        const int nblk = (total - kg + KS - 1) / KS;
+        owed += 1 * ((total + KS - 1) / KS - nblk) + (nblk == 0 ? 1 : 0);
+        return nblk;
+    };
+    auto make_up = [&]() FPS_INLINE {
+        if (KS > 1)
+            for (; owed > 0; --owed) __syncthreads();
+    };
 
     if (rows.rows <= 0) {
         // no real row: this wave only copies its share of the K and V blocks, barrier for barrier
@@ -77,12 +94,15 @@ void attn_fp8_kernel(AttnArgs a) {
             const uint32_t classes = G.nh_classes[nh - 1] & box.classes;
             if (!classes) continue;
             BlockWalk<MB> walk(G, box, nh);
-            const int nblk = walk.begin(classes);
+            const int total = walk.begin(classes);
+            const int nblk = blocks_of_group(total);
+            if (nblk == 0) continue;
+            walk.skip(kg);
             KeyBlock nxt = walk.block();
             stage(par, k_blk(nxt));
             stage(2 + par, v_blk(nxt));
             if (nblk > 1) {
-                walk.next();
+                walk.skip(KS);
                 nxt = walk.block();
                 stage(par ^ 1, k_blk(nxt));
             }
@@ -92,7 +112,7 @@ void attn_fp8_kernel(AttnArgs a) {
                 __syncthreads();
                 const KeyBlock v_next = nxt;
                 if (i + 2 < nblk) {
-                    walk.next();
+                    walk.skip(KS);
                     nxt = walk.block();
                     stage(par, k_blk(nxt));
                 }
@@ -103,7 +123,9 @@ void attn_fp8_kernel(AttnArgs a) {
             __syncthreads();
             par ^= 1;
         }
+        make_up();
         __syncthreads();
+        if (KS > 1) __syncthreads();
         return;
     }
 
@@ -130,7 +152,10 @@ void attn_fp8_kernel(AttnArgs a) {
         const uint32_t classes = G.nh_classes[NH - 1] & box.classes;
         if (!classes) return;
         BlockWalk<MB> walk(G, box, NH);
-        const int nblk = walk.begin(classes);
+        const int total = walk.begin(classes);
+        const int nblk = blocks_of_group(total);
+        if (nblk == 0) return;
+        walk.skip(kg);
 
         v16f s[NB];                                        // S^T, blocks of 32 keys
         v8i pb[2];                                         // P^T as packed E4M3: contraction steps 0 and 1
@@ -236,7 +261,7 @@ void attn_fp8_kernel(AttnArgs a) {
         float sc = sqc * load_uniform(sk_head, nxt.group);
         float svv = VCH ? 1.f : load_uniform(sv_head, nxt.group);
         if (nblk > 1) {
-            walk.next();
+            walk.skip(KS);
             nxt = walk.block();
             stage(par ^ 1, k_blk(nxt));
         }
@@ -269,7 +294,7 @@ void attn_fp8_kernel(AttnArgs a) {
             const bool fetch_k = i + 2 < nblk;
             const uint8_t* ksrc = nullptr;
             if (fetch_k) {
-                walk.next();
+                walk.skip(KS);
                 nxt = walk.block();
                 ksrc = k_blk(nxt);
             }
@@ -368,17 +393,35 @@ void attn_fp8_kernel(AttnArgs a) {
     pipeline(Count<2>{});
     pipeline(Count<1>{});
 
+    make_up();
+    __syncthreads();                                       // all waves are done with the staged tiles
+    if constexpr (KS > 1) {
+        // O and l of a group are relative to its reference, a power of two: moving them to the largest is exact
+        const SplitMerge<W, KS> merge{lds, row_block, lane};
+        float ref = VCH || m_run == -INFINITY ? m_run : m_base;        // -inf: the group had no block, all zero
+        if (kg > 0) merge.leave(kg, acc, ref, l_run);
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll 1
+        for (int g = 1; g < KS; ++g) {
+            const v4f o = merge.numbers(g);
+            const float top = __builtin_fmaxf(ref, o[0]);   // finite: group 0 has a block
+            const float mine = fast_exp2(ref - top), theirs = fast_exp2(o[0] - top);
+            merge.add(g, acc, mine, theirs);
+            l_run = __builtin_fmaf(o[1], theirs, l_run * mine);
+            ref = top;
+        }
+    }
     const float l = sum_over_row_pair(l_run);
     const float inv = l > 0.f ? 1.0f / l : 0.f;            // l already carries the factor 448
-    __syncthreads();                                       // all waves are done with the staged tiles
-    store_rows(a, rows, lane, acc, inv, lds + wave * kStoreRegionBytes,
+    store_rows(a, rows, lane, acc, inv, lds + row_block * kStoreRegionBytes,
                VCH ? a.sv + (size_t)bh * 128 : nullptr);
 }
 
-template <int SB, int W, bool MB>
+template <int SB, int W, bool MB, int KS = 1>
 static void launch(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
-    if (vch) attn_fp8_kernel<SB, W, true, MB><<<grid, W * 64, 0, st>>>(a);
-    else     attn_fp8_kernel<SB, W, false, MB><<<grid, W * 64, 0, st>>>(a);
+    if (vch) attn_fp8_kernel<SB, W, true, MB, KS><<<grid, KS * W * 64, 0, st>>>(a);
+    else     attn_fp8_kernel<SB, W, false, MB, KS><<<grid, KS * W * 64, 0, st>>>(a);
 }
 
 void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
@@ -386,23 +429,43 @@ void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
     const bool four = query_waves(g) == 4;
     switch (g.BS == 128 ? 4 : g.KBS) {
         case 4:
-            if (g.KB > 1) launch<4, 4, true>(a, vch, grid, st);
-            else          launch<4, 4, false>(a, vch, grid, st);
+            if (g.KB > 1) {
+                if (split_keys(a, 2)) launch<4, 4, true, 2>(a, vch, grid, st);
+                else                  launch<4, 4, true>(a, vch, grid, st);
+            } else {
+                if (split_keys(a, 2)) launch<4, 4, false, 2>(a, vch, grid, st);
+                else                  launch<4, 4, false>(a, vch, grid, st);
+            }
             break;
         case 3:
-            if (g.NS == 1) launch<3, 3, false>(a, vch, grid, st);
-            else if (four) launch<3, 4, true>(a, vch, grid, st);
-            else           launch<3, 3, true>(a, vch, grid, st);
+            if (g.NS == 1) {
+                if (split_keys(a, 2)) launch<3, 3, false, 2>(a, vch, grid, st);
+                else                  launch<3, 3, false>(a, vch, grid, st);
+            } else if (four) {
+                launch<3, 4, true>(a, vch, grid, st);
+            } else {
+                launch<3, 3, true>(a, vch, grid, st);
+            }
             break;
         case 2:
-            if (g.NS == 1) launch<2, 2, false>(a, vch, grid, st);
-            else if (four) launch<2, 4, true>(a, vch, grid, st);
-            else           launch<2, 2, true>(a, vch, grid, st);
+            if (g.NS == 1) {
+                if (split_keys(a, 4)) launch<2, 2, false, 4>(a, vch, grid, st);
+                else                  launch<2, 2, false>(a, vch, grid, st);
+            } else if (four) {
+                launch<2, 4, true>(a, vch, grid, st);
+            } else {
+                launch<2, 2, true>(a, vch, grid, st);
+            }
             break;
         default:
-            if (g.NS == 1) launch<1, 1, false>(a, vch, grid, st);
-            else if (four) launch<1, 4, true>(a, vch, grid, st);
-            else           launch<1, 1, true>(a, vch, grid, st);
+            if (g.NS == 1) {
+                if (split_keys(a, 4)) launch<1, 1, false, 4>(a, vch, grid, st);
+                else                  launch<1, 1, false>(a, vch, grid, st);
+            } else if (four) {
+                launch<1, 4, true>(a, vch, grid, st);
+            } else {
+                launch<1, 1, true>(a, vch, grid, st);
+            }
             break;
     }
 }

@@ -356,6 +356,37 @@ def test_every_item_of_an_even_row_is_computed(prec, heads, grid, tile):
         gu.assert_parity(st, f"{grid} {tile} head {h}")
 
 
+# heads, grid, tile, window, heads compared.  128-slot tiles split their keys in two, smaller ones (of one
+# scale group) in two or four, where a launch is small and a window has four or eight blocks
+SPLIT_CASES = [
+    (2, (4, 8, 16), (1, 8, 16), (7, 1, 1), (0, 1)),          # 4 blocks: the fewest that are split
+    (2, (3, 8, 16), (1, 8, 16), (5, 1, 1), (0,)),            # 3 blocks: not split
+    (2, (5, 13, 37), (1, 8, 16), (3, 3, 3), (0, 1)),         # odd counts, cut tiles with idle waves, walks of one block
+    (2, (3, 13, 40), (2, 8, 16), (3, 3, 3), (0, 1)),         # tiles of two blocks
+    (2, (4, 13, 20), (1, 7, 11), (3, 3, 3), (0, 1)),         # 77 tokens: three sub-blocks, keys in two
+    (2, (5, 7, 18), (3, 4, 4), (3, 3, 5), (0, 1)),           # 48 tokens: two sub-blocks, keys in four
+    (2, (4, 14, 18), (2, 4, 4), (3, 3, 3), (0, 1)),          # 32 tokens: one sub-block, keys in four
+    (40, (4, 8, 26), (2, 4, 4), (3, 3, 3), (0, 39)),         # 1120 items: too many to split
+    (40, (6, 8, 26), (3, 4, 4), (3, 3, 3), (0, 39)),         # 1120 items
+    (40, (4, 14, 22), (1, 7, 11), (3, 3, 3), (0, 39)),       # 640 items
+]
+
+
+@pytest.mark.parametrize("prec,vscale", [(fps.PREC_FP8, fps.VSCALE_TILE), (fps.PREC_FP8, fps.VSCALE_CHANNEL),
+                                         (fps.PREC_BF16, fps.VSCALE_TILE)])
+@pytest.mark.parametrize("heads,grid,tile,window,compared", SPLIT_CASES)
+def test_keys_split_over_wave_groups(prec, vscale, heads, grid, tile, window, compared):
+    say("split", prec, vscale, heads, grid, tile, window)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=heads, n_outlier=3, config_id=17)
+    run = gu.GpuRun(w)
+    out, vis = run.attn(prec, vscale=vscale, visited=True)
+    assert np.array_equal(vis.cpu().numpy().astype(bool), fo.tile_mask(run.g, window))
+    for h in compared:
+        st = gu.compare_head(run, out, h, prec, window, vscale=vscale)
+        say("  head", h, st)
+        gu.assert_parity(st, f"{grid} {tile} head {h}")
+
+
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
 @pytest.mark.parametrize("tile,rest", [((1, 1, 128), r) for r in (1, 31, 32, 33, 64, 65, 96, 97, 127)] +
                          [((1, 2, 128), r) for r in (1, 48, 63, 64, 65, 127)])
