@@ -191,7 +191,7 @@ def main():
         "mfma_only_sustained_tflops": mfma_sustained,
         "attention_frac_of_sustained_mfma": flop / (attn_ms * 1e-3) / 1e12 / mfma_sustained,
         "quantize_GBps": quant_bytes / (quant_ms * 1e-3) / 1e9,
-        "roofline": {"bound": "mfma", "kernel": "attn_fp8_wide_kernel", "achieved": flop / (attn_ms * 1e-3) / 1e12,
+        "roofline": {"bound": "mfma", "kernel": "attn_fp8_kernel", "achieved": flop / (attn_ms * 1e-3) / 1e12,
                      "peak": FP8_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": flop / (attn_ms * 1e-3) / 1e12 / FP8_PEAK_TFLOPS,
                      "traffic": traffic.get("bytes"), "traffic_range": traffic.get("range"),
