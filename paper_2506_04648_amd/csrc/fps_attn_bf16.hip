@@ -4,15 +4,22 @@
 // pair is 64 KB here, so K and V are single-buffered: V(i) streams in while P(i) is taken (after every
 // wave has finished PV(i-1)), K(i+2) during PV(i) (after every wave has finished QK(i+1)); two barriers
 // per iteration.
-// V's per-tile scale is a power of two, so the PV product accumulates straight into O: a tile's weight
-// 2^E, E = log2(s^V) + m, is applied by keeping O relative to the largest E met so far -- O is rescaled
-// (exactly) only when that grows, and a tile below it has the difference folded into the exponent of
-// its weights before they are rounded to fp16.
+// V's scale per group is a power of two, so the PV product accumulates straight into O: O is kept relative to
+// 2^e_ref, and a block's weights are 2^(S' + log2(s^V) - e_ref) with 2^14 on top, rounded to fp16.  e_ref
+// moves, and O with it (exactly: powers of two), where a block needs it:
+//   up,   so that no weight of the block exceeds 2^14: e_ref >= log2(s^V) + the block's row maximum;
+//   down, so that the block's weights keep their bits: e_ref <= log2(s^V) + m + kMaxFold, m the row reference.
+// fp16 holds all 11 bits of weights down to 2^-28 of 2^e_ref, hence those of at least 2^-24 of the row's largest
+// weight whatever the scales of the groups met before -- a group of zeros (scale 1) beside values of 1e-6, or a
+// group of large values whose keys have no weight.  Following only the largest scale met, as in a
+// running maximum, such groups cost the row one bit per binade: output errors of 0.3 RMS at V of 1e-6 beside zeros.
+// Groups of like magnitude never move O down.
 #include "fps_attn_device.h"
 
 namespace fps {
 
 union Bf16x8 { uint4 u; v8bf v; v8h h; };
+constexpr int kMaxFold = 4;                // binades by which a block's weights may lie under 2^14
 
 template <int SB, int W, bool MB, int KS>
 __global__ __launch_bounds__(KS * W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -117,7 +124,8 @@ void attn_bf16_kernel(AttnArgs a) {
 
     Bf16x8 qop[8];                                         // Q^T, contraction steps of 16 channels
     float m_run = -INFINITY, l_run = 0.f;                  // row reference; sum of 2^14 P relative to it
-    float e_ref = 0.f;                                     // the largest weight exponent E met so far
+    float e_ref = 0.f;                                     // O is relative to 2^e_ref
+    int e_v_max = -127;                                    // of the largest V scale met
     v16f acc[4];
     {
         const uint4* p = reinterpret_cast<const uint4*>(a.q + (((tile0 + u) * TSB + qs) * 32 + n) * 256);
@@ -145,7 +153,8 @@ void attn_bf16_kernel(AttnArgs a) {
         Bf16x8 pop[NH];                                // P^T in fp16: contraction steps of 16 keys
         Bf16x8 ring[4];                                    // MFMA operands on their way from LDS
         float alpha_acc = 1.f;                             // rescale owed to O before the block's PV
-        float alpha_l = 1.f, below = 0.f, cm = 0.f;
+        float alpha_l = 1.f, cm = 0.f;
+        float to_l = 0.f;                                  // log2 of what the weights' sum counts in the row sum
 
         // operand j of the K block: key block j/8, contraction step j%8
         auto k_operand = [&](int j) FPS_INLINE { return ldsK4[j * 64 + lane]; };
@@ -172,22 +181,37 @@ void attn_bf16_kernel(AttnArgs a) {
             reinterpret_cast<uint32_t*>(&pop[2 * kb + (i >> 2)].u)[i & 3] = wd;
         };
         // the row reference and weight exponents of the block whose row maximum mx was taken; svv: its
-        // V scale, 2^e exactly
+        // V scale, 2^e exactly.  O holds every earlier block but for the rescale alpha_acc.
         auto new_reference = [&](float mx, float svv) FPS_INLINE {
-            const float e_v = (float)((int)((__float_as_uint(svv) >> 23) & 0xFFu) - 127);
-            mx = max_over_row_pair(mx);
-            const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(mx * sc));
-            const float e_new = e_v + m_new;
-            const float e_top = m_run == -INFINITY ? e_new : __builtin_fmaxf(e_ref, e_new);
+            const int e_vi = (int)((__float_as_uint(svv) >> 23) & 0xFFu) - 127;
+            const float e_v = (float)e_vi;
+            const float top = __builtin_ceilf(max_over_row_pair(mx) * sc);
+            const float m_new = __builtin_fmaxf(m_run, top);
+            const float e_low = e_v + top;
+            float e_new = m_run == -INFINITY ? e_low : __builtin_fmaxf(e_ref, e_low);
+            const float e_high = e_v + m_new + (float)kMaxFold;
+            // e_ref <= e_v_max + m_run, so groups of like magnitude need only a scalar comparison here
+            if (e_vi + kMaxFold < e_v_max && __any(e_new > e_high)) {
+                // O moves down, as far as its largest element allows: up to 2^100 (2^126 times at most)
+                float o = 0.f;
+#pragma unroll
+                for (int db = 0; db < 4; ++db)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o = __builtin_fmaxf(o, __builtin_fabsf(acc[db][r]));
+                const int e_o = (int)(__float_as_uint(max_over_row_pair(o)) >> 23) - 127;
+                e_new = __builtin_fmaxf(__builtin_fminf(e_new, e_high), e_new - (float)min(99 - e_o, 126));
+            }
+            e_v_max = max(e_v_max, e_vi);
             alpha_l = fast_exp2(m_run - m_new);            // 0 on the first block (m_run = -inf)
-            alpha_acc = m_run == -INFINITY ? 1.0f : fast_exp2(e_ref - e_top);
+            alpha_acc = m_run == -INFINITY ? 1.0f : fast_exp2(e_ref - e_new);
             m_run = m_new;
-            // <= 0: this block's weight relative to O's scale; 64 binades down every fp16 weight is zero
-            below = __builtin_fmaxf(e_new - e_top, -64.0f);
-            e_ref = e_top;
-            // 2^14 * 2^(S' - m) * 2^below: the factor 2^14 keeps small weights in fp16's normal range
+            e_ref = e_new;
+            // <= 0: the block's largest weight relative to 2^14; 64 binades down every fp16 weight is zero
+            const float below = __builtin_fmaxf(e_low - e_new, -64.0f);
+            // 2^14 * 2^(S' - top) * 2^below: the factor 2^14 keeps small weights in fp16's normal range
             // and cancels against the row sum, which is taken of the same values
-            cm = kFp16PScaleLog2 - m_new + below;
+            cm = kFp16PScaleLog2 - top + below;
+            to_l = top - m_new - below;
         };
 
         // prologue: S(0) and its row reference, then K(1) on its way
@@ -245,8 +269,7 @@ void attn_bf16_kernel(AttnArgs a) {
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            // the row sum was taken of weights scaled by 2^below
-            l_run = __builtin_fmaf(rs, fast_exp2(-below), l_run * alpha_l);
+            l_run = __builtin_fmaf(rs, fast_exp2(to_l), l_run * alpha_l);
             if (n_next < 16 * NH) mask_cut_half(s[NB - 1], (NH - 1) & 1, n_next - 16 * (NH - 1), h);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // V(i): this thread's share landed
             __syncthreads();             // every wave has finished QK(i+1): the K buffer is free; V(i) visible
@@ -285,7 +308,7 @@ void attn_bf16_kernel(AttnArgs a) {
         float rs = 0.f;
 #pragma unroll
         for (int k = 0; k < 4 * NH; ++k) weights_pair(k >> 3, k & 7, rs);
-        l_run = __builtin_fmaf(rs, fast_exp2(-below), l_run * alpha_l);
+        l_run = __builtin_fmaf(rs, fast_exp2(to_l), l_run * alpha_l);
         if (__any(alpha_acc != 1.0f)) {
 #pragma unroll
             for (int db = 0; db < 4; ++db) acc[db] *= alpha_acc;

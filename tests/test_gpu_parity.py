@@ -408,6 +408,30 @@ def test_cut_tiles_at_the_edges_of_sub_blocks(prec, tile, rest):
         _check_quantize(run, [0], f"cut {tile} {rest}")
 
 
+@pytest.mark.parametrize("heads", [1, 40])                # keys split over wave groups, and not
+@pytest.mark.parametrize("grid,tile", [((4, 12, 12), (2, 4, 4)), ((6, 12, 12), (3, 4, 4)), ((3, 15, 48), (1, 5, 16)),
+                                       ((3, 24, 48), (1, 8, 16)), ((4, 16, 48), (2, 8, 16))])
+@pytest.mark.parametrize("outlying", ["zero", "large"])
+def test_bf16_v_groups_of_very_different_magnitude(outlying, grid, tile, heads):
+    """One V tile of zeros, or of values 2^34 times the others' whose keys have no weight, beside tiles
+    of values of 1e-6: the other tiles' weights keep their bits."""
+    say("V magnitudes", outlying, grid, tile, heads)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=(3, 3, 3), heads=heads, n_outlier=0, config_id=35)
+    q, k, v = (a.copy() for a in synth.qkv_raster(dataclasses.replace(w, heads=1), 0, [0]))
+    v *= np.float32(1e-6)
+    group = np.s_[0, tile[0]:2 * tile[0], tile[1]:2 * tile[1], tile[2]:2 * tile[2]]
+    if outlying == "zero":
+        v[group] = 0.0
+    else:
+        q, k[group] = np.abs(q), -16 * np.abs(k[group])    # scores about -190: weights below 2^-100
+        v[group] *= np.float32(2.0 ** 34)
+    run = gu.GpuRun(w, qkv=[np.repeat(synth.round_to_bf16(a), heads, axis=0) for a in (q, k, v)])
+    out = run.attn(fps.PREC_BF16)
+    st = gu.compare_head(run, out, heads - 1, fps.PREC_BF16, w.window)
+    say("  ", st)
+    gu.assert_parity(st, f"{outlying} {grid} {tile}")
+
+
 SMALL_GROUP_CASES = [                            # tile, sub-tile; key blocks of 1, 2 or 3 sub-blocks
     ((1, 1, 1), None), ((1, 1, 17), None), ((2, 4, 4), None),                     # one wave a workgroup
     ((1, 3, 11), None), ((3, 4, 4), None), ((1, 8, 8), None),                     # two
