@@ -15,13 +15,13 @@ struct BlockOrigin {
 };
 __device__ __forceinline__ BlockOrigin block_origin(const Geom& g, int blk) {
     BlockOrigin o;
-    const int group = blk / g.KBS;                       // 32-bit: the block count fits a grid dimension
+    const int group = quotient(blk, g.KBS, g.rc_kbs);           // 32-bit: the block count fits a grid dimension
     o.slot0 = (blk - group * g.KBS) * g.BS;
-    const int tile_lin = group / g.NS, s = group - tile_lin * g.NS;
-    const int bh = tile_lin / g.M;
+    const int tile_lin = quotient(group, g.NS, g.rc_ns), s = group - tile_lin * g.NS;
+    const int bh = quotient(tile_lin, g.M, g.rc_m);
     const int u = tile_lin - bh * g.M;
-    const int ut = u / (g.nW * g.nH), rem = u - ut * (g.nW * g.nH);
-    const int uh = rem / g.nW, uw = rem - uh * g.nW;
+    const int ut = quotient(u, g.nW * g.nH, g.rc_layer), rem = u - ut * (g.nW * g.nH);
+    const int uh = quotient(rem, g.nW, g.rc_row), uw = rem - uh * g.nW;
     o.box = real_box(g, ((ut == g.nT - 1) << 2) | ((uh == g.nH - 1) << 1) | (uw == g.nW - 1), s);
     o.tile_lin = tile_lin;
     o.slot_base = s * g.QSP;
@@ -36,6 +36,8 @@ template <bool RASTER>
 __device__ __forceinline__ const uint4* token_row(const uint4* x, const Geom& g, const BlockOrigin& o, int r) {
     const int k = o.slot0 + r;
     if (k >= o.box.n) return nullptr;
+    // rows and planes of a sub-tile that is whole along h and w follow each other in a tiled tensor
+    if (!RASTER && o.box.plane == g.Qh * g.Qw) return x + (o.tile_lin * g.TSP + o.slot_base + k) * 16;
     const Offset d = real_token(o.box, k);
     const long long row = RASTER ? o.raster0 + ((long long)d.t * g.H + d.h) * g.W + d.w
                                  : o.tile_lin * g.TSP + o.slot_base + (d.t * g.Qh + d.h) * g.Qw + d.w;
@@ -56,19 +58,18 @@ __device__ __forceinline__ uint32_t amax_of_pairs(uint32_t m2) {        // the l
     const uint32_t lo = m2 & 0xFFFFu, hi = m2 >> 16;
     return lo > hi ? lo : hi;
 }
-__device__ __forceinline__ uint32_t amax_bits16(const uint4& v, uint32_t m) {
-    const uint32_t p = amax_of_pairs(amax_pairs16(v, 0u));
-    return p > m ? p : m;
-}
-
-// workgroup-wide max of m over WAVES waves (red: WAVES words of LDS); every thread gets the result
-template <int WAVES>
-__device__ __forceinline__ uint32_t workgroup_max(uint32_t m, uint32_t* red) {
+// max of m over a wave, and over a workgroup of WAVES waves (red: WAVES words of LDS); every thread gets it
+__device__ __forceinline__ uint32_t wave_max(uint32_t m) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         const uint32_t o = (uint32_t)__shfl_xor((int)m, off);
         m = o > m ? o : m;
     }
+    return m;
+}
+template <int WAVES>
+__device__ __forceinline__ uint32_t workgroup_max(uint32_t m, uint32_t* red) {
+    m = wave_max(m);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     m = red[0];
@@ -96,20 +97,45 @@ static __global__ void amax_to_pow2_kernel(float* p, int n) {        // amax -> 
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = __uint_as_float((uint32_t)(127 + pow2_exponent_for_fp16(p[i])) << 23);
 }
-// amax over the KBS blocks of each quantisation group: one workgroup per block, merged with an
-// atomic max on the float bit pattern (amax_bits must be cleared first)
-template <bool RASTER>
-__global__ __launch_bounds__(256) void block_amax_kernel(const uint4* __restrict__ x,
-                                                         uint32_t* __restrict__ amax_bits, Geom g) {
-    __shared__ uint32_t red[4];
-    uint32_t m = 0;
-    const BlockOrigin org = block_origin(g, blockIdx.x);
-    for (int c = threadIdx.x; c < g.BS * 16; c += 256) {
-        const uint4* row = token_row<RASTER>(x, g, org, c >> 4);
-        if (row) m = amax_bits16(row[c & 15], m);
+// N of the 16-byte chunks of a block that THREADS threads hold, chunk c = 8 channels (c & 15) of slot c >> 4: v[i] of
+// thread tid is chunk tid + THREADS (first + i), zero for padding.  All N loads are in flight at once.
+template <bool RASTER, int THREADS, int N>
+__device__ __forceinline__ void load_chunks(const uint4* x, const Geom& g, const BlockOrigin& o, int tid, int first,
+                                            uint4 (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint4* row = token_row<RASTER>(x, g, o, (tid >> 4) + THREADS / 16 * (first + i));
+        v[i] = make_uint4(0, 0, 0, 0);
+        if (row) v[i] = row[tid & 15];
     }
-    m = workgroup_max<4>(m, red);
-    if (threadIdx.x == 0) atomicMax(&amax_bits[blockIdx.x / g.KBS], m << 16);
+}
+
+// amax over the KBS blocks of each quantisation group, merged with an atomic max on the float bit
+// pattern (amax_bits must be cleared first).  A workgroup of 256 threads takes one block of 128 slots, or
+// four of 32, one a wave: finding out where a block sits costs a wave more than reading its 8 KB.
+template <int BS, bool RASTER>
+__global__ __launch_bounds__(256) void block_amax_kernel(const uint4* __restrict__ x,
+                                                         uint32_t* __restrict__ amax_bits, Geom g, int blocks) {
+    constexpr int THREADS = BS == 128 ? 256 : 64;
+    __shared__ uint32_t red[THREADS / 64];
+    const int blk = BS == 128 ? blockIdx.x : blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (BS != 128 && blk >= blocks) return;
+    const int tid = BS == 128 ? threadIdx.x : threadIdx.x & 63;
+    uint4 v[BS * 16 / THREADS];
+    load_chunks<RASTER, THREADS>(x, g, block_origin(g, blk), tid, 0, v);
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < BS * 16 / THREADS; ++i) m = amax_pairs16(v[i], m);
+    m = amax_of_pairs(m);
+    m = BS == 128 ? workgroup_max<4>(m, red) : wave_max(m);
+    if (tid == 0) atomicMax(&amax_bits[blk / g.KBS], m << 16);
+}
+template <int BS>
+static void launch_block_amax(const void* x, int raster, float* amax, const Geom& g, hipStream_t st) {
+    const int blocks = g.BH * g.M * g.KB, grid = BS == 128 ? blocks : (blocks + 3) / 4;
+    const uint4* xi = (const uint4*)x;
+    if (raster) block_amax_kernel<BS, true><<<grid, 256, 0, st>>>(xi, (uint32_t*)amax, g, blocks);
+    else        block_amax_kernel<BS, false><<<grid, 256, 0, st>>>(xi, (uint32_t*)amax, g, blocks);
 }
 
 }  // namespace fps

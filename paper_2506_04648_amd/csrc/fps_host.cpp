@@ -77,24 +77,29 @@ int check_shape(const fps_shape* s, Geom* g) {
     g->T = s->T; g->H = s->H; g->W = s->W;
     g->Tt = s->Tt; g->Th = s->Th; g->Tw = s->Tw;
     g->nT = nT; g->nH = nH; g->nW = nW;
-    g->M = (int)m; g->TS = (int)ts;
+    g->M = (int)m;
     g->Qt = qt; g->Qh = qh; g->Qw = qw;
     g->nsT = s->Tt / qt; g->nsH = s->Th / qh; g->nsW = s->Tw / qw;
     g->NS = ns; g->QS = qs;
-    g->inv_qplane = 1.0f / (float)(qh * qw);
-    g->inv_qw = 1.0f / (float)qw;
     g->BS = bs; g->KBS = kbs; g->QSP = kbs * bs; g->KB = (int)kb; g->TSP = (int)kb * bs;
     g->lastT = s->T - (nT - 1) * s->Tt;
     g->lastH = s->H - (nH - 1) * s->Th;
     g->lastW = s->W - (nW - 1) * s->Tw;
     g->gT = (s->T + qt - 1) / qt; g->gH = (s->H + qh - 1) / qh; g->gW = (s->W + qw - 1) / qw;
     g->cutT = s->T - (g->gT - 1) * qt; g->cutH = s->H - (g->gH - 1) * qh; g->cutW = s->W - (g->gW - 1) * qw;
+    for (int h = 0; h < 2; ++h)
+        for (int w = 0; w < 2; ++w)
+            g->inv_plane[h][w] = 1.0f / (float)((h ? g->cutH : qh) * (w ? g->cutW : qw));
+    g->inv_w[0] = 1.0f / (float)qw;
+    g->inv_w[1] = 1.0f / (float)g->cutW;
     g->KBG = bs == 128 ? kbs : 1;
+    g->rc_kbs = reciprocal(kbs); g->rc_ns = reciprocal(ns); g->rc_m = reciprocal((int)m);
+    g->rc_layer = reciprocal(nH * nW); g->rc_row = reciprocal(nW);
     for (int nh = 0; nh < 8; ++nh) g->nh_classes[nh] = 0;
     for (int c = 0; c < 8; ++c) {
         const int n = ((c & 4) ? g->cutT : qt) * ((c & 2) ? g->cutH : qh) * ((c & 1) ? g->cutW : qw);
-        if (n >= 128) g->nh_classes[7] |= 1u << c;
-        if (n % 128) g->nh_classes[(n % 128 + 15) / 16 - 1] |= 1u << c;
+        if (n >= 128) g->nh_classes[7] |= (uint8_t)(1u << c);
+        if (n % 128) g->nh_classes[(n % 128 + 15) / 16 - 1] |= (uint8_t)(1u << c);
     }
     return FPS_OK;
 }

@@ -11,18 +11,29 @@ constexpr int kHeadDim = 128;
 constexpr int kMaxTileTokens = 32768;                // largest supported tile
 constexpr int kMaxScoreSlots = 4096;                 // largest tile the score debug call accepts
 
+// n / d for any 32-bit n, given m = reciprocal(d): four scalar instructions instead of the ~35 of a division by a
+// run-time value.  m = floor((2^32 - 1) / d) is at least 2^32/d - 1, so n m / 2^32 falls short of n / d by less than
+// n / 2^32 < 1 and its floor by at most 1.
+inline uint32_t reciprocal(int d) { return 0xFFFFFFFFu / (uint32_t)d; }
+__host__ __device__ inline int quotient(int n, int d, uint32_t m) {
+    const uint32_t q = (uint32_t)(((uint64_t)(uint32_t)n * m) >> 32);
+    return (int)(q + ((uint32_t)n - q * (uint32_t)d >= (uint32_t)d ? 1u : 0u));
+}
+
 // Everything the kernels derive from an fps_shape.
 struct Geom {
     int BH;              // B * heads
     int T, H, W;
     int Tt, Th, Tw;
     int nT, nH, nW;
-    int M, TS;
+    int M;
     // Quantisation sub-tile (Qt,Qh,Qw) (= the tile when none is given): a tile is NS = nsT*nsH*nsW
     // sub-tiles of QS tokens, each with its own scale; sub-tile s = (st*nsH + sh)*nsW + sw.
     int Qt, Qh, Qw;
     int nsT, nsH, nsW, NS, QS;
-    float inv_qplane, inv_qw;   // 1/(Qh*Qw) and 1/Qw as correctly rounded floats, for div_by_recip
+    // 1/(rows*columns) and 1/columns of a sub-tile as correctly rounded floats, for div_by_recip: [1] along an
+    // axis that the grid's edge cuts, [0] along one it does not
+    float inv_plane[2][2], inv_w[2];
     // The kernels work on blocks of BS slots (128 or 32).  A sub-tile occupies KBS = ceil(QS/BS)
     // consecutive blocks (QSP = KBS*BS slots, slot rr < QS holding the token of in-sub-tile rank
     // rr, the rest padding), a tile KB = NS*KBS blocks (TSP = KB*BS slots).  Block index =
@@ -40,7 +51,8 @@ struct Geom {
     int KBG;
     // Bit c of nh_classes[nh - 1]: sub-tiles cut along the axes of c (4: T, 2: H, 1: W) have a key
     // block whose real tokens fill nh 16-key halves.
-    uint32_t nh_classes[8];
+    uint8_t nh_classes[8];
+    uint32_t rc_kbs, rc_ns, rc_m, rc_layer, rc_row;   // reciprocals of KBS, NS, M, nH*nW, nW
 };
 
 // n / d for 0 <= n < 2^21, given inv_d = 1.0f / d correctly rounded.  Exact: (n + 1/2) / d is at
@@ -64,8 +76,8 @@ __host__ __device__ inline SubTile sub_tile_origin(const Geom& g, int s) {
 // padding of the sub-tile (rr >= QS).
 __host__ __device__ inline bool sub_slot_coords(const Geom& g, const SubTile& o, int rr, int* rt, int* rh, int* rw) {
     if (rr >= g.QS) return false;
-    const int a = div_by_recip(rr, g.inv_qplane), rem = rr - a * (g.Qh * g.Qw);
-    const int b = div_by_recip(rem, g.inv_qw), c = rem - b * g.Qw;
+    const int a = div_by_recip(rr, g.inv_plane[0][0]), rem = rr - a * (g.Qh * g.Qw);
+    const int b = div_by_recip(rem, g.inv_w[0]), c = rem - b * g.Qw;
     *rt = o.t0 + a; *rh = o.h0 + b; *rw = o.w0 + c;
     return true;
 }
@@ -107,8 +119,9 @@ __host__ __device__ inline RealBox real_box(const Geom& g, int c, int s) {
     b.eh = b.n ? (eh < g.Qh ? eh : g.Qh) : 1;
     b.ew = b.n ? (ew < g.Qw ? ew : g.Qw) : 1;
     b.plane = b.eh * b.ew;
-    b.inv_plane = 1.0f / (float)b.plane;
-    b.inv_w = 1.0f / (float)b.ew;
+    const bool ch = b.eh < g.Qh, cw = b.ew < g.Qw;        // then they are cutH, cutW
+    b.inv_plane = ch ? (cw ? g.inv_plane[1][1] : g.inv_plane[1][0]) : (cw ? g.inv_plane[0][1] : g.inv_plane[0][0]);
+    b.inv_w = cw ? g.inv_w[1] : g.inv_w[0];
     return b;
 }
 // offset of real token k of the box from the sub-tile's origin

@@ -20,6 +20,8 @@
 //       exact power-of-two scaling per scale group (see pack_bf16_kernel)
 #include "fps_device_common.h"
 
+#include <type_traits>
+
 namespace fps {
 
 // ---- raster -> tiled (bf16, 16-byte chunks of 8 channels) -------------------------------------
@@ -74,53 +76,67 @@ __global__ void tile_unorder_kernel(const uint4* __restrict__ in, uint4* __restr
 // For tiles of several blocks the tile amax is computed beforehand (tile_amax != nullptr).
 // RASTER: `in` is the raster tensor and the block's tokens are gathered from it (padding slots read
 // as zero), which fuses the tile ordering into this pass.
+// Bound by HBM, small calls by latency.  Loads in flight: all of a thread's for V, which has to have the block
+// anyway; two for K and one for Q, between stores -- at 720p (40 heads) a Q of all loads, then all stores takes 284
+// instead of 264 us, although it is the faster one at 480p (40.7 against 45.7 us).
 template <int BS, bool RASTER>
 __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict__ in,
                                                         uint4* __restrict__ out,
                                                         float* __restrict__ vscale, int role, Geom g,
                                                         const float* __restrict__ tile_amax) {
-    __shared__ uint16_t tile[BS * 128];
-    __shared__ uint32_t red[4];
+    constexpr int THREADS = 256, U = BS * 16 / THREADS;    // U: 16-byte chunks per thread
+    __shared__ __attribute__((aligned(16))) uint16_t tile[BS * 128];
+    __shared__ uint32_t red[THREADS / 64];
     const long long blk = blockIdx.x;
     uint4* dst = out + blk * (BS * 16);
-    constexpr int kChunks = BS * 16;
     const BlockOrigin org = block_origin(g, blockIdx.x);
-    auto load = [&](int c) {                               // chunk c = 8 channels (c & 15) of slot c >> 4
-        const uint4* row = token_row<RASTER>(in, g, org, c >> 4);
-        return row ? row[c & 15] : make_uint4(0, 0, 0, 0);
-    };
-    if (role == FPS_ROLE_Q) {
-        for (int c = threadIdx.x; c < kChunks; c += 256) dst[c] = load(c);
+    if (role != FPS_ROLE_V) {
+        auto copy = [&](auto n_tag) __attribute__((always_inline)) {       // N chunks at a time
+            constexpr int N = decltype(n_tag)::value;
+#pragma unroll
+            for (int first = 0; first < U; first += N) {
+                uint4 v[N];
+                load_chunks<RASTER, THREADS>(in, g, org, threadIdx.x, first, v);
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    int c = threadIdx.x + THREADS * (first + i);
+                    if (role == FPS_ROLE_K) {              // 32x32x16 operand: lane 32h + n, step ks
+                        const int j = c >> 4, c8 = c & 15; // row, 8-channel chunk
+                        const int sb = j >> 5, n = j & 31, ks = c8 >> 1, h = c8 & 1;
+                        c = (sb * 8 + ks) * 64 + 32 * h + n;
+                    }
+                    dst[c] = v[i];
+                }
+                __builtin_amdgcn_sched_barrier(0);         // the next loads follow these stores
+            }
+        };
+        if (role == FPS_ROLE_Q) copy(std::integral_constant<int, 1>{});
+        else                    copy(std::integral_constant<int, 2>{});
         return;
     }
-    if (role == FPS_ROLE_K) {
-        for (int c = threadIdx.x; c < kChunks; c += 256) {
-            const int j = c >> 4, c8 = c & 15;             // row, 8-channel chunk
-            const int sb = j >> 5, n = j & 31, ks = c8 >> 1, h = c8 & 1;   // 32x32x16 operand: lane 32h + n, step ks
-            dst[(sb * 8 + ks) * 64 + 32 * h + n] = load(c);
-        }
-        return;
-    }
+    uint4 v[U];
+    load_chunks<RASTER, THREADS>(in, g, org, threadIdx.x, 0, v);
     uint4* t4 = reinterpret_cast<uint4*>(tile);
     uint32_t mb = 0;
-    for (int c = threadIdx.x; c < kChunks; c += 256) {
-        const uint4 v = load(c);
-        t4[c] = v;
-        mb = amax_bits16(v, mb);
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        t4[threadIdx.x + THREADS * i] = v[i];
+        mb = amax_pairs16(v[i], mb);
     }
     float amax;
     if (tile_amax) {
         amax = tile_amax[blk / g.KBS];
         __syncthreads();
     } else {
-        mb = workgroup_max<4>(mb, red);                       // also orders the LDS writes above
+        mb = workgroup_max<THREADS / 64>(amax_of_pairs(mb), red);   // also orders the LDS writes above
         amax = __uint_as_float(mb << 16);
     }
     const int e = pow2_exponent_for_fp16(amax);
     const float down = __uint_as_float((uint32_t)(127 - e) << 23);     // 2^-e
     if (!tile_amax && threadIdx.x == 0) vscale[blk] = __uint_as_float((uint32_t)(127 + e) << 23);
-    for (int c = threadIdx.x; c < kChunks; c += 256) {
-        const int lane = c & 63;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        const int c = threadIdx.x + THREADS * i, lane = c & 63;
         union { uint4 v; _Float16 h[8]; } o;
         const int kk = c >> 8, db = (c >> 6) & 3, hh = lane >> 5, n = lane & 31;
 #pragma unroll
@@ -131,7 +147,6 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
         dst[c] = o.v;
     }
 }
-
 // ---- debug unpack of E4M3 tensors ---------------------------------------------------------------
 // one workgroup per block of BS slots of the tile-ordered output; padding slots become zero
 template <int BS>
@@ -202,8 +217,8 @@ int launch_pack_bf16(const Geom& g, const void* x, int raster, int role, void* x
     const float* tile_amax = nullptr;
     if (role == FPS_ROLE_V && g.KBS > 1) {                  // `vscale` holds the tile amax meanwhile
         clear_kernel<<<(ntiles + 255) / 256, 256, 0, st>>>((uint32_t*)vscale, ntiles);
-        if (raster) block_amax_kernel<true><<<blocks, 256, 0, st>>>((const uint4*)x, (uint32_t*)vscale, g);
-        else        block_amax_kernel<false><<<blocks, 256, 0, st>>>((const uint4*)x, (uint32_t*)vscale, g);
+        if (g.BS == 128) launch_block_amax<128>(x, raster, vscale, g, st);
+        else             launch_block_amax<32>(x, raster, vscale, g, st);
         tile_amax = vscale;
     }
     const uint4* xi = (const uint4*)x;

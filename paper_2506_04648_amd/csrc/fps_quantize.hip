@@ -326,8 +326,7 @@ int launch_quantize(const Geom& g, const void* x, int raster, int role, int vsca
         }
     } else {                            // group amax over many blocks first; `scales` holds it meanwhile
         clear_kernel<<<(groups + 255) / 256, 256, 0, st>>>((uint32_t*)scales, groups);
-        if (raster) block_amax_kernel<true><<<blocks, 256, 0, st>>>(xi, (uint32_t*)scales, g);
-        else        block_amax_kernel<false><<<blocks, 256, 0, st>>>(xi, (uint32_t*)scales, g);
+        launch_block_amax<128>(x, raster, scales, g, st);
         launch_quantize_nb<128, 1>(g, xi, raster, role, xo, scales, scales, blocks, st);
         amax_to_scale_kernel<<<(groups + 255) / 256, 256, 0, st>>>(scales, groups);
     }

@@ -465,6 +465,36 @@ def test_small_scale_groups_for_every_workgroup_shape(prec, tile, qtile):
         gu.assert_parity(st, f"{tile} {qtile} per-channel V")
 
 
+@pytest.mark.parametrize("tile,qtile", SMALL_GROUP_CASES + [((1, 8, 16), None), ((2, 8, 16), None), ((3, 9, 10), None),
+                                                            ((2, 8, 16), (1, 8, 16))])
+def test_bf16_packing_for_every_block_shape(tile, qtile):
+    """One to three blocks of 32 or 128 slots a group, whole and cut: the fused and the separate call
+    give the same bytes, and V's scales are those of the groups' largest values."""
+    import torch
+    say("bf16 packing", tile, qtile)
+    grid = (2 * tile[0], max(1, 3 * tile[1] - tile[1] // 2), max(1, 4 * tile[2] - (2 * tile[2]) // 3))
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=(3, 3, 3), heads=3, n_outlier=3, config_id=36)
+    run = gu.GpuRun(w, qtile=qtile)
+    for role, (xp, vs) in enumerate(run.pack_bf16()):
+        fused, fused_vs = fps.pack_tiles_bf16(run.shape, run.raster[role], role, raster=True)
+        assert torch.equal(xp, fused)
+        if role == fps.ROLE_V:
+            assert torch.equal(vs, fused_vs)
+            for h in range(3):
+                _, scales = fo.quantize_tiles(fo.tile_order(run.qkv[role][h].astype(np.float64), run.g), run.g)
+                amax = synth.round_to_bf16(scales.astype(np.float32) * np.float32(448.0))   # the scales are amax / 448
+                want = np.where(amax > 0, np.exp2(np.floor(np.log2(amax)) - 14.0), 1.0)
+                real = _groups_with_tokens(run.g)
+                assert np.array_equal(vs[0, h].cpu().numpy()[real], want[real])
+        else:
+            assert vs is None and fused_vs is None
+
+
+def _groups_with_tokens(g):
+    """Groups that hold a real token (the scale of the others is 1 by definition)."""
+    return np.flatnonzero(fo.quantize_tiles(np.repeat(fo.valid_tokens(g)[:, None], 128, axis=1).astype(np.float64), g)[1] != 1.0)
+
+
 @pytest.mark.parametrize("grid,tile,window", [((4, 16, 16), (2, 4, 4), (1, 3, 3)),
                                               ((2, 13, 40), (1, 8, 16), (3, 3, 3)),
                                               ((3, 13, 20), (2, 8, 16), (3, 3, 3))])
