@@ -108,6 +108,7 @@ int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, c
     a.out_f32 = out_f32;
     a.out_raster = out_raster;
     a.qblocks = g.TSP / (32 * query_waves(g));
+    a.rc_qblocks = reciprocal(a.qblocks);
     a.total = g.BH * g.M * a.qblocks;
     a.rotate = g.nW * a.qblocks % 2 == 0;
     a.chunk = ((a.total + 7) / 8 + 3) / 4 * 4;

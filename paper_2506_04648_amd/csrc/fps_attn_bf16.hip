@@ -40,7 +40,8 @@ void attn_bf16_kernel(AttnArgs a) {
     if (!work_item(a, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave) % W, kg = KS > 1 ? __builtin_amdgcn_readfirstlane(wave) / W : 0;
-    const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
+    const int ut = quotient(u, G.nW * G.nH, G.rc_layer), urem = u - ut * (G.nW * G.nH);
+    const int uh = quotient(urem, G.nW, G.rc_row), uw = urem - uh * G.nW;
     const int ucls = tile_class(G, ut, uh, uw);
     // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
     // waves of cut tiles fall on different SIMDs
@@ -226,6 +227,9 @@ void attn_bf16_kernel(AttnArgs a) {
             ring[j & 3].u = k_operand(j);
             qk_step(j);
         }
+        // every wave has finished QK(0), so the K buffer is free: K(1) is on its way while the row maximum is taken
+        __syncthreads();
+        if (nblk > 1) stage(0, k_blk(nxt));
         if (cur.n < 16 * NH) mask_cut_half(s[NB - 1], (NH - 1) & 1, cur.n - 16 * (NH - 1), h);
         {
             float mx = -INFINITY;
@@ -234,8 +238,6 @@ void attn_bf16_kernel(AttnArgs a) {
                 mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[k >> 3][2 * (k & 7)]), s[k >> 3][2 * (k & 7) + 1]);
             new_reference(mx, svv);
         }
-        __syncthreads();                                   // every wave has finished QK(0): the K buffer is free
-        if (nblk > 1) stage(0, k_blk(nxt));
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
 
@@ -289,8 +291,9 @@ void attn_bf16_kernel(AttnArgs a) {
                     mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[j >> 3][2 * (j & 7)]), s[j >> 3][2 * (j & 7) + 1]);
                     asm volatile("" : "+v"(mx));
                 }
-                // K's copies ride in the first half
-                constexpr int every = NH >= CPT ? 2 : 1, per = CPT > 4 * NH ? 2 : 1;
+                // K's copies ride in the first half, so that they have landed when the phase ends: one a step, for blocks
+                // of up to three halves two to four (32-token tiles, window 5x21x21: 354 -> 334 us, one a step against two)
+                constexpr int every = NH >= CPT ? 2 : 1, per = (CPT + 2 * NH - 1) / (2 * NH);
                 if (fetch_k && j % every == 0) {
 #pragma unroll
                     for (int c = j / every * per; c < (j / every + 1) * per && c < CPT; ++c) stage_chunk(0, ksrc, c);

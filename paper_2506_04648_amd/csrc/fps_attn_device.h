@@ -62,6 +62,7 @@ struct AttnArgs {
     int out_f32;
     int out_raster;        // output in raster order (real tokens only) instead of tile order
     int qblocks;           // query blocks (work items) of a tile
+    uint32_t rc_qblocks;
     int chunk;             // work items per XCD, a multiple of 4
     int rotate;            // deal each four consecutive work items in a turning order (see work_item)
     int total;             // BH * M * qblocks
@@ -113,9 +114,9 @@ __device__ __forceinline__ bool work_item(const AttnArgs& a, int* bh, int* u, in
     }
     const int wi = xcd * a.chunk + slot;
     if (wi >= a.total) return false;
-    const int tile_lin = wi / a.qblocks;
+    const int tile_lin = quotient(wi, a.qblocks, a.rc_qblocks);
     *jq = wi - tile_lin * a.qblocks;
-    *bh = tile_lin / a.g.M;
+    *bh = quotient(tile_lin, a.g.M, a.g.rc_m);
     *u = tile_lin - *bh * a.g.M;
     return true;
 }

@@ -41,7 +41,8 @@ void attn_fp8_kernel(AttnArgs a) {
     if (!work_item(a, &bh, &u, &jq)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave) % W, kg = KS > 1 ? __builtin_amdgcn_readfirstlane(wave) / W : 0;
-    const int uw = u % G.nW, uh = (u / G.nW) % G.nH, ut = u / (G.nW * G.nH);
+    const int ut = quotient(u, G.nW * G.nH, G.rc_layer), urem = u - ut * (G.nW * G.nH);
+    const int uh = quotient(urem, G.nW, G.rc_row), uw = urem - uh * G.nW;
     const int ucls = tile_class(G, ut, uh, uw);
     // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
     // waves of cut tiles fall on different SIMDs
