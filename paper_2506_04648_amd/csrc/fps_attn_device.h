@@ -492,13 +492,16 @@ inline int window_blocks(const AttnArgs& a) {
     const long long tiles = (long long)span(a.g.nT, a.rt) * span(a.g.nH, a.rh) * span(a.g.nW, a.rw);
     return (int)(tiles * a.g.NS * a.g.KBG > 1 << 20 ? 1 << 20 : tiles * a.g.NS * a.g.KBG);
 }
-// The keys of a work item are split over `ks` wave groups where the launch's waves are few enough to be
-// all resident at once with that (8 waves of these kernels' registers per CU, 256 CUs) and the walk is
-// long enough to pay for adding up.  A wave alone on its SIMD takes 1.6 us a 128-key block, two that share one 2.3
-// us for two.  Attention, split against not: 225 items of up to 27 blocks 45.2 -> 37.9 us (two groups), 64
-// one-wave items of up to 9 blocks 11.6 -> 10.3 us (four groups).
+// The keys of a work item are split over `ks` wave groups where all the launch's workgroups are resident at once
+// with that, and the walk is long enough to pay for adding up.  Workgroups are placed whole: of 8 waves of these
+// kernels' registers on each of 256 CUs, workgroups of three waves, split in two, fill six (300 items of 77 tokens:
+// split 47.1 us FP8, 57.5 BF16, in a second and mostly empty round; not split 44.6 and 53.1), and the wave
+// groups' LDS buffers (16 to 32 KB a wave) allow no more.  A wave alone on its SIMD takes 1.6 us a 128-key block, two that
+// share one 2.3 us for two.  Attention, split against not: 225 items of up to 27 blocks 45.2 -> 37.9 us, of 6 blocks
+// 15.5 -> 15.2, of 4 blocks 13.0 -> 13.6 (two groups); 64 one-wave items of up to 9 blocks 11.6 -> 10.3 (four groups).
 inline bool split_keys(const AttnArgs& a, int ks) {
-    return (long long)a.total * query_waves(a.g) * ks <= 8 * 256 && window_blocks(a) >= 2 * ks;
+    const int resident = 256 * (8 / (query_waves(a.g) * ks)), blocks = window_blocks(a);
+    return a.total <= resident && blocks >= 2 * ks && blocks >= 6;
 }
 
 // Kernel launchers of the two precisions; grid: workgroups

@@ -357,10 +357,12 @@ def test_every_item_of_an_even_row_is_computed(prec, heads, grid, tile):
 
 
 # heads, grid, tile, window, heads compared.  128-slot tiles split their keys in two, smaller ones (of one
-# scale group) in two or four, where a launch is small and a window has four or eight blocks
+# scale group) in two or four, where a launch is small and a window has six or eight blocks
 SPLIT_CASES = [
-    (2, (4, 8, 16), (1, 8, 16), (7, 1, 1), (0, 1)),          # 4 blocks: the fewest that are split
+    (2, (4, 8, 16), (1, 8, 16), (7, 1, 1), (0, 1)),          # 4 blocks: not split
     (2, (3, 8, 16), (1, 8, 16), (5, 1, 1), (0,)),            # 3 blocks: not split
+    (2, (6, 8, 16), (1, 8, 16), (11, 1, 1), (0, 1)),         # 6 blocks: the fewest that are split
+    (2, (6, 8, 16), (1, 8, 16), (7, 1, 1), (0, 1)),          # walks of 4, 5 and 6 blocks
     (2, (5, 13, 37), (1, 8, 16), (3, 3, 3), (0, 1)),         # odd counts, cut tiles with idle waves, walks of one block
     (2, (3, 13, 40), (2, 8, 16), (3, 3, 3), (0, 1)),         # tiles of two blocks
     (2, (4, 13, 20), (1, 7, 11), (3, 3, 3), (0, 1)),         # 77 tokens: three sub-blocks, keys in two
@@ -369,6 +371,7 @@ SPLIT_CASES = [
     (40, (4, 8, 26), (2, 4, 4), (3, 3, 3), (0, 39)),         # 1120 items: too many to split
     (40, (6, 8, 26), (3, 4, 4), (3, 3, 3), (0, 39)),         # 1120 items
     (40, (4, 14, 22), (1, 7, 11), (3, 3, 3), (0, 39)),       # 640 items
+    (5, (5, 20, 43), (1, 7, 11), (3, 3, 3), (0, 4)),         # 300 items of three waves
 ]
 
 
@@ -385,6 +388,21 @@ def test_keys_split_over_wave_groups(prec, vscale, heads, grid, tile, window, co
         st = gu.compare_head(run, out, h, prec, window, vscale=vscale)
         say("  head", h, st)
         gu.assert_parity(st, f"{grid} {tile} head {h}")
+
+
+@pytest.mark.parametrize("prec,vscale", [(fps.PREC_FP8, fps.VSCALE_TILE), (fps.PREC_FP8, fps.VSCALE_CHANNEL),
+                                         (fps.PREC_BF16, fps.VSCALE_TILE)])
+def test_keys_split_over_wave_groups_of_tiles_in_sub_tiles(prec, vscale):
+    """Tiles of two 128-slot scale groups, cut along every axis."""
+    say("split, sub-tiles", prec, vscale)
+    w = dataclasses.replace(synth.TINY, grid=(3, 13, 40), tile=(2, 8, 16), window=(3, 3, 3), heads=2, n_outlier=3,
+                            config_id=18)
+    run = gu.GpuRun(w, qtile=(1, 8, 16))
+    out = run.attn(prec, vscale=vscale)
+    for h in range(2):
+        st = gu.compare_head(run, out, h, prec, w.window, vscale=vscale)
+        say("  head", h, st)
+        gu.assert_parity(st, f"head {h}")
 
 
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])

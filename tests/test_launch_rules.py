@@ -1,0 +1,82 @@
+"""CPU checks of host rules of the kernel sources, compiled here without a GPU: which attention launches
+split their keys, and division by a stored reciprocal."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+PROGRAM = r"""
+#include "fps_attn_device.h"
+#include <cstdio>
+#include <cstring>
+using namespace fps;
+int main() {
+    // a tile of `tokens` in one scale group, `items` work items, a window of `blocks` tiles
+    int tokens, items, blocks, ks;
+    while (std::scanf("%d %d %d %d", &tokens, &items, &blocks, &ks) == 4) {
+        AttnArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.g.BS = tokens <= 96 ? 32 : 128;
+        a.g.KBS = a.g.KB = (tokens + a.g.BS - 1) / a.g.BS;
+        a.g.KBG = a.g.BS == 128 ? a.g.KBS : 1;
+        a.g.NS = 1;
+        a.g.TSP = a.g.KB * a.g.BS;
+        a.g.nT = blocks; a.g.nH = a.g.nW = 1;
+        a.rt = blocks;
+        a.total = items;
+        std::printf("%d %d\n", query_waves(a.g), (int)split_keys(a, ks));
+    }
+    unsigned bad = 0;
+    for (int d : {1, 2, 3, 5, 7, 10, 12, 630, 3024, 65535, 1 << 20}) {
+        const uint32_t m = reciprocal(d);
+        for (long long k = 0; k < 2000; ++k)                 // n to either side of the multiples of d below 2^30
+            for (int o = -1; o <= 1; ++o) {
+                const long long n = ((1LL << 30) / d * k / 1999) * d + o;
+                if (n >= 0 && n < (1LL << 30)) bad += quotient((int)n, d, m) != n / d;
+            }
+    }
+    std::printf("bad quotients %u\n", bad);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = d / "rules.hip", d / "rules"
+    src.write_text(PROGRAM)
+    res = subprocess.run([HIPCC, "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                          "-I" + os.path.join(ROOT, "include"),
+                          "-I" + os.path.join(ROOT, "paper_2506_04648_amd", "csrc"), str(src), "-o", str(exe)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    return str(exe)
+
+
+# tokens of a tile, work items, key blocks of the window, wave groups -> waves of a workgroup without them, split
+RULES = [
+    (128, 256, 27, 2, 4, True), (128, 257, 27, 2, 4, False),        # 8 waves a workgroup: one a CU
+    (77, 256, 27, 2, 3, True), (77, 257, 27, 2, 3, False), (77, 341, 27, 2, 3, False),   # 6 waves: still one a CU
+    (48, 256, 27, 4, 2, True), (48, 257, 27, 4, 2, False),          # 8 waves
+    (32, 512, 27, 4, 1, True), (32, 513, 27, 4, 1, False),          # 4 waves: two a CU
+    (128, 64, 6, 2, 4, True), (128, 64, 5, 2, 4, False),            # two groups: at least three blocks each
+    (32, 64, 8, 4, 1, True), (32, 64, 7, 4, 1, False),              # four groups: two each
+]
+
+
+def test_keys_are_split_where_all_workgroups_are_resident_at_once(program):
+    lines = "\n".join(" ".join(map(str, r[:4])) for r in RULES)
+    out = subprocess.run([program], input=lines, capture_output=True, text=True, check=True).stdout.splitlines()
+    got = [tuple(map(int, line.split())) for line in out[:-1]]
+    assert got == [(r[4], int(r[5])) for r in RULES]
+
+
+def test_quotients_by_a_stored_reciprocal_are_exact(program):
+    out = subprocess.run([program], input="", capture_output=True, text=True, check=True).stdout
+    assert out.splitlines()[-1] == "bad quotients 0"
