@@ -49,13 +49,15 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // as integers, and the quotient is (1 + delta) times the ideal 448 x / amax = 7 X 2^j / A, delta the
 // rounding error of s (|delta| <= 2^-24).  A rounding boundary of E4M3 is M 2^i with M < 32 odd (also in its
 // subnormal range), and |7 X 2^j / A - M 2^i| is zero or at least 1/(A M) > 2^-13 of it.  So an
-// ideal quotient off the boundaries stays on its side through all of these roundings (2^-17 together);
+// ideal quotient off the boundaries stays on its side through all of these roundings and the nudge (below
+// 2^-16 together: 2^-17 for the 17 bits, 2^-19 for 16 ulps, the rest single roundings);
 // one ON a boundary comes out of the rounding to 17 bits as the boundary itself, and the exact
 // quotient lies beside it in the direction of delta, which is the same for the whole scale group: exactly
 // on it (a tie, for the conversion to settle) if 448 s = amax.  Ties of the ideal quotient are
 // common: 6 % of the 16-channel units of normal data hold one.
 //
-// The product is formed as fma(x, rs, kTiny): a zero of either sign (padding, common) then gives code 0; for
+// The product is formed as fma(x, rs, kTiny), so that a zero (padding, common) does not meet the nudge: it gives
+// code 0, whatever its sign; per-channel scales keep the sign of a zero (SIGNED), as the quotient has it.  For
 // other inputs the addend is far below an ulp of anything that does not round to zero.  No clamp is
 // needed: |x| <= amax makes the product at most 448 (1 + 2^-18), far below the next boundary (464).
 struct Divisor {
@@ -71,24 +73,25 @@ __device__ __forceinline__ Divisor divisor_of(float s, float amax) {
 // exact quotients are taken
 __device__ __forceinline__ bool is_divisor(float s) { return __float_as_uint(s) >= 0x00800000u; }
 
+template <bool SIGNED>
 __device__ __forceinline__ float divide(float x, const Divisor& d) {
-    const uint32_t q = __float_as_uint(__builtin_fmaf(x, d.rs, kTiny));
+    const uint32_t q = __float_as_uint(__builtin_fmaf(x, d.rs, SIGNED ? __builtin_copysignf(kTiny, x) : kTiny));
     return __uint_as_float(((q + 0x40u) & ~0x7Fu) + (uint32_t)d.nudge);
 }
 
 // 16 bf16 (two uint4) -> 16 E4M3 codes (one uint4); scale(i), divisor(i): of element i.  One copy of the
 // exact quotient in a loop: code that has to be fetched is what a launch of few workgroups waits for.
-template <typename D, typename S>
+template <bool SIGNED, typename D, typename S>
 __device__ __forceinline__ uint4 encode16(const uint4& lo, const uint4& hi, bool usable, D&& divisor, S&& scale) {
     const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
     uint32_t o[4];
     if (__builtin_expect(usable, 1)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            int r = __builtin_amdgcn_cvt_pk_fp8_f32(divide(bf16_lo(w[2 * i]), divisor(4 * i)),
-                                                    divide(bf16_hi(w[2 * i]), divisor(4 * i + 1)), 0, false);
-            r = __builtin_amdgcn_cvt_pk_fp8_f32(divide(bf16_lo(w[2 * i + 1]), divisor(4 * i + 2)),
-                                                divide(bf16_hi(w[2 * i + 1]), divisor(4 * i + 3)), r, true);
+            int r = __builtin_amdgcn_cvt_pk_fp8_f32(divide<SIGNED>(bf16_lo(w[2 * i]), divisor(4 * i)),
+                                                    divide<SIGNED>(bf16_hi(w[2 * i]), divisor(4 * i + 1)), 0, false);
+            r = __builtin_amdgcn_cvt_pk_fp8_f32(divide<SIGNED>(bf16_lo(w[2 * i + 1]), divisor(4 * i + 2)),
+                                                divide<SIGNED>(bf16_hi(w[2 * i + 1]), divisor(4 * i + 3)), r, true);
             o[i] = (uint32_t)r;
         }
     } else {
@@ -176,7 +179,7 @@ __global__ __launch_bounds__(THREADS * NB) void quantize_tiles_kernel(const uint
 #pragma unroll
     for (int i = 0; i < U; ++i) {
         const int unit = tid + THREADS * i;
-        const uint4 codes = encode16(lo[i], hi[i], usable, [&](int) { return div; }, [&](int) { return s; });
+        const uint4 codes = encode16<false>(lo[i], hi[i], usable, [&](int) { return div; }, [&](int) { return s; });
         const int j = unit >> 3, c16 = unit & 7;
         if (role == FPS_ROLE_Q) {
             dst[unit] = codes;
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(256) void quantize_channels_kernel(const uint4* __r
 #pragma unroll
     for (int i = 0; i < U; ++i)
         reinterpret_cast<uint4*>(stage)[tid + 256 * i] =
-            encode16(lo[i], hi[i], usable, [&](int k) { return d[k]; }, [&](int k) { return sc[c16 * 16 + k]; });
+            encode16<true>(lo[i], hi[i], usable, [&](int k) { return d[k]; }, [&](int k) { return sc[c16 * 16 + k]; });
     __syncthreads();
     write_v_block<BS, 256>(stage, reinterpret_cast<uint4*>(xq + blk * (BS * 128)), tid);
 }

@@ -209,6 +209,22 @@ def test_codes_for_every_significand_of_amax(vscale, exponent):
         assert int(((codes != wc) & ~zero_sign).sum()) == 0, role
 
 
+def test_per_channel_codes_keep_the_sign_of_zeros():
+    """A negative zero, and a negative value that rounds to zero, give the code of -0."""
+    say("per-channel signs of zeros")
+    rng = np.random.default_rng(13)
+    x = np.float32(2.0) ** rng.integers(-110, 1, size=(128, 128)) * rng.choice([-1.0, 1.0], size=(128, 128))
+    x[rng.random((128, 128)) < 0.3] = -0.0
+    x[rng.random((128, 128)) < 0.1] = 0.0
+    x[7] = 1.5                                               # every channel's largest value
+    xb = synth.round_to_bf16(x.astype(np.float32))
+    shape = fps.make_shape(1, (1, 8, 16), (1, 8, 16))
+    xq, _ = fps.quantize_tiles(shape, gu.to_device_bf16(xb[None, None]), fps.ROLE_V, vscale=fps.VSCALE_CHANNEL)
+    codes = fps.debug_unpack_q8(shape, xq, fps.ROLE_V)[0, 0].cpu().numpy()
+    assert np.any((codes == 0x80) & (xb == 0)) and np.any((codes == 0x80) & (xb != 0))
+    assert np.array_equal(codes >> 7, np.signbit(xb).astype(np.uint8))
+
+
 # ---- the matrix instruction's accumulation accuracy -------------------------------------------
 def test_score_accumulation_error_model(tiny):
     """Raw E4M3 scores of single tile pairs against the exact integer dot products: the layout is
