@@ -64,10 +64,12 @@ struct Divisor {
     float rs;
     int nudge;
 };
+__device__ __forceinline__ bool is_finite(float a) { return (__float_as_uint(a) & 0x7FFFFFFFu) < 0x7F800000u; }
 constexpr float kTiny = 1.3e-30f;
 __device__ __forceinline__ Divisor divisor_of(float s, float amax) {
     const float rest = __builtin_fmaf(-448.0f, s, amax);   // its sign is exact
-    return Divisor{1.0f / s, rest > 0.0f ? 16 : rest < 0.0f ? -16 : 0};
+    // NaN in a group: its scale is 1, exactly, and ties go to even
+    return Divisor{1.0f / s, !is_finite(amax) ? 0 : rest > 0.0f ? 16 : rest < 0.0f ? -16 : 0};
 }
 // a scale below the normal range has lost bits of amax / 448, and its reciprocal may be infinite: the
 // exact quotients are taken
@@ -237,10 +239,12 @@ __global__ __launch_bounds__(256) void quantize_channels_kernel(const uint4* __r
     __shared__ __attribute__((aligned(16))) uint8_t stage[BS * 128];
     __shared__ float sc[128];
     __shared__ Divisor div[128];
+    __shared__ int exact;                                    // some channel's scale is no divisor
     const int tid = threadIdx.x, c16 = tid & 7;
     const long long blk = blockIdx.x;
     const long long bh = blk / ((long long)g.M * g.KB);
     const BlockOrigin org = block_origin(g, blockIdx.x);
+    if (tid == 0) exact = 0;
     constexpr int U = BS / 32;
     uint4 lo[U], hi[U];
 #pragma unroll
@@ -250,20 +254,21 @@ __global__ __launch_bounds__(256) void quantize_channels_kernel(const uint4* __r
         hi[i] = lo[i];
         if (row) { lo[i] = row[2 * c16]; hi[i] = row[2 * c16 + 1]; }
     }
+    __syncthreads();
     if (tid < 128) {
         const float a = amax[bh * 128 + tid];
         const float s = a == 0.0f ? 1.0f : a / 448.0f;
         sc[tid] = s;
         div[tid] = divisor_of(s, a);
+        // beside a channel with an infinity or a NaN the exact quotients are taken too: their clamp makes those -448
+        const bool bad = !is_divisor(s) || !is_finite(a);
+        if (__ballot(bad) != 0 && (tid & 63) == 0) exact = 1;
     }
     __syncthreads();
     Divisor d[16];                                           // of the thread's 16 channels
-    bool usable = true;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        d[i] = div[c16 * 16 + i];
-        usable = usable && is_divisor(sc[c16 * 16 + i]);
-    }
+    for (int i = 0; i < 16; ++i) d[i] = div[c16 * 16 + i];
+    const bool usable = exact == 0;
 #pragma unroll
     for (int i = 0; i < U; ++i)
         reinterpret_cast<uint4*>(stage)[tid + 256 * i] =

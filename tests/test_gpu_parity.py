@@ -225,6 +225,25 @@ def test_per_channel_codes_keep_the_sign_of_zeros():
     assert np.array_equal(codes >> 7, np.signbit(xb).astype(np.uint8))
 
 
+@pytest.mark.parametrize("vscale", [fps.VSCALE_TILE, fps.VSCALE_CHANNEL])
+def test_ties_beside_a_nan_go_to_even(vscale):
+    """A scale group with a NaN has scale 1: its other values, all halfway between two codes here, are
+    rounded to the even one."""
+    say("ties beside NaN", vscale)
+    codes = np.arange(0x08, 0x7E, dtype=np.uint8)
+    ties = 0.5 * (e4m3.decode(codes) + e4m3.decode(codes + 1))
+    even = np.where(codes % 2 == 0, codes, codes + 1)
+    pick = np.random.default_rng(14).integers(0, codes.size, size=(128, 128))
+    x = ties[pick]
+    x[3] = np.nan                                            # in every channel and in the tile
+    shape = fps.make_shape(1, (1, 8, 16), (1, 8, 16))
+    xq, sc = fps.quantize_tiles(shape, gu.to_device_bf16(x.astype(np.float32)[None, None]), fps.ROLE_V, vscale=vscale)
+    got = fps.debug_unpack_q8(shape, xq, fps.ROLE_V)[0, 0].cpu().numpy()
+    assert np.all(sc.cpu().numpy() == 1.0)
+    finite = np.isfinite(x)
+    assert np.array_equal(got[finite], even[pick][finite])
+
+
 # ---- the matrix instruction's accumulation accuracy -------------------------------------------
 def test_score_accumulation_error_model(tiny):
     """Raw E4M3 scores of single tile pairs against the exact integer dot products: the layout is
