@@ -18,6 +18,7 @@ __device__ __forceinline__ int key_of_slot(int h, int jj) { return 8 * (jj >> 2)
 // on an E4M3 rounding midpoint although the true quotient lies beside it; the sign of the exact
 // residual x - q*s (one fma) tells on which side, and q is moved one float ulp that way.
 __device__ __forceinline__ float quotient_for_rne(float x, float s) {
+    if (s < 0x1p-60f) { x *= 0x1p64f; s *= 0x1p64f; }   // exactly; so that the residual does not underflow
     float q = x / s;
     uint32_t qb = __float_as_uint(q);
     const float a = __builtin_fabsf(q);

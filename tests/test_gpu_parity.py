@@ -182,20 +182,23 @@ def test_quantize_special_values():
     assert torch.all(sc == 1.0) and torch.all(xq == 0)
 
 
-@pytest.mark.parametrize("exponent", [0, 100, -120])     # at -120 the scales are subnormal numbers
+# the scales' exponents lie 9 below; at -117 they are just above the least normal number, at -118 on both
+# sides of it, from -119 on subnormal
+@pytest.mark.parametrize("exponent", [0, 100, -117, -118, -120, -126])
 @pytest.mark.parametrize("vscale", [fps.VSCALE_TILE, fps.VSCALE_CHANNEL])
 def test_codes_for_every_significand_of_amax(vscale, exponent):
-    """One scale group per 8-bit significand of amax, random significands and 19 binades of values in
-    each: every way in which a quotient can lie on or next to a rounding boundary."""
+    """One scale group per 8-bit significand of amax; in each, every significand in 19 binades: every way
+    in which a quotient can lie on or next to a rounding boundary."""
     say("quantize significands", vscale, exponent)
     rng = np.random.default_rng(12)
     g = fo.Geometry(1, 8, 16 * 128, 1, 8, 16)                # 128 tiles of 128 tokens, 128 channels
     shape = fps.make_shape(1, (1, 8, 16 * 128), (1, 8, 16))
     # axis 1 of the groups: the values of one scale (a tile's, or 16384 tokens of a channel)
     amax = (np.arange(128, 256) * 2.0 ** (exponent - 7))[:, None]
-    x = rng.integers(128, 256, size=(128, 128 * 128)) * 2.0 ** (exponent - 7 - rng.integers(0, 19, size=(128, 128 * 128)))
+    every = np.resize(np.arange(128, 256)[:, None] * 2.0 ** -np.arange(19.0), 128 * 128) * 2.0 ** (exponent - 7)
+    x = rng.permuted(np.repeat(every[None], 128, axis=0), axis=1)
     x = np.minimum(x, amax) * rng.choice([-1.0, 1.0], size=x.shape)
-    x[:, :1] = amax
+    x[:, :1] = amax                                          # 2432 combinations, each 6 or 7 times before this one
     x = x.reshape(g.L_padded, 128) if vscale == fps.VSCALE_TILE else np.ascontiguousarray(x.T)
     xb = synth.round_to_bf16(x.astype(np.float32))
     tiled = gu.to_device_bf16(xb[None, None])
