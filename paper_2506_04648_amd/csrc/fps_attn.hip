@@ -110,7 +110,7 @@ int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, c
     a.qblocks = g.TSP / (32 * query_waves(g));
     a.rc_qblocks = reciprocal(a.qblocks);
     a.total = g.BH * g.M * a.qblocks;
-    a.rotate = g.nW * a.qblocks % 2 == 0;
+    a.rotate = deal_in_turns(g.nW * a.qblocks);
     a.chunk = ((a.total + 7) / 8 + 3) / 4 * 4;
     const int grid = a.chunk * 8;
     if (prec == FPS_PREC_FP8) launch_attn_fp8(a, vscale == FPS_VSCALE_CHANNEL, grid, st);

@@ -101,10 +101,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // for the one whose turn it is.  How long an item takes depends on its place in the row of tiles (cut
 // tiles and the grid's edges are short), so with a row of 4, 8, .. items one engine gets all the short ones and
 // stands idle: 21x30x52 tokens x 12 heads, tile (1,8,16), four tiles a row, had 355 of 512 workgroups
-// resident.  There (an even number of items a row) each group of four items is dealt in an
-// order that turns from group to group: attention 375 -> 320 us, BF16 545 -> 502 us, (2,8,16) tiles in sub-tiles of 64
-// tokens 1975 -> 1906 us.  An odd number spreads by itself, and turning it costs locality (21x45x80, five tiles a
-// row, 3.87 -> 3.92 ms; (6,8,8) tiles on the first grid, 21 items a row, 301 -> 306 us).
+// resident.  There (deal_in_turns) each group of four items is dealt in an order that turns from group to group; with
+// the group's index over 4 and 16 added, so that it also turns from row to row where a row is 8, 16 or 32 items.
 __device__ __forceinline__ bool work_item(const AttnArgs& a, int* bh, int* u, int* jq) {
     const int xcd = blockIdx.x & 7;
     int slot = blockIdx.x >> 3;
@@ -479,6 +477,18 @@ struct SplitMerge {
         }
     }
 };
+
+// Rows of two or of 4, 8, .. items are dealt in a turning order (see work_item): attention in order against turning, us:
+//   2 items   20 tokens wide, 24 heads, tile (1,8,16)           213 -> 204
+//   4         52 wide, 12 heads                                 366 -> 315    BF16 548 -> 503
+//   8         120 wide, 6 heads; 52 wide, tile (2,8,16)         393 -> 384, 574 -> 548
+//   16, 32    250 wide, tile (1,8,16); 52 wide, tile (4,16,16)  416 -> 412, 1456 -> 1408
+//   12, 20    192 and 310 wide                                  419 -> 420, 400 -> 398
+// Others spread by themselves, and turning costs them locality:
+//   5, 7      80 and 112 wide                                   310 -> 313, 346 -> 345
+//   6         96 wide, 8 heads; 720p of that width, 40 heads    386 -> 404, 4887 -> 5037    BF16 616 -> 644
+//   10, 18    160 wide; 48 wide, tile (6,8,8)                   423 -> 426, 701 -> 705
+inline bool deal_in_turns(int items_per_row) { return items_per_row % 4 == 0 || items_per_row == 2; }
 
 // waves of a workgroup (= sub-blocks of a query block)
 inline int query_waves(const Geom& g) {

@@ -1,5 +1,5 @@
 """CPU checks of host rules of the kernel sources, compiled here without a GPU: which attention launches
-split their keys, and division by a stored reciprocal."""
+split their keys or deal their items in turns, and division by a stored reciprocal."""
 import os
 import shutil
 import subprocess
@@ -30,6 +30,8 @@ int main() {
         a.total = items;
         std::printf("%d %d\n", query_waves(a.g), (int)split_keys(a, ks));
     }
+    for (int row = 1; row <= 20; ++row) std::printf("%d", (int)deal_in_turns(row));
+    std::printf("\n");
     unsigned bad = 0;
     for (int d : {1, 2, 3, 5, 7, 10, 12, 630, 3024, 65535, 1 << 20}) {
         const uint32_t m = reciprocal(d);
@@ -73,8 +75,13 @@ RULES = [
 def test_keys_are_split_where_all_workgroups_are_resident_at_once(program):
     lines = "\n".join(" ".join(map(str, r[:4])) for r in RULES)
     out = subprocess.run([program], input=lines, capture_output=True, text=True, check=True).stdout.splitlines()
-    got = [tuple(map(int, line.split())) for line in out[:-1]]
+    got = [tuple(map(int, line.split())) for line in out[:-2]]
     assert got == [(r[4], int(r[5])) for r in RULES]
+
+
+def test_items_of_rows_of_six_or_ten_are_dealt_in_order(program):
+    out = subprocess.run([program], input="", capture_output=True, text=True, check=True).stdout.splitlines()
+    assert [i + 1 for i, c in enumerate(out[-2]) if c == "1"] == [2, 4, 8, 12, 16, 20]
 
 
 def test_quotients_by_a_stored_reciprocal_are_exact(program):
