@@ -128,8 +128,9 @@ size_t fps_num_groups(const fps_shape* shape);
  * or 0 on an invalid shape. */
 size_t fps_tile_slots(const fps_shape* shape);
 
-/* BS, the slots of one block (the unit the kernels stage and a workgroup's query rows): 128, or 32
- * when a quantisation group has at most 96 tokens; TSP is a multiple of it.  0 on an invalid shape. */
+/* BS, the slots of one block: 128, or 32 when a quantisation group has at most 96 tokens.  A group is rounded
+ * up to whole blocks (one block of 128, or one to three of 32, is what the attention kernels stage at a time), and
+ * TSP is a multiple of BS.  0 on an invalid shape. */
 size_t fps_block_slots(const fps_shape* shape);
 
 /* Bytes of one packed tensor for the given precision (all B*heads): M*TSP*head_dim bytes for FP8,
@@ -195,8 +196,8 @@ int fps_debug_unpack_q8(const fps_shape* shape, const void* xq, fps_role role,
  * the profiler's FETCH_SIZE / WRITE_SIZE counters. */
 int fps_debug_copy(const void* src, void* dst, size_t bytes, void* stream);
 
-/* Debug: a kernel that does nothing but issue the FP8 matrix instruction of the attention kernel
- * (v_mfma_f32_16x16x128_f8f6f4, 8 independent accumulator chains per wave, no memory traffic in
+/* Debug: a kernel that does nothing but issue an FP8 matrix instruction (v_mfma_f32_16x16x128_f8f6f4, of the same
+ * rate as the attention kernel's 32x32x64; 8 independent accumulator chains per wave, no memory traffic in
  * the loop): `workgroups` workgroups of 256 threads, `iters` loop trips of 8 instructions per
  * wave.  FLOPs launched = workgroups * 4 waves * iters * 8 * 65536.  Timed by the caller, it gives
  * the matrix rate the chip sustains, the yardstick next to the datasheet peak.  `sink` is device

@@ -46,7 +46,7 @@ __global__ __launch_bounds__(64) void scores_fp8_kernel(const uint8_t* __restric
     for (int r = 0; r < 16; ++r) o[(size_t)n * out_pitch + 8 * (r >> 2) + 4 * h + (r & 3)] = s[r];
 }
 
-// MFMA-only loop: 8 independent accumulator chains of the attention kernel's matrix instruction.
+// MFMA-only loop: 8 independent accumulator chains of 16x16x128 (the attention kernel's 32x32x64 has the same rate).
 __global__ __launch_bounds__(256) void mfma_rate_kernel(float* __restrict__ sink, int iters, int x) {
     v8i a = {x, x, x, x, x, x, x, x};
     v8i b = a;

@@ -185,8 +185,9 @@ void attn_fp8_kernel(AttnArgs a) {
             const int db = step / J, j = step % J;
             v16f r = VCH ? acc[db] : j == 0 ? zero16() : tq[db & 1];
             if (TAIL && j == J - 1) {
-                // a single sub-block: 32x32x16 instructions, 16 keys each, at the same rate per key; a
-                // lane's 8 contraction slots of half e are the keys of its registers 8e .. 8e + 7
+                // a single sub-block: 32x32x16 instructions, 16 keys each.  They take 32.5 clocks against 64.9 of a
+                // 32x32x64, so two halves cost what half of one would and a single half less.  A lane's 8
+                // contraction slots of half e are the keys of its registers 8e .. 8e + 7
 #pragma unroll
                 for (int e = 0; e < (NH % 2 ? 1 : 2); ++e) {
                     const long va = (long)((uint64_t)(uint32_t)vop[2 * e] | ((uint64_t)(uint32_t)vop[2 * e + 1] << 32));
