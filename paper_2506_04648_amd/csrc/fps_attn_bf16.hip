@@ -70,9 +70,10 @@ void attn_bf16_kernel(AttnArgs a) {
         for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
     };
 
-    // Of a walk of `total` blocks, those of this wave group.  Group 0 never has fewer than another; what a group
-    // has fewer barriers than group 0 (two a block, three a walk) it makes up for at the end, as every barrier
-    // is one of the whole workgroup.  (Made up for within the walk, they cost 110 spilled registers.)
+    typedef BlockList<MB, KS> List;
+    // Of a list of `total` blocks, those of this wave group.  Group 0 never has fewer than another; what a group
+    // has fewer barriers than group 0 (two a block, three a list) it makes up for at the end, as every barrier
+    // is one of the whole workgroup.  (Made up for within the list, they cost 110 spilled registers.)
     int owed = 0;
     auto blocks_of_group = [&](int total) FPS_INLINE {
         if (KS == 1) return total;
@@ -90,14 +91,13 @@ void attn_bf16_kernel(AttnArgs a) {
         for (int nh = 2 * SB; nh >= 1; --nh) {
             const uint32_t classes = G.nh_classes[nh - 1] & box.classes;
             if (!classes) continue;
-            BlockWalk<MB> walk(G, box, nh);
-            const int total = walk.begin(classes);
-            const int nblk = blocks_of_group(total);
+            List list(G, box, nh, classes, kg);
+            const int nblk = blocks_of_group(list.total());
             if (nblk == 0) continue;
-            walk.skip(kg);
-            KeyBlock cur = walk.block(), nxt = cur;
+            list.fill(0);
+            KeyBlock cur = list.block(0), nxt = cur;
             stage(0, k_blk(cur));
-            if (nblk > 1) { walk.skip(KS); nxt = walk.block(); }
+            if (nblk > 1) nxt = list.block(1);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();                               // K(0) visible
             __syncthreads();                               // QK(0) done
@@ -110,8 +110,8 @@ void attn_bf16_kernel(AttnArgs a) {
                 __syncthreads();                           // QK(i+1) done; V(i) visible
                 cur = nxt;
                 if (i + 2 < nblk) {
-                    walk.skip(KS);
-                    nxt = walk.block();
+                    if (((i + 2) & 63) == 0) list.fill(i + 2);
+                    nxt = list.block(i + 2);
                     stage(0, k_blk(nxt));
                 }
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -144,11 +144,10 @@ void attn_bf16_kernel(AttnArgs a) {
         constexpr int NB = (NH + 1) / 2;                   // 32-key sub-blocks
         const uint32_t classes = G.nh_classes[NH - 1] & box.classes;
         if (!classes) return;
-        BlockWalk<MB> walk(G, box, NH);
-        const int total = walk.begin(classes);
-        const int nblk = blocks_of_group(total);
+        List list(G, box, NH, classes, kg);
+        const int nblk = blocks_of_group(list.total());
         if (nblk == 0) return;
-        walk.skip(kg);
+        list.fill(0);
 
         v16f s[NB];                                        // S^T, blocks of 32 keys
         Bf16x8 pop[NH];                                // P^T in fp16: contraction steps of 16 keys
@@ -216,10 +215,10 @@ void attn_bf16_kernel(AttnArgs a) {
         };
 
         // prologue: S(0) and its row reference, then K(1) on its way
-        KeyBlock cur = walk.block(), nxt = cur;
+        KeyBlock cur = list.block(0), nxt = cur;
         stage(0, k_blk(cur));
         float svv = load_uniform(sv_head, cur.group);
-        if (nblk > 1) { walk.skip(KS); nxt = walk.block(); }
+        if (nblk > 1) nxt = list.block(1);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
 #pragma unroll
@@ -249,7 +248,10 @@ void attn_bf16_kernel(AttnArgs a) {
             const float svv_next = load_uniform(sv_head, nxt.group);
             cur = nxt;
             const bool fetch_k = i + 2 < nblk;
-            if (fetch_k) { walk.skip(KS); nxt = walk.block(); }
+            if (fetch_k) {
+                if (((i + 2) & 63) == 0) list.fill(i + 2);
+                nxt = list.block(i + 2);
+            }
             const uint8_t* ksrc = k_blk(nxt);
 
             // step (kb, ks): a pair of weights of score block kb beside the MFMA (kb - 1, ks) that

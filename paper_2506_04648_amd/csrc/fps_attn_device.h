@@ -46,6 +46,7 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 struct AttnArgs {
     const uint8_t* q;
@@ -243,16 +244,17 @@ __device__ __forceinline__ void store_rows_as(const AttnArgs& a, const QueryRows
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        uint4 val[kRows / kRowsPerStore];
+        // not uint4: the compiler left an array of those in scratch memory in one kernel
+        u32x4 val[kRows / kRowsPerStore];
 #pragma unroll
         for (int i = 0; i < kRows / kRowsPerStore; ++i)
-            val[i] = *reinterpret_cast<const uint4*>(wave_lds + (i * kRowsPerStore + (lane >> kLanesShift)) * kPitch +
+            val[i] = *reinterpret_cast<const u32x4*>(wave_lds + (i * kRowsPerStore + (lane >> kLanesShift)) * kPitch +
                                                      chunk * 16);
 #pragma unroll
         for (int i = 0; i < kRows / kRowsPerStore; ++i) {
             const int row = pass * kRows + i * kRowsPerStore + (lane >> kLanesShift);
             if (row < q.rows)
-                reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(a.out) + q.out_row(a, row) * kRowBytes)[chunk] = val[i];
+                reinterpret_cast<u32x4*>(reinterpret_cast<uint8_t*>(a.out) + q.out_row(a, row) * kRowBytes)[chunk] = val[i];
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -349,93 +351,103 @@ struct KeyBox {
     }
 };
 
-// One axis of a walk over sub-tiles: `off` is the axis' share of the scale-group index, tile * (step of
-// the next tile) + place in tile * (step of the next sub-tile).
-template <bool MB>
-struct AxisWalk {
-    int i, first, last;                 // sub-tile along the axis
-    int sub, off, off_first;
-    int ns, step, wrap;                 // sub-tiles per tile; off's step within a tile, and to the next tile
+// n / d for n >= 0 of a lane and uniform d > 0, given rcp = 1.0f / d to an ulp or two: the estimate is exact
+// below 2^20, beyond it the loops settle it.
+__device__ __forceinline__ int divide_lane(int n, int d, float rcp) {
+    int q = (int)(((float)n + 0.5f) * rcp), r = n - q * d;
+    while (r < 0) { --q; r += d; }
+    while (r >= d) { ++q; r -= d; }
+    return q;
+}
+
+// One axis of a class of sub-tiles in the box: the sub-tiles first .. first + count - 1 along the axis.
+struct AxisPart {
+    int first, count;
     // the axis' full sub-tiles of the tiles lo .. hi, or (cut_part) only its last one, which is cut
-    __device__ __forceinline__ void init(int lo, int hi, int tiles, int g, bool cut_part, bool has_cut, int ns_, int step_,
-                                         int tile_step) {
-        ns = MB ? ns_ : 1;
-        step = MB ? step_ : tile_step;
-        wrap = tile_step - (ns - 1) * step;
-        const int tile = cut_part ? tiles - 1 : lo;
+    __device__ __forceinline__ AxisPart(int lo, int hi, int ns, int g, bool cut_part, bool has_cut) {
         first = cut_part ? g - 1 : lo * ns;
-        last = cut_part ? g - 1 : min((hi + 1) * ns, g) - 1 - (has_cut ? 1 : 0);
-        off_first = tile * tile_step + (MB ? (first - tile * ns) * step : 0);
-        reset();
+        count = cut_part ? 1 : min((hi + 1) * ns, g) - (has_cut ? 1 : 0) - first;
     }
-    __device__ __forceinline__ void reset() { i = first; off = off_first; sub = 0; }
-    __device__ __forceinline__ bool advance() {            // false: the axis is exhausted (and reset)
-        if (i == last) { reset(); return false; }
-        ++i;
-        if (!MB) { off += step; return true; }
-        if (++sub == ns) { sub = 0; off += wrap; } else { off += step; }
-        return true;
-    }
-    __device__ __forceinline__ int count() const { return last - first + 1; }
 };
 
 // One key block: packed slots of one scale group, the first n of them real tokens.  Indices count from
 // the head's first tile.
 struct KeyBlock { int blk, group, n; };
 
-// The key blocks of NH 16-key halves of the box, class by class.
-template <bool MB>
-struct BlockWalk {
+// The key blocks of NH 16-key halves of the box, class by class, w fastest; of every KS of them the one with
+// index kg (mod KS).  A lane works out the place of one block, so that a wave has the next 64 in two vector
+// registers and a block costs its loop two v_readlane: stepping through the box axis by axis took 25 to 40 scalar
+// instructions a block, and with tiles of several blocks 228 scalar registers were spilled to lanes of vector
+// registers (now 16).  Attention: 64-token sub-tiles of (2,8,16) tiles, 21x30x52 tokens x 24 heads, 1920 -> 1859 us, one-block
+// tiles of that grid x 12 heads 315 -> 311.
+template <bool MB, int KS>
+struct BlockList {
     const Geom& G;
     const KeyBox& box;
-    uint32_t classes;                   // classes still to come
-    int NH;
-    AxisWalk<MB> t, h, w;
-    int n, jb, jb0, jb1;                // real tokens of a sub-tile of the class; its blocks of NH halves
-    __device__ __forceinline__ BlockWalk(const Geom& G_, const KeyBox& box_, int nh) : G(G_), box(box_), NH(nh) {}
-    __device__ __forceinline__ void enter(int c) {
+    uint32_t classes;
+    int NH, kg;
+    int group, meta;                    // this lane's block: scale group; real tokens + 256 * (block within the group)
+    __device__ __forceinline__ BlockList(const Geom& G_, const KeyBox& box_, int nh, uint32_t classes_, int kg_)
+        : G(G_), box(box_), classes(classes_), NH(nh), kg(kg_), group(0), meta(0) {}
+    // f(t, h, w parts, real tokens of a sub-tile, first block, blocks of NH halves) for every class
+    template <typename F>
+    __device__ __forceinline__ void for_classes(F&& f) const {
         const bool et = KeyBox::has_cut(box.t1, G.nT, G.cutT, G.Qt), eh = KeyBox::has_cut(box.h1, G.nH, G.cutH, G.Qh),
                    ew = KeyBox::has_cut(box.w1, G.nW, G.cutW, G.Qw);
-        const int per_tile = MB ? G.NS : 1;
-        t.init(box.t0, box.t1, G.nT, G.gT, c & 4, et, G.nsT, G.nsH * G.nsW, G.nH * G.nW * per_tile);
-        h.init(box.h0, box.h1, G.nH, G.gH, c & 2, eh, G.nsH, G.nsW, G.nW * per_tile);
-        w.init(box.w0, box.w1, G.nW, G.gW, c & 1, ew, G.nsW, 1, per_tile);
-        n = ((c & 4) ? G.cutT : G.Qt) * ((c & 2) ? G.cutH : G.Qh) * ((c & 1) ? G.cutW : G.Qw);
-        jb0 = NH == 8 || !MB ? 0 : n >> 7;                 // 128-slot blocks; smaller groups have one
-        jb1 = MB ? (NH == 8 ? (n + 15) >> 7 : jb0 + 1) : 1;
-        jb = jb0;
-    }
-    // n blocks ahead, not past the last one
-    __device__ __forceinline__ void skip(int n_blocks) {
-        for (int i = 0; i < n_blocks; ++i) next();
-    }
-    // sets the walk to its first block; returns the number of blocks
-    __device__ __forceinline__ int begin(uint32_t classes_) {
-        int total = 0;
-        for (uint32_t left = classes_; left; left &= left - 1) {
-            enter(__builtin_ctz(left));
-            total += t.count() * h.count() * w.count() * (jb1 - jb0);
+        for (uint32_t left = classes; left; left &= left - 1) {
+            const int c = __builtin_ctz(left);
+            const AxisPart t(box.t0, box.t1, MB ? G.nsT : 1, G.gT, c & 4, et), h(box.h0, box.h1, MB ? G.nsH : 1, G.gH, c & 2, eh),
+                w(box.w0, box.w1, MB ? G.nsW : 1, G.gW, c & 1, ew);
+            const int n = ((c & 4) ? G.cutT : G.Qt) * ((c & 2) ? G.cutH : G.Qh) * ((c & 1) ? G.cutW : G.Qw);
+            const int jb0 = NH == 8 || !MB ? 0 : n >> 7;       // 128-slot blocks; smaller groups have one
+            f(t, h, w, n, jb0, MB && NH == 8 ? (n + 15) >> 7 : 1);
         }
-        classes = classes_;
-        enter_next();
-        return total;
     }
-    __device__ __forceinline__ void enter_next() {
-        enter(__builtin_ctz(classes));
-        classes &= classes - 1;
+    __device__ __forceinline__ int total() const {
+        int sum = 0;
+        for_classes([&](const AxisPart& t, const AxisPart& h, const AxisPart& w, int, int, int blocks) FPS_INLINE {
+            sum += t.count * h.count * w.count * blocks;
+        });
+        return sum;
     }
-    __device__ __forceinline__ void next() {               // not past the last block
-        if (MB) {
-            if (++jb < jb1) return;
-            jb = jb0;
-        }
-        if (!w.advance() && !h.advance() && !t.advance()) enter_next();
+    // lane l gets the wave group's block first + l
+    __device__ __forceinline__ void fill(int first) {
+        int i = kg + KS * (first + (int)(threadIdx.x & 63));
+        const float inv_st = __builtin_amdgcn_rcpf((float)G.nsT), inv_sh = __builtin_amdgcn_rcpf((float)G.nsH),
+                    inv_sw = __builtin_amdgcn_rcpf((float)G.nsW);
+        for_classes([&](const AxisPart& t, const AxisPart& h, const AxisPart& w, int n, int jb0, int blocks) FPS_INLINE {
+            const int size = t.count * h.count * w.count * blocks;
+            if (i >= 0 && i < size) {
+                int rest = i, jb = jb0;
+                if (MB) {
+                    const int q = divide_lane(rest, blocks, __builtin_amdgcn_rcpf((float)blocks));
+                    jb += rest - q * blocks;
+                    rest = q;
+                }
+                const int row = divide_lane(rest, w.count, __builtin_amdgcn_rcpf((float)w.count));
+                const int layer = divide_lane(row, h.count, __builtin_amdgcn_rcpf((float)h.count));
+                int it = t.first + layer, ih = h.first + row - layer * h.count, iw = w.first + rest - row * w.count;
+                int sub = 0;                                   // scale group within its tile
+                if (MB) {
+                    const int ut = divide_lane(it, G.nsT, inv_st), uh = divide_lane(ih, G.nsH, inv_sh),
+                              uw = divide_lane(iw, G.nsW, inv_sw);
+                    sub = ((it - ut * G.nsT) * G.nsH + (ih - uh * G.nsH)) * G.nsW + (iw - uw * G.nsW);
+                    it = ut; ih = uh; iw = uw;
+                }
+                const int tile = (it * G.nH + ih) * G.nW + iw;
+                group = MB ? tile * G.NS + sub : tile;
+                meta = (MB ? min(128, n - 128 * jb) : n) + 256 * jb;
+            }
+            i -= size;                                         // negative once found: sizes are below 2^31
+        });
     }
-    __device__ __forceinline__ KeyBlock block() const {
+    // block i of the wave group; fill() has covered it
+    __device__ __forceinline__ KeyBlock block(int i) const {
+        const int m = __builtin_amdgcn_readlane(meta, i & 63);
         KeyBlock b;
-        b.group = t.off + h.off + w.off;
-        b.blk = MB ? b.group * G.KBG + jb : b.group;
-        b.n = MB ? min(128, n - 128 * jb) : n;
+        b.group = __builtin_amdgcn_readlane(group, i & 63);
+        b.n = m & 255;
+        b.blk = MB ? b.group * G.KBG + (m >> 8) : b.group;
         return b;
     }
 };

@@ -18,18 +18,30 @@
 // tiles in three).  Powers of two commute with fp32 rounding: same results.
 // VCH: V carries one scale per channel (the paper's variant) instead of one per tile; the PV MFMA
 // then accumulates straight into O and the scales are applied once in the epilogue.
+// P: key blocks (small scale groups) that one step of the pipeline takes, each with scales of its own: as many of SB
+// sub-blocks as fill four, so that the barriers, the row reference and the bookkeeping of a step, 30 of the 150
+// to 180 vector instructions of a block of 48 or 64 keys, serve two or four blocks.  K and V of a step are double-buffered
+// where a workgroup has four waves; with less LDS a wave than that, K(i+2) and V(i) each stream into the one buffer
+// while the other product runs, two barriers a step.  Attention on 21x30x52 tokens, one block a step against P: 64-token
+// sub-tiles of (2,8,16) tiles, window 3x3x3, x 24 heads 1859 -> 1770 us; x 12 heads tile (3,4,4), window 3x5x7 799 -> 773, tile
+// (2,4,4) 522 -> 511 and (2,8,4), window 3x3x5, 339 -> 334.
 #include "fps_attn_device.h"
 
 namespace fps {
 
-template <int SB, int W, bool VCH, bool MB, int KS>
+template <int SB, int W, bool VCH, bool MB, int KS, int P>
 __global__ __launch_bounds__(KS * W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fp8_kernel(AttnArgs a) {
     constexpr int NTHR = KS * W * 64;
     constexpr int CPT = SB * 4 / W;                        // 16-byte chunks per thread per operand block
-    constexpr int BLOCK_BYTES = SB * 4096;
+    constexpr int BLOCK_BYTES = SB * 4096, STEP_BYTES = P * BLOCK_BYTES;
     static_assert(CPT >= 1 && CPT <= 4 && CPT * W == SB * 4, "every wave copies the same share of a block");
-    constexpr int GROUP_BYTES = 4 * BLOCK_BYTES;           // K even, K odd, V even, V odd
+    static_assert(KS == 1 || P == 1, "wave groups take single blocks");
+    static_assert(P * SB <= 4, "scores of a step: at most 4 sub-blocks");
+    // two buffers each for K and V where that leaves room for 8 waves on a CU, otherwise one
+    constexpr bool TWO = P * SB <= W;
+    constexpr int VBUF = TWO ? 2 : 1;                      // V's (first) buffer
+    constexpr int GROUP_BYTES = 2 * VBUF * STEP_BYTES;     // K even, K odd, V even, V odd; or K, V
     constexpr int LDS_BYTES = KS * GROUP_BYTES > SplitMerge<W, KS>::kBytes ? KS * GROUP_BYTES : SplitMerge<W, KS>::kBytes;
     // the groups' blocks; afterwards their sums and the output transpose
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
@@ -62,21 +74,35 @@ void attn_fp8_kernel(AttnArgs a) {
     const uint8_t* const v_head = a.v + tile0 * TSB * 4096;
     const float* const sk_head = a.sk + tile0 * NS;
     const float* const sv_head = a.sv + tile0 * NS;
-    auto k_blk = [&](const KeyBlock& b) FPS_INLINE { return k_head + (size_t)b.blk * BLOCK_BYTES; };
-    auto v_blk = [&](const KeyBlock& b) FPS_INLINE { return v_head + (size_t)b.blk * BLOCK_BYTES; };
-    auto stage_chunk = [&](int buf, const uint8_t* src, int c) FPS_INLINE {
-        dma_chunk_of(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * BLOCK_BYTES + wave_s * (CPT * 1024));
-    };
-    auto stage = [&](int buf, const uint8_t* src) FPS_INLINE {
+    // the key blocks of a step: of a list of `count`, those from P * step on; past the end the last one again
+    // (its weights are then made zero)
+    struct Step { KeyBlock b[P]; };
+    typedef BlockList<MB, KS> List;
+    auto step_blocks = [&](const List& list, int count, int step) FPS_INLINE {
+        Step st;
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
+        for (int g = 0; g < P; ++g) st.b[g] = list.block(P == 1 ? step : min(P * step + g, count - 1));
+        return st;
     };
-    auto lds_block = [&](int buf) FPS_INLINE { return lds + kg * GROUP_BYTES + buf * BLOCK_BYTES; };
-    int par = 0;                                           // parity of the current block's K and V buffers
+    // chunk c of the wave's share of the step's blocks
+    auto stage_chunk = [&](int buf, const uint8_t* head, const Step& st, int c) FPS_INLINE {
+        const int g = c / CPT;
+        dma_chunk_of(c % CPT, head + (size_t)st.b[g].blk * BLOCK_BYTES + wave_s * (CPT * 1024), lane * 16,
+                     lds_base + buf * STEP_BYTES + g * BLOCK_BYTES + wave_s * (CPT * 1024));
+    };
+    auto stage = [&](int buf, const uint8_t* head, const Step& st) FPS_INLINE {
+#pragma unroll
+        for (int c = 0; c < P * CPT; ++c) stage_chunk(buf, head, st, c);
+    };
+    auto lds_block = [&](int buf) FPS_INLINE { return lds + kg * GROUP_BYTES + buf * STEP_BYTES; };
+    auto landed = []() FPS_INLINE { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    int par = 0;                                           // TWO: parity of the current step's K and V buffers
+    auto k_buf = [&](int ahead) FPS_INLINE { return TWO ? par ^ ahead : 0; };
+    auto v_buf = [&](int ahead) FPS_INLINE { return VBUF + (TWO ? par ^ ahead : 0); };
 
-    // Of a walk of `total` blocks, those of this wave group.  Group 0 never has fewer than another; what a group
-    // has fewer barriers than group 0 (one a block, one a walk) it makes up for at the end, as every barrier
-    // is one of the whole workgroup.  (Made up for within the walk, they cost 110 spilled registers.)
+    // Of a list of `total` blocks, those of this wave group.  Group 0 never has fewer than another; what a group
+    // has fewer barriers than group 0 (one a block, one a list) it makes up for at the end, as every barrier
+    // is one of the whole workgroup.  (Made up for within the list, they cost 110 spilled registers.)
     int owed = 0;
     auto blocks_of_group = [&](int total) FPS_INLINE {
         if (KS == 1) return total;
@@ -94,38 +120,54 @@ void attn_fp8_kernel(AttnArgs a) {
         for (int nh = 2 * SB; nh >= 1; --nh) {
             const uint32_t classes = G.nh_classes[nh - 1] & box.classes;
             if (!classes) continue;
-            BlockWalk<MB> walk(G, box, nh);
-            const int total = walk.begin(classes);
-            const int nblk = blocks_of_group(total);
-            if (nblk == 0) continue;
-            walk.skip(kg);
-            KeyBlock nxt = walk.block();
-            stage(par, k_blk(nxt));
-            stage(2 + par, v_blk(nxt));
-            if (nblk > 1) {
-                walk.skip(KS);
-                nxt = walk.block();
-                stage(par ^ 1, k_blk(nxt));
+            List list(G, box, nh, classes, kg);
+            const int count = blocks_of_group(list.total());
+            if (count == 0) continue;
+            const int steps = (count + P - 1) / P;
+            list.fill(0);
+            Step cur = step_blocks(list, count, 0), nxt = cur;
+            if (steps > 1) nxt = step_blocks(list, count, 1);
+            stage(k_buf(0), k_head, cur);
+            if (TWO) {
+                stage(v_buf(0), v_head, cur);
+                if (steps > 1) stage(k_buf(1), k_head, nxt);
+            } else {
+                landed();
+                __syncthreads();                           // K(0) visible
+                __syncthreads();                           // QK(0) done
+                if (steps > 1) stage(k_buf(0), k_head, nxt);
             }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            landed();
             __syncthreads();
-            for (int i = 0; i + 1 < nblk; ++i) {
-                __syncthreads();
-                const KeyBlock v_next = nxt;
-                if (i + 2 < nblk) {
-                    walk.skip(KS);
-                    nxt = walk.block();
-                    stage(par, k_blk(nxt));
+            for (int i = 0; i + 1 < steps; ++i) {
+                if (TWO) {
+                    __syncthreads();
+                } else {
+                    stage(v_buf(0), v_head, cur);
+                    landed();
+                    __syncthreads();                       // QK(i+1) done; V(i) visible
                 }
-                stage(2 + (par ^ 1), v_blk(v_next));
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                cur = nxt;
+                if (i + 2 < steps) {
+                    if (((P * (i + 2)) & 63) == 0) list.fill(P * (i + 2));
+                    nxt = step_blocks(list, count, i + 2);
+                    stage(k_buf(0), k_head, nxt);
+                }
+                if (TWO) stage(v_buf(1), v_head, cur);
+                landed();
+                if (!TWO) __syncthreads();                 // PV(i) done; K(i+2) visible
                 par ^= 1;
+            }
+            if (!TWO) {
+                stage(v_buf(0), v_head, cur);
+                landed();
+                __syncthreads();
             }
             __syncthreads();
             par ^= 1;
         }
         make_up();
-        __syncthreads();
+        if (TWO) __syncthreads();
         if (KS > 1) __syncthreads();
         return;
     }
@@ -134,7 +176,8 @@ void attn_fp8_kernel(AttnArgs a) {
     float m_run = -INFINITY;
     float l_run = 0.f;                                     // running sum of 448 * P (this lane's keys)
     float alpha = 1.f;                                     // VCH: rescale owed to O before the delayed PV
-    float m_base = 0.f, w_cur = 1.f, w_prev = 0.f;         // fixed reference and weights: see above
+    float m_base = 0.f, w_cur = 1.f;                       // fixed reference and weight: see above
+    float w_owed = 0.f;                                    // weight of the fma owed to O's last channel block
     v16f acc[4];
     {
         const uint4* p = reinterpret_cast<const uint4*>(a.q + (((tile0 + u) * TSB + qs) * 32 + n) * 128 + 32 * h);
@@ -146,32 +189,37 @@ void attn_fp8_kernel(AttnArgs a) {
     const float sqc = load_uniform(a.sq, (tile0 + u) * NS + rows.group) * kLog2eOverSqrtD;
 
     auto pipeline = [&](auto nh_tag) FPS_INLINE {
-        constexpr int NH = decltype(nh_tag)::value;        // 16-key halves
-        constexpr int NB = (NH + 1) / 2;                   // 32-key sub-blocks
-        constexpr int J = (NB + 1) / 2;                    // contraction steps of the PV product: two sub-blocks each,
+        constexpr int NH = decltype(nh_tag)::value;        // 16-key halves of a block
+        constexpr int NB = (NH + 1) / 2;                   // 32-key sub-blocks of a block
+        constexpr int NT = P * NB;                         // and of a step: block kb / NB, its sub-block kb % NB
+        constexpr int J = (NB + 1) / 2;                    // contraction steps of a block's PV product: two sub-blocks each,
         constexpr bool TAIL = NB % 2 != 0;                 // the last one of an odd number by itself
+        constexpr int R = 4 * P;                           // PV products of 32 channels: channel block r / P, key block r % P
         const uint32_t classes = G.nh_classes[NH - 1] & box.classes;
         if (!classes) return;
-        BlockWalk<MB> walk(G, box, NH);
-        const int total = walk.begin(classes);
-        const int nblk = blocks_of_group(total);
-        if (nblk == 0) return;
-        walk.skip(kg);
+        List list(G, box, NH, classes, kg);
+        const int count = blocks_of_group(list.total());
+        if (count == 0) return;
+        const int steps = (count + P - 1) / P;
+        const bool odd = P > 1 && count < P * steps;       // the last step is not full
+        list.fill(0);
 
-        v16f s[NB];                                        // S^T, blocks of 32 keys
-        v8i pb[2];                                         // P^T as packed E4M3: contraction steps 0 and 1
-        v16f tq[2];                                        // raw V^T P^T of a channel block, until its fma
-        pb[0] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
-        pb[1] = pb[0];
-        // operand `step` of a staged block -- K: 32-key sub-block * 2 + contraction step; V: 32-channel
-        // block * J + contraction step (keys of sub-blocks 2j and 2j + 1)
+        v16f s[NT];                                        // S^T, blocks of 32 keys
+        v8i pb[P * J];                                     // P^T as packed E4M3, per contraction step
+        v16f tq[2];                                        // raw V^T P^T of a product, until its fma
+#pragma unroll
+        for (int i = 0; i < P * J; ++i) pb[i] = v8i{0, 0, 0, 0, 0, 0, 0, 0};
+        auto has_half = [](int t) { return 2 * ((t >> 1) % NB) + (t & 1) < NH; };   // half t & 1 of sub-block t >> 1
+        // operand `step` of the staged blocks -- K: 32-key sub-block * 2 + contraction step; V: product * J +
+        // contraction step (keys of sub-blocks 2j and 2j + 1)
         auto load_k = [&](const uint8_t* buf, int step) FPS_INLINE {
+            const int kb = step >> 1, at = ((kb / NB * SB + kb % NB) * 4 + (step & 1) * 2) * 64;
             const uint4* b4 = reinterpret_cast<const uint4*>(buf);
-            return make_v8i(b4[(step * 2 + 0) * 64 + lane], b4[(step * 2 + 1) * 64 + lane]);
+            return make_v8i(b4[at + lane], b4[at + 64 + lane]);
         };
         auto load_v = [&](const uint8_t* buf, int step) FPS_INLINE {
-            const int db = step / J, j = step % J;
-            const uint4* b4 = reinterpret_cast<const uint4*>(buf);
+            const int r = step / J, j = step % J, db = r / P, g = r % P;
+            const uint4* b4 = reinterpret_cast<const uint4*>(buf) + g * (BLOCK_BYTES / 16);
             const uint4 lo = b4[((2 * j + 0) * 4 + db) * 64 + lane];
             if (TAIL && j == J - 1) return make_v8i(lo, lo);           // only the lower half is used
             return make_v8i(lo, b4[((2 * j + 1) * 4 + db) * 64 + lane]);
@@ -182,8 +230,9 @@ void attn_fp8_kernel(AttnArgs a) {
                                                                    0, 0, 0, 0, 0, 0);
         };
         auto pv_mfma = [&](const v8i& vop, int step) FPS_INLINE {
-            const int db = step / J, j = step % J;
-            v16f r = VCH ? acc[db] : j == 0 ? zero16() : tq[db & 1];
+            const int r = step / J, j = step % J, db = r / P;
+            const v8i& pj = pb[r % P * J + j];
+            v16f x = VCH ? acc[db] : j == 0 ? zero16() : tq[r & 1];
             if (TAIL && j == J - 1) {
                 // a single sub-block: 32x32x16 instructions, 16 keys each.  They take 32.5 clocks against 64.9 of a
                 // 32x32x64, so two halves cost what half of one would and a single half less.  A lane's 8
@@ -191,21 +240,22 @@ void attn_fp8_kernel(AttnArgs a) {
 #pragma unroll
                 for (int e = 0; e < (NH % 2 ? 1 : 2); ++e) {
                     const long va = (long)((uint64_t)(uint32_t)vop[2 * e] | ((uint64_t)(uint32_t)vop[2 * e + 1] << 32));
-                    const long pa = (long)((uint64_t)(uint32_t)pb[j][2 * e] | ((uint64_t)(uint32_t)pb[j][2 * e + 1] << 32));
-                    r = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(va, pa, r, 0, 0, 0);
+                    const long pa = (long)((uint64_t)(uint32_t)pj[2 * e] | ((uint64_t)(uint32_t)pj[2 * e + 1] << 32));
+                    x = __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(va, pa, x, 0, 0, 0);
                 }
             } else {
-                r = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vop, pb[j], r, 0, 0, 0, 0, 0, 0);
+                x = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vop, pj, x, 0, 0, 0, 0, 0, 0);
             }
-            if (VCH) acc[db] = r; else tq[db & 1] = r;
+            if (VCH) acc[db] = x; else tq[r & 1] = x;
         };
-        // half `half` of O^T(db) += s^V 2^(m - m_base) * raw, pinned where it is written
-        auto pv_accumulate_half = [&](int db, int half) FPS_INLINE {
+        // half `half` of O^T(r / P) += w * raw product r, w = s^V 2^(m - m_base), pinned where it is written
+        auto pv_accumulate_half = [&](int r, int half, float w) FPS_INLINE {
             if (VCH) return;
 #pragma unroll
-            for (int r = 8 * half; r < 8 * half + 8; ++r) acc[db][r] = __builtin_fmaf(tq[db & 1][r], w_prev, acc[db][r]);
-            asm volatile("" : "+v"(acc[db]));
+            for (int i = 8 * half; i < 8 * half + 8; ++i) acc[r / P][i] = __builtin_fmaf(tq[r & 1][i], w, acc[r / P][i]);
+            asm volatile("" : "+v"(acc[r / P]));
         };
+        auto pv_accumulate = [&](int r, float w) FPS_INLINE { pv_accumulate_half(r, 0, w); pv_accumulate_half(r, 1, w); };
         // row maximum of half `e` of score block kb
         auto max_half = [&](float mx, int kb, int e) FPS_INLINE {
 #pragma unroll
@@ -214,32 +264,46 @@ void attn_fp8_kernel(AttnArgs a) {
             asm volatile("" : "+v"(mx));
             return mx;
         };
+        // the first half of a block's row maximum starts it
+        auto max_of_half = [&](float (&mx)[P], int t) FPS_INLINE {
+            if (has_half(t)) mx[t / (2 * NB)] = max_half(t % (2 * NB) == 0 ? -INFINITY : mx[t / (2 * NB)], t >> 1, t & 1);
+        };
         float cm = 0.f;
         // the weights of half `e` of score block kb and their FP8 codes
-        auto weights_half = [&](int kb, int e, float sc, float& rs) FPS_INLINE {
+        auto weights_half = [&](int kb, int e, float sc, float c, float& rs) FPS_INLINE {
+            v8i& pj = pb[kb / NB * J + kb % NB / 2];
+            const int at = 4 * (kb % NB % 2) + 2 * e;
 #pragma unroll
             for (int q2 = 0; q2 < 2; ++q2) {
                 float p[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    p[r] = fast_exp2(__builtin_fmaf(s[kb][8 * e + 4 * q2 + r], sc, cm));
+                    p[r] = fast_exp2(__builtin_fmaf(s[kb][8 * e + 4 * q2 + r], sc, c));
                     rs += p[r];
                 }
-                int pw = pb[kb >> 1][4 * (kb & 1) + 2 * e + q2];
+                int pw = pj[at + q2];
                 pw = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], pw, false);
                 pw = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], pw, true);
                 asm volatile("" : "+v"(pw), "+v"(rs));     // keep the pass where it is written
-                pb[kb >> 1][4 * (kb & 1) + 2 * e + q2] = pw;
+                pj[at + q2] = pw;
             }
         };
-        // the row reference of the block whose row maximum mx was taken
-        auto new_reference = [&](float mx, float sc) FPS_INLINE {
-            mx = max_over_row_pair(mx);
-            const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(mx * sc));
+        auto mask_blocks = [&](const int (&nn)[P]) FPS_INLINE {
+#pragma unroll
+            for (int g = 0; g < P; ++g)
+                if (nn[g] < 16 * NH) mask_cut_half(s[g * NB + NB - 1], (NH - 1) & 1, nn[g] - 16 * (NH - 1), h);
+        };
+        // the row reference of the step whose row maxima mx (per block, not scaled) were taken
+        auto new_reference = [&](const float (&mx)[P], const float (&sc)[P]) FPS_INLINE {
+            float top = P == 1 ? max_over_row_pair(mx[0]) * sc[0] : mx[0] * sc[0];
+#pragma unroll
+            for (int g = 1; g < P; ++g) top = __builtin_fmaxf(top, mx[g] * sc[g]);
+            if (P > 1) top = max_over_row_pair(top);
+            const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(top));
             if (VCH) {
                 alpha = fast_exp2(m_run - m_new);
             } else {
-                m_base = m_run == -INFINITY ? m_new : m_base;          // the item's first block
+                m_base = m_run == -INFINITY ? m_new : m_base;          // the item's first step
                 w_cur = fast_exp2(m_new - m_base);
             }
             m_run = m_new;
@@ -249,144 +313,176 @@ void attn_fp8_kernel(AttnArgs a) {
 #pragma unroll
                 for (int db = 0; db < 4; ++db) acc[db] *= down;
                 l_run *= down;
-                w_prev *= down;            // the last channel block's fma is still owed
+                w_owed *= down;            // the last product's fma is still owed
                 m_base = m_run;
                 w_cur = 1.0f;
             }
         };
+        auto load_scales = [&](const Step& st, float (&sc)[P], float (&sv)[P]) FPS_INLINE {
+#pragma unroll
+            for (int g = 0; g < P; ++g) {
+                sc[g] = sqc * load_uniform(sk_head, st.b[g].group);
+                sv[g] = VCH ? 1.f : load_uniform(sv_head, st.b[g].group);
+            }
+        };
+        // the step's share of the row sums, and the rescale that O owes (VCH)
+        auto add_row_sums = [&](float rs) FPS_INLINE {
+            if (VCH) l_run = l_run * alpha + rs;
+            else     l_run = __builtin_fmaf(rs, w_cur, l_run);
+        };
+        auto rescale = [&]() FPS_INLINE {
+            if (VCH && __any(alpha != 1.0f)) {
+#pragma unroll
+                for (int db = 0; db < 4; ++db) acc[db] *= alpha;
+            }
+        };
 
         // prologue: K(0), V(0), K(1) staged; S(0) and its row reference
-        KeyBlock nxt = walk.block();
-        const int n0 = nxt.n;
-        stage(par, k_blk(nxt));
-        stage(2 + par, v_blk(nxt));
-        float sc = sqc * load_uniform(sk_head, nxt.group);
-        float svv = VCH ? 1.f : load_uniform(sv_head, nxt.group);
-        if (nblk > 1) {
-            walk.skip(KS);
-            nxt = walk.block();
-            stage(par ^ 1, k_blk(nxt));
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        Step cur = step_blocks(list, count, 0), nxt = cur;
+        if (steps > 1) nxt = step_blocks(list, count, 1);
+        float sc[P], svv[P], mx[P];
+        int n_cut[P];
+#pragma unroll
+        for (int g = 0; g < P; ++g) n_cut[g] = cur.b[g].n;
+        stage(k_buf(0), k_head, cur);
+        if (TWO) stage(v_buf(0), v_head, cur);
+        load_scales(cur, sc, svv);
+        if (TWO && steps > 1) stage(k_buf(1), k_head, nxt);
+        landed();
         __syncthreads();
 #pragma unroll
-        for (int step = 0; step < 2 * NB; ++step) qk_mfma(load_k(lds_block(par), step), step);
-        if (n0 < 16 * NH) mask_cut_half(s[NB - 1], (NH - 1) & 1, n0 - 16 * (NH - 1), h);
-        {
-            float mx = -INFINITY;
-#pragma unroll
-            for (int k = 0; k < NH; ++k) mx = max_half(mx, k >> 1, k & 1);
-            w_prev = 0.f;
-            new_reference(mx, sc);
+        for (int step = 0; step < 2 * NT; ++step) qk_mfma(load_k(lds_block(k_buf(0)), step), step);
+        if (!TWO) {
+            __syncthreads();                               // every wave is past QK(0)
+            if (steps > 1) stage(k_buf(0), k_head, nxt);
         }
-        if (!VCH) tq[1] = zero16();
+        mask_blocks(n_cut);
+#pragma unroll
+        for (int t = 0; t < 2 * NT; ++t) max_of_half(mx, t);
+        w_owed = 0.f;
+        new_reference(mx, sc);
+        if (!VCH) tq[(R - 1) & 1] = zero16();
+        if (!TWO) {
+            landed();
+            __syncthreads();                               // K(1) visible
+        }
 
         // iteration i: P(i) | S(i+1) = K(i+1) Q^T, then row maximum of S(i+1) | O += s^V (V^T P^T)(i)
-        for (int i = 0; i + 1 < nblk; ++i) {
-            const uint8_t* knxt = lds_block(par ^ 1);            // K(i+1)
-            const uint8_t* vcur = lds_block(2 + par);            // V(i)
-            __syncthreads();             // every wave is past QK(i) and PV(i-1); staged blocks are visible
+        for (int i = 0; i + 1 < steps; ++i) {
+            const uint8_t* knxt = lds_block(k_buf(1));           // K(i+1)
+            const uint8_t* vcur = lds_block(v_buf(0));           // V(i)
+            if (TWO) __syncthreads();    // every wave is past QK(i) and PV(i-1); staged blocks are visible
             v8i op[3];                   // MFMA operands on their way from LDS, two steps ahead
             op[0] = load_k(knxt, 0);
             op[1] = load_k(knxt, 1);
-            const int n_next = nxt.n;
-            const uint8_t* vsrc = v_blk(nxt);
-            const float sc_next = sqc * load_uniform(sk_head, nxt.group);
-            const float sv_next = VCH ? 1.f : load_uniform(sv_head, nxt.group);
-            const bool fetch_k = i + 2 < nblk;
-            const uint8_t* ksrc = nullptr;
+#pragma unroll
+            for (int g = 0; g < P; ++g) n_cut[g] = nxt.b[g].n;
+            const Step v_step = TWO ? nxt : cur;                 // V(i+1), or V(i)
+            float sc_next[P], sv_next[P];
+            load_scales(nxt, sc_next, sv_next);
+            cur = nxt;
+            const bool fetch_k = i + 2 < steps;
             if (fetch_k) {
-                walk.skip(KS);
-                nxt = walk.block();
-                ksrc = k_blk(nxt);
+                if (((P * (i + 2)) & 63) == 0) list.fill(P * (i + 2));
+                nxt = step_blocks(list, count, i + 2);
             }
 
             // ---- P(i) and its FP8 codes  |  QK(i+1) ------------------------------------------
             // step t: the exponentials of half a score block (block t/2, registers 8(t%2)..+7); the
             // MFMAs that refill a block follow one block behind, so steps 0, 1 have none (they take
-            // the fma still owed to the last channel block of PV(i-1)) and the last two nothing else
+            // the fma still owed to the last product of PV(i-1)) and the last two nothing else
             float rs = 0.f;
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int t = 0; t < 2 * NB + 2; ++t) {
+            for (int t = 0; t < 2 * NT + 2; ++t) {
                 if (t >= 2) {
-                    if (t < 2 * NB) op[t % 3] = load_k(knxt, t);       // operand of step t + 2
+                    if (t < 2 * NT) op[t % 3] = load_k(knxt, t);       // operand of step t + 2
                     qk_mfma(op[(t - 2) % 3], t - 2);
                 }
-                if (t < 2) pv_accumulate_half(3, t);                   // PV(i-1)'s last block
-                if (t < NH) weights_half(t >> 1, t & 1, sc, rs);
-                if (t < CPT && fetch_k) stage_chunk(par, ksrc, t);     // K(i) was consumed last iteration
+                if (t < 2) pv_accumulate_half(R - 1, t, w_owed);       // PV(i-1)'s last product
+                if (t < 2 * NT && has_half(t)) weights_half(t >> 1, t & 1, sc[t / (2 * NB)], cm, rs);
+                constexpr int per = (P * CPT + 2 * NT + 1) / (2 * NT + 2);
+#pragma unroll
+                for (int c = t * per; c < (t + 1) * per && c < P * CPT; ++c) {
+                    if (!TWO)         stage_chunk(v_buf(0), v_head, v_step, c);          // V(i-1) was consumed
+                    else if (fetch_k) stage_chunk(k_buf(0), k_head, nxt, c);             // K(i) was consumed last iteration
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (VCH) l_run = l_run * alpha + rs;
-            else     l_run = __builtin_fmaf(rs, w_cur, l_run);
-            w_prev = svv * w_cur;
-            sc = sc_next;
-            svv = sv_next;
+            add_row_sums(rs);
+            float wg[P];                                         // weights of the step's products
+#pragma unroll
+            for (int g = 0; g < P; ++g) {
+                wg[g] = svv[g] * w_cur;
+                sc[g] = sc_next[g];
+                svv[g] = sv_next[g];
+            }
+            w_owed = wg[P - 1];
+            if (!TWO) {
+                landed();
+                __syncthreads();         // every wave is past QK(i+1); V(i) is visible
+            }
             op[0] = load_v(vcur, 0);
             op[1] = load_v(vcur, 1);
-            if (n_next < 16 * NH) mask_cut_half(s[NB - 1], (NH - 1) & 1, n_next - 16 * (NH - 1), h);
-            if (VCH && __any(alpha != 1.0f)) {
-#pragma unroll
-                for (int db = 0; db < 4; ++db) acc[db] *= alpha;
-            }
+            mask_blocks(n_cut);
+            rescale();
 
             // ---- row maximum of S(i+1)  |  PV(i) ---------------------------------------------
-            // step k: the MFMA of channel block k/J, contraction step k%J, a 16-key half of the row
-            // maximum, and the fma of a channel block whose last MFMA was issued two or three steps
+            // step k: the MFMA of product k/J, contraction step k%J, 16-key halves of the row
+            // maximum, and the fma of a product whose last MFMA was issued two or three steps
             // earlier (a 16-pass result may be read 18 issue slots after its instruction)
-            float mx = __builtin_fmaxf(__builtin_fmaxf(s[0][0], s[0][1]), __builtin_fmaxf(s[0][2], s[0][3]));
+            constexpr int STEPS = R * J, HPS = (2 * NT + STEPS - 1) / STEPS;
 #pragma unroll
-            for (int k = 0; k < 4 * J; ++k) {
-                if (k + 2 < 4 * J) op[(k + 2) % 3] = load_v(vcur, k + 2);
+            for (int k = 0; k < STEPS; ++k) {
+                if (k + 2 < STEPS) op[(k + 2) % 3] = load_v(vcur, k + 2);
                 if (J == 2) {                              // before tq[..] is refilled
-                    if (k >= 3) pv_accumulate_half((k - 3) >> 1, (k - 3) & 1);
+                    if (k >= 3) pv_accumulate_half((k - 3) >> 1, (k - 3) & 1, wg[((k - 3) >> 1) % P]);
                 } else if (k >= 2) {
-                    pv_accumulate_half(k - 2, 0);
-                    pv_accumulate_half(k - 2, 1);
+                    pv_accumulate(k - 2, wg[(k - 2) % P]);
                 }
                 pv_mfma(op[k % 3], k);
-                if (k < NH) {
-                    if (k == 0) {
-                        mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][4]), s[0][5]);
-                        mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[0][6]), s[0][7]);
-                        asm volatile("" : "+v"(mx));
-                    } else {
-                        mx = max_half(mx, k >> 1, k & 1);
-                    }
+#pragma unroll
+                for (int t = k * HPS; t < (k + 1) * HPS && t < 2 * NT; ++t) max_of_half(mx, t);
+                static_assert(P * CPT <= STEPS, "one copy a step");
+                if (k < P * CPT) {
+                    if (TWO)          stage_chunk(v_buf(1), v_head, v_step, k);          // V(i-1) was consumed last iteration
+                    else if (fetch_k) stage_chunk(k_buf(0), k_head, nxt, k);             // K(i+1) was consumed
                 }
-                if (k < CPT) stage_chunk(2 + (par ^ 1), vsrc, k);      // V(i-1) was consumed last iteration
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (J == 1) pv_accumulate_half(2, 0);
-            pv_accumulate_half(2, 1);
+            if (J == 1) pv_accumulate_half(R - 2, 0, wg[(R - 2) % P]);
+            pv_accumulate_half(R - 2, 1, wg[(R - 2) % P]);
             new_reference(mx, sc);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's share of the staged blocks landed
+            landed();                    // this thread's share of the staged blocks
+            if (!TWO) __syncthreads();   // every wave is past PV(i); K(i+2) is visible
             par ^= 1;
         }
 
-        // the last block's P and PV
-        __syncthreads();
-        pv_accumulate_half(3, 0);
-        pv_accumulate_half(3, 1);
+        // the last step's P and PV
+        if (TWO) __syncthreads();
+        else     stage(v_buf(0), v_head, cur);
+        if (!VCH) pv_accumulate(R - 1, w_owed);
         float rs = 0.f;
 #pragma unroll
-        for (int t = 0; t < NH; ++t) weights_half(t >> 1, t & 1, sc, rs);
-        if (VCH) l_run = l_run * alpha + rs;
-        else     l_run = __builtin_fmaf(rs, w_cur, l_run);
-        w_prev = svv * w_cur;
-        if (VCH && __any(alpha != 1.0f)) {
-#pragma unroll
-            for (int db = 0; db < 4; ++db) acc[db] *= alpha;
+        for (int t = 0; t < 2 * NT; ++t) {
+            // a block past the end has no weights
+            const float c = t / (2 * NB) > 0 && odd && count <= P * (steps - 1) + t / (2 * NB) ? -INFINITY : cm;
+            if (has_half(t)) weights_half(t >> 1, t & 1, sc[t / (2 * NB)], c, rs);
+        }
+        add_row_sums(rs);
+        rescale();
+        if (!TWO) {
+            landed();
+            __syncthreads();
         }
 #pragma unroll
-        for (int db = 0; db < 4; ++db) {
+        for (int r = 0; r < R; ++r) {
 #pragma unroll
-            for (int j = 0; j < J; ++j) pv_mfma(load_v(lds_block(2 + par), db * J + j), db * J + j);
-            if (db > 0) { pv_accumulate_half(db - 1, 0); pv_accumulate_half(db - 1, 1); }
+            for (int j = 0; j < J; ++j) pv_mfma(load_v(lds_block(v_buf(0)), r * J + j), r * J + j);
+            if (r > 0) pv_accumulate(r - 1, svv[(r - 1) % P] * w_cur);
         }
-        pv_accumulate_half(3, 0);
-        pv_accumulate_half(3, 1);
+        pv_accumulate(R - 1, svv[P - 1] * w_cur);
+        if (!TWO) __syncthreads();                         // both buffers are free
         par ^= 1;
     };
     if constexpr (SB > 3) { pipeline(Count<8>{}); pipeline(Count<7>{}); }
@@ -396,7 +492,7 @@ void attn_fp8_kernel(AttnArgs a) {
     pipeline(Count<1>{});
 
     make_up();
-    __syncthreads();                                       // all waves are done with the staged tiles
+    if (TWO) __syncthreads();                              // all waves are done with the staged tiles
     if constexpr (KS > 1) {
         // O and l of a group are relative to its reference, a power of two: moving them to the largest is exact
         const SplitMerge<W, KS> merge{lds, row_block, lane};
@@ -420,10 +516,10 @@ void attn_fp8_kernel(AttnArgs a) {
                VCH ? a.sv + (size_t)bh * 128 : nullptr);
 }
 
-template <int SB, int W, bool MB, int KS = 1>
+template <int SB, int W, bool MB, int KS = 1, int P = 1>
 static void launch(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
-    if (vch) attn_fp8_kernel<SB, W, true, MB, KS><<<grid, KS * W * 64, 0, st>>>(a);
-    else     attn_fp8_kernel<SB, W, false, MB, KS><<<grid, KS * W * 64, 0, st>>>(a);
+    if (vch) attn_fp8_kernel<SB, W, true, MB, KS, P><<<grid, KS * W * 64, 0, st>>>(a);
+    else     attn_fp8_kernel<SB, W, false, MB, KS, P><<<grid, KS * W * 64, 0, st>>>(a);
 }
 
 void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
@@ -452,21 +548,21 @@ void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
         case 2:
             if (g.NS == 1) {
                 if (split_keys(a, 4)) launch<2, 2, false, 4>(a, vch, grid, st);
-                else                  launch<2, 2, false>(a, vch, grid, st);
+                else                  launch<2, 2, false, 1, 2>(a, vch, grid, st);
             } else if (four) {
-                launch<2, 4, true>(a, vch, grid, st);
+                launch<2, 4, true, 1, 2>(a, vch, grid, st);
             } else {
-                launch<2, 2, true>(a, vch, grid, st);
+                launch<2, 2, true, 1, 2>(a, vch, grid, st);
             }
             break;
         default:
             if (g.NS == 1) {
                 if (split_keys(a, 4)) launch<1, 1, false, 4>(a, vch, grid, st);
-                else                  launch<1, 1, false>(a, vch, grid, st);
+                else                  launch<1, 1, false, 1, 2>(a, vch, grid, st);
             } else if (four) {
-                launch<1, 4, true>(a, vch, grid, st);
+                launch<1, 4, true, 1, 4>(a, vch, grid, st);
             } else {
-                launch<1, 1, true>(a, vch, grid, st);
+                launch<1, 1, true, 1, 2>(a, vch, grid, st);
             }
             break;
     }

@@ -443,6 +443,42 @@ def test_keys_split_over_wave_groups_of_tiles_in_sub_tiles(prec, vscale):
         gu.assert_parity(st, f"head {h}")
 
 
+@pytest.mark.parametrize("vscale", [fps.VSCALE_TILE, fps.VSCALE_CHANNEL])
+@pytest.mark.parametrize("tile,qtile", [((2, 4, 4), None), ((3, 4, 4), None), ((2, 8, 4), None),
+                                        ((2, 4, 8), (1, 4, 4)), ((2, 8, 8), (2, 4, 8)), ((1, 4, 12), (1, 4, 4))])
+@pytest.mark.parametrize("tiles,window", [(1, 1), (4, 3), (5, 5), (9, 9)])
+def test_small_groups_two_or_four_a_step(vscale, tile, qtile, tiles, window):
+    """Lists of 1, 2, 3, .. blocks of small scale groups, of which the kernel takes two or four at a time."""
+    say("groups a step", vscale, tile, qtile, tiles, window)
+    w = dataclasses.replace(synth.TINY, grid=(tile[0], tile[1], tile[2] * tiles - 1), tile=tile, window=(1, 1, window),
+                            heads=2, n_outlier=3, config_id=27)
+    run = gu.GpuRun(w, qtile=qtile)
+    out = run.attn(fps.PREC_FP8, vscale=vscale)
+    for h in range(2):
+        st = gu.compare_head(run, out, h, fps.PREC_FP8, w.window, vscale=vscale)
+        gu.assert_parity(st, "groups a step")
+
+
+@pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
+@pytest.mark.parametrize("heads", [1, 8])                 # keys split over wave groups, and not
+@pytest.mark.parametrize("tile,qtile", [((1, 8, 16), None), ((2, 8, 16), None), ((2, 4, 4), None),
+                                        ((2, 8, 16), (1, 8, 8))])
+@pytest.mark.parametrize("blocks", [64, 66, 130])
+def test_lists_of_key_blocks_longer_than_a_wave(prec, heads, tile, qtile, blocks):
+    """The kernels list the next 64 key blocks at a time, one a lane: walks that end with, just past and well past
+    a full list, one row of tiles whose last is cut."""
+    say("block lists", prec, heads, tile, qtile, blocks)
+    slots = tile[0] * tile[1] * tile[2]
+    per_tile = 4 if qtile else max(1, slots // 128)
+    n = blocks // per_tile + 1                             # the whole tiles' walk is the longest
+    w = dataclasses.replace(synth.TINY, grid=(tile[0], tile[1], tile[2] * n - tile[2] // 2), tile=tile,
+                            window=(1, 1, 2 * n - 1), heads=heads, n_outlier=3, config_id=25)
+    run = gu.GpuRun(w, qtile=qtile)
+    out = run.attn(prec)
+    st = gu.compare_head(run, out, heads - 1, prec, w.window, q_tiles=[0, n - 1])
+    gu.assert_parity(st, "block lists")
+
+
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
 @pytest.mark.parametrize("tile,rest", [((1, 1, 128), r) for r in (1, 31, 32, 33, 64, 65, 96, 97, 127)] +
                          [((1, 2, 128), r) for r in (1, 48, 63, 64, 65, 127)])
