@@ -24,6 +24,7 @@ constexpr int kMaxFold = 4;                // binades by which a block's weights
 template <int SB, int W, bool MB, int KS>
 __global__ __launch_bounds__(KS * W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bf16_kernel(AttnArgs a) {
+    load_arguments<(sizeof(AttnArgs) + 63) / 64>();
     constexpr int NTHR = KS * W * 64;
     constexpr int CPT = SB * 8 / W;                        // 16-byte chunks per thread per operand block
     constexpr int BLOCK_BYTES = SB * 8192;
@@ -36,12 +37,11 @@ void attn_bf16_kernel(AttnArgs a) {
     const int NS = MB ? G.NS : 1;
     const int KBG = MB && SB == 4 ? G.KBG : 1;             // key blocks of a scale group
     const int TSB = MB ? NS * KBG * SB : SB;               // sub-blocks of a tile
-    int bh, u, jq;
-    if (!work_item(a, &bh, &u, &jq)) return;
+    int bh, ut, uh, uw, jq;
+    if (!work_item(a, &bh, &ut, &uh, &uw, &jq)) return;
+    const int u = (ut * G.nH + uh) * G.nW + uw;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, n = lane & 31;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave) % W, kg = KS > 1 ? __builtin_amdgcn_readfirstlane(wave) / W : 0;
-    const int ut = quotient(u, G.nW * G.nH, G.rc_layer), urem = u - ut * (G.nW * G.nH);
-    const int uh = quotient(urem, G.nW, G.rc_row), uw = urem - uh * G.nW;
     const int ucls = tile_class(G, ut, uh, uw);
     // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
     // waves of cut tiles fall on different SIMDs

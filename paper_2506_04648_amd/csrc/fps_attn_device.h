@@ -30,8 +30,9 @@
 // does not depend on the order in which key tiles arrive (apart from values in the subnormal
 // range of the format).  The denominator accumulates the unrounded P.
 #pragma once
-#include "fps_internal.h"
+#include "fps_attn_plan.h"
 
+#include <stddef.h>
 #include <type_traits>
 
 namespace fps {
@@ -67,6 +68,8 @@ struct AttnArgs {
     int chunk;             // work items per XCD, a multiple of 4
     int rotate;            // deal each four consecutive work items in a turning order (see work_item)
     int total;             // BH * M * qblocks
+    int planned;           // the items are dealt by `plan`, not in raster order
+    ItemPlan plan;
 };
 
 // Every lambda of the kernels captures the accumulators by reference; left to the inliner's cost
@@ -94,8 +97,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v2f{lo, hi}, v2bf));
 }
 
-// Work item of this workgroup: query block jq of tile u of head bh.  Workgroups are dealt round-robin to
-// the 8 XCDs by the hardware; giving XCD x the contiguous range [x*chunk, (x+1)*chunk) of items keeps
+// Work item of this workgroup: query block jq of tile (ut, uh, uw) of head bh.  Workgroups are dealt round-robin to
+// the 8 XCDs by the hardware; giving XCD x the contiguous range [x*chunk, (x+1)*chunk) of items (or that part of every section) keeps
 // the key tiles of neighbouring query tiles of one head in that XCD's L2.
 //
 // Within an XCD the hardware deals workgroups in order and round-robin to four shader engines, waiting
@@ -104,20 +107,35 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // stands idle: 21x30x52 tokens x 12 heads, tile (1,8,16), four tiles a row, had 355 of 512 workgroups
 // resident.  There (deal_in_turns) each group of four items is dealt in an order that turns from group to group; with
 // the group's index over 4 and 16 added, so that it also turns from row to row where a row is 8, 16 or 32 items.
-__device__ __forceinline__ bool work_item(const AttnArgs& a, int* bh, int* u, int* jq) {
+__device__ __forceinline__ bool work_item(const AttnArgs& a, int* bh, int* ut, int* uh, int* uw, int* jq) {
+    const Geom& G = a.g;
     const int xcd = blockIdx.x & 7;
     int slot = blockIdx.x >> 3;
-    if (a.rotate) {
-        const int group = slot >> 2;
-        slot = 4 * group + ((slot + group + (group >> 2) + (group >> 4)) & 3);
+    if (!a.planned) {
+        if (a.rotate) {
+            const int group = slot >> 2;
+            slot = 4 * group + ((slot + group + (group >> 2) + (group >> 4)) & 3);
+        }
+        const int wi = xcd * a.chunk + slot;
+        if (wi >= a.total) return false;
+        const int tile_lin = quotient(wi, a.qblocks, a.rc_qblocks);
+        *jq = wi - tile_lin * a.qblocks;
+        *bh = quotient(tile_lin, G.M, G.rc_m);
+        const int u = tile_lin - *bh * G.M;
+        *ut = quotient(u, G.nW * G.nH, G.rc_layer);
+        const int rem = u - *ut * (G.nW * G.nH);
+        *uh = quotient(rem, G.nW, G.rc_row);
+        *uw = rem - *uh * G.nW;
+        return true;
     }
-    const int wi = xcd * a.chunk + slot;
-    if (wi >= a.total) return false;
-    const int tile_lin = quotient(wi, a.qblocks, a.rc_qblocks);
-    *jq = wi - tile_lin * a.qblocks;
-    *bh = quotient(tile_lin, a.g.M, a.g.rc_m);
-    *u = tile_lin - *bh * a.g.M;
-    return true;
+    // the plan is indexed by values known on the device only: read where it lies, in the kernel's argument segment
+    // (AttnArgs is the kernels' only argument), since the compiler may copy an indexed argument to scratch memory
+    typedef const __attribute__((address_space(4))) char* args_ptr;
+    const auto& p = *(const __attribute__((address_space(4))) ItemPlan*)((args_ptr)__builtin_amdgcn_kernarg_segment_ptr() +
+                                                                        offsetof(AttnArgs, plan));
+    static_assert(kSectionLanes == 32, "half a wave");
+    const int sec = __popc((uint32_t)__ballot((int)(p.section[1 + (threadIdx.x & 31)] & kSectionStart) <= slot));
+    return planned_item(p, G, a.qblocks, a.rc_qblocks, xcd, slot, sec, bh, ut, uh, uw, jq);
 }
 
 template <typename G_>

@@ -443,6 +443,25 @@ def test_keys_split_over_wave_groups_of_tiles_in_sub_tiles(prec, vscale):
         gu.assert_parity(st, f"head {h}")
 
 
+@pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
+@pytest.mark.parametrize("heads,grid,tile,window,shift", [
+    (40, (3, 13, 40), (1, 8, 16), (3, 1, 3), False),        # 720 items, cut along h and w
+    (40, (3, 13, 40), (1, 8, 16), (1, 3, 1), True),
+    (9, (5, 13, 20), (2, 8, 16), (3, 3, 3), False),         # 216 tiles of two query blocks
+    (60, (4, 10, 30), (2, 4, 4), (1, 5, 3), False)])        # 2880 one-wave workgroups
+def test_items_dealt_by_length(prec, heads, grid, tile, window, shift):
+    """Launches of more workgroups than CUs whose heads fit an XCD's L2: each item once."""
+    say("by length", prec, heads, grid, tile, window, shift)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=heads, n_outlier=3, config_id=26)
+    win = window + ((fps.EDGE_SHIFT,) if shift else ())
+    run = gu.GpuRun(w)
+    out, vis = run.attn(prec, window=win, visited=True)
+    assert np.array_equal(vis.cpu().numpy().astype(bool), fo.tile_mask(run.g, win))
+    for h in (0, heads - 1):
+        st = gu.compare_head(run, out, h, prec, win)
+        gu.assert_parity(st, f"by length head {h}")
+
+
 @pytest.mark.parametrize("vscale", [fps.VSCALE_TILE, fps.VSCALE_CHANNEL])
 @pytest.mark.parametrize("tile,qtile", [((2, 4, 4), None), ((3, 4, 4), None), ((2, 8, 4), None),
                                         ((2, 4, 8), (1, 4, 4)), ((2, 8, 8), (2, 4, 8)), ((1, 4, 12), (1, 4, 4))])

@@ -87,3 +87,75 @@ def test_items_of_rows_of_six_or_ten_are_dealt_in_order(program):
 def test_quotients_by_a_stored_reciprocal_are_exact(program):
     out = subprocess.run([program], input="", capture_output=True, text=True, check=True).stdout
     assert out.splitlines()[-1] == "bad quotients 0"
+
+
+PLAN_PROGRAM = r"""
+#include "fps_attn_plan.h"
+#include <cstdio>
+#include <cstring>
+#include <vector>
+using namespace fps;
+int main() {
+    int BH, T, H, W, Tt, Th, Tw, rt, rh, rw, shift, qblocks, waves;
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d", &BH, &T, &H, &W, &Tt, &Th, &Tw, &rt, &rh, &rw, &shift, &qblocks, &waves) == 13) {
+        Geom g;
+        std::memset(&g, 0, sizeof(g));
+        g.BH = BH; g.T = T; g.H = H; g.W = W; g.Tt = Tt; g.Th = Th; g.Tw = Tw;
+        g.nT = (T + Tt - 1) / Tt; g.nH = (H + Th - 1) / Th; g.nW = (W + Tw - 1) / Tw;
+        g.M = g.nT * g.nH * g.nW; g.TSP = 128;
+        ItemPlan p;
+        const int slots = plan_items(g, {rt, rh, rw}, shift, qblocks, waves, 128, p);
+        std::vector<int> seen((size_t)BH * g.M * qblocks, 0);
+        int bad = 0, rises = 0;
+        for (int xcd = 0; xcd < 8 && slots; ++xcd) {
+            double last = 1e30;
+            for (int slot = 0; slot < slots; ++slot) {
+                int sec = 0, bh, t, h, w, jq;
+                for (int l = 1; l <= kSectionLanes; ++l) sec += (int)(p.section[l] & kSectionStart) <= slot;
+                if (!planned_item(p, g, qblocks, reciprocal(qblocks), xcd, slot, sec, &bh, &t, &h, &w, &jq)) continue;
+                if (bh < 0 || bh >= BH || t < 0 || t >= g.nT || h < 0 || h >= g.nH || w < 0 || w >= g.nW || jq < 0 || jq >= qblocks) ++bad;
+                else ++seen[(size_t)(((bh * g.nT + t) * g.nH + h) * g.nW + w) * qblocks + jq];
+                auto span = [&](int n, int tile, int size, int r, int u) {   // tokens of the window along an axis
+                    if (shift) u = n > 2 * r + 1 ? (u < r ? r : u > n - 1 - r ? n - 1 - r : u) : n / 2;
+                    const int lo = u > r ? u - r : 0, hi = u + r < n - 1 ? u + r : n - 1;
+                    return (double)((hi + 1) * tile < size ? (hi + 1) * tile : size) - lo * tile;
+                };
+                const double len = span(g.nT, Tt, T, rt, t) * span(g.nH, Th, H, rh, h) * span(g.nW, Tw, W, rw, w);
+                if (len > 6 * last) ++rises;     // a level is a band of 1.25 or, the last, wider; three of them
+                last = len;
+            }
+        }
+        for (int s : seen) bad += slots ? s != 1 : 0;
+        std::printf("%d %d %d\n", slots, bad, rises);
+    }
+}
+"""
+
+
+def test_items_dealt_by_length_are_each_dealt_once(tmp_path):
+    """Every work item once, in range, over windows from one tile to all, cut and uncut grids, both edge rules; the
+    lengths fall but for the levels' width; launches with more keys than the L2s hold twice, and small ones, stay in raster order."""
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    src, exe = tmp_path / "plan.hip", tmp_path / "plan"
+    src.write_text(PLAN_PROGRAM)
+    res = subprocess.run([HIPCC, "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                          "-I" + os.path.join(ROOT, "include"),
+                          "-I" + os.path.join(ROOT, "paper_2506_04648_amd", "csrc"), str(src), "-o", str(exe)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    grids = [(1, 8, 16), (5, 23, 37), (10, 26, 36), (7, 9, 130), (17, 3, 5), (1, 1, 100)]
+    radii = [(0, 0, 0), (1, 1, 1), (3, 1, 2), (2, 0, 4), (40, 40, 99)]
+    cases = [(bh, *g, *t, *r, shift, qb, waves) for bh in (1, 3, 24) for g in grids for t in ((1, 8, 16), (2, 4, 4), (1, 1, 1))
+             for r in radii for shift in (0, 1) for qb, waves in ((1, 4), (2, 4), (1, 1))]
+    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True,
+                         text=True, check=True).stdout.split("\n")
+    planned = 0
+    for c, line in zip(cases, out):
+        slots, bad, rises = map(int, line.split())
+        tiles = -(-c[1] // c[4]) * -(-c[2] // c[5]) * -(-c[3] // c[6])
+        small, large = c[0] * tiles * c[11] <= (2048 if c[12] == 1 else 256), 2 * c[0] * tiles * 128 * 128 > 64 << 20
+        assert (slots == 0) == (small or large), c
+        assert bad == 0 and rises == 0, (c, line)
+        planned += slots > 0
+    assert planned > 100
