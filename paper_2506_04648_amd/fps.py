@@ -140,12 +140,13 @@ def make_step_cfg(step, num_steps, alpha1, alpha2, regimes) -> StepCfg:
 
 
 def _stream():
+    # the handle alone: building a Stream object around it takes 3 us, as long as the launch itself
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 # ---- host helpers ---------------------------------------------------------------------------
