@@ -24,47 +24,50 @@
 
 namespace fps {
 
-// ---- raster -> tiled (bf16, 16-byte chunks of 8 channels) -------------------------------------
-__global__ void tile_order_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, Geom g,
-                                  long long n_chunks) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_chunks) return;
-    const int c16 = (int)(i & 15);
-    const long long pos = i >> 4;                       // bh * (M*TSP) + u*TSP + r
-    const int r = (int)(pos % g.TSP);
-    const long long bu = pos / g.TSP;
-    const int u = (int)(bu % g.M);
-    const long long bh = bu / g.M;
-    const int uw = u % g.nW, uh = (u / g.nW) % g.nH, ut = u / (g.nW * g.nH);
-    const int s = r / g.QSP;
-    int rt = 0, rh = 0, rw = 0;
-    const bool slot_used = sub_slot_coords(g, sub_tile_origin(g, s), r - s * g.QSP, &rt, &rh, &rw);
-    const int t = ut * g.Tt + rt, h = uh * g.Th + rh, w = uw * g.Tw + rw;
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (slot_used && t < g.T && h < g.H && w < g.W) {
-        const long long src = (((bh * g.T + t) * g.H + h) * (long long)g.W + w) * 16 + c16;
-        val = in[src];
-    }
-    out[i] = val;
+// ---- raster <-> tiled: 16-byte chunks, CPR of them a token -----------------------------------------
+// Bound by HBM.  A wave moves 32 slots, which lie in one sub-tile: where that is costs scalar instructions once, a
+// slot's place in it two products by stored reciprocals.  With a chunk a thread and its place by 64-bit divisions, 12
+// heads x 21x30x52 tokens in (1,8,16) tiles took 52 us to tile order and 47 back, now 36 and 35; 24 heads in (2,8,16)
+// tiles with sub-tiles of 64 tokens 107 and 91 us, now 78 and 73 (6.1 and 5.5 TB/s).
+// NT: the input is read past the caches, for tensors that do not fit them (launch_reorder).
+template <bool NT>
+__device__ __forceinline__ uint4 load_once(const uint4* p) {
+    if (!NT) return *p;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
 }
-
-// ---- tiled -> raster (elem_bytes 2 or 4; 16-byte chunks) ---------------------------------------
-__global__ void tile_unorder_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, Geom g,
-                                    int chunks_per_row, long long n_chunks) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_chunks) return;
-    const int c = (int)(i % chunks_per_row);
-    long long tok = i / chunks_per_row;                 // ((bh*T + t)*H + h)*W + w
-    const int w = (int)(tok % g.W); tok /= g.W;
-    const int h = (int)(tok % g.H); tok /= g.H;
-    const int t = (int)(tok % g.T);
-    const long long bh = tok / g.T;
-    const int u = ((t / g.Tt) * g.nH + h / g.Th) * g.nW + w / g.Tw;
-    const int rt = t % g.Tt, rh = h % g.Th, rw = w % g.Tw;
-    const int s = ((rt / g.Qt) * g.nsH + rh / g.Qh) * g.nsW + rw / g.Qw;
-    const int r = s * g.QSP + ((rt % g.Qt) * g.Qh + rh % g.Qh) * g.Qw + rw % g.Qw;
-    const long long src = ((bh * g.M + u) * (long long)g.TSP + r) * chunks_per_row + c;
-    out[i] = in[src];
+template <int CPR, bool TO_TILES, bool NT>
+__global__ __launch_bounds__(256) void reorder_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, Geom g,
+                                                      int segments) {
+    constexpr int U = 8, SLOTS = 64 * U / CPR;          // loads in flight, and the slots they cover
+    const int seg = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (seg >= segments) return;
+    const int lane = threadIdx.x & 63, c = lane & (CPR - 1), per_block = g.BS >> 5;      // 4 or 1
+    const int blk = per_block == 1 ? seg : seg >> 2;
+    const BlockOrigin org = block_origin(g, blk);
+    const int slot0 = org.slot0 + 32 * (seg & (per_block - 1));                         // in the sub-tile
+    const long long tiled0 = org.tile_lin * g.TSP + org.slot_base + slot0;
+#pragma unroll
+    for (int first = 0; first < 32; first += SLOTS) {
+        uint4 v[U];
+        long long row[U];                               // in the raster tensor; -1: padding
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int r = first + 64 / CPR * i + lane / CPR, k = slot0 + r;
+            const int t = div_by_recip(k, g.inv_plane[0][0]), rem = k - t * (g.Qh * g.Qw);
+            const int h = div_by_recip(rem, g.inv_w[0]), w = rem - h * g.Qw;
+            const bool token = k < g.QS && t * org.box.plane < org.box.n && h < org.box.eh && w < org.box.ew;
+            row[i] = token ? org.raster0 + ((long long)t * g.H + h) * g.W + w : -1;
+            v[i] = make_uint4(0, 0, 0, 0);
+            if (token) v[i] = load_once<NT>(in + (TO_TILES ? row[i] : tiled0 + r) * CPR + c);
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int r = first + 64 / CPR * i + lane / CPR;
+            if (TO_TILES)         out[(tiled0 + r) * CPR + c] = v[i];
+            else if (row[i] >= 0) out[row[i] * CPR + c] = v[i];
+        }
+    }
 }
 
 // ---- BF16 operand packing -----------------------------------------------------------------------
@@ -189,17 +192,28 @@ __global__ void copy_kernel(const uint4* __restrict__ in, uint4* __restrict__ ou
 
 static inline int grid_for(long long n, int block) { return (int)((n + block - 1) / block); }
 
+// Input and output together beyond the Infinity Cache's 256 MB: the input, not read again soon, leaves the cache to the
+// output.  478 MB 92 -> 78 us, 403 MB back 80 -> 73, in fp32 806 MB 162 -> 163; of 232 MB, which the cache holds, 36.0 -> 38.6
+// and 35 -> 38.5.
+template <int CPR, bool TO_TILES>
+static void launch_reorder(const Geom& g, const void* in, void* out, hipStream_t st) {
+    const int segments = g.BH * g.M * (g.TSP / 32), grid = grid_for(segments, 4);
+    const long long bytes = ((long long)g.BH * g.T * g.H * g.W + 32LL * segments) * CPR * 16;
+    const uint4* xi = (const uint4*)in;
+    uint4* xo = (uint4*)out;
+    if (bytes > (256LL << 20)) reorder_kernel<CPR, TO_TILES, true><<<grid, 256, 0, st>>>(xi, xo, g, segments);
+    else                       reorder_kernel<CPR, TO_TILES, false><<<grid, 256, 0, st>>>(xi, xo, g, segments);
+}
+
 int launch_tile_order(const Geom& g, const void* in, void* out, hipStream_t st) {
-    const long long n = (long long)g.BH * g.M * g.TSP * 16;
-    tile_order_kernel<<<grid_for(n, 256), 256, 0, st>>>((const uint4*)in, (uint4*)out, g, n);
+    launch_reorder<16, true>(g, in, out, st);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FPS_OK : hip_fail(e, "tile_order launch");
 }
 
 int launch_tile_unorder(const Geom& g, const void* in, int elem_bytes, void* out, hipStream_t st) {
-    const int cpr = kHeadDim * elem_bytes / 16;
-    const long long n = (long long)g.BH * g.T * g.H * g.W * cpr;
-    tile_unorder_kernel<<<grid_for(n, 256), 256, 0, st>>>((const uint4*)in, (uint4*)out, g, cpr, n);
+    if (elem_bytes == 2) launch_reorder<16, false>(g, in, out, st);
+    else                 launch_reorder<32, false>(g, in, out, st);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? FPS_OK : hip_fail(e, "tile_unorder launch");
 }

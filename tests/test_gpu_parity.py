@@ -45,6 +45,26 @@ def test_tile_order_roundtrip_bit_exact(grid, tile):
         assert np.array_equal(back32[0].cpu().numpy(), a)
 
 
+@pytest.mark.parametrize("tile,qtile", [((1, 8, 16), None), ((2, 8, 16), (1, 8, 8)), ((3, 4, 4), None)])
+def test_tile_order_of_more_than_the_caches_hold(tile, qtile):
+    """Input and output beyond 256 MB are read another way: round trip of every head, bit for bit."""
+    import torch
+    say("tile_order of a large tensor", tile, qtile)
+    grid, heads = (5, 23, 37), 150                          # 163 MB, tiled at least 177 MB
+    one = gu.GpuRun(dataclasses.replace(synth.TINY, grid=grid, tile=tile, heads=1), qtile=qtile)
+    shape = fps.make_shape(heads, grid, tile, qtile=qtile)
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    x = torch.randn((1, heads) + grid + (128,), generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    slots = torch.from_numpy(np.asarray(one.slots)[fo.token_positions(one.g)]).to("cuda:0")
+    t = fps.tile_order(shape, x)
+    assert x.numel() * 2 + t.numel() * 2 > 256 << 20
+    want = torch.zeros_like(t)
+    want[:, :, slots] = x.flatten(2, 4)
+    assert torch.equal(t, want)
+    assert torch.equal(fps.tile_unorder(shape, t), x)
+    assert torch.equal(fps.tile_unorder(shape, t.float()), x.float())
+
+
 def _check_quantize(run, heads_slots, label):
     g = run.g
     for role, (xq, sc) in enumerate(run.quantize()):
