@@ -97,16 +97,23 @@ static __global__ void amax_to_pow2_kernel(float* p, int n) {        // amax -> 
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = __uint_as_float((uint32_t)(127 + pow2_exponent_for_fp16(p[i])) << 23);
 }
+// a load that, if NT, leaves nothing in the caches
+template <bool NT>
+__device__ __forceinline__ uint4 load_chunk(const uint4* p) {
+    if (!NT) return *p;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
+}
 // N of the 16-byte chunks of a block that THREADS threads hold, chunk c = 8 channels (c & 15) of slot c >> 4: v[i] of
 // thread tid is chunk tid + THREADS (first + i), zero for padding.  All N loads are in flight at once.
-template <bool RASTER, int THREADS, int N>
+template <bool RASTER, int THREADS, bool NT = false, int N>
 __device__ __forceinline__ void load_chunks(const uint4* x, const Geom& g, const BlockOrigin& o, int tid, int first,
                                             uint4 (&v)[N]) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const uint4* row = token_row<RASTER>(x, g, o, (tid >> 4) + THREADS / 16 * (first + i));
         v[i] = make_uint4(0, 0, 0, 0);
-        if (row) v[i] = row[tid & 15];
+        if (row) v[i] = load_chunk<NT>(row + (tid & 15));
     }
 }
 

@@ -30,12 +30,6 @@ namespace fps {
 // heads x 21x30x52 tokens in (1,8,16) tiles took 52 us to tile order and 47 back, now 36 and 35; 24 heads in (2,8,16)
 // tiles with sub-tiles of 64 tokens 107 and 91 us, now 78 and 73 (6.1 and 5.5 TB/s).
 // NT: the input is read past the caches, for tensors that do not fit them (launch_reorder).
-template <bool NT>
-__device__ __forceinline__ uint4 load_once(const uint4* p) {
-    if (!NT) return *p;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
-}
 template <int CPR, bool TO_TILES, bool NT>
 __global__ __launch_bounds__(256) void reorder_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, Geom g,
                                                       int segments) {
@@ -59,7 +53,7 @@ __global__ __launch_bounds__(256) void reorder_kernel(const uint4* __restrict__ 
             const bool token = k < g.QS && t * org.box.plane < org.box.n && h < org.box.eh && w < org.box.ew;
             row[i] = token ? org.raster0 + ((long long)t * g.H + h) * g.W + w : -1;
             v[i] = make_uint4(0, 0, 0, 0);
-            if (token) v[i] = load_once<NT>(in + (TO_TILES ? row[i] : tiled0 + r) * CPR + c);
+            if (token) v[i] = load_chunk<NT>(in + (TO_TILES ? row[i] : tiled0 + r) * CPR + c);
         }
 #pragma unroll
         for (int i = 0; i < U; ++i) {

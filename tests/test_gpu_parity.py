@@ -626,6 +626,26 @@ def _groups_with_tokens(g):
     return np.flatnonzero(fo.quantize_tiles(np.repeat(fo.valid_tokens(g)[:, None], 128, axis=1).astype(np.float64), g)[1] != 1.0)
 
 
+@pytest.mark.parametrize("heads,tile", [(5, (2, 4, 4)), (12, (2, 4, 4)), (45, (2, 4, 4)), (45, (2, 8, 8))])
+def test_per_channel_maxima_of_many_blocks(heads, tile):
+    """1, 2 and 8 blocks a workgroup, the last of a head with fewer: every channel's scale, wherever its maximum is."""
+    import torch
+    say("per-channel maxima", heads, tile)
+    grid = (9, 27, 42)                                      # 385 blocks a head, of 32 slots, or of 128: 120
+    shape = fps.make_shape(heads, grid, tile)
+    gen = torch.Generator(device="cuda:0").manual_seed(heads)
+    x = torch.randn((1, heads) + grid + (128,), generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    flat = x.view(heads, -1, 128)
+    for c in range(128):                                    # a maximum of its own, in the first, last or another token
+        at = [0, flat.shape[1] - 1, (c * 7919) % flat.shape[1]][c % 3]
+        flat[:, at, c] = 8.0 + c * (-1) ** c
+    want = (flat.float().abs().amax(dim=1).cpu() / torch.tensor(448.0)).numpy()
+    for raster in (True, False):
+        src = x if raster else fps.tile_order(shape, x)
+        _, sc = fps.quantize_tiles(shape, src, fps.ROLE_V, vscale=fps.VSCALE_CHANNEL, raster=raster)
+        assert np.array_equal(sc[0].cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 @pytest.mark.parametrize("grid,tile,window", [((4, 16, 16), (2, 4, 4), (1, 3, 3)),
                                               ((2, 13, 40), (1, 8, 16), (3, 3, 3)),
                                               ((3, 13, 20), (2, 8, 16), (3, 3, 3))])
