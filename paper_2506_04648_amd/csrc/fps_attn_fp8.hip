@@ -18,13 +18,13 @@
 // tiles in three).  Powers of two commute with fp32 rounding: same results.
 // VCH: V carries one scale per channel (the paper's variant) instead of one per tile; the PV MFMA
 // then accumulates straight into O and the scales are applied once in the epilogue.
-// P: key blocks (small scale groups) that one step of the pipeline takes, each with scales of its own: as many of SB
-// sub-blocks as fill four, so that the barriers, the row reference and the bookkeeping of a step, 30 of the 150
-// to 180 vector instructions of a block of 48 or 64 keys, serve two or four blocks.  K and V of a step are double-buffered
-// where a workgroup has four waves; with less LDS a wave than that, K(i+2) and V(i) each stream into the one buffer
-// while the other product runs, two barriers a step.  Attention on 21x30x52 tokens, one block a step against P: 64-token
-// sub-tiles of (2,8,16) tiles, window 3x3x3, x 24 heads 1859 -> 1770 us; x 12 heads tile (3,4,4), window 3x5x7 799 -> 773, tile
-// (2,4,4) 522 -> 511 and (2,8,4), window 3x3x5, 339 -> 334.
+// P: key blocks (small scale groups) that one step of the pipeline takes, each with scales and a row reference of its own:
+// as many of SB sub-blocks as fill four, so that the barriers and the bookkeeping of a step serve two or four blocks.  K and
+// V of a step are double-buffered where a workgroup has four waves; with less LDS a wave than that, K(i+2) and V(i) each
+// stream into the one buffer while the other product runs, two barriers a step.  Attention on 21x30x52 tokens, one block a
+// step against P, us: 24 heads, 64-token sub-tiles of (2,8,16) tiles, window 3x3x3, 1278 -> 1220; 12 heads, 16-token
+// sub-tiles of (2,4,8) tiles, that window, 872 -> 745; tile (3,4,4), window 3x5x7, 783 -> 763, tile (2,4,4) 508 -> 495 and
+// (2,8,4), window 3x3x5, 326 -> 324.
 #include "fps_attn_device.h"
 
 namespace fps {
@@ -175,8 +175,7 @@ void attn_fp8_kernel(AttnArgs a) {
     v8i qop[2];                                            // Q^T, contraction steps 0 and 1
     float m_run = -INFINITY;
     float l_run = 0.f;                                     // running sum of 448 * P (this lane's keys)
-    float alpha = 1.f;                                     // VCH: rescale owed to O before the delayed PV
-    float m_base = 0.f, w_cur = 1.f;                       // fixed reference and weight: see above
+    float m_base = 0.f;                                    // fixed reference: see above
     float w_owed = 0.f;                                    // weight of the fma owed to O's last channel block
     v16f acc[4];
     {
@@ -194,7 +193,9 @@ void attn_fp8_kernel(AttnArgs a) {
         constexpr int NT = P * NB;                         // and of a step: block kb / NB, its sub-block kb % NB
         constexpr int J = (NB + 1) / 2;                    // contraction steps of a block's PV product: two sub-blocks each,
         constexpr bool TAIL = NB % 2 != 0;                 // the last one of an odd number by itself
-        constexpr int R = 4 * P;                           // PV products of 32 channels: channel block r / P, key block r % P
+        constexpr int R = 4 * P;                           // PV products of 32 channels
+        auto db_of = [](int r) { return VCH ? r % 4 : r / P; };        // channel block of product r,
+        auto kb_of = [](int r) { return VCH ? r / 4 : r % P; };        // and key block of the step
         const uint32_t classes = G.nh_classes[NH - 1] & box.classes;
         if (!classes) return;
         List list(G, box, NH, classes, kg);
@@ -218,7 +219,7 @@ void attn_fp8_kernel(AttnArgs a) {
             return make_v8i(b4[at + lane], b4[at + 64 + lane]);
         };
         auto load_v = [&](const uint8_t* buf, int step) FPS_INLINE {
-            const int r = step / J, j = step % J, db = r / P, g = r % P;
+            const int r = step / J, j = step % J, db = db_of(r), g = kb_of(r);
             const uint4* b4 = reinterpret_cast<const uint4*>(buf) + g * (BLOCK_BYTES / 16);
             const uint4 lo = b4[((2 * j + 0) * 4 + db) * 64 + lane];
             if (TAIL && j == J - 1) return make_v8i(lo, lo);           // only the lower half is used
@@ -230,8 +231,8 @@ void attn_fp8_kernel(AttnArgs a) {
                                                                    0, 0, 0, 0, 0, 0);
         };
         auto pv_mfma = [&](const v8i& vop, int step) FPS_INLINE {
-            const int r = step / J, j = step % J, db = r / P;
-            const v8i& pj = pb[r % P * J + j];
+            const int r = step / J, j = step % J, db = db_of(r);
+            const v8i& pj = pb[kb_of(r) * J + j];
             v16f x = VCH ? acc[db] : j == 0 ? zero16() : tq[r & 1];
             if (TAIL && j == J - 1) {
                 // a single sub-block: 32x32x16 instructions, 16 keys each.  They take 32.5 clocks against 64.9 of a
@@ -248,12 +249,13 @@ void attn_fp8_kernel(AttnArgs a) {
             }
             if (VCH) acc[db] = x; else tq[r & 1] = x;
         };
-        // half `half` of O^T(r / P) += w * raw product r, w = s^V 2^(m - m_base), pinned where it is written
+        // half `half` of O^T += w * raw product r, w = s^V 2^(m - m_base), pinned where it is written
         auto pv_accumulate_half = [&](int r, int half, float w) FPS_INLINE {
             if (VCH) return;
+            const int db = db_of(r);
 #pragma unroll
-            for (int i = 8 * half; i < 8 * half + 8; ++i) acc[r / P][i] = __builtin_fmaf(tq[r & 1][i], w, acc[r / P][i]);
-            asm volatile("" : "+v"(acc[r / P]));
+            for (int i = 8 * half; i < 8 * half + 8; ++i) acc[db][i] = __builtin_fmaf(tq[r & 1][i], w, acc[db][i]);
+            asm volatile("" : "+v"(acc[db]));
         };
         auto pv_accumulate = [&](int r, float w) FPS_INLINE { pv_accumulate_half(r, 0, w); pv_accumulate_half(r, 1, w); };
         // row maximum of half `e` of score block kb
@@ -268,7 +270,9 @@ void attn_fp8_kernel(AttnArgs a) {
         auto max_of_half = [&](float (&mx)[P], int t) FPS_INLINE {
             if (has_half(t)) mx[t / (2 * NB)] = max_half(t % (2 * NB) == 0 ? -INFINITY : mx[t / (2 * NB)], t >> 1, t & 1);
         };
-        float cm = 0.f;
+        // of the step's blocks: log2(448) less the reference; the reference's weight, relative to m_base, or (VCH) the
+        // rescale that it owes to what is added up so far
+        float cm[P], rel[P];
         // the weights of half `e` of score block kb and their FP8 codes
         auto weights_half = [&](int kb, int e, float sc, float c, float& rs) FPS_INLINE {
             v8i& pj = pb[kb / NB * J + kb % NB / 2];
@@ -293,21 +297,20 @@ void attn_fp8_kernel(AttnArgs a) {
             for (int g = 0; g < P; ++g)
                 if (nn[g] < 16 * NH) mask_cut_half(s[g * NB + NB - 1], (NH - 1) & 1, nn[g] - 16 * (NH - 1), h);
         };
-        // the row reference of the step whose row maxima mx (per block, not scaled) were taken
-        auto new_reference = [&](const float (&mx)[P], const float (&sc)[P]) FPS_INLINE {
-            float top = P == 1 ? max_over_row_pair(mx[0]) * sc[0] : mx[0] * sc[0];
+        // the row references of the step's blocks, whose row maxima mx (not scaled) were taken: each block has its own, since
+        // one shared by the step would take bits of the weights, and V's scales may make up for small weights
+        auto new_references = [&](const float (&mx)[P], const float (&sc)[P]) FPS_INLINE {
+            const bool first = m_run == -INFINITY;         // the item's first step
+            float m[P];
 #pragma unroll
-            for (int g = 1; g < P; ++g) top = __builtin_fmaxf(top, mx[g] * sc[g]);
-            if (P > 1) top = max_over_row_pair(top);
-            const float m_new = __builtin_fmaxf(m_run, __builtin_ceilf(top));
-            if (VCH) {
-                alpha = fast_exp2(m_run - m_new);
-            } else {
-                m_base = m_run == -INFINITY ? m_new : m_base;          // the item's first step
-                w_cur = fast_exp2(m_new - m_base);
+            for (int g = 0; g < P; ++g) {
+                const float m_old = g == 0 ? m_run : m[g - 1];
+                m[g] = __builtin_fmaxf(m_old, __builtin_ceilf(max_over_row_pair(mx[g]) * sc[g]));
+                if (!VCH && g == 0) m_base = first ? m[0] : m_base;
+                rel[g] = fast_exp2(VCH ? m_old - m[g] : m[g] - m_base);
+                cm[g] = kLog2Of448 - m[g];                 // 448 * 2^(S' - m) = 2^(S' + (log2(448) - m))
             }
-            m_run = m_new;
-            cm = kLog2Of448 - m_new;       // 448 * 2^(S' - m) = 2^(S' + (log2(448) - m))
+            m_run = m[P - 1];
             if (!VCH && __any(m_run - m_base > kMaxDrift)) {
                 const float down = fast_exp2(m_base - m_run);
 #pragma unroll
@@ -315,7 +318,8 @@ void attn_fp8_kernel(AttnArgs a) {
                 l_run *= down;
                 w_owed *= down;            // the last product's fma is still owed
                 m_base = m_run;
-                w_cur = 1.0f;
+#pragma unroll
+                for (int g = 0; g < P; ++g) rel[g] = fast_exp2(m[g] - m_run);
             }
         };
         auto load_scales = [&](const Step& st, float (&sc)[P], float (&sv)[P]) FPS_INLINE {
@@ -325,15 +329,15 @@ void attn_fp8_kernel(AttnArgs a) {
                 sv[g] = VCH ? 1.f : load_uniform(sv_head, st.b[g].group);
             }
         };
-        // the step's share of the row sums, and the rescale that O owes (VCH)
-        auto add_row_sums = [&](float rs) FPS_INLINE {
-            if (VCH) l_run = l_run * alpha + rs;
-            else     l_run = __builtin_fmaf(rs, w_cur, l_run);
+        // block g's share of the row sums, and the rescale that O owes it (VCH)
+        auto add_row_sum = [&](int g, float rs) FPS_INLINE {
+            if (VCH) l_run = l_run * rel[g] + rs;
+            else     l_run = __builtin_fmaf(rs, rel[g], l_run);
         };
-        auto rescale = [&]() FPS_INLINE {
-            if (VCH && __any(alpha != 1.0f)) {
+        auto rescale = [&](int g) FPS_INLINE {
+            if (VCH && __any(rel[g] != 1.0f)) {
 #pragma unroll
-                for (int db = 0; db < 4; ++db) acc[db] *= alpha;
+                for (int db = 0; db < 4; ++db) acc[db] *= rel[g];
             }
         };
 
@@ -360,7 +364,7 @@ void attn_fp8_kernel(AttnArgs a) {
 #pragma unroll
         for (int t = 0; t < 2 * NT; ++t) max_of_half(mx, t);
         w_owed = 0.f;
-        new_reference(mx, sc);
+        new_references(mx, sc);
         if (!VCH) tq[(R - 1) & 1] = zero16();
         if (!TWO) {
             landed();
@@ -391,7 +395,9 @@ void attn_fp8_kernel(AttnArgs a) {
             // step t: the exponentials of half a score block (block t/2, registers 8(t%2)..+7); the
             // MFMAs that refill a block follow one block behind, so steps 0, 1 have none (they take
             // the fma still owed to the last product of PV(i-1)) and the last two nothing else
-            float rs = 0.f;
+            float rs[P];
+#pragma unroll
+            for (int g = 0; g < P; ++g) rs[g] = 0.f;
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 2 * NT + 2; ++t) {
@@ -400,7 +406,10 @@ void attn_fp8_kernel(AttnArgs a) {
                     qk_mfma(op[(t - 2) % 3], t - 2);
                 }
                 if (t < 2) pv_accumulate_half(R - 1, t, w_owed);       // PV(i-1)'s last product
-                if (t < 2 * NT && has_half(t)) weights_half(t >> 1, t & 1, sc[t / (2 * NB)], cm, rs);
+                if (t < 2 * NT && has_half(t)) {
+                    const int g = t / (2 * NB);
+                    weights_half(t >> 1, t & 1, sc[g], cm[g], rs[g]);
+                }
                 constexpr int per = (P * CPT + 2 * NT + 1) / (2 * NT + 2);
 #pragma unroll
                 for (int c = t * per; c < (t + 1) * per && c < P * CPT; ++c) {
@@ -409,11 +418,11 @@ void attn_fp8_kernel(AttnArgs a) {
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            add_row_sums(rs);
             float wg[P];                                         // weights of the step's products
 #pragma unroll
             for (int g = 0; g < P; ++g) {
-                wg[g] = svv[g] * w_cur;
+                add_row_sum(g, rs[g]);
+                wg[g] = svv[g] * rel[g];
                 sc[g] = sc_next[g];
                 svv[g] = sv_next[g];
             }
@@ -425,7 +434,7 @@ void attn_fp8_kernel(AttnArgs a) {
             op[0] = load_v(vcur, 0);
             op[1] = load_v(vcur, 1);
             mask_blocks(n_cut);
-            rescale();
+            rescale(0);
 
             // ---- row maximum of S(i+1)  |  PV(i) ---------------------------------------------
             // step k: the MFMA of product k/J, contraction step k%J, 16-key halves of the row
@@ -440,6 +449,7 @@ void attn_fp8_kernel(AttnArgs a) {
                 } else if (k >= 2) {
                     pv_accumulate(k - 2, wg[(k - 2) % P]);
                 }
+                if (VCH && k > 0 && k % (4 * J) == 0) rescale(k / (4 * J));
                 pv_mfma(op[k % 3], k);
 #pragma unroll
                 for (int t = k * HPS; t < (k + 1) * HPS && t < 2 * NT; ++t) max_of_half(mx, t);
@@ -452,7 +462,7 @@ void attn_fp8_kernel(AttnArgs a) {
             }
             if (J == 1) pv_accumulate_half(R - 2, 0, wg[(R - 2) % P]);
             pv_accumulate_half(R - 2, 1, wg[(R - 2) % P]);
-            new_reference(mx, sc);
+            new_references(mx, sc);
             landed();                    // this thread's share of the staged blocks
             if (!TWO) __syncthreads();   // every wave is past PV(i); K(i+2) is visible
             par ^= 1;
@@ -465,12 +475,16 @@ void attn_fp8_kernel(AttnArgs a) {
         float rs = 0.f;
 #pragma unroll
         for (int t = 0; t < 2 * NT; ++t) {
+            const int g = t / (2 * NB);
             // a block past the end has no weights
-            const float c = t / (2 * NB) > 0 && odd && count <= P * (steps - 1) + t / (2 * NB) ? -INFINITY : cm;
-            if (has_half(t)) weights_half(t >> 1, t & 1, sc[t / (2 * NB)], c, rs);
+            const float c = g > 0 && odd && count <= P * (steps - 1) + g ? -INFINITY : cm[g];
+            if (has_half(t)) weights_half(t >> 1, t & 1, sc[g], c, rs);
+            if (t % (2 * NB) == 2 * NB - 1) {
+                add_row_sum(g, rs);
+                rs = 0.f;
+            }
         }
-        add_row_sums(rs);
-        rescale();
+        rescale(0);
         if (!TWO) {
             landed();
             __syncthreads();
@@ -478,10 +492,13 @@ void attn_fp8_kernel(AttnArgs a) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
 #pragma unroll
-            for (int j = 0; j < J; ++j) pv_mfma(load_v(lds_block(v_buf(0)), r * J + j), r * J + j);
-            if (r > 0) pv_accumulate(r - 1, svv[(r - 1) % P] * w_cur);
+            for (int j = 0; j < J; ++j) {
+                if (j == 0 && r > 0 && r % 4 == 0) rescale(r / 4);
+                pv_mfma(load_v(lds_block(v_buf(0)), r * J + j), r * J + j);
+            }
+            if (r > 0) pv_accumulate(r - 1, svv[kb_of(r - 1)] * rel[kb_of(r - 1)]);
         }
-        pv_accumulate(R - 1, svv[P - 1] * w_cur);
+        pv_accumulate(R - 1, svv[P - 1] * rel[P - 1]);
         if (!TWO) __syncthreads();                         // both buffers are free
         par ^= 1;
     };

@@ -1,5 +1,6 @@
 """GPU parity: every step of the HIP path, called through the C ABI, against the CPU oracle."""
 import dataclasses
+import math
 import sys
 
 import numpy as np
@@ -496,6 +497,46 @@ def test_small_groups_two_or_four_a_step(vscale, tile, qtile, tiles, window):
     for h in range(2):
         st = gu.compare_head(run, out, h, fps.PREC_FP8, w.window, vscale=vscale)
         gu.assert_parity(st, "groups a step")
+
+
+@pytest.mark.parametrize("vscale", [fps.VSCALE_TILE, fps.VSCALE_CHANNEL])
+@pytest.mark.parametrize("tile,qtile", [((2, 4, 4), None), ((3, 4, 4), None), ((2, 8, 16), (1, 8, 8)),
+                                        ((2, 8, 8), (2, 4, 8)), ((2, 4, 8), (1, 4, 4)), ((1, 4, 12), (1, 4, 4))])
+@pytest.mark.parametrize("rise", [1.25, 2.0])
+def test_blocks_taken_together_keep_their_weights_bits(vscale, tile, qtile, rise):
+    """Of the first four scale groups each has scores 2^20 (or 2^32) times the last one's weights, and channels of V to itself:
+    a group's weights are rounded against the largest score met so far, not against one of a group still to come, or
+    its channels would be lost.  Every key of a group has one score, so 448 P is one number between 224 and 448, whose
+    code is off by at most 2^-4 of it; V's codes are exact, its sums of one sign within the matrix instruction's 2^-11."""
+    import torch
+    say("weights' bits", vscale, tile, qtile, rise)
+    q = qtile or tile
+    per_tile = tile[0] * tile[1] * tile[2] // (q[0] * q[1] * q[2])
+    n = -(-36 // per_tile)                                  # walks of at least 36 blocks
+    grid, heads = (tile[0], tile[1], tile[2] * n), 24       # too many items for a split of the keys
+    shape = fps.make_shape(heads, grid, tile, qtile=qtile)
+    at = [torch.arange(size) // s for size, s in zip(grid, q)]
+    nh, nw = grid[1] // q[1], grid[2] // q[2]
+    rank = (at[0][:, None, None] * nh + at[1][None, :, None]) * nw + at[2][None, None, :]     # order of the groups
+    level = rank.clamp(max=3)
+    shade = torch.tensor([1.0, 1.5, 1.75])[torch.arange(rank.numel()).view(rank.shape) % 3]
+    key = (rise * level).double()
+    val = torch.zeros(grid + (128,))
+    for r in range(4):
+        val[..., r::4] = torch.where(level == r, shade, torch.zeros(()))[..., None]
+    score = 128 * key.view(-1) / math.sqrt(128)
+    want = torch.softmax(score, 0) @ val.view(-1, 128).double()
+
+    def on_device(x):
+        return x.to("cuda:0", torch.bfloat16).expand((1, heads) + grid + (128,)).contiguous()
+    packed = [fps.quantize_tiles(shape, on_device(x), role, vscale=vscale, raster=True)
+              for role, x in enumerate((torch.ones(grid + (128,)), key[..., None], val))]
+    (qq, sq), (kq, sk), (vq, sv) = packed
+    out = fps.attn_fwd(shape, (1, 1, 2 * n - 1), fps.PREC_FP8, qq, kq, vq, sq, sk, sv, vscale=vscale,
+                       out_dtype=torch.float32, raster_out=True)
+    off = (out.double().cpu() / want - 1).abs().amax()
+    say("  largest relative error", float(off))
+    assert off <= 2.0 ** -4 + 2.0 ** -10
 
 
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
