@@ -544,6 +544,16 @@ inline bool split_keys(const AttnArgs& a, int ks) {
     return a.total <= resident && blocks >= 2 * ks && blocks >= 6;
 }
 
+// FP8, small scale groups: several key blocks go through a step together where the walk is long enough to pay for the part of
+// the last step that may be empty and, in workgroups of fewer than four waves, for the one buffer of K and V that leaves
+// room for.  There two blocks against one, 1.00 = as fast, 12x30x52 tokens in groups of 32 to 64, 3, 12 and 30 heads, both
+// scale modes of V:
+//   blocks of a window       7            9            15           21           25 to 28     35 to 45     60 and more
+//   time                     0.99-1.08    0.99-1.07    0.98-1.04    0.95-1.02    0.94-1.03    0.95-1.00    0.93-1.02
+// and of one block, on 21x30x52 tokens x 12 heads, 1.07 to 1.13.  Four waves have two buffers of either: of two blocks, groups
+// of 64 tokens, 66.6 -> 67.6 us (216 tiles 8.1 -> 9.2), of four 81.9 -> 78.9, and of four groups of 16 tokens 121 -> 110.
+inline bool blocks_together(const AttnArgs& a) { return window_blocks(a) >= (query_waves(a.g) == 4 ? 4 : 26); }
+
 // Kernel launchers of the two precisions; grid: workgroups
 void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st);
 void launch_attn_bf16(const AttnArgs& a, int grid, hipStream_t st);

@@ -541,7 +541,7 @@ static void launch(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
 
 void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
     const Geom& g = a.g;
-    const bool four = query_waves(g) == 4;
+    const bool four = query_waves(g) == 4, together = blocks_together(a);
     switch (g.BS == 128 ? 4 : g.KBS) {
         case 4:
             if (g.KB > 1) {
@@ -565,21 +565,28 @@ void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
         case 2:
             if (g.NS == 1) {
                 if (split_keys(a, 4)) launch<2, 2, false, 4>(a, vch, grid, st);
-                else                  launch<2, 2, false, 1, 2>(a, vch, grid, st);
+                else if (together)    launch<2, 2, false, 1, 2>(a, vch, grid, st);
+                else                  launch<2, 2, false>(a, vch, grid, st);
             } else if (four) {
-                launch<2, 4, true, 1, 2>(a, vch, grid, st);
-            } else {
+                if (together) launch<2, 4, true, 1, 2>(a, vch, grid, st);
+                else          launch<2, 4, true>(a, vch, grid, st);
+            } else if (together) {
                 launch<2, 2, true, 1, 2>(a, vch, grid, st);
+            } else {
+                launch<2, 2, true>(a, vch, grid, st);
             }
             break;
         default:
             if (g.NS == 1) {
                 if (split_keys(a, 4)) launch<1, 1, false, 4>(a, vch, grid, st);
-                else                  launch<1, 1, false, 1, 2>(a, vch, grid, st);
+                else if (together)    launch<1, 1, false, 1, 2>(a, vch, grid, st);
+                else                  launch<1, 1, false>(a, vch, grid, st);
             } else if (four) {
                 launch<1, 4, true, 1, 4>(a, vch, grid, st);
-            } else {
+            } else if (together) {
                 launch<1, 1, true, 1, 2>(a, vch, grid, st);
+            } else {
+                launch<1, 1, true>(a, vch, grid, st);
             }
             break;
     }

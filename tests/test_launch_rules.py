@@ -14,7 +14,19 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstring>
 using namespace fps;
-int main() {
+int main(int argc, char**) {
+    // with an argument: windows of 1 or 3 x span x 1 tiles, each of 1 to 4 scale groups of 32 or 64 tokens
+    for (int span = 1; span <= 9 && argc > 1; span += 2)
+        for (int i = 0; i < 8; ++i) {
+            const int ns = 1 + i / 2;
+            AttnArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.g.BS = 32; a.g.KBS = 1 + i % 2; a.g.KBG = 1; a.g.NS = ns; a.g.TSP = 32 * a.g.KBS * ns;
+            a.g.nT = 3; a.g.nH = 100; a.g.nW = 1;
+            a.rt = span > 1; a.rh = (span - 1) / 2;
+            std::printf("%d %d %d\n", query_waves(a.g), window_blocks(a), (int)blocks_together(a));
+        }
+    if (argc > 1) return 0;
     // a tile of `tokens` in one scale group, `items` work items, a window of `blocks` tiles
     int tokens, items, blocks, ks;
     while (std::scanf("%d %d %d %d", &tokens, &items, &blocks, &ks) == 4) {
@@ -82,6 +94,16 @@ def test_keys_are_split_where_all_workgroups_are_resident_at_once(program):
 def test_items_of_rows_of_six_or_ten_are_dealt_in_order(program):
     out = subprocess.run([program], input="", capture_output=True, text=True, check=True).stdout.splitlines()
     assert [i + 1 for i, c in enumerate(out[-2]) if c == "1"] == [2, 4, 8, 12, 16, 20]
+
+
+def test_blocks_are_taken_together_on_long_walks(program):
+    """Shorter walks are slower so: up to 25 blocks in workgroups of fewer than four waves, up to 3 in others."""
+    out = subprocess.run([program, "together"], capture_output=True, text=True, check=True).stdout
+    rows = [tuple(map(int, line.split())) for line in out.splitlines()]
+    assert {(1, b) for b in (1, 2, 3, 9, 15, 18, 21, 27, 30)} <= {r[:2] for r in rows}
+    assert {(4, b) for b in (2, 4, 18, 36)} <= {r[:2] for r in rows}
+    for waves, blocks, together in rows:
+        assert together == (blocks > (3 if waves == 4 else 25)), (waves, blocks)
 
 
 def test_quotients_by_a_stored_reciprocal_are_exact(program):
