@@ -559,6 +559,41 @@ def test_lists_of_key_blocks_longer_than_a_wave(prec, heads, tile, qtile, blocks
     gu.assert_parity(st, "block lists")
 
 
+@pytest.mark.parametrize("tile,qtile", [((1, 1, 1), None), ((1, 1, 2), (1, 1, 1))])
+def test_heads_of_a_million_blocks(tile, qtile):
+    """Heads whose block numbers are beyond what a division by a float reciprocal gives exactly.  BF16: the weights are
+    rounded to 2^-12 of themselves, the rest is fp32."""
+    import torch
+    say("a million blocks", tile, qtile)
+    grid, tw = (1, 1024, 1024), tile[2]
+    shape = fps.make_shape(1, grid, tile, qtile=qtile)
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    x = [torch.randn((1, 1) + grid + (128,), generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(3)]
+    packed = [fps.pack_tiles_bf16(shape, t, role, raster=True) for role, t in enumerate(x)]
+    out = fps.attn_fwd(shape, (1, 3, 3), fps.PREC_BF16, packed[0][0], packed[1][0], packed[2][0], sv=packed[2][1],
+                       out_dtype=torch.float32, raster_out=True)[0, 0, 0]
+    del packed
+    q, k, v = (t[0, 0, 0].float() for t in x)
+    offsets = [(dh, dw) for dh in (-1, 0, 1) for dw in range(1 - 2 * tw, 2 * tw)]
+    row, col = torch.arange(1024, device="cuda:0")[:, None], torch.arange(1024, device="cuda:0")[None, :]
+
+    def beside(t, o):
+        return torch.roll(t, (-o[0], -o[1]), (0, 1))
+    scores = []
+    for o in offsets:
+        r, c = row + o[0], col + o[1]
+        kept = (r >= 0) & (r < 1024) & (c >= 0) & (c < 1024) & ((c // tw - col // tw).abs() <= 1)
+        scores.append(((q * beside(k, o)).sum(-1) / math.sqrt(128)).masked_fill(~kept, float("-inf")))
+    p = torch.softmax(torch.stack(scores), 0)
+    want, size = torch.zeros_like(out), torch.zeros_like(out)
+    for i, o in enumerate(offsets):
+        want += p[i][..., None] * beside(v, o)
+        size += p[i][..., None] * beside(v, o).abs()
+    excess = ((out - want).abs() - 2.0 ** -11 * size).amax()
+    say("  largest error beyond the weights' rounding", float(excess))
+    assert excess <= 0
+
+
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
 @pytest.mark.parametrize("tile,rest", [((1, 1, 128), r) for r in (1, 31, 32, 33, 64, 65, 96, 97, 127)] +
                          [((1, 2, 128), r) for r in (1, 48, 63, 64, 65, 127)])
