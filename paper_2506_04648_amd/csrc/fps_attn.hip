@@ -113,7 +113,7 @@ int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, c
     a.rotate = deal_in_turns(g.nW * a.qblocks);
     a.chunk = ((a.total + 7) / 8 + 3) / 4 * 4;
     const int slots = plan_items(g, {a.rt, a.rh, a.rw}, a.edge_shift, a.qblocks, query_waves(g), prec == FPS_PREC_FP8 ? 128 : 256,
-                                 a.plan);
+                                 window_blocks(a), a.plan);
     a.planned = slots > 0;
     const int grid = 8 * (a.planned ? slots : a.chunk);
     if (prec == FPS_PREC_FP8) launch_attn_fp8(a, vscale == FPS_VSCALE_CHANNEL, grid, st);

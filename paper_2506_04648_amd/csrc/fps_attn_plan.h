@@ -85,29 +85,34 @@ inline int plan_axis(int n, int tile, int size, int r, bool shift, AxisLevel* le
     return levels;
 }
 
-// Plans a launch of g.BH * g.M * qblocks work items of `waves` waves; returns the slots of an XCD, or 0: raster order.
+// Plans a launch of g.BH * g.M * qblocks work items of `waves` waves, the longest walk `blocks` key blocks; returns the
+// slots of an XCD, a multiple of four, or 0: raster order.
 //
-// Dealt by falling length where there are more workgroups than CUs and an XCD's share of K and V is at most 8 MB (L2: 4).
 // In raster order the launch waits for engines whose turn it is while others are free, and ends with whatever comes last.
-// Attention, raster order against this, us:
-//                                           K and V, an XCD's share
-//   24 x 10x26x36 tokens, window 7x3x5                       7.2 MB   434 -> 404
-//   7 x 12x40x48, tile (4,8,8), window 5x5x7                 4.9      498 -> 453
-//   11 x 7x32x48, window 3x7x3                               3.6      118 -> 92.9
-//   40 x 10x12x10, tile (2,8,16)                             3.5      66.5 -> 54.2
-//   10 x 10x13x22, tile (6,8,8), BF16                        3.0      56.0 -> 47.6
-//   11 x 6x21x20, window 5x1x1                               0.8      22.5 -> 20.1
-// of 22 random calls of up to 8 MB the median gains 3 %.  More K and V lose by the order's wider reach -- several heads, or four
-// layers of tiles along T and their windows at a time instead of two -- about what it gives or more:
-//   18 x 6x56x64, tile (2,8,16), window 4x5x1               11.8      273 -> 277
-//   12 x 21x30x52                                           12.9      316 -> 331    BF16 492 -> 565
-//   40 x 21x45x80, window 7x5x5                            103      11660 -> 12780
-// (By length within each layer only, those gain a per cent at best, 3733 -> 3701 with window 5x3x3, and lose as often, tile
-// (6,8,8) 292 -> 308.)  One-wave workgroups that are all resident at once, eight a CU, do better spread as they come: 672
-// items of up to 35 blocks 36.8 -> 39.5.
+// By falling length it loses some of what neighbours share in the L2, and a little for looking up the plan.  So dealt
+// where there are more workgroups than CUs, the longest walk is of 12 blocks or more and 1.1 times the mean, and an XCD's
+// share of K and V is at most 8 MB of packed slots (L2: 4).  Attention, time against raster order, 510 random calls of up
+// to 8 MB and 257 to 5000 items of twelve tilings, both precisions:
+//   longest / mean >= 1.1, blocks     1-3     4-7     8-11    12-15   16-31   32 and more
+//     mean                            0.95    0.95    0.97    0.93    0.90    0.87
+//     slower by 2 %, of calls         5/14    6/27    6/27    5/38    3/91    5/144
+//   blocks >= 12, longest / mean      <1.05   <1.1    <1.2    <1.3    <1.5    more
+//     mean                            1.00    0.98    0.91    0.90    0.88    0.87
+//     slower by 2 %, of calls         3/110   5/37    5/57    1/65    3/79    4/72
+// The slowest call outside the rule takes 1.27 of raster order's time, the slowest inside 1.10.  Beyond 8 MB, same rule
+// otherwise, 97 random calls: 7 to 9 MB 0.96, to 12 MB 0.93, to 16 MB 0.96, to 25 MB 0.98; but us
+//   12 x 21x30x52, window 3x3x3, tile (1,8,16)       15.8 MB   310 -> 320    BF16 (31.5 MB) 495 -> 540
+//   12 x 21x30x52, window 3x5x7, tile (3,4,4)        17.1      770 -> 821
+//   40 x 21x45x80, window 7x5x5, tile (1,8,16)       98.4      11.21 -> 11.23 ms
+// (By length within each layer only, those gain a per cent at best and lose as often.)  One-wave workgroups that are all
+// resident at once, eight a CU, are left in raster order; 58 random calls of up to 400 items took 0.94 of its time by
+// length, up to 1024 1.00 (one in eight 2 to 10 % more) and up to 2048 0.91.
+// Levels at 95 and 85 % instead of 90 and 72: 122 calls 0.91 instead of 0.89; at 80 and 50 %: 0.89, the slowest 1.23.
+constexpr int kPlannedBlocks = 12;
 constexpr long long kPlannedKeyBytes = 64 << 20;
-inline int plan_items(const Geom& g, const int (&radius)[3], bool shift, int qblocks, int waves, int row_bytes,
+inline int plan_items(const Geom& g, const int (&radius)[3], bool shift, int qblocks, int waves, int row_bytes, int blocks,
                       ItemPlan& p) {
+    if (blocks < kPlannedBlocks) return 0;
     if (2LL * g.BH * g.M * g.TSP * row_bytes > kPlannedKeyBytes) return 0;
     const long long items = (long long)g.BH * g.M * qblocks;
     if (items <= (waves == 1 ? 2048 : 256) || items > (1 << 28)) return 0;
@@ -118,10 +123,13 @@ inline int plan_items(const Geom& g, const int (&radius)[3], bool shift, int qbl
     for (int i = 0; i < 3; ++i) n[i] = plan_axis(n_tiles[i], tile[i], size[i], radius[i], shift, p.level[i], tokens[i]);
     double length[kMaxSections];
     int sections = 0;
+    double all = 0;
     for (int t = 0; t < n[0]; ++t)
         for (int h = 0; h < n[1]; ++h)
             for (int w = 0; w < n[2]; ++w) {
                 const double len = (double)tokens[0][t] * (double)tokens[1][h] * (double)tokens[2][w];
+                all += len * AxisLevel::upper(p.level[0][t].skip_count) * AxisLevel::upper(p.level[1][h].skip_count) *
+                       AxisLevel::upper(p.level[2][w].skip_count);
                 int i = sections++;                        // insertion sort, longest first
                 for (; i > 0 && length[i - 1] < len; --i) {
                     length[i] = length[i - 1];
@@ -130,6 +138,7 @@ inline int plan_items(const Geom& g, const int (&radius)[3], bool shift, int qbl
                 length[i] = len;
                 p.section[i] = (uint32_t)(t | h << 2 | w << 4) << 26;
             }
+    if (length[0] * g.M < 1.1 * all) return 0;             // about all of one length
     int slots = 0;
     for (int s = 0; s < sections; ++s) {
         const uint32_t word = p.section[s];
@@ -138,6 +147,7 @@ inline int plan_items(const Geom& g, const int (&radius)[3], bool shift, int qbl
                       AxisLevel::upper(p.level[1][(word >> 28) & 3].skip_count) *
                       AxisLevel::upper(p.level[2][word >> 30].skip_count) * qblocks + 7) / 8;
     }
+    slots = (slots + 3) / 4 * 4;                           // as the turning order wants them
     p.section[sections] = (uint32_t)slots;
     for (int s = sections + 1; s <= kSectionLanes; ++s) p.section[s] = kSectionStart;
     return slots;

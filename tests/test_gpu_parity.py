@@ -465,21 +465,37 @@ def test_keys_split_over_wave_groups_of_tiles_in_sub_tiles(prec, vscale):
 
 
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
-@pytest.mark.parametrize("heads,grid,tile,window,shift", [
-    (40, (3, 13, 40), (1, 8, 16), (3, 1, 3), False),        # 720 items, cut along h and w
-    (40, (3, 13, 40), (1, 8, 16), (1, 3, 1), True),
-    (9, (5, 13, 20), (2, 8, 16), (3, 3, 3), False),         # 216 tiles of two query blocks
-    (60, (4, 10, 30), (2, 4, 4), (1, 5, 3), False)])        # 2880 one-wave workgroups
-def test_items_dealt_by_length(prec, heads, grid, tile, window, shift):
-    """Launches of more workgroups than CUs whose heads fit an XCD's L2: each item once."""
-    say("by length", prec, heads, grid, tile, window, shift)
+@pytest.mark.parametrize("heads,grid,tile,qtile,window,shift", [
+    (40, (3, 13, 40), (1, 8, 16), None, (3, 3, 3), False),        # 720 items, cut along h and w
+    (10, (3, 26, 70), (1, 8, 16), None, (3, 3, 3), True),         # 600
+    (14, (5, 13, 20), (2, 8, 16), None, (3, 3, 3), False),        # 336: two query blocks a tile, idle ones in cut tiles
+    (12, (5, 13, 20), (2, 8, 16), (1, 8, 16), (3, 3, 3), False),  # 288, a scale group each
+    (8, (14, 13, 20), (6, 8, 8), None, (3, 3, 1), False),         # 432: three query blocks
+    (8, (9, 30, 20), (4, 16, 16), None, (3, 1, 3), False),        # 768: eight query blocks
+    (20, (5, 14, 33), (1, 7, 11), None, (5, 1, 5), False),        # three waves
+    (12, (7, 8, 37), (3, 4, 4), None, (3, 3, 3), False),          # two waves
+    (60, (4, 10, 30), (2, 4, 4), None, (3, 5, 3), False)])        # 2880 one-wave workgroups
+def test_items_dealt_by_length(prec, heads, grid, tile, qtile, window, shift):
+    """Launches of more workgroups than CUs whose heads fit an XCD's L2 and whose walks are of different length: each item
+    once."""
+    say("by length", prec, heads, grid, tile, qtile, window, shift)
     w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=heads, n_outlier=3, config_id=26)
     win = window + ((fps.EDGE_SHIFT,) if shift else ())
-    run = gu.GpuRun(w)
+    run = gu.GpuRun(w, qtile=qtile)
+    mask = fo.tile_mask(run.g, win)
+    # what the rule asks for, so that no case is dealt in raster order unnoticed: items, blocks of the longest walk (its
+    # keys in blocks of at most 128), longest walk over the mean
+    tsp = fps.tile_slots(run.shape)
+    sb = 4 if fps.block_slots(run.shape) == 128 else tsp // 32
+    items, blocks = heads * run.g.M * (tsp // 32 // sb), int(mask.sum(1).max()) * max(1, tsp // 128)
+    keys = mask @ fo.valid_tokens(run.g).reshape(run.g.M, -1).sum(1)
+    assert items > (2048 if sb == 1 else 256) and blocks >= 12 and keys.max() > 1.12 * keys.mean()
+    assert 2 * heads * run.g.M * tsp * (128 if prec == fps.PREC_FP8 else 256) <= 64 << 20
     out, vis = run.attn(prec, window=win, visited=True)
-    assert np.array_equal(vis.cpu().numpy().astype(bool), fo.tile_mask(run.g, win))
+    assert np.array_equal(vis.cpu().numpy().astype(bool), mask)
+    tiles = None if run.g.L_padded < 6000 else gu.sample_q_tiles(run.g, np.random.default_rng(3))
     for h in (0, heads - 1):
-        st = gu.compare_head(run, out, h, prec, win)
+        st = gu.compare_head(run, out, h, prec, win, q_tiles=tiles)
         gu.assert_parity(st, f"by length head {h}")
 
 

@@ -118,45 +118,83 @@ PLAN_PROGRAM = r"""
 #include <vector>
 using namespace fps;
 int main() {
-    int BH, T, H, W, Tt, Th, Tw, rt, rh, rw, shift, qblocks, waves;
-    while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d", &BH, &T, &H, &W, &Tt, &Th, &Tw, &rt, &rh, &rw, &shift, &qblocks, &waves) == 13) {
+    int BH, T, H, W, Tt, Th, Tw, rt, rh, rw, shift, qblocks, waves, blocks;
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d", &BH, &T, &H, &W, &Tt, &Th, &Tw, &rt, &rh, &rw, &shift, &qblocks, &waves, &blocks) == 14) {
         Geom g;
         std::memset(&g, 0, sizeof(g));
         g.BH = BH; g.T = T; g.H = H; g.W = W; g.Tt = Tt; g.Th = Th; g.Tw = Tw;
         g.nT = (T + Tt - 1) / Tt; g.nH = (H + Th - 1) / Th; g.nW = (W + Tw - 1) / Tw;
         g.M = g.nT * g.nH * g.nW; g.TSP = 128;
         ItemPlan p;
-        const int slots = plan_items(g, {rt, rh, rw}, shift, qblocks, waves, 128, p);
+        const int slots = plan_items(g, {rt, rh, rw}, shift, qblocks, waves, 128, blocks, p);
+        const int n[3] = {g.nT, g.nH, g.nW}, tile[3] = {Tt, Th, Tw}, size[3] = {T, H, W}, r[3] = {rt, rh, rw};
+        auto window = [&](int i, int u) {                    // tokens of the window along axis i
+            if (shift) u = n[i] > 2 * r[i] + 1 ? (u < r[i] ? r[i] : u > n[i] - 1 - r[i] ? n[i] - 1 - r[i] : u) : n[i] / 2;
+            const int lo = u > r[i] ? u - r[i] : 0, hi = u + r[i] < n[i] - 1 ? u + r[i] : n[i] - 1;
+            return ((hi + 1) * tile[i] < size[i] ? (hi + 1) * tile[i] : size[i]) - lo * tile[i];
+        };
+        // every position of a level in the same band of the most tokens, bands falling from level to level
+        int bad_levels = 0;
+        long long tokens[3][kAxisLevels], most[3];
+        int levels[3];
+        double spread = 1;                                   // longest item over the mean, of the levels' own lengths
+        for (int i = 0; i < 3; ++i) {
+            AxisLevel level[kAxisLevels];
+            levels[i] = plan_axis(n[i], tile[i], size[i], r[i], shift, level, tokens[i]);
+            most[i] = 0;
+            for (int u = 0; u < n[i]; ++u) most[i] = most[i] > window(i, u) ? most[i] : window(i, u);
+            auto band = [&](int u) { const long long x = 100LL * window(i, u); return x >= 90 * most[i] ? 0 : x >= 72 * most[i] ? 1 : 2; };
+            std::vector<int> seen(n[i], 0);
+            int last = -1;
+            double sum = 0;
+            long long longest = 0;
+            for (int l = 0; l < levels[i]; ++l) {
+                const int count = AxisLevel::upper(level[l].skip_count), first = AxisLevel::lower(level[l].first_len1),
+                          len1 = AxisLevel::upper(level[l].first_len1), skip = AxisLevel::lower(level[l].skip_count);
+                const int of_level = band(first);
+                bad_levels += of_level <= last;
+                last = of_level;
+                for (int k = 0; k < count; ++k) {
+                    const int u = first + k + (k >= len1 ? skip : 0);
+                    if (u < 0 || u >= n[i]) { ++bad_levels; continue; }
+                    ++seen[u];
+                    bad_levels += band(u) != of_level;
+                }
+                sum += (double)tokens[i][l] * count;
+                longest = longest > tokens[i][l] ? longest : tokens[i][l];
+            }
+            for (int c : seen) bad_levels += c != 1;
+            spread *= longest * n[i] / sum;
+        }
         std::vector<int> seen((size_t)BH * g.M * qblocks, 0);
         int bad = 0, rises = 0;
-        for (int xcd = 0; xcd < 8 && slots; ++xcd) {
-            double last = 1e30;
+        double last = 1e30;
+        for (int s = 0; slots && s < kMaxSections && (int)(p.section[s] & kSectionStart) < slots; ++s) {
+            const uint32_t w = p.section[s];
+            const double len = (double)tokens[0][(w >> 26) & 3] * tokens[1][(w >> 28) & 3] * tokens[2][w >> 30];
+            rises += len > last;
+            last = len;
+        }
+        bad += slots % 4;
+        for (int xcd = 0; xcd < 8 && slots; ++xcd)
             for (int slot = 0; slot < slots; ++slot) {
                 int sec = 0, bh, t, h, w, jq;
                 for (int l = 1; l <= kSectionLanes; ++l) sec += (int)(p.section[l] & kSectionStart) <= slot;
                 if (!planned_item(p, g, qblocks, reciprocal(qblocks), xcd, slot, sec, &bh, &t, &h, &w, &jq)) continue;
                 if (bh < 0 || bh >= BH || t < 0 || t >= g.nT || h < 0 || h >= g.nH || w < 0 || w >= g.nW || jq < 0 || jq >= qblocks) ++bad;
                 else ++seen[(size_t)(((bh * g.nT + t) * g.nH + h) * g.nW + w) * qblocks + jq];
-                auto span = [&](int n, int tile, int size, int r, int u) {   // tokens of the window along an axis
-                    if (shift) u = n > 2 * r + 1 ? (u < r ? r : u > n - 1 - r ? n - 1 - r : u) : n / 2;
-                    const int lo = u > r ? u - r : 0, hi = u + r < n - 1 ? u + r : n - 1;
-                    return (double)((hi + 1) * tile < size ? (hi + 1) * tile : size) - lo * tile;
-                };
-                const double len = span(g.nT, Tt, T, rt, t) * span(g.nH, Th, H, rh, h) * span(g.nW, Tw, W, rw, w);
-                if (len > 6 * last) ++rises;     // a level is a band of 1.25 or, the last, wider; three of them
-                last = len;
             }
-        }
         for (int s : seen) bad += slots ? s != 1 : 0;
-        std::printf("%d %d %d\n", slots, bad, rises);
+        std::printf("%d %d %d %d %.12f\n", slots, bad, rises, bad_levels, spread);
     }
 }
 """
 
 
 def test_items_dealt_by_length_are_each_dealt_once(tmp_path):
-    """Every work item once, in range, over windows from one tile to all, cut and uncut grids, both edge rules; the
-    lengths fall but for the levels' width; launches with more keys than the L2s hold twice, and small ones, stay in raster order."""
+    """Every work item once, in range, over windows from one tile to all, cut and uncut grids, both edge rules; sections in
+    falling order of their length, an axis' levels of positions within their bands.  Launches with more keys than the L2s
+    hold twice, small ones, those of short walks and those of about one length stay in raster order."""
     if not shutil.which(HIPCC):
         pytest.skip("no hipcc")
     src, exe = tmp_path / "plan.hip", tmp_path / "plan"
@@ -168,16 +206,21 @@ def test_items_dealt_by_length_are_each_dealt_once(tmp_path):
     assert res.returncode == 0, res.stderr[-2000:]
     grids = [(1, 8, 16), (5, 23, 37), (10, 26, 36), (7, 9, 130), (17, 3, 5), (1, 1, 100)]
     radii = [(0, 0, 0), (1, 1, 1), (3, 1, 2), (2, 0, 4), (40, 40, 99)]
-    cases = [(bh, *g, *t, *r, shift, qb, waves) for bh in (1, 3, 24) for g in grids for t in ((1, 8, 16), (2, 4, 4), (1, 1, 1))
-             for r in radii for shift in (0, 1) for qb, waves in ((1, 4), (2, 4), (1, 1))]
+    cases = [(bh, *g, *t, *r, shift, qb, waves, blocks) for bh in (1, 3, 24) for g in grids
+             for t in ((1, 8, 16), (2, 4, 4), (1, 1, 1)) for r in radii for shift in (0, 1)
+             for qb, waves, blocks in ((1, 4, 12), (2, 4, 40), (1, 1, 27), (1, 4, 11))]
     out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True,
                          text=True, check=True).stdout.split("\n")
-    planned = 0
+    planned = level = 0
     for c, line in zip(cases, out):
-        slots, bad, rises = map(int, line.split())
+        slots, bad, rises, bad_levels = map(int, line.split()[:4])
+        spread = float(line.split()[4])
         tiles = -(-c[1] // c[4]) * -(-c[2] // c[5]) * -(-c[3] // c[6])
         small, large = c[0] * tiles * c[11] <= (2048 if c[12] == 1 else 256), 2 * c[0] * tiles * 128 * 128 > 64 << 20
-        assert (slots == 0) == (small or large), c
-        assert bad == 0 and rises == 0, (c, line)
+        short = c[13] < 12
+        if abs(spread - 1.1) > 1e-9:
+            assert (slots == 0) == (small or large or short or spread < 1.1), (c, line)
+        assert bad == 0 and rises == 0 and bad_levels == 0, (c, line)
         planned += slots > 0
-    assert planned > 100
+        level += slots == 0 and not (small or large or short)
+    assert planned > 100 and level > 20
