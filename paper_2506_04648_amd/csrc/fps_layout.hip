@@ -25,24 +25,27 @@
 namespace fps {
 
 // ---- raster <-> tiled: 16-byte chunks, CPR of them a token -----------------------------------------
-// Bound by HBM.  A wave moves 32 slots, which lie in one sub-tile: where that is costs scalar instructions once, a
+// Bound by HBM.  A wave's slots, 32 or a part of 32, lie in one sub-tile: where that is costs scalar instructions once, a
 // slot's place in it two products by stored reciprocals.  With a chunk a thread and its place by 64-bit divisions, 12
 // heads x 21x30x52 tokens in (1,8,16) tiles took 52 us to tile order and 47 back, now 36 and 35; 24 heads in (2,8,16)
 // tiles with sub-tiles of 64 tokens 107 and 91 us, now 78 and 73 (6.1 and 5.5 TB/s).
 // NT: the input is read past the caches, for tensors that do not fit them (launch_reorder).
-template <int CPR, bool TO_TILES, bool NT>
+// U: loads in flight of a wave.  8: all 32 slots, in fp32 16 and then 16; 4: two or four waves share the 32.
+template <int CPR, int U> constexpr int kWavesOfSegment = U == 8 ? 1 : 32 * CPR / (64 * U);
+template <int CPR, bool TO_TILES, bool NT, int U>
 __global__ __launch_bounds__(256) void reorder_kernel(const uint4* __restrict__ in, uint4* __restrict__ out, Geom g,
-                                                      int segments) {
-    constexpr int U = 8, SLOTS = 64 * U / CPR;          // loads in flight, and the slots they cover
-    const int seg = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (seg >= segments) return;
+                                                      int waves) {
+    constexpr int SLOTS = 64 * U / CPR;                 // the slots that the loads cover
+    constexpr int PARTS = kWavesOfSegment<CPR, U>;
+    const int wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), seg = wave / PARTS;
+    if (wave >= waves) return;
     const int lane = threadIdx.x & 63, c = lane & (CPR - 1), per_block = g.BS >> 5;      // 4 or 1
     const int blk = per_block == 1 ? seg : seg >> 2;
     const BlockOrigin org = block_origin(g, blk);
-    const int slot0 = org.slot0 + 32 * (seg & (per_block - 1));                         // in the sub-tile
+    const int slot0 = org.slot0 + 32 * (seg & (per_block - 1)) + SLOTS * (wave % PARTS);    // in the sub-tile
     const long long tiled0 = org.tile_lin * g.TSP + org.slot_base + slot0;
 #pragma unroll
-    for (int first = 0; first < 32; first += SLOTS) {
+    for (int first = 0; first < 32 / PARTS; first += SLOTS) {
         uint4 v[U];
         long long row[U];                               // in the raster tensor; -1: padding
 #pragma unroll
@@ -189,14 +192,22 @@ static inline int grid_for(long long n, int block) { return (int)((n + block - 1
 // Input and output together beyond the Infinity Cache's 256 MB: the input, not read again soon, leaves the cache to the
 // output.  478 MB 92 -> 78 us, 403 MB back 80 -> 73, in fp32 806 MB 162 -> 163; of 232 MB, which the cache holds, 36.0 -> 38.6
 // and 35 -> 38.5.
+template <int CPR, bool TO_TILES, bool NT, int U>
+static void launch_reorder_as(const Geom& g, int segments, const void* in, void* out, hipStream_t st) {
+    const int waves = segments * kWavesOfSegment<CPR, U>;
+    reorder_kernel<CPR, TO_TILES, NT, U><<<grid_for(waves, 4), 256, 0, st>>>((const uint4*)in, (uint4*)out, g, waves);
+}
+
+// Fewer than 4096 segments of 32 slots, 16 a CU: half as many loads a wave and more waves.  From tile order in fp32, 8 loads
+// a wave against 4: 384 segments 6.6 -> 4.4 us (a chunk a thread 4.5), 1536 8.4 -> 6.0 (6.8), 2688 13.5 -> 11.4 (17.7), of tile (4,16,16)
+// or (1,8,16); 5040 of tile (1,7,15) 17.2 -> 18.1 and in bf16 8.7 -> 10.0.
 template <int CPR, bool TO_TILES>
 static void launch_reorder(const Geom& g, const void* in, void* out, hipStream_t st) {
-    const int segments = g.BH * g.M * (g.TSP / 32), grid = grid_for(segments, 4);
+    const int segments = g.BH * g.M * (g.TSP / 32);
     const long long bytes = ((long long)g.BH * g.T * g.H * g.W + 32LL * segments) * CPR * 16;
-    const uint4* xi = (const uint4*)in;
-    uint4* xo = (uint4*)out;
-    if (bytes > (256LL << 20)) reorder_kernel<CPR, TO_TILES, true><<<grid, 256, 0, st>>>(xi, xo, g, segments);
-    else                       reorder_kernel<CPR, TO_TILES, false><<<grid, 256, 0, st>>>(xi, xo, g, segments);
+    if (segments < 4096)            launch_reorder_as<CPR, TO_TILES, false, 4>(g, segments, in, out, st);
+    else if (bytes > (256LL << 20)) launch_reorder_as<CPR, TO_TILES, true, 8>(g, segments, in, out, st);
+    else                            launch_reorder_as<CPR, TO_TILES, false, 8>(g, segments, in, out, st);
 }
 
 int launch_tile_order(const Geom& g, const void* in, void* out, hipStream_t st) {
