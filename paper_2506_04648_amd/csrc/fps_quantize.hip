@@ -206,12 +206,11 @@ __global__ __launch_bounds__(THREADS * NB) void quantize_tiles_kernel(const uint
 // block with the per-channel scales; finally turn the stored maxima into scales in place.
 // A workgroup of 256 threads takes `per` consecutive blocks of a head, thread = (token group tid/16, 8-channel
 // chunk tid%16): the maxima stay in registers from block to block, and what costs as much as reading a block -- bringing
-// those of 16 token groups together and 128 atomics in memory -- is done once.  Read past the caches: the tensor
-// is read again only when all of it has been, and beyond the Infinity Cache's 256 MB nothing of it would be left.  The
-// whole quantisation of V, a block a workgroup and cached against this: 40 heads of 720p 366 -> 344 us (cached 375); 12
-// heads x 21x30x52 tokens in 32-slot blocks, tile (3,4,4), 115 -> 69, 24 heads in 64-token sub-tiles 180 -> 113; of 128-slot
-// blocks, 100 MB, 57 -> 56.
-template <int BS, bool RASTER>
+// those of 16 token groups together and 128 atomics in memory -- is done once.  The whole quantisation of V, a
+// block a workgroup against up to eight, us: 10x30x52 tokens x 13 heads in 32-slot blocks, tile (3,4,4), 69.6 -> 45.3, x 25
+// heads 105 -> 73.9; in 128-slot blocks x 13 and 25 heads 34.9 -> 34.0 and 52.8 -> 51.6, 40 heads of 720p 366 -> 345.
+// NT: read past the caches (launch_quantize_channels).
+template <int BS, bool RASTER, bool NT>
 __global__ __launch_bounds__(256) void channel_amax_kernel(const uint4* __restrict__ x,
                                                            uint32_t* __restrict__ amax_bits, Geom g, int per,
                                                            int parts) {
@@ -223,7 +222,7 @@ __global__ __launch_bounds__(256) void channel_amax_kernel(const uint4* __restri
 #pragma unroll 1
     for (int b = first; b < last; ++b) {
         uint4 v[BS / 16];
-        load_chunks<RASTER, 256, true>(x, g, block_origin(g, bh * blocks + b), tid, 0, v);
+        load_chunks<RASTER, 256, NT>(x, g, block_origin(g, bh * blocks + b), tid, 0, v);
 #pragma unroll
         for (int i = 0; i < BS / 16; ++i) {
             const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
@@ -297,6 +296,19 @@ __global__ __launch_bounds__(256) void quantize_channels_kernel(const uint4* __r
     write_v_block<BS, 256>(stage, reinterpret_cast<uint4*>(xq + (long long)blk * (BS * 128)), tid);
 }
 
+template <int BS, bool RASTER>
+static void launch_channel_amax_from(const Geom& g, const uint4* x, bool past_caches, uint32_t* amax, int per, int parts,
+                                     int grid, hipStream_t st) {
+    if (past_caches) channel_amax_kernel<BS, RASTER, true><<<grid, 256, 0, st>>>(x, amax, g, per, parts);
+    else             channel_amax_kernel<BS, RASTER, false><<<grid, 256, 0, st>>>(x, amax, g, per, parts);
+}
+template <int BS>
+static void launch_channel_amax(const Geom& g, const uint4* x, int raster, bool past_caches, uint32_t* amax, int per, int parts,
+                                int grid, hipStream_t st) {
+    if (raster) launch_channel_amax_from<BS, true>(g, x, past_caches, amax, per, parts, grid, st);
+    else        launch_channel_amax_from<BS, false>(g, x, past_caches, amax, per, parts, grid, st);
+}
+
 static int launch_quantize_channels(const Geom& g, const void* x, int raster, void* xq, float* scales,
                                     hipStream_t st) {
     const int blocks = g.BH * g.M * g.KB, n = g.BH * 128;
@@ -307,13 +319,14 @@ static int launch_quantize_channels(const Geom& g, const void* x, int raster, vo
     const int head = g.M * g.KB, most = blocks / 2048, per = most < 1 ? 1 : most > 8 ? 8 : most;
     const int parts = (head + per - 1) / per, grid = g.BH * parts;
     uint32_t* const amax = (uint32_t*)scales;
-    if (g.BS == 128) {
-        if (raster) channel_amax_kernel<128, true><<<grid, 256, 0, st>>>(xi, amax, g, per, parts);
-        else        channel_amax_kernel<128, false><<<grid, 256, 0, st>>>(xi, amax, g, per, parts);
-    } else {
-        if (raster) channel_amax_kernel<32, true><<<grid, 256, 0, st>>>(xi, amax, g, per, parts);
-        else        channel_amax_kernel<32, false><<<grid, 256, 0, st>>>(xi, amax, g, per, parts);
-    }
+    // V and its codes together beyond the Infinity Cache's 256 MB: nothing of V would be left when it is read again, so it
+    // leaves the cache to what else is there.  The whole quantisation, cached against past the caches, us: V and codes of
+    // 40 MB 20.9 -> 21.6, 185 MB 73.9 -> 77.6, 252 MB 72.9 -> 74.6, 281 MB 105 -> 109; 331 and 370 MB 93.6 -> 93.8 and 137 -> 138;
+    // 417 MB 128 -> 121, 550 MB 183 -> 171, 40 heads of 720p, 1.2 GB, 374 -> 345.
+    const long long slots = (long long)blocks * g.BS, tokens = raster ? (long long)g.BH * g.T * g.H * g.W : slots;
+    const bool past_caches = 256 * tokens + 128 * slots > (320LL << 20);
+    if (g.BS == 128) launch_channel_amax<128>(g, xi, raster, past_caches, amax, per, parts, grid, st);
+    else             launch_channel_amax<32>(g, xi, raster, past_caches, amax, per, parts, grid, st);
     if (g.BS == 128) {
         if (raster) quantize_channels_kernel<128, true><<<blocks, 256, 0, st>>>(xi, xo, scales, g);
         else        quantize_channels_kernel<128, false><<<blocks, 256, 0, st>>>(xi, xo, scales, g);

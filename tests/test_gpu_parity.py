@@ -720,9 +720,11 @@ def _groups_with_tokens(g):
     return np.flatnonzero(fo.quantize_tiles(np.repeat(fo.valid_tokens(g)[:, None], 128, axis=1).astype(np.float64), g)[1] != 1.0)
 
 
-@pytest.mark.parametrize("heads,tile", [(5, (2, 4, 4)), (12, (2, 4, 4)), (45, (2, 4, 4)), (45, (2, 8, 8))])
+@pytest.mark.parametrize("heads,tile", [(5, (2, 4, 4)), (12, (2, 4, 4)), (45, (2, 4, 4)), (45, (2, 8, 8)), (90, (2, 4, 4)),
+                                        (90, (2, 8, 8))])
 def test_per_channel_maxima_of_many_blocks(heads, tile):
-    """1, 2 and 8 blocks a workgroup, the last of a head with fewer: every channel's scale, wherever its maximum is."""
+    """1, 2 and 8 blocks a workgroup, the last of a head with fewer, and (90 heads) read past the caches: every channel's scale,
+    wherever its maximum is."""
     import torch
     say("per-channel maxima", heads, tile)
     grid = (9, 27, 42)                                      # 385 blocks a head, of 32 slots, or of 128: 120
