@@ -142,7 +142,8 @@ def make_step_cfg(step, num_steps, alpha1, alpha2, regimes) -> StepCfg:
 def _stream():
     # the handle alone: building a Stream object around it takes 3 us, as long as the launch itself
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # not in torch's documented interface
+    return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):

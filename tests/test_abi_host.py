@@ -187,3 +187,16 @@ def test_reciprocal_division_identity_used_by_the_kernels():
         n = np.unique(np.clip(np.concatenate([k * d - 1, k * d, k * d + 1, k * d + d // 2]), 0, (1 << 17) - 1))
         q = ((n.astype(np.float32) + np.float32(0.5)) * inv).astype(np.int64)
         assert np.array_equal(q, n // d), d
+
+
+def test_current_stream_without_the_private_entry(monkeypatch):
+    """A torch that lacks the raw handle's entry gives the same stream by way of its Stream object."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x4560 + device, raising=False)
+    assert fps._stream() == 0x4563
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert fps._stream() == 0x1230
