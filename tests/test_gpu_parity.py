@@ -577,6 +577,22 @@ def test_lists_of_key_blocks_longer_than_a_wave(prec, heads, tile, qtile, blocks
     gu.assert_parity(st, "block lists")
 
 
+@pytest.mark.parametrize("tile,qtile", [((2, 4, 4), None), ((3, 4, 4), None), ((2, 4, 8), (1, 4, 4)), ((1, 4, 12), (1, 4, 4)),
+                                        ((3, 6, 8), (1, 6, 8)), ((2, 8, 8), (2, 4, 8))])
+@pytest.mark.parametrize("blocks,vscale", [(65, fps.VSCALE_TILE), (67, fps.VSCALE_CHANNEL), (130, fps.VSCALE_TILE)])
+def test_lists_of_small_groups_longer_than_a_wave(tile, qtile, blocks, vscale):
+    """Every kernel that takes two or four small groups a step, on a list of more than 64 whose last step is not full: one
+    row of groups, the last of them cut, in too many items for a split of the keys."""
+    say("lists of small groups", tile, qtile, blocks, vscale)
+    q = qtile or tile
+    w = dataclasses.replace(synth.TINY, grid=(q[0], q[1], q[2] * blocks + q[2] // 2), tile=tile, window=(1, 1, 299), heads=8,
+                            n_outlier=3, config_id=28)
+    run = gu.GpuRun(w, qtile=qtile)
+    out = run.attn(fps.PREC_FP8, vscale=vscale)
+    st = gu.compare_head(run, out, 7, fps.PREC_FP8, w.window, vscale=vscale, q_tiles=[0, run.g.M - 1])
+    gu.assert_parity(st, "lists of small groups")
+
+
 @pytest.mark.parametrize("tile,qtile", [((1, 1, 1), None), ((1, 1, 2), (1, 1, 1))])
 def test_heads_of_a_million_blocks(tile, qtile):
     """Heads whose block numbers are beyond what a division by a float reciprocal gives exactly.  BF16: the weights are
