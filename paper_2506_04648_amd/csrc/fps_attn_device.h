@@ -68,7 +68,8 @@ struct AttnArgs {
     int chunk;             // work items per XCD, a multiple of 4
     int rotate;            // deal each four consecutive work items in a turning order (see work_item)
     int total;             // BH * M * qblocks
-    int planned;           // the items are dealt by `plan`, not in raster order
+    int tail;              // the items of an XCD are dealt in raster order up to this slot, the rest by `plan` (plan_tail);
+                           // -1: all by `plan` (plan_items)
     ItemPlan plan;
 };
 
@@ -117,8 +118,18 @@ __device__ __forceinline__ bool work_item(const AttnArgs& a, int* bh, int* ut, i
         const int group = slot >> 2;
         slot = 4 * group + ((slot + group + (group >> 2) + (group >> 4)) & 3);
     }
-    if (!a.planned) {
-        const int wi = xcd * a.chunk + slot;
+    // the plan is indexed by values known on the device only: read where it lies, in the kernel's argument segment
+    // (AttnArgs is the kernels' only argument), since the compiler may copy an indexed argument to scratch memory
+    typedef const __attribute__((address_space(4))) char* args_ptr;
+    const auto& p = *(const __attribute__((address_space(4))) ItemPlan*)((args_ptr)__builtin_amdgcn_kernarg_segment_ptr() +
+                                                                        offsetof(AttnArgs, plan));
+    static_assert(kSectionLanes == 32, "half a wave");
+    auto section = [&]() FPS_INLINE {
+        return __popc((uint32_t)__ballot((int)(p.section[1 + (threadIdx.x & 31)] & kSectionStart) <= slot));
+    };
+    if (a.tail >= 0) {
+        int wi = xcd * a.chunk + slot;
+        if (slot >= a.tail) wi = tail_item(p, G, a.qblocks, a.rc_qblocks, xcd * a.chunk + a.tail, slot, section());
         if (wi >= a.total) return false;
         const int tile_lin = quotient(wi, a.qblocks, a.rc_qblocks);
         *jq = wi - tile_lin * a.qblocks;
@@ -130,14 +141,7 @@ __device__ __forceinline__ bool work_item(const AttnArgs& a, int* bh, int* ut, i
         *uw = rem - *uh * G.nW;
         return true;
     }
-    // the plan is indexed by values known on the device only: read where it lies, in the kernel's argument segment
-    // (AttnArgs is the kernels' only argument), since the compiler may copy an indexed argument to scratch memory
-    typedef const __attribute__((address_space(4))) char* args_ptr;
-    const auto& p = *(const __attribute__((address_space(4))) ItemPlan*)((args_ptr)__builtin_amdgcn_kernarg_segment_ptr() +
-                                                                        offsetof(AttnArgs, plan));
-    static_assert(kSectionLanes == 32, "half a wave");
-    const int sec = __popc((uint32_t)__ballot((int)(p.section[1 + (threadIdx.x & 31)] & kSectionStart) <= slot));
-    return planned_item(p, G, a.qblocks, a.rc_qblocks, xcd, slot, sec, bh, ut, uh, uw, jq);
+    return planned_item(p, G, a.qblocks, a.rc_qblocks, xcd, slot, section(), bh, ut, uh, uw, jq);
 }
 
 template <typename G_>

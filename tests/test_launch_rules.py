@@ -224,3 +224,84 @@ def test_items_dealt_by_length_are_each_dealt_once(tmp_path):
         planned += slots > 0
         level += slots == 0 and not (small or large or short)
     assert planned > 100 and level > 20
+
+
+TAIL_PROGRAM = r"""
+#include "fps_attn_plan.h"
+#include <cstdio>
+#include <cstring>
+#include <vector>
+using namespace fps;
+int main() {
+    int BH, T, H, W, rt, rh, rw, shift, qblocks, waves, row_bytes, blocks;
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d %d", &BH, &T, &H, &W, &rt, &rh, &rw, &shift, &qblocks, &waves, &row_bytes, &blocks) == 12) {
+        Geom g;
+        std::memset(&g, 0, sizeof(g));
+        g.BH = BH; g.T = g.nT = T; g.H = H; g.W = W; g.Tt = 1; g.Th = 8; g.Tw = 16;
+        g.nH = (H + 7) / 8; g.nW = (W + 15) / 16; g.M = g.nT * g.nH * g.nW; g.TSP = 128;
+        g.rc_layer = reciprocal(g.nH * g.nW);
+        const int total = BH * g.M * qblocks, chunk = ((total + 7) / 8 + 3) / 4 * 4, layer = g.nH * g.nW * qblocks;
+        ItemPlan p;
+        const int first = plan_tail(g, {rt, rh, rw}, shift, qblocks, waves, row_bytes, blocks, chunk, p);
+        std::vector<int> seen(8 * chunk, 0);
+        int bad = 0, rises = 0;
+        for (int xcd = 0; xcd < 8 && first >= 0; ++xcd) {
+            int last = 1 << 30;
+            for (int slot = 0; slot < chunk; ++slot) {
+                int sec = 0, wi = xcd * chunk + slot;
+                for (int l = 1; l <= kSectionLanes; ++l) sec += (int)(p.section[l] & kSectionStart) <= slot;
+                if (slot >= first) wi = tail_item(p, g, qblocks, reciprocal(qblocks), xcd * chunk + first, slot, sec);
+                if (wi < xcd * chunk || wi >= (xcd + 1) * chunk) { ++bad; continue; }
+                ++seen[wi];
+                if (slot < first) continue;
+                // lengths within a layer fall by levels: each at most 1 / 0.72 of the last one's shortest, or an axis' third level
+                const int uh = wi / qblocks / g.nW % g.nH, uw = wi / qblocks % g.nW;
+                auto window = [&](int u, int n, int tile, int size, int r) {
+                    if (shift) u = n > 2 * r + 1 ? (u < r ? r : u > n - 1 - r ? n - 1 - r : u) : n / 2;
+                    const int lo = u > r ? u - r : 0, hi = u + r < n - 1 ? u + r : n - 1;
+                    return ((hi + 1) * tile < size ? (hi + 1) * tile : size) - lo * tile;
+                };
+                const int len = window(uh, g.nH, 8, H, rh) * window(uw, g.nW, 16, W, rw);
+                if (slot == first) last = len;
+                rises += len > last * 1.25;                  // the first section holds the longest items
+            }
+        }
+        for (int s : seen) bad += first >= 0 && s != 1;
+        const int n = first < 0 ? 0 : chunk - first;
+        std::printf("%d %d %d %d %d %d\n", first, bad, rises, chunk, layer, n);
+    }
+}
+"""
+
+
+def test_the_tail_dealt_by_length_deals_each_item_once(tmp_path):
+    """The sorted end of an XCD's chunk is whole layers' worth of items, wherever in a layer it starts, each dealt once; one
+    round of workgroups or two (FP8); none where everything is resident at once, a layer is longer than that or walks are short."""
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    src, exe = tmp_path / "tail.hip", tmp_path / "tail"
+    src.write_text(TAIL_PROGRAM)
+    res = subprocess.run([HIPCC, "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                          "-I" + os.path.join(ROOT, "include"),
+                          "-I" + os.path.join(ROOT, "paper_2506_04648_amd", "csrc"), str(src), "-o", str(exe)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    cases = [(bh, *grid, *r, shift, qb, waves, row, blocks)
+             for bh in (1, 7, 12) for grid in ((21, 30, 52), (5, 90, 119), (3, 23, 37), (40, 8, 33), (2, 200, 300))
+             for r in ((1, 1, 1), (2, 0, 3), (0, 40, 1)) for shift in (0, 1) for qb in (1, 3)
+             for waves, row, blocks in ((4, 128, 27), (4, 256, 27), (2, 128, 105), (1, 128, 12), (3, 128, 11))]
+    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True,
+                         text=True, check=True).stdout.split("\n")
+    tails = 0
+    for c, line in zip(cases, out):
+        first, bad, rises, chunk, layer, n = map(int, line.split())
+        waves, row, blocks = c[9:]
+        assert bad == 0 and rises == 0, (c, line)
+        rounds = 32 * (8 // waves)
+        wanted = rounds * (1 if row > 128 else 2)
+        if blocks < 12 or chunk <= rounds or layer > min(chunk, wanted):
+            assert first == -1, (c, line)
+        if first >= 0:
+            assert n % layer == 0 and n <= chunk and (wanted <= n < wanted + layer or n > chunk - layer), (c, line)
+            tails += 1
+    assert tails > 40
