@@ -30,7 +30,8 @@ void attn_bf16_kernel(AttnArgs a) {
     constexpr int BLOCK_BYTES = SB * 8192;
     static_assert(CPT >= 1 && CPT <= 8 && CPT * W == SB * 8, "every wave copies the same share of a block");
     constexpr int GROUP_BYTES = 2 * BLOCK_BYTES;           // K, V
-    constexpr int LDS_BYTES = KS * GROUP_BYTES > SplitMerge<W, KS>::kBytes ? KS * GROUP_BYTES : SplitMerge<W, KS>::kBytes;
+    constexpr int END_BYTES = KS > 1 ? SplitMerge<W, KS>::kBytes : W * store_region_bytes(4);
+    constexpr int LDS_BYTES = KS * GROUP_BYTES > END_BYTES ? KS * GROUP_BYTES : END_BYTES;
     // the groups' blocks; afterwards their sums and the output transpose
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
     const Geom& G = a.g;
@@ -336,26 +337,34 @@ void attn_bf16_kernel(AttnArgs a) {
     make_up();
     if constexpr (KS > 1) {                                // every wave is done with the buffers
         // O of a group is relative to 2^e_ref, l to 2^m_run: moving both to the largest is exact
-        const SplitMerge<W, KS> merge{lds, row_block, lane};
+        typedef SplitMerge<W, KS> Merge;
+        const Merge merge{lds, row_block, kg, lane};
         // without a block: O and l are zero and their references the lowest
-        float ref = m_run == -INFINITY ? -INFINITY : e_ref;
-        if (kg > 0) merge.leave(kg, acc, ref, l_run, m_run);
+        merge.leave(acc, m_run == -INFINITY ? -INFINITY : e_ref, l_run, m_run);
         __syncthreads();
-        if (kg > 0) return;
-#pragma unroll 1
-        for (int g = 1; g < KS; ++g) {
-            const v4f o = merge.numbers(g);
-            const float top = __builtin_fmaxf(ref, o[0]), m_top = __builtin_fmaxf(m_run, o[2]);   // finite: group 0 has a block
-            merge.add(g, acc, fast_exp2(ref - top), fast_exp2(o[0] - top));
-            l_run = __builtin_fmaf(o[1], fast_exp2(o[2] - m_top), l_run * fast_exp2(m_run - m_top));
-            ref = top;
-            m_run = m_top;
+        v4f o[KS];
+        float top = -INFINITY, m_top = -INFINITY, l = 0.f, factor[KS];
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            o[g] = merge.numbers(g);
+            top = __builtin_fmaxf(top, o[g][0]);           // finite: group 0 has a block
+            m_top = __builtin_fmaxf(m_top, o[g][2]);
         }
-        e_ref = ref;
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            factor[g] = fast_exp2(o[g][0] - top);
+            l = __builtin_fmaf(o[g][1], fast_exp2(o[g][2] - m_top), l);
+        }
+        v16f own[Merge::kOwn];
+        merge.add(acc, factor, own);
+        l = sum_over_row_pair(l);
+        store_rows(a, rows, lane, own, l > 0.f ? fast_exp2(top - m_top) / l : 0.f, merge.store_region(), nullptr,
+                   32 * Merge::kOwn * kg);
+    } else {
+        const float l = sum_over_row_pair(l_run);
+        const float inv = l > 0.f ? fast_exp2(e_ref - m_run) / l : 0.f;
+        store_rows(a, rows, lane, acc, inv, lds + row_block * store_region_bytes(4));
     }
-    const float l = sum_over_row_pair(l_run);
-    const float inv = l > 0.f ? fast_exp2(e_ref - m_run) / l : 0.f;
-    store_rows(a, rows, lane, acc, inv, lds + row_block * kStoreRegionBytes);
 }
 
 template <int SB, int W, bool MB, int KS = 1>

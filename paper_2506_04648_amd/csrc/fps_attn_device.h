@@ -81,7 +81,6 @@ constexpr float kLog2eOverSqrtD = 0.12751743f;   // log2(e) / sqrt(128)
 constexpr float kLog2Of448 = 8.8073549f;          // log2(448)
 constexpr float kFp16PScaleLog2 = 14.0f;          // BF16 mode holds 2^14 * P in fp16
 constexpr float kMaxDrift = 64.0f;                // largest m - m_base before O and l are moved to a new reference
-constexpr int kStoreRegionBytes = 32 * (256 + 16);  // per-wave LDS region of the output transpose (16 rows of fp32: less)
 
 // Scales are read-only for the whole launch and indexed uniformly: reading them through the constant
 // address space lets the compiler use scalar loads, which do not queue behind the vector-memory
@@ -229,33 +228,35 @@ __device__ __forceinline__ bool any_real_row(const Geom& G, int cls, int jq, int
     return false;
 }
 
-// Epilogue: O = acc * inv (times the per-channel V scale if any), fp32 or bf16, tile or raster order.  A
-// lane holds 4 channels of one row per accumulator quarter, so direct stores would be 8- or 16-byte
-// pieces of many rows; instead each wave transposes its rows through a private LDS region -- all 32 rows at
+// Epilogue: O = acc * inv (times the per-channel V scale if any), fp32 or bf16, tile or raster order; the ND blocks of 32
+// channels from channel c0 on.  A lane holds 4 channels of one row per accumulator quarter, so direct stores would be 8- or
+// 16-byte pieces of many rows; instead each wave transposes its rows through a private LDS region -- all 32 rows at
 // once in bf16, 16 a pass in fp32 (rows n < 16 are held by lanes 0..15 and 32..47) -- and writes whole rows
-// (256 or 512 contiguous bytes).  The reads and stores of a pass are unrolled, so that one LDS round trip and one
-// address calculation do not wait for the other: 720p attention 3.84 -> 3.81 ms, dense BF16 12x37x70 x 16 heads
+// (of all channels 256 or 512 contiguous bytes).  The reads and stores of a pass are unrolled, so that one LDS round trip and
+// one address calculation do not wait for the other: 720p attention 3.84 -> 3.81 ms, dense BF16 12x37x70 x 16 heads
 // 8.27 -> 8.25 ms, one-wave workgroups of 32 tokens 12.4 -> 11.8 us.  The caller guarantees that no wave
 // still reads the LDS buffers.
-template <bool F32>
-__device__ __forceinline__ void store_rows_as(const AttnArgs& a, const QueryRows& q, int lane, const v16f (&acc)[4],
-                                              float inv, uint8_t* wave_lds, const float* ch_scale) {
-    constexpr int kRowBytes = F32 ? 512 : 256, kRows = F32 ? 16 : 32;   // rows a pass
+constexpr int store_region_bytes(int nd) { return 32 * (nd * 64 + 16); }   // a wave's; 16 rows of fp32: less
+template <bool F32, int ND>
+__device__ __forceinline__ void store_rows_as(const AttnArgs& a, const QueryRows& q, int lane, const v16f (&acc)[ND],
+                                              float inv, uint8_t* wave_lds, const float* ch_scale, int c0) {
+    constexpr int kElem = F32 ? 4 : 2, kRowBytes = ND * 32 * kElem, kRows = F32 ? 16 : 32;   // rows a pass
     constexpr int kPitch = kRowBytes + 16;                 // padding keeps the column writes off one bank
-    constexpr int kLanesShift = F32 ? 5 : 4, kRowsPerStore = 64 >> kLanesShift;
-    static_assert(kRows * kPitch <= kStoreRegionBytes, "the wave's region holds a pass");
-    const int h = lane >> 5, n = lane & 31, chunk = lane & ((1 << kLanesShift) - 1);
+    constexpr int kLanes = kRowBytes / 16, kRowsPerStore = 64 / kLanes;
+    static_assert(kRows * kPitch <= store_region_bytes(ND), "the wave's region holds a pass");
+    const int h = lane >> 5, n = lane & 31, chunk = lane % kLanes;
+    uint8_t* const out = reinterpret_cast<uint8_t*>(a.out) + c0 * kElem;
 #pragma unroll
     for (int pass = 0; pass < 32 / kRows; ++pass) {
         if (!F32 || (n >> 4) == pass) {
             uint8_t* const row = wave_lds + (n & (kRows - 1)) * kPitch;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+            for (int db = 0; db < ND; ++db)
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
                     const int col = 32 * db + 8 * q4 + 4 * h;
                     v4f o = v4f{acc[db][4 * q4], acc[db][4 * q4 + 1], acc[db][4 * q4 + 2], acc[db][4 * q4 + 3]} * inv;
-                    if (ch_scale) o *= *reinterpret_cast<const v4f*>(ch_scale + col);
+                    if (ch_scale) o *= *reinterpret_cast<const v4f*>(ch_scale + c0 + col);
                     if (F32) {
                         *reinterpret_cast<v4f*>(row + col * 4) = o;
                     } else {
@@ -272,22 +273,22 @@ __device__ __forceinline__ void store_rows_as(const AttnArgs& a, const QueryRows
         u32x4 val[kRows / kRowsPerStore];
 #pragma unroll
         for (int i = 0; i < kRows / kRowsPerStore; ++i)
-            val[i] = *reinterpret_cast<const u32x4*>(wave_lds + (i * kRowsPerStore + (lane >> kLanesShift)) * kPitch +
-                                                     chunk * 16);
+            val[i] = *reinterpret_cast<const u32x4*>(wave_lds + (i * kRowsPerStore + lane / kLanes) * kPitch + chunk * 16);
 #pragma unroll
         for (int i = 0; i < kRows / kRowsPerStore; ++i) {
-            const int row = pass * kRows + i * kRowsPerStore + (lane >> kLanesShift);
+            const int row = pass * kRows + i * kRowsPerStore + lane / kLanes;
             if (row < q.rows)
-                reinterpret_cast<u32x4*>(reinterpret_cast<uint8_t*>(a.out) + q.out_row(a, row) * kRowBytes)[chunk] = val[i];
+                reinterpret_cast<u32x4*>(out + q.out_row(a, row) * (128 * kElem))[chunk] = val[i];
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
 }
-__device__ __forceinline__ void store_rows(const AttnArgs& a, const QueryRows& q, int lane, const v16f (&acc)[4],
-                                           float inv, uint8_t* wave_lds, const float* ch_scale = nullptr) {
-    if (a.out_f32) store_rows_as<true>(a, q, lane, acc, inv, wave_lds, ch_scale);
-    else           store_rows_as<false>(a, q, lane, acc, inv, wave_lds, ch_scale);
+template <int ND>
+__device__ __forceinline__ void store_rows(const AttnArgs& a, const QueryRows& q, int lane, const v16f (&acc)[ND],
+                                           float inv, uint8_t* wave_lds, const float* ch_scale = nullptr, int c0 = 0) {
+    if (a.out_f32) store_rows_as<true>(a, q, lane, acc, inv, wave_lds, ch_scale, c0);
+    else           store_rows_as<false>(a, q, lane, acc, inv, wave_lds, ch_scale, c0);
 }
 
 __device__ __forceinline__ v8i make_v8i(const uint4& lo, const uint4& hi) {
@@ -481,40 +482,60 @@ struct BlockList {
     }
 };
 
-// Key split (KS > 1): where the wave groups 1 .. KS - 1 leave O and up to three numbers per lane for group 0.  In LDS,
-// behind the regions of the output transpose.
+// Key split (KS > 1): the wave groups add up their O and row sums.  Each group takes 4 / KS of the channel blocks of 32, leaves
+// what it has of the others in LDS with three numbers a lane, adds up its own after a barrier and stores it; the LDS holds the
+// regions of the output transpose first.  (Group 0 adding up and storing everything, one group after the other: attention on
+// 64 one-wave items of four groups, 4x16x16 tokens x 2 heads, 8.0 us, now 7.0, BF16 8.7, now 7.8; 225 items of two 36.6,
+// now 35.6.)
 template <int W, int KS>
 struct SplitMerge {
-    static constexpr int kWaveBytes = 64 * (64 + 4) * 4;
-    static constexpr int kBytes = W * kStoreRegionBytes + (KS - 1) * W * kWaveBytes;
+    static constexpr int kOwn = 4 / KS;                    // channel blocks of a group
+    static constexpr int kStoreBytes = store_region_bytes(kOwn);
+    static constexpr int kWaveBytes = 64 * 16 * ((4 - kOwn) * 4 + 1);
+    static constexpr int kBytes = KS * W * (kStoreBytes + kWaveBytes);
     uint8_t* lds;
-    int row_block, lane;                // the 32 query rows of the work item that the wave has
-    __device__ __forceinline__ uint4* region(int kg) const {
-        return reinterpret_cast<uint4*>(lds + W * kStoreRegionBytes + ((kg - 1) * W + row_block) * kWaveBytes);
+    int row_block, kg, lane;            // the 32 query rows of the work item that the wave has; its group
+    __device__ __forceinline__ uint8_t* store_region() const { return lds + (kg * W + row_block) * kStoreBytes; }
+    __device__ __forceinline__ v4f* region(int from) const {
+        return reinterpret_cast<v4f*>(lds + KS * W * kStoreBytes + (from * W + row_block) * kWaveBytes) + lane;
     }
-    __device__ __forceinline__ void leave(int kg, const v16f (&acc)[4], float x, float y, float z = 0.f) const {
-        uint4* r = region(kg);
+    // where group `from` leaves its share of group `to`
+    __device__ __forceinline__ v4f* share(int from, int to) const { return region(from) + (to - (to > from)) * kOwn * 4 * 64; }
+    __device__ __forceinline__ void leave(const v16f (&acc)[4], float x, float y, float z = 0.f) const {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const v4f v = v4f{acc[i >> 2][4 * (i & 3)], acc[i >> 2][4 * (i & 3) + 1], acc[i >> 2][4 * (i & 3) + 2],
-                              acc[i >> 2][4 * (i & 3) + 3]};
-            *reinterpret_cast<v4f*>(r + i * 64 + lane) = v;
+        for (int g = 0; g < KS; ++g) {
+            if (g == kg) continue;
+#pragma unroll
+            for (int i = 0; i < 4 * kOwn; ++i) {
+                const int db = g * kOwn + i / 4, r = 4 * (i & 3);
+                share(kg, g)[i * 64] = v4f{acc[db][r], acc[db][r + 1], acc[db][r + 2], acc[db][r + 3]};
+            }
         }
-        reinterpret_cast<v4f*>(r + 16 * 64)[lane] = v4f{x, y, z, 0.f};
+        region(kg)[(4 - kOwn) * 4 * 64] = v4f{x, y, z, 0.f};
     }
-    __device__ __forceinline__ v4f numbers(int kg) const {
-        return reinterpret_cast<const v4f*>(region(kg) + 16 * 64)[lane];
-    }
-    // acc = acc * mine + theirs * factor
-    __device__ __forceinline__ void add(int kg, v16f (&acc)[4], float mine, float factor) const {
-        const uint4* r = region(kg);
+    __device__ __forceinline__ v4f numbers(int g) const { return region(g)[(4 - kOwn) * 4 * 64]; }
+    // own = the sum over the groups of their accumulators, times factor[g]
+    __device__ __forceinline__ void add(const v16f (&acc)[4], const float (&factor)[KS], v16f (&own)[kOwn]) const {
+        float mine = factor[0];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const v4f v = *reinterpret_cast<const v4f*>(r + i * 64 + lane);
-            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // a few loads ahead, not all: no registers for them
+        for (int g = 0; g < KS; ++g) {
+            if (g != kg) continue;
+            mine = factor[g];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                acc[i >> 2][4 * (i & 3) + j] = __builtin_fmaf(v[j], factor, acc[i >> 2][4 * (i & 3) + j] * mine);
+            for (int j = 0; j < kOwn; ++j) own[j] = acc[g * kOwn + j];
+        }
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) own[j] *= mine;
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            if (g == kg) continue;
+#pragma unroll
+            for (int i = 0; i < 4 * kOwn; ++i) {
+                const v4f v = share(g, kg)[i * 64];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    own[i / 4][4 * (i & 3) + k] = __builtin_fmaf(v[k], factor[g], own[i / 4][4 * (i & 3) + k]);
+            }
         }
     }
 };

@@ -43,7 +43,8 @@ void attn_fp8_kernel(AttnArgs a) {
     constexpr bool TWO = P * SB <= W;
     constexpr int VBUF = TWO ? 2 : 1;                      // V's (first) buffer
     constexpr int GROUP_BYTES = 2 * VBUF * STEP_BYTES;     // K even, K odd, V even, V odd; or K, V
-    constexpr int LDS_BYTES = KS * GROUP_BYTES > SplitMerge<W, KS>::kBytes ? KS * GROUP_BYTES : SplitMerge<W, KS>::kBytes;
+    constexpr int END_BYTES = KS > 1 ? SplitMerge<W, KS>::kBytes : W * store_region_bytes(4);
+    constexpr int LDS_BYTES = KS * GROUP_BYTES > END_BYTES ? KS * GROUP_BYTES : END_BYTES;
     // the groups' blocks; afterwards their sums and the output transpose
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_BYTES];
     const Geom& G = a.g;
@@ -510,27 +511,34 @@ void attn_fp8_kernel(AttnArgs a) {
 
     make_up();
     if (TWO) __syncthreads();                              // all waves are done with the staged tiles
+    const float* const ch_scale = VCH ? a.sv + (size_t)bh * 128 : nullptr;
+    // l carries the factor 448
+    auto inverse = [](float l) FPS_INLINE { l = sum_over_row_pair(l); return l > 0.f ? 1.0f / l : 0.f; };
     if constexpr (KS > 1) {
         // O and l of a group are relative to its reference, a power of two: moving them to the largest is exact
-        const SplitMerge<W, KS> merge{lds, row_block, lane};
-        float ref = VCH || m_run == -INFINITY ? m_run : m_base;        // -inf: the group had no block, all zero
-        if (kg > 0) merge.leave(kg, acc, ref, l_run);
+        typedef SplitMerge<W, KS> Merge;
+        const Merge merge{lds, row_block, kg, lane};
+        // -inf: the group had no block, all zero
+        merge.leave(acc, VCH || m_run == -INFINITY ? m_run : m_base, l_run);
         __syncthreads();
-        if (kg > 0) return;
-#pragma unroll 1
-        for (int g = 1; g < KS; ++g) {
-            const v4f o = merge.numbers(g);
-            const float top = __builtin_fmaxf(ref, o[0]);   // finite: group 0 has a block
-            const float mine = fast_exp2(ref - top), theirs = fast_exp2(o[0] - top);
-            merge.add(g, acc, mine, theirs);
-            l_run = __builtin_fmaf(o[1], theirs, l_run * mine);
-            ref = top;
+        v4f o[KS];
+        float top = -INFINITY, l = 0.f, factor[KS];
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            o[g] = merge.numbers(g);
+            top = __builtin_fmaxf(top, o[g][0]);           // finite: group 0 has a block
         }
+#pragma unroll
+        for (int g = 0; g < KS; ++g) {
+            factor[g] = fast_exp2(o[g][0] - top);
+            l = __builtin_fmaf(o[g][1], factor[g], l);
+        }
+        v16f own[Merge::kOwn];
+        merge.add(acc, factor, own);
+        store_rows(a, rows, lane, own, inverse(l), merge.store_region(), ch_scale, 32 * Merge::kOwn * kg);
+    } else {
+        store_rows(a, rows, lane, acc, inverse(l_run), lds + row_block * store_region_bytes(4), ch_scale);
     }
-    const float l = sum_over_row_pair(l_run);
-    const float inv = l > 0.f ? 1.0f / l : 0.f;            // l already carries the factor 448
-    store_rows(a, rows, lane, acc, inv, lds + row_block * kStoreRegionBytes,
-               VCH ? a.sv + (size_t)bh * 128 : nullptr);
 }
 
 template <int SB, int W, bool MB, int KS = 1, int P = 1>
