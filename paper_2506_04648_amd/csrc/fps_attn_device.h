@@ -63,6 +63,7 @@ struct AttnArgs {
     int edge_shift;        // 1: clamp the window centre into the grid instead of truncating
     int out_f32;
     int out_raster;        // output in raster order (real tokens only) instead of tile order
+    int waves;             // sub-blocks of 32 rows of a work item
     int qblocks;           // query blocks (work items) of a tile
     uint32_t rc_qblocks;
     int chunk;             // work items per XCD, a multiple of 4
@@ -220,7 +221,7 @@ __device__ __forceinline__ void zero_padding_rows(const AttnArgs& a, const Query
 // Some wave of query block jq has a real row.
 template <int SB, int W, bool MB>
 __device__ __forceinline__ bool any_real_row(const Geom& G, int cls, int jq, int sbg) {
-    if (!MB) return true;                                  // the block is the tile
+    if (!MB && W >= SB) return true;                       // the block is the tile
     for (int w = 0; w < W; ++w) {
         const int qs = jq * W + w, group = qs / sbg;
         if (real_tokens(G, cls, sub_tile_origin(G, group)) > 32 * (qs - group * sbg)) return true;
@@ -574,6 +575,41 @@ inline int window_blocks(const AttnArgs& a) {
 inline bool split_keys(const AttnArgs& a, int ks) {
     const int resident = 256 * (8 / (query_waves(a.g) * ks)), blocks = window_blocks(a);
     return a.total <= resident && blocks >= 2 * ks && blocks >= 6;
+}
+
+// Narrow items: FP8 launches of few 128-row items are cut into items of 32 rows, whose keys four wave groups share, or of 64
+// rows and two groups: four waves a workgroup either way, and one buffer of K and V each (64 KB a workgroup of 64 rows, so two
+// on a CU; 128 KB, one on a CU, of 32).  Twice or four times the workgroups reach more CUs, and where walks differ in length
+// the longest, which the launch waits for, takes half a CU of its own.  Each workgroup stages K and V for itself, and a step has
+// two barriers: where the CUs were loaded evenly that costs more.  14 700 random calls of one and several blocks a tile,
+// time against 128 rows (keys in two groups up to 256 items, else in one), by items, longest walk over the mean and blocks:
+//   32 rows   items          1-32    33-64   65-80   81-100     64 rows   1-64    65-128
+//     blocks  4-5            0.79    0.82    1.12    1.30                 0.87    0.90
+//             6-11           0.73    0.74    1.07    1.19                 0.84    0.84
+//             12-29          0.67    0.66    0.89    1.05                 0.82    0.81
+//             30 and more    0.62    0.59    0.80    0.90                 0.79    0.79
+//   64 rows   longest/mean   1-1.15  -1.3    -1.5    -1.8    more
+//     129-256 items, blocks 6-11     1.04    1.03    1.02    0.99    0.96
+//                    12-29           1.05    0.97    0.93    0.88    0.84
+//                    30 and more     1.04    0.91    0.87    0.84    0.81
+//     257-288        12-29           0.97    1.01    0.98    0.91    0.83
+//                    30 and more     0.86    0.89    0.87    0.78    0.72
+//     289-400        12-29           1.06    1.10    1.06    1.02    0.93
+//                    30 and more     0.95    0.99    0.97    0.90    0.82
+// The slowest inside the rule 1.24.  225 items of up to 27 blocks, 5x23x37 tokens x 5 heads: 35.6 -> 30.9 us.
+// Waves (of 32 rows) of an item; 128-slot blocks only, otherwise query_waves.
+inline int narrow_waves(long long items, int blocks, double longest_over_mean) {
+    if (blocks < 6 || items > 400) return 4;
+    if (items <= 64) return 1;
+    if (items <= 128) return 2;
+    if (items <= 256) return blocks >= 12 && longest_over_mean >= 1.3 ? 2 : 4;
+    return blocks >= 30 && (items <= 288 || longest_over_mean >= 1.8) ? 2 : 4;
+}
+inline int fp8_row_waves(const AttnArgs& a, int blocks) {
+    const Geom& g = a.g;
+    const long long items = (long long)g.BH * g.M * (g.TSP / 128);
+    if (g.BS != 128 || items > 400) return query_waves(g);
+    return narrow_waves(items, blocks, longest_over_mean(g, {a.rt, a.rh, a.rw}, a.edge_shift));
 }
 
 // FP8, small scale groups: several key blocks go through a step together where the walk is long enough to pay for the part of

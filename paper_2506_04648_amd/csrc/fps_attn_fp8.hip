@@ -20,7 +20,7 @@
 // then accumulates straight into O and the scales are applied once in the epilogue.
 // P: key blocks (small scale groups) that one step of the pipeline takes, each with scales and a row reference of its own:
 // as many of SB sub-blocks as fill four, so that the barriers and the bookkeeping of a step serve two or four blocks.  K and
-// V of a step are double-buffered where a workgroup has four waves; with less LDS a wave than that, K(i+2) and V(i) each
+// V of a step are double-buffered where a workgroup has four waves of rows; with less LDS a wave than that, K(i+2) and V(i) each
 // stream into the one buffer while the other product runs, two barriers a step.  Attention on 21x30x52 tokens, one block a
 // step against P, us: 24 heads, 64-token sub-tiles of (2,8,16) tiles, window 3x3x3, 1278 -> 1220; 12 heads, 16-token
 // sub-tiles of (2,4,8) tiles, that window, 872 -> 745; tile (3,4,4), window 3x5x7, 783 -> 763, tile (2,4,4) 508 -> 495 and
@@ -36,7 +36,7 @@ void attn_fp8_kernel(AttnArgs a) {
     constexpr int NTHR = KS * W * 64;
     constexpr int CPT = SB * 4 / W;                        // 16-byte chunks per thread per operand block
     constexpr int BLOCK_BYTES = SB * 4096, STEP_BYTES = P * BLOCK_BYTES;
-    static_assert(CPT >= 1 && CPT <= 4 && CPT * W == SB * 4, "every wave copies the same share of a block");
+    static_assert(CPT >= 1 && CPT * W == SB * 4, "every wave copies the same share of a block");
     static_assert(KS == 1 || P == 1, "wave groups take single blocks");
     static_assert(P * SB <= 4, "scores of a step: at most 4 sub-blocks");
     // two buffers each for K and V where that leaves room for 8 waves on a CU, otherwise one
@@ -59,7 +59,7 @@ void attn_fp8_kernel(AttnArgs a) {
     const int ucls = tile_class(G, ut, uh, uw);
     // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
     // waves of cut tiles fall on different SIMDs
-    const int row_block = W == 4 ? (wave_s + kg + u) & 3 : wave_s;
+    const int row_block = W == 4 || (SB == 4 && W == 2) ? (wave_s + kg + u) & (W - 1) : wave_s;
     const int qs = jq * W + row_block;
     QueryRows rows;
     rows.init(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
@@ -102,13 +102,13 @@ void attn_fp8_kernel(AttnArgs a) {
     auto v_buf = [&](int ahead) FPS_INLINE { return VBUF + (TWO ? par ^ ahead : 0); };
 
     // Of a list of `total` blocks, those of this wave group.  Group 0 never has fewer than another; what a group
-    // has fewer barriers than group 0 (one a block, one a list) it makes up for at the end, as every barrier
-    // is one of the whole workgroup.  (Made up for within the list, they cost 110 spilled registers.)
+    // has fewer barriers than group 0 (one a block, one a list; with one buffer two and three) it makes up for at the end,
+    // as every barrier is one of the whole workgroup.  (Made up for within the list, they cost 110 spilled registers.)
     int owed = 0;
     auto blocks_of_group = [&](int total) FPS_INLINE {
         if (KS == 1) return total;
         const int nblk = (total - kg + KS - 1) / KS;
-        owed += 1 * ((total + KS - 1) / KS - nblk) + (nblk == 0 ? 1 : 0);
+        owed += (TWO ? 1 : 2) * ((total + KS - 1) / KS - nblk) + (nblk == 0 ? (TWO ? 1 : 3) : 0);
         return nblk;
     };
     auto make_up = [&]() FPS_INLINE {
@@ -454,10 +454,11 @@ void attn_fp8_kernel(AttnArgs a) {
                 pv_mfma(op[k % 3], k);
 #pragma unroll
                 for (int t = k * HPS; t < (k + 1) * HPS && t < 2 * NT; ++t) max_of_half(mx, t);
-                static_assert(P * CPT <= STEPS, "one copy a step");
-                if (k < P * CPT) {
-                    if (TWO)          stage_chunk(v_buf(1), v_head, v_step, k);          // V(i-1) was consumed last iteration
-                    else if (fetch_k) stage_chunk(k_buf(0), k_head, nxt, k);             // K(i+1) was consumed
+                constexpr int per = (P * CPT + STEPS - 1) / STEPS;
+#pragma unroll
+                for (int c = k * per; c < (k + 1) * per && c < P * CPT; ++c) {
+                    if (TWO)          stage_chunk(v_buf(1), v_head, v_step, c);          // V(i-1) was consumed last iteration
+                    else if (fetch_k) stage_chunk(k_buf(0), k_head, nxt, c);             // K(i+1) was consumed
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -553,10 +554,14 @@ void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
     switch (g.BS == 128 ? 4 : g.KBS) {
         case 4:
             if (g.KB > 1) {
-                if (split_keys(a, 2)) launch<4, 4, true, 2>(a, vch, grid, st);
+                if (a.waves == 1)          launch<4, 1, true, 4>(a, vch, grid, st);
+                else if (a.waves == 2)     launch<4, 2, true, 2>(a, vch, grid, st);
+                else if (split_keys(a, 2)) launch<4, 4, true, 2>(a, vch, grid, st);
                 else                  launch<4, 4, true>(a, vch, grid, st);
             } else {
-                if (split_keys(a, 2)) launch<4, 4, false, 2>(a, vch, grid, st);
+                if (a.waves == 1)          launch<4, 1, false, 4>(a, vch, grid, st);
+                else if (a.waves == 2)     launch<4, 2, false, 2>(a, vch, grid, st);
+                else if (split_keys(a, 2)) launch<4, 4, false, 2>(a, vch, grid, st);
                 else                  launch<4, 4, false>(a, vch, grid, st);
             }
             break;

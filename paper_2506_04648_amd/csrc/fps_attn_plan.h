@@ -72,15 +72,34 @@ __host__ __device__ inline int tail_item(const P& p, const Geom& g, int qblocks,
     return base + layer * layer_items + (ahead < 0 ? ahead + layer_items : ahead);
 }
 
+// Tokens along an axis of n tiles in the window of position u.
+inline long long tokens_in_window(int u, int n, int tile, int size, int r, bool shift) {
+    if (shift) u = n > 2 * r + 1 ? (u < r ? r : u > n - 1 - r ? n - 1 - r : u) : n / 2;
+    const int lo = u > r ? u - r : 0, hi = u < n - 1 - r ? u + r : n - 1;
+    return (long long)(hi == n - 1 ? size : (hi + 1) * tile) - (long long)lo * tile;
+}
+
+// Tokens in the fullest window over their mean.
+inline double longest_over_mean(const Geom& g, const int (&radius)[3], bool shift) {
+    const int n[3] = {g.nT, g.nH, g.nW}, tile[3] = {g.Tt, g.Th, g.Tw}, size[3] = {g.T, g.H, g.W};
+    double ratio = 1;
+    for (int i = 0; i < 3; ++i) {
+        long long sum = 0, most = 0;
+        for (int u = 0; u < n[i]; ++u) {
+            const long long x = tokens_in_window(u, n[i], tile[i], size[i], radius[i], shift);
+            sum += x;
+            most = x > most ? x : most;
+        }
+        ratio *= (double)most * n[i] / (double)sum;
+    }
+    return ratio;
+}
+
 // One axis of n tiles: the levels of its positions by the tokens in their windows, at least
 // 90, 72 and 0 % of the most.  That number rises along the axis, stays and falls, so the positions above a
 // threshold are a range.
 inline int plan_axis(int n, int tile, int size, int r, bool shift, AxisLevel* level, long long* tokens) {
-    auto in_window = [&](int u) {
-        if (shift) u = n > 2 * r + 1 ? (u < r ? r : u > n - 1 - r ? n - 1 - r : u) : n / 2;
-        const int lo = u > r ? u - r : 0, hi = u < n - 1 - r ? u + r : n - 1;
-        return (long long)(hi == n - 1 ? size : (hi + 1) * tile) - (long long)lo * tile;
-    };
+    auto in_window = [&](int u) { return tokens_in_window(u, n, tile, size, r, shift); };
     const int top = r < n - 1 ? r : n - 1;                 // a position of the most
     static const int percent[kAxisLevels] = {90, 72, 0};
     int levels = 0, lo = top, hi = top - 1;                // the range so far: lo .. hi, empty

@@ -466,6 +466,39 @@ def test_keys_split_over_wave_groups_of_tiles_in_sub_tiles(prec, vscale):
         gu.assert_parity(st, f"head {h}")
 
 
+# heads, grid, tile, sub-tile, window, heads compared
+NARROW_CASES = [
+    (1, (7, 13, 37), (1, 8, 16), None, (3, 3, 3), (0,)),     # 42 items of 128 rows: 32 rows each, keys in four
+    (1, (7, 8, 16), (1, 8, 16), None, (13, 1, 1), (0,)),     # 7 blocks: groups of one and of two
+    (2, (3, 13, 40), (2, 8, 16), None, (3, 3, 3), (0, 1)),   # 48 items, two blocks a tile, idle waves
+    (3, (6, 13, 37), (1, 8, 16), None, (3, 3, 3), (0, 2)),   # 108 items: 64 rows, keys in two; blocks of 8, 5, 7 and 3 halves
+    (4, (3, 13, 40), (2, 8, 16), (1, 8, 16), (3, 3, 3), (0, 3)),   # 96 items, two scale groups a tile
+    (5, (5, 21, 37), (1, 8, 16), None, (3, 3, 3), (0, 4)),   # 225 items of very different length
+    (13, (2, 24, 48), (1, 8, 16), None, (3, 5, 5), (0, 12)),   # 234 items of like length: 128 rows, keys in two
+    (3, (10, 24, 48), (1, 8, 16), None, (5, 5, 5), (0, 2)),  # 270 items
+]
+
+
+@pytest.mark.parametrize("vscale,f32", [(fps.VSCALE_TILE, True), (fps.VSCALE_CHANNEL, True), (fps.VSCALE_TILE, False)])
+@pytest.mark.parametrize("heads,grid,tile,qtile,window,compared", NARROW_CASES)
+def test_narrow_items(vscale, f32, heads, grid, tile, qtile, window, compared):
+    """Launches of few FP8 items: 32 or 64 rows each, the keys shared by four or two wave groups."""
+    say("narrow items", vscale, f32, heads, grid, tile, qtile, window)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=heads, n_outlier=3, config_id=27)
+    run = gu.GpuRun(w, qtile=qtile)
+    out, vis = run.attn(fps.PREC_FP8, vscale=vscale, visited=True)
+    assert np.array_equal(vis.cpu().numpy().astype(bool), fo.tile_mask(run.g, window))
+    if not f32:
+        import torch
+        half = run.attn(fps.PREC_FP8, vscale=vscale, out_dtype=torch.bfloat16)
+        assert torch.equal(half, out.to(torch.bfloat16))
+        return
+    for h in compared:
+        st = gu.compare_head(run, out, h, fps.PREC_FP8, window, vscale=vscale)
+        say("  head", h, st)
+        gu.assert_parity(st, f"{grid} {tile} head {h}")
+
+
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
 @pytest.mark.parametrize("heads,grid,tile,qtile,window,shift", [
     (40, (3, 13, 40), (1, 8, 16), None, (3, 3, 3), False),        # 720 items, cut along h and w

@@ -305,3 +305,83 @@ def test_the_tail_dealt_by_length_deals_each_item_once(tmp_path):
             assert n % layer == 0 and n <= chunk and (wanted <= n < wanted + layer or n > chunk - layer), (c, line)
             tails += 1
     assert tails > 40
+
+
+NARROW_PROGRAM = r"""
+#include "fps_attn_device.h"
+#include <cstdio>
+#include <cstring>
+using namespace fps;
+int main() {
+    int BH, n[3], tile[3], size[3], r[3], shift;
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d %d", &BH, size, size + 1, size + 2, tile, tile + 1, tile + 2, r, r + 1, r + 2, &shift) == 11) {
+        for (int i = 0; i < 3; ++i) n[i] = (size[i] + tile[i] - 1) / tile[i];
+        AttnArgs a;
+        std::memset(&a, 0, sizeof(a));
+        Geom& g = a.g;
+        g.BH = BH; g.T = size[0]; g.H = size[1]; g.W = size[2]; g.Tt = tile[0]; g.Th = tile[1]; g.Tw = tile[2];
+        g.nT = n[0]; g.nH = n[1]; g.nW = n[2]; g.M = n[0] * n[1] * n[2];
+        const int tokens = tile[0] * tile[1] * tile[2];
+        g.BS = tokens <= 96 ? 32 : 128; g.NS = 1; g.KBS = g.KB = (tokens + g.BS - 1) / g.BS; g.KBG = g.BS == 128 ? g.KBS : 1;
+        g.TSP = g.KB * g.BS;
+        a.rt = r[0]; a.rh = r[1]; a.rw = r[2]; a.edge_shift = shift;
+        std::printf("%.9f %d %d\n", longest_over_mean(g, {r[0], r[1], r[2]}, shift), window_blocks(a), fp8_row_waves(a, window_blocks(a)));
+    }
+    for (int items : {1, 64, 65, 128, 129, 256, 257, 288, 289, 400, 401})
+        for (int blocks : {5, 6, 11, 12, 29, 30})
+            for (double s : {1.0, 1.3, 1.8}) std::printf("%d", narrow_waves(items, blocks, s));
+    std::printf("\n");
+}
+"""
+
+
+def test_launches_of_few_items_take_narrow_ones(tmp_path):
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    src, exe = tmp_path / "narrow.hip", tmp_path / "narrow"
+    src.write_text(NARROW_PROGRAM)
+    res = subprocess.run([HIPCC, "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                          "-I" + os.path.join(ROOT, "include"),
+                          "-I" + os.path.join(ROOT, "paper_2506_04648_amd", "csrc"), str(src), "-o", str(exe)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    cases = [(bh, *grid, *tile, *r, shift) for bh in (1, 3, 5, 9) for grid in ((5, 23, 37), (8, 24, 48), (1, 1, 5000))
+             for tile in ((1, 8, 16), (2, 8, 16), (3, 4, 4)) for r in ((1, 1, 1), (0, 1, 2), (9, 9, 9)) for shift in (0, 1)]
+    out = subprocess.run([str(exe)], input="\n".join(" ".join(map(str, c)) for c in cases), capture_output=True,
+                         text=True, check=True).stdout.split("\n")
+
+    def rule(items, blocks, spread):
+        if blocks < 6 or items > 400:
+            return 4
+        if items <= 128:
+            return 1 if items <= 64 else 2
+        narrow = blocks >= 12 and spread >= 1.3 if items <= 256 else blocks >= 30 and (items <= 288 or spread >= 1.8)
+        return 2 if narrow else 4
+
+    seen = set()
+    for c, line in zip(cases, out):
+        spread, blocks, waves = line.split()
+        bh, size, tile, r, shift = c[0], c[1:4], c[4:7], c[7:10], c[10]
+        want, items = 1.0, bh
+        for s, t, k in zip(size, tile, r):
+            n = -(-s // t)
+            items *= n
+            lengths = []
+            for u in range(n):
+                if shift:
+                    u = min(max(u, k), n - 1 - k) if n > 2 * k + 1 else n // 2
+                lengths.append(sum(min(t, s - v * t) for v in range(max(0, u - k), min(n - 1, u + k) + 1)))
+            want *= max(lengths) * n / sum(lengths)
+        assert abs(float(spread) - want) < 1e-6 * want, (c, line)
+        slots = tile[0] * tile[1] * tile[2]
+        if slots <= 96:
+            assert int(waves) == -(-slots // 32), (c, line)
+        elif abs(want - 1.3) > 1e-6 and abs(want - 1.8) > 1e-6:
+            assert int(waves) == rule(items * -(-slots // 128), int(blocks), want), (c, line)
+            seen.add(int(waves))
+    assert seen == {1, 2, 4}
+    it = iter(out[len(cases)])
+    for items in (1, 64, 65, 128, 129, 256, 257, 288, 289, 400, 401):
+        for blocks in (5, 6, 11, 12, 29, 30):
+            for s in (1.0, 1.3, 1.8):
+                assert int(next(it)) == rule(items, blocks, s), (items, blocks, s)
