@@ -108,7 +108,7 @@ int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, c
     a.out_f32 = out_f32;
     a.out_raster = out_raster;
     const int row_bytes = prec == FPS_PREC_FP8 ? 128 : 256, blocks = window_blocks(a);
-    a.waves = prec == FPS_PREC_FP8 ? fp8_row_waves(a, blocks) : query_waves(g);
+    a.waves = row_waves(a, blocks, prec == FPS_PREC_FP8);
     a.qblocks = g.TSP / (32 * a.waves);
     a.rc_qblocks = reciprocal(a.qblocks);
     a.total = g.BH * g.M * a.qblocks;

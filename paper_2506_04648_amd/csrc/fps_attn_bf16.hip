@@ -28,7 +28,7 @@ void attn_bf16_kernel(AttnArgs a) {
     constexpr int NTHR = KS * W * 64;
     constexpr int CPT = SB * 8 / W;                        // 16-byte chunks per thread per operand block
     constexpr int BLOCK_BYTES = SB * 8192;
-    static_assert(CPT >= 1 && CPT <= 8 && CPT * W == SB * 8, "every wave copies the same share of a block");
+    static_assert(CPT >= 1 && CPT <= 16 && CPT * W == SB * 8, "every wave copies the same share of a block");
     constexpr int GROUP_BYTES = 2 * BLOCK_BYTES;           // K, V
     constexpr int END_BYTES = KS > 1 ? SplitMerge<W, KS>::kBytes : W * store_region_bytes(4);
     constexpr int LDS_BYTES = KS * GROUP_BYTES > END_BYTES ? KS * GROUP_BYTES : END_BYTES;
@@ -46,7 +46,7 @@ void attn_bf16_kernel(AttnArgs a) {
     const int ucls = tile_class(G, ut, uh, uw);
     // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
     // waves of cut tiles fall on different SIMDs
-    const int row_block = W == 4 ? (wave_s + kg + u) & 3 : wave_s;
+    const int row_block = W == 4 || (SB == 4 && W == 2) ? (wave_s + kg + u) & (W - 1) : wave_s;
     const int qs = jq * W + row_block;
     QueryRows rows;
     rows.init(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
@@ -378,10 +378,12 @@ void launch_attn_bf16(const AttnArgs& a, int grid, hipStream_t st) {
     switch (g.BS == 128 ? 4 : g.KBS) {
         case 4:
             if (g.KB > 1) {
-                if (split_keys(a, 2)) launch<4, 4, true, 2>(a, grid, st);
+                if (a.waves == 2)          launch<4, 2, true, 2>(a, grid, st);
+                else if (split_keys(a, 2)) launch<4, 4, true, 2>(a, grid, st);
                 else                  launch<4, 4, true>(a, grid, st);
             } else {
-                if (split_keys(a, 2)) launch<4, 4, false, 2>(a, grid, st);
+                if (a.waves == 2)          launch<4, 2, false, 2>(a, grid, st);
+                else if (split_keys(a, 2)) launch<4, 4, false, 2>(a, grid, st);
                 else                  launch<4, 4, false>(a, grid, st);
             }
             break;

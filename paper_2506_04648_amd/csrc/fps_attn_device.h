@@ -577,11 +577,11 @@ inline bool split_keys(const AttnArgs& a, int ks) {
     return a.total <= resident && blocks >= 2 * ks && blocks >= 6;
 }
 
-// Narrow items: FP8 launches of few 128-row items are cut into items of 32 rows, whose keys four wave groups share, or of 64
-// rows and two groups: four waves a workgroup either way, and one buffer of K and V each (64 KB a workgroup of 64 rows, so two
-// on a CU; 128 KB, one on a CU, of 32).  Twice or four times the workgroups reach more CUs, and where walks differ in length
+// Narrow items: launches of few 128-row items are cut into items of 32 rows (FP8), whose keys four wave groups share, or of 64
+// rows and two groups: four waves a workgroup either way, and one buffer of K and V each (FP8 64 KB a workgroup of 64 rows, so
+// two on a CU; 128 KB, one on a CU, of 32 rows and in BF16).  Twice or four times the workgroups reach more CUs, and where walks differ in length
 // the longest, which the launch waits for, takes half a CU of its own.  Each workgroup stages K and V for itself, and a step has
-// two barriers: where the CUs were loaded evenly that costs more.  14 700 random calls of one and several blocks a tile,
+// two barriers: where the CUs were loaded evenly that costs more.  14 700 random FP8 calls of one and several blocks a tile,
 // time against 128 rows (keys in two groups up to 256 items, else in one), by items, longest walk over the mean and blocks:
 //   32 rows   items          1-32    33-64   65-80   81-100     64 rows   1-64    65-128
 //     blocks  4-5            0.79    0.82    1.12    1.30                 0.87    0.90
@@ -597,6 +597,8 @@ inline bool split_keys(const AttnArgs& a, int ks) {
 //     289-400        12-29           1.06    1.10    1.06    1.02    0.93
 //                    30 and more     0.95    0.99    0.97    0.90    0.82
 // The slowest inside the rule 1.24.  225 items of up to 27 blocks, 5x23x37 tokens x 5 heads: 35.6 -> 30.9 us.
+// BF16, 64 rows, up to 128 items, 13 400 calls: blocks 2-3 0.94, 4-5 0.90, 6-8 0.85, 9-29 0.82, more 0.79, the slowest of 6
+// blocks or more 0.99; 117 items of up to 21 blocks 39.0 -> 31.0 us.
 // Waves (of 32 rows) of an item; 128-slot blocks only, otherwise query_waves.
 inline int narrow_waves(long long items, int blocks, double longest_over_mean) {
     if (blocks < 6 || items > 400) return 4;
@@ -605,10 +607,11 @@ inline int narrow_waves(long long items, int blocks, double longest_over_mean) {
     if (items <= 256) return blocks >= 12 && longest_over_mean >= 1.3 ? 2 : 4;
     return blocks >= 30 && (items <= 288 || longest_over_mean >= 1.8) ? 2 : 4;
 }
-inline int fp8_row_waves(const AttnArgs& a, int blocks) {
+inline int row_waves(const AttnArgs& a, int blocks, bool fp8) {
     const Geom& g = a.g;
     const long long items = (long long)g.BH * g.M * (g.TSP / 128);
     if (g.BS != 128 || items > 400) return query_waves(g);
+    if (!fp8) return items <= 128 && blocks >= 6 ? 2 : 4;
     return narrow_waves(items, blocks, longest_over_mean(g, {a.rt, a.rh, a.rw}, a.edge_shift));
 }
 

@@ -479,22 +479,24 @@ NARROW_CASES = [
 ]
 
 
-@pytest.mark.parametrize("vscale,f32", [(fps.VSCALE_TILE, True), (fps.VSCALE_CHANNEL, True), (fps.VSCALE_TILE, False)])
+@pytest.mark.parametrize("prec,vscale,f32", [(fps.PREC_FP8, fps.VSCALE_TILE, True), (fps.PREC_FP8, fps.VSCALE_CHANNEL, True),
+                                             (fps.PREC_FP8, fps.VSCALE_TILE, False), (fps.PREC_BF16, fps.VSCALE_TILE, True),
+                                             (fps.PREC_BF16, fps.VSCALE_TILE, False)])
 @pytest.mark.parametrize("heads,grid,tile,qtile,window,compared", NARROW_CASES)
-def test_narrow_items(vscale, f32, heads, grid, tile, qtile, window, compared):
-    """Launches of few FP8 items: 32 or 64 rows each, the keys shared by four or two wave groups."""
-    say("narrow items", vscale, f32, heads, grid, tile, qtile, window)
+def test_narrow_items(prec, vscale, f32, heads, grid, tile, qtile, window, compared):
+    """Launches of few items: 32 (FP8) or 64 rows each, the keys shared by four or two wave groups."""
+    say("narrow items", prec, vscale, f32, heads, grid, tile, qtile, window)
     w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=heads, n_outlier=3, config_id=27)
     run = gu.GpuRun(w, qtile=qtile)
-    out, vis = run.attn(fps.PREC_FP8, vscale=vscale, visited=True)
+    out, vis = run.attn(prec, vscale=vscale, visited=True)
     assert np.array_equal(vis.cpu().numpy().astype(bool), fo.tile_mask(run.g, window))
     if not f32:
         import torch
-        half = run.attn(fps.PREC_FP8, vscale=vscale, out_dtype=torch.bfloat16)
+        half = run.attn(prec, vscale=vscale, out_dtype=torch.bfloat16)
         assert torch.equal(half, out.to(torch.bfloat16))
         return
     for h in compared:
-        st = gu.compare_head(run, out, h, fps.PREC_FP8, window, vscale=vscale)
+        st = gu.compare_head(run, out, h, prec, window, vscale=vscale)
         say("  head", h, st)
         gu.assert_parity(st, f"{grid} {tile} head {h}")
 
