@@ -5,7 +5,8 @@
 // walks the box of key tiles given by Eq. 2 -- tile pairs outside the box are never scheduled -- in key
 // blocks of at most SB sub-blocks of 32 keys, staged through LDS.  A key block lies in one scale
 // group (a tile, or a quantisation sub-tile):
-//   SB = 4, W = 4        groups of more than 96 tokens; a group is one or several 128-slot blocks
+//   SB = 4, W = 4        groups of more than 96 tokens; a group is one or several 128-slot blocks.  W = 2 or 1
+//                        in launches of few items (narrow_waves)
 //   SB = 1, 2, 3         groups of at most 32, 64, 96 tokens, one block each.  W = SB where the tile is
 //                        one group, so that a workgroup is one tile and walks its window exactly; a tile
 //                        of several groups gives its workgroups four of its sub-blocks, or SB where it
@@ -15,8 +16,8 @@
 //                        tiles, window 3x3x3, x 24 heads.)
 // MB = true: a tile is several key blocks.
 // KS = 2 or 4 (launches that would leave the chip half empty): KS times W waves; wave group kg takes the
-// blocks kg, kg + KS, .. of every walk, with buffers of its own, and group 0 adds up the groups' O and row
-// sums at the end.
+// blocks kg, kg + KS, .. of every walk, with buffers of its own; at the end each group adds up, and stores, a share of
+// the channels (SplitMerge).
 //
 // Scores are produced transposed, S^T = K Q^T, on the 32x32 matrix instructions, so that a lane's
 // accumulator holds one query row and a fixed set of keys: lane (n, h) = lane & 31, lane >> 5 holds
@@ -570,8 +571,9 @@ inline int window_blocks(const AttnArgs& a) {
 // kernels' registers on each of 256 CUs, workgroups of three waves, split in two, fill six (300 items of 77 tokens:
 // split 47.1 us FP8, 57.5 BF16, in a second and mostly empty round; not split 44.6 and 53.1), and the wave
 // groups' LDS buffers (16 to 32 KB a wave) allow no more.  A wave alone on its SIMD takes 1.6 us a 128-key block, two that
-// share one 2.3 us for two.  Attention, split against not: 225 items of up to 27 blocks 45.2 -> 37.9 us, of 6 blocks
-// 15.5 -> 15.2, of 4 blocks 13.0 -> 13.6 (two groups); 64 one-wave items of up to 9 blocks 11.6 -> 10.3 (four groups).
+// share one 2.3 us for two.  Attention, split against not, before SplitMerge's adding up was shared: 225 items of up to 27
+// blocks 45.2 -> 37.9 us, of 6 blocks 15.5 -> 15.2, of 4 blocks 13.0 -> 13.6 (two groups); 64 one-wave items of up to 9 blocks
+// 11.6 -> 10.3 (four groups).
 inline bool split_keys(const AttnArgs& a, int ks) {
     const int resident = 256 * (8 / (query_waves(a.g) * ks)), blocks = window_blocks(a);
     return a.total <= resident && blocks >= 2 * ks && blocks >= 6;
