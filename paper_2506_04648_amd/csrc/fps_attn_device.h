@@ -617,6 +617,12 @@ inline int row_waves(const AttnArgs& a, int blocks, bool fp8) {
     return narrow_waves(items, blocks, longest_over_mean(g, {a.rt, a.rh, a.rw}, a.edge_shift));
 }
 
+// FP8 items of 64 rows that leave CUs without a second workgroup (up to 128 items of 128 rows) and have long walks: four wave
+// groups, 128 KB of buffers.  16 000 random calls of 65 to 128 items, time against two groups, by blocks: 6-8 1.06, 9-11 1.02,
+// 12-29 0.97 (one in six slower by 5 % or more), 30-59 0.90, the slowest 1.10, more 0.86; 120 items of (4,8,8) tiles, window
+// 3x9x9 of 60 blocks, 45.2 -> 41.7 us.
+inline bool narrow_in_four(const AttnArgs& a) { return a.waves == 2 && a.total <= 256 && window_blocks(a) >= 30; }
+
 // FP8, small scale groups: several key blocks go through a step together where the walk is long enough to pay for the part of
 // the last step that may be empty and, in workgroups of fewer than four waves, for the one buffer of K and V that leaves
 // room for.  There two blocks against one, 1.00 = as fast, 12x30x52 tokens in groups of 32 to 64, 3, 12 and 30 heads, both

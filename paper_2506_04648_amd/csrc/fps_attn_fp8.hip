@@ -29,6 +29,7 @@
 
 namespace fps {
 
+
 template <int SB, int W, bool VCH, bool MB, int KS, int P>
 __global__ __launch_bounds__(KS * W * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_fp8_kernel(AttnArgs a) {
@@ -555,11 +556,13 @@ void launch_attn_fp8(const AttnArgs& a, bool vch, int grid, hipStream_t st) {
         case 4:
             if (g.KB > 1) {
                 if (a.waves == 1)          launch<4, 1, true, 4>(a, vch, grid, st);
+                else if (narrow_in_four(a)) launch<4, 2, true, 4>(a, vch, grid, st);
                 else if (a.waves == 2)     launch<4, 2, true, 2>(a, vch, grid, st);
                 else if (split_keys(a, 2)) launch<4, 4, true, 2>(a, vch, grid, st);
                 else                  launch<4, 4, true>(a, vch, grid, st);
             } else {
                 if (a.waves == 1)          launch<4, 1, false, 4>(a, vch, grid, st);
+                else if (narrow_in_four(a)) launch<4, 2, false, 4>(a, vch, grid, st);
                 else if (a.waves == 2)     launch<4, 2, false, 2>(a, vch, grid, st);
                 else if (split_keys(a, 2)) launch<4, 4, false, 2>(a, vch, grid, st);
                 else                  launch<4, 4, false>(a, vch, grid, st);

@@ -473,6 +473,8 @@ NARROW_CASES = [
     (2, (3, 13, 40), (2, 8, 16), None, (3, 3, 3), (0, 1)),   # 48 items, two blocks a tile, idle waves
     (3, (6, 13, 37), (1, 8, 16), None, (3, 3, 3), (0, 2)),   # 108 items: 64 rows, keys in two; blocks of 8, 5, 7 and 3 halves
     (4, (3, 13, 40), (2, 8, 16), (1, 8, 16), (3, 3, 3), (0, 3)),   # 96 items, two scale groups a tile
+    (3, (6, 13, 37), (1, 8, 16), None, (5, 3, 3), (0, 2)),   # 108 items of up to 30 blocks: FP8 keys in four
+    (2, (7, 13, 37), (2, 8, 16), None, (5, 3, 3), (0, 1)),   # 96 items of up to 48, two blocks a tile
     (5, (5, 21, 37), (1, 8, 16), None, (3, 3, 3), (0, 4)),   # 225 items of very different length
     (13, (2, 24, 48), (1, 8, 16), None, (3, 5, 5), (0, 12)),   # 234 items of like length: 128 rows, keys in two
     (3, (10, 24, 48), (1, 8, 16), None, (5, 5, 5), (0, 2)),  # 270 items

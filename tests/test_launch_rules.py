@@ -328,6 +328,16 @@ int main() {
         std::printf("%.9f %d %d %d\n", longest_over_mean(g, {r[0], r[1], r[2]}, shift), window_blocks(a),
                     row_waves(a, window_blocks(a), true), row_waves(a, window_blocks(a), false));
     }
+    for (int waves : {1, 2, 4})
+        for (int total : {256, 258})
+            for (int blocks : {29, 30}) {
+                AttnArgs a;
+                std::memset(&a, 0, sizeof(a));
+                a.g.nT = blocks; a.g.nH = a.g.nW = a.g.NS = a.g.KBG = 1;
+                a.rt = blocks; a.waves = waves; a.total = total;
+                std::printf("%d", (int)narrow_in_four(a));
+            }
+    std::printf("\n");
     for (int items : {1, 64, 65, 128, 129, 256, 257, 288, 289, 400, 401})
         for (int blocks : {5, 6, 11, 12, 29, 30})
             for (double s : {1.0, 1.3, 1.8}) std::printf("%d", narrow_waves(items, blocks, s));
@@ -383,7 +393,8 @@ def test_launches_of_few_items_take_narrow_ones(tmp_path):
             assert int(waves) == rule(items * -(-slots // 128), int(blocks), want), (c, line)
             seen.add(int(waves))
     assert seen == {1, 2, 4}
-    it = iter(out[len(cases)])
+    assert out[len(cases)] == "000001000000"
+    it = iter(out[len(cases) + 1])
     for items in (1, 64, 65, 128, 129, 256, 257, 288, 289, 400, 401):
         for blocks in (5, 6, 11, 12, 29, 30):
             for s in (1.0, 1.3, 1.8):
