@@ -107,21 +107,7 @@ int launch_attn(const Geom& g, const fps_window& win, int prec, const void* q, c
     a.edge_shift = win.edge == FPS_EDGE_SHIFT;
     a.out_f32 = out_f32;
     a.out_raster = out_raster;
-    const int row_bytes = prec == FPS_PREC_FP8 ? 128 : 256, blocks = window_blocks(a);
-    a.waves = row_waves(a, blocks, prec == FPS_PREC_FP8);
-    a.qblocks = g.TSP / (32 * a.waves);
-    a.rc_qblocks = reciprocal(a.qblocks);
-    a.total = g.BH * g.M * a.qblocks;
-    a.rotate = deal_in_turns(g.nW * a.qblocks);
-    a.chunk = ((a.total + 7) / 8 + 3) / 4 * 4;
-    const int waves = query_waves(g);                      // of a workgroup, in narrow items with its wave groups
-    const int slots = plan_items(g, {a.rt, a.rh, a.rw}, a.edge_shift, a.qblocks, waves, row_bytes, blocks, a.plan);
-    const int grid = 8 * (slots > 0 ? slots : a.chunk);
-    a.tail = -1;
-    if (slots == 0) {
-        const int tail = plan_tail(g, {a.rt, a.rh, a.rw}, a.edge_shift, a.qblocks, waves, row_bytes, blocks, a.chunk, a.plan);
-        a.tail = tail < 0 ? a.chunk : tail;
-    }
+    const int grid = 8 * plan_launch(a, prec == FPS_PREC_FP8);
     if (prec == FPS_PREC_FP8) launch_attn_fp8(a, vscale == FPS_VSCALE_CHANNEL, grid, st);
     else                      launch_attn_bf16(a, grid, st);
     hipError_t e = hipGetLastError();

@@ -580,34 +580,39 @@ inline bool split_keys(const AttnArgs& a, int ks) {
 }
 
 // Narrow items: launches of few 128-row items are cut into items of 32 rows (FP8), whose keys four wave groups share, or of 64
-// rows and two groups: four waves a workgroup either way, and one buffer of K and V each (FP8 64 KB a workgroup of 64 rows, so
-// two on a CU; 128 KB, one on a CU, of 32 rows and in BF16).  Twice or four times the workgroups reach more CUs, and where walks differ in length
-// the longest, which the launch waits for, takes half a CU of its own.  Each workgroup stages K and V for itself, and a step has
-// two barriers: where the CUs were loaded evenly that costs more.  14 700 random FP8 calls of one and several blocks a tile,
-// time against 128 rows (keys in two groups up to 256 items, else in one), by items, longest walk over the mean and blocks:
-//   32 rows   items          1-32    33-64   65-80   81-100     64 rows   1-64    65-128
-//     blocks  4-5            0.79    0.82    1.12    1.30                 0.87    0.90
-//             6-11           0.73    0.74    1.07    1.19                 0.84    0.84
-//             12-29          0.67    0.66    0.89    1.05                 0.82    0.81
-//             30 and more    0.62    0.59    0.80    0.90                 0.79    0.79
-//   64 rows   longest/mean   1-1.15  -1.3    -1.5    -1.8    more
-//     129-256 items, blocks 6-11     1.04    1.03    1.02    0.99    0.96
-//                    12-29           1.05    0.97    0.93    0.88    0.84
-//                    30 and more     1.04    0.91    0.87    0.84    0.81
-//     257-288        12-29           0.97    1.01    0.98    0.91    0.83
-//                    30 and more     0.86    0.89    0.87    0.78    0.72
-//     289-400        12-29           1.06    1.10    1.06    1.02    0.93
-//                    30 and more     0.95    0.99    0.97    0.90    0.82
-// The slowest inside the rule 1.24.  225 items of up to 27 blocks, 5x23x37 tokens x 5 heads: 35.6 -> 30.9 us.
-// BF16, 64 rows, up to 128 items, 13 400 calls: blocks 2-3 0.94, 4-5 0.90, 6-8 0.85, 9-29 0.82, more 0.79, the slowest of 6
-// blocks or more 0.99; 117 items of up to 21 blocks 39.0 -> 31.0 us.
+// rows and two groups: four waves a workgroup either way (eight in narrow_in_four), and one buffer of K and V each (FP8 64 KB a
+// workgroup of 64 rows, so two on a CU; 128 KB, one on a CU, of 32 rows and in BF16).  Twice or four times the workgroups reach
+// more CUs, and where walks differ in length the longest, which the launch waits for, takes half a CU of its own.  Each
+// workgroup stages K and V for itself, and a step has two barriers: where the CUs were loaded evenly, or the hardware puts two
+// long items on one CU, that costs more.  79 000 random FP8 calls, time against 128 rows (keys in two groups up to 256
+// items, else in one): cells' means, the slowest call and the share slower by 3 %, by items, blocks and the longest walk over
+// the mean:
+//   1-64       6 blocks or more                     0.55-0.72   0.95   none      (32 rows; 65 items and more 1.05 to 1.3)
+//   65-128     6 blocks or more                     0.64-0.83   0.99   none      (64 rows)
+//   129-160    12 or more        1.3 or more        0.78-0.87   1.09   0.2 %
+//   161-256    12 to 99          1.5 or more        0.79-0.91   1.11   0.4 %
+//                                1.3 to 1.5         0.84-0.96   1.13   3 %       (not taken)
+//              100 or more       1.3 or more        0.79-0.89   1.14   0.1 %
+//   257-288    30 to 99          1.5 or more        0.72-0.85   1.09   0.3 %
+//                                1.1 to 1.5         0.81-0.94   1.30   10 %      (not taken)
+//              40 or more        less than 1.1      0.78-0.87   1.12   2 %       (30 to 39 blocks 1.14, 7 %, not taken)
+//              100 or more       1.3 or more        0.69-0.85   1.02   none      (1.1 to 1.3 1.11, 5 %, not taken)
+//   289-320    30 or more        1.8 or more        0.72-0.85   0.98   none
+//   321-400    60 or more        1.8 or more        0.76-0.85   1.07   0.2 %     (30 to 59 blocks 1.10, 3 %, not taken)
+// Where the slow calls are few no property of theirs was found that tells them apart.
+// 225 items of up to 27 blocks, 5x23x37 tokens x 5 heads: 35.6 -> 30.9 us.
+// BF16, 64 rows, up to 128 items, 18 000 calls: none slower; blocks 6-8 0.85, 9-29 0.82, more 0.79; 117 items of up to 21
+// blocks 39.0 -> 31.0 us.  (2-3 blocks 0.94, 4-5 0.90, not taken; more than 128 items not measured.)
 // Waves (of 32 rows) of an item; 128-slot blocks only, otherwise query_waves.
 inline int narrow_waves(long long items, int blocks, double longest_over_mean) {
     if (blocks < 6 || items > 400) return 4;
     if (items <= 64) return 1;
     if (items <= 128) return 2;
-    if (items <= 256) return blocks >= 12 && longest_over_mean >= 1.3 ? 2 : 4;
-    return blocks >= 30 && (items <= 288 || longest_over_mean >= 1.8) ? 2 : 4;
+    if (items <= 160) return blocks >= 12 && longest_over_mean >= 1.3 ? 2 : 4;
+    const bool uneven = longest_over_mean >= (blocks >= 100 ? 1.3 : 1.5);
+    if (items <= 256) return blocks >= 12 && uneven ? 2 : 4;
+    if (items <= 288) return (blocks >= 30 && uneven) || (blocks >= 40 && longest_over_mean < 1.1) ? 2 : 4;
+    return blocks >= (items <= 320 ? 30 : 60) && longest_over_mean >= 1.8 ? 2 : 4;
 }
 inline int row_waves(const AttnArgs& a, int blocks, bool fp8) {
     const Geom& g = a.g;
@@ -620,8 +625,37 @@ inline int row_waves(const AttnArgs& a, int blocks, bool fp8) {
 // FP8 items of 64 rows that leave CUs without a second workgroup (up to 128 items of 128 rows) and have long walks: four wave
 // groups, 128 KB of buffers.  16 000 random calls of 65 to 128 items, time against two groups, by blocks: 6-8 1.06, 9-11 1.02,
 // 12-29 0.97 (one in six slower by 5 % or more), 30-59 0.90, the slowest 1.10, more 0.86; 120 items of (4,8,8) tiles, window
-// 3x9x9 of 60 blocks, 45.2 -> 41.7 us.
+// 3x9x9 of 60 blocks, 45.2 -> 41.7 us.  (Against 128 rows none of them is slower: see above.)
 inline bool narrow_in_four(const AttnArgs& a) { return a.waves == 2 && a.total <= 256 && window_blocks(a) >= 30; }
+
+// Cuts a launch into work items and plans the order in which they are dealt; returns the workgroups of an XCD.
+//
+// plan_items rounds every section up to the same number of slots on each XCD, so up to 256 items of 128 rows, cut in two, may
+// need more than the 64 workgroups that an XCD holds at once, two on a CU; the last of them then wait for a long one to end.
+// Those stay whole, one on a CU: cut in two, 240 random calls took 0.92 of that time, but one in eight was slower by 3 % or
+// more, the slowest 1.34.
+inline int plan_launch(AttnArgs& a, bool fp8) {
+    const Geom& g = a.g;
+    // narrow items in two groups are workgroups of four waves as well; the plans pass over launches of 256 workgroups or less,
+    // which those in four groups are
+    const int radius[3] = {a.rt, a.rh, a.rw}, row_bytes = fp8 ? 128 : 256, blocks = window_blocks(a), waves = query_waves(g);
+    auto cut = [&](int of_rows) {
+        a.waves = of_rows;
+        a.qblocks = g.TSP / (32 * a.waves);
+        a.rc_qblocks = reciprocal(a.qblocks);
+        a.total = g.BH * g.M * a.qblocks;
+        return plan_items(g, radius, a.edge_shift, a.qblocks, waves, row_bytes, blocks, a.plan);
+    };
+    int slots = cut(row_waves(a, blocks, fp8));
+    if (a.waves < waves && a.total <= 512 && slots > 64) slots = cut(waves);
+    a.rotate = deal_in_turns(g.nW * a.qblocks);
+    a.chunk = ((a.total + 7) / 8 + 3) / 4 * 4;
+    a.tail = -1;
+    if (slots > 0) return slots;
+    const int tail = plan_tail(g, radius, a.edge_shift, a.qblocks, waves, row_bytes, blocks, a.chunk, a.plan);
+    a.tail = tail < 0 ? a.chunk : tail;
+    return a.chunk;
+}
 
 // FP8, small scale groups: several key blocks go through a step together where the walk is long enough to pay for the part of
 // the last step that may be empty and, in workgroups of fewer than four waves, for the one buffer of K and V that leaves
