@@ -588,17 +588,17 @@ inline bool split_keys(const AttnArgs& a, int ks) {
 // items, else in one): cells' means, the slowest call and the share slower by 3 %, by items, blocks and the longest walk over
 // the mean:
 //   1-64       6 blocks or more                     0.55-0.72   0.95   none      (32 rows; 65 items and more 1.05 to 1.3)
-//   65-128     6 blocks or more                     0.64-0.83   0.99   none      (64 rows)
-//   129-160    12 or more        1.3 or more        0.78-0.87   1.09   0.2 %
-//   161-256    12 to 99          1.5 or more        0.79-0.91   1.11   0.4 %
-//                                1.3 to 1.5         0.84-0.96   1.13   3 %       (not taken)
-//              100 or more       1.3 or more        0.79-0.89   1.14   0.1 %
-//   257-288    30 to 99          1.5 or more        0.72-0.85   1.09   0.3 %
-//                                1.1 to 1.5         0.81-0.94   1.30   10 %      (not taken)
-//              40 or more        less than 1.1      0.78-0.87   1.12   2 %       (30 to 39 blocks 1.14, 7 %, not taken)
-//              100 or more       1.3 or more        0.69-0.85   1.02   none      (1.1 to 1.3 1.11, 5 %, not taken)
-//   289-320    30 or more        1.8 or more        0.72-0.85   0.98   none
-//   321-400    60 or more        1.8 or more        0.76-0.85   1.07   0.2 %     (30 to 59 blocks 1.10, 3 %, not taken)
+//   65-128     6 or more                            0.64-0.83   0.99   none      (64 rows)
+//   129-160    12 or more        1.3 or more        0.80-0.87   1.09   0.2 %
+//   161-256    12 to 17          1.5 or more        0.88        1.06   0.9 %     (1.3 to 1.5 0.94, 1.13, 10 %: not taken)
+//              18 to 59          1.4 or more        0.84-0.89   1.11   0.8 %     (1.3 to 1.4 0.89-0.91, 1.13, 3 %: not taken)
+//              60 or more        1.3 or more        0.82-0.87   1.14   0.4 %
+//   257-288    40 to 59          1.4 or more        0.79-0.85   1.07   0.3 %     (1.1 to 1.4 0.87-0.91, 1.30, 14 %: not taken)
+//              60 or more        1.3 or more        0.74-0.86   1.09   0.3 %     (1.1 to 1.3 0.88, 1.13, 7 %: not taken)
+//              40 or more        less than 1.1      0.82-0.85   1.12   2 %
+//              30 to 39          1.4 or more        0.84-0.91   1.20   2 %       (less 0.85-0.93, 1.24, 15 %): not taken
+//   289-320    30 or more        1.8 or more        0.74-0.83   0.98   none
+//   321-400    40 or more        1.8 or more        0.81-0.85   1.07   0.3 %     (30 to 39 blocks 0.89, 1.10, 7 %: not taken)
 // Where the slow calls are few no property of theirs was found that tells them apart.
 // 225 items of up to 27 blocks, 5x23x37 tokens x 5 heads: 35.6 -> 30.9 us.
 // BF16, 64 rows, up to 128 items, 18 000 calls: none slower; blocks 6-8 0.85, 9-29 0.82, more 0.79; 117 items of up to 21
@@ -609,10 +609,10 @@ inline int narrow_waves(long long items, int blocks, double longest_over_mean) {
     if (items <= 64) return 1;
     if (items <= 128) return 2;
     if (items <= 160) return blocks >= 12 && longest_over_mean >= 1.3 ? 2 : 4;
-    const bool uneven = longest_over_mean >= (blocks >= 100 ? 1.3 : 1.5);
+    const bool uneven = longest_over_mean >= (blocks >= 60 ? 1.3 : blocks >= 18 ? 1.4 : 1.5);
     if (items <= 256) return blocks >= 12 && uneven ? 2 : 4;
-    if (items <= 288) return (blocks >= 30 && uneven) || (blocks >= 40 && longest_over_mean < 1.1) ? 2 : 4;
-    return blocks >= (items <= 320 ? 30 : 60) && longest_over_mean >= 1.8 ? 2 : 4;
+    if (items <= 288) return blocks >= 40 && (uneven || longest_over_mean < 1.1) ? 2 : 4;
+    return blocks >= (items <= 320 ? 30 : 40) && longest_over_mean >= 1.8 ? 2 : 4;
 }
 inline int row_waves(const AttnArgs& a, int blocks, bool fp8) {
     const Geom& g = a.g;

@@ -339,8 +339,8 @@ int main() {
             }
     std::printf("\n");
     for (int items : {1, 64, 65, 128, 129, 160, 161, 256, 257, 288, 289, 320, 321, 400, 401})
-        for (int blocks : {5, 6, 11, 12, 29, 30, 39, 40, 59, 60, 99, 100})
-            for (double s : {1.0, 1.1, 1.3, 1.5, 1.8}) std::printf("%d", narrow_waves(items, blocks, s));
+        for (int blocks : {5, 6, 11, 12, 17, 18, 29, 30, 39, 40, 59, 60})
+            for (double s : {1.0, 1.1, 1.3, 1.4, 1.5, 1.8}) std::printf("%d", narrow_waves(items, blocks, s));
     std::printf("\n");
 }
 """
@@ -366,13 +366,15 @@ def test_launches_of_few_items_take_narrow_ones(tmp_path):
             return 4
         if items <= 128:
             return 1 if items <= 64 else 2
-        uneven = spread >= (1.3 if blocks >= 100 or items <= 160 else 1.5)
+        if items <= 160:
+            return 2 if blocks >= 12 and spread >= 1.3 else 4
+        uneven = spread >= (1.3 if blocks >= 60 else 1.4 if blocks >= 18 else 1.5)
         if items <= 256:
             narrow = blocks >= 12 and uneven
         elif items <= 288:
-            narrow = blocks >= 30 and uneven or blocks >= 40 and spread < 1.1
+            narrow = blocks >= 40 and (uneven or spread < 1.1)
         else:
-            narrow = blocks >= (30 if items <= 320 else 60) and spread >= 1.8
+            narrow = blocks >= (30 if items <= 320 else 40) and spread >= 1.8
         return 2 if narrow else 4
 
     seen = set()
@@ -395,15 +397,15 @@ def test_launches_of_few_items_take_narrow_ones(tmp_path):
             assert int(waves) == int(waves_bf16) == -(-slots // 32), (c, line)
         else:
             assert int(waves_bf16) == (2 if items * -(-slots // 128) <= 128 and int(blocks) >= 6 else 4), (c, line)
-        if slots > 96 and min(abs(want - edge) for edge in (1.1, 1.3, 1.5, 1.8)) > 1e-6:
+        if slots > 96 and min(abs(want - edge) for edge in (1.1, 1.3, 1.4, 1.5, 1.8)) > 1e-6:
             assert int(waves) == rule(items * -(-slots // 128), int(blocks), want), (c, line)
             seen.add(int(waves))
     assert seen == {1, 2, 4}
     assert out[len(cases)] == "000001000000"
     it = iter(out[len(cases) + 1])
     for items in (1, 64, 65, 128, 129, 160, 161, 256, 257, 288, 289, 320, 321, 400, 401):
-        for blocks in (5, 6, 11, 12, 29, 30, 39, 40, 59, 60, 99, 100):
-            for s in (1.0, 1.1, 1.3, 1.5, 1.8):
+        for blocks in (5, 6, 11, 12, 17, 18, 29, 30, 39, 40, 59, 60):
+            for s in (1.0, 1.1, 1.3, 1.4, 1.5, 1.8):
                 assert int(next(it)) == rule(items, blocks, s), (items, blocks, s)
 
 
