@@ -417,14 +417,15 @@ def test_every_item_of_an_even_row_is_computed(prec, heads, grid, tile):
         gu.assert_parity(st, f"{grid} {tile} head {h}")
 
 
-# heads, grid, tile, window, heads compared.  128-slot tiles split their keys in two, smaller ones (of one
-# scale group) in two or four, where a launch is small and a window has six or eight blocks
+# heads, grid, tile, window, heads compared.  Where a launch is small and a window has six or eight blocks the keys are shared:
+# by two wave groups for three sub-blocks, by four for two or one; tiles of 128 slots, at most 64 of them here, are cut into
+# items of 32 rows (FP8) whose keys four groups share, or of 64 rows and two groups (BF16).  test_launch_rules.py has the routes
 SPLIT_CASES = [
-    (2, (4, 8, 16), (1, 8, 16), (7, 1, 1), (0, 1)),          # 4 blocks: not split
-    (2, (3, 8, 16), (1, 8, 16), (5, 1, 1), (0,)),            # 3 blocks: not split
-    (2, (6, 8, 16), (1, 8, 16), (11, 1, 1), (0, 1)),         # 6 blocks: the fewest that are split
+    (2, (4, 8, 16), (1, 8, 16), (7, 1, 1), (0, 1)),          # 4 blocks: neither cut nor split
+    (2, (3, 8, 16), (1, 8, 16), (5, 1, 1), (0,)),            # 3 blocks: neither
+    (2, (6, 8, 16), (1, 8, 16), (11, 1, 1), (0, 1)),         # 6 blocks: the fewest
     (2, (6, 8, 16), (1, 8, 16), (7, 1, 1), (0, 1)),          # walks of 4, 5 and 6 blocks
-    (2, (5, 13, 37), (1, 8, 16), (3, 3, 3), (0, 1)),         # odd counts, cut tiles with idle waves, walks of one block
+    (2, (5, 13, 37), (1, 8, 16), (3, 3, 3), (0, 1)),         # odd counts, cut tiles with idle items, walks of one block
     (2, (3, 13, 40), (2, 8, 16), (3, 3, 3), (0, 1)),         # tiles of two blocks
     (2, (4, 13, 20), (1, 7, 11), (3, 3, 3), (0, 1)),         # 77 tokens: three sub-blocks, keys in two
     (2, (5, 7, 18), (3, 4, 4), (3, 3, 5), (0, 1)),           # 48 tokens: two sub-blocks, keys in four
@@ -477,7 +478,9 @@ NARROW_CASES = [
     (2, (7, 13, 37), (2, 8, 16), None, (5, 3, 3), (0, 1)),   # 96 items of up to 48, two blocks a tile
     (5, (5, 21, 37), (1, 8, 16), None, (3, 3, 3), (0, 4)),   # 225 items of very different length
     (13, (2, 24, 48), (1, 8, 16), None, (3, 5, 5), (0, 12)),   # 234 items of like length: 128 rows, keys in two
-    (3, (10, 24, 48), (1, 8, 16), None, (5, 5, 5), (0, 2)),  # 270 items
+    (3, (10, 24, 48), (1, 8, 16), None, (5, 5, 5), (0, 2)),  # 270 items of up to 1.25 times the mean: 128 rows
+    (6, (15, 8, 48), (1, 8, 16), None, (29, 1, 5), (5,)),    # 270 of one length: FP8 64 rows
+    (5, (7, 21, 37), (1, 8, 16), None, (7, 3, 3), (4,)),     # 315 of twice the mean: FP8 64 rows, more than fit at once
 ]
 
 
@@ -501,6 +504,109 @@ def test_narrow_items(prec, vscale, f32, heads, grid, tile, qtile, window, compa
         st = gu.compare_head(run, out, h, prec, window, vscale=vscale)
         say("  head", h, st)
         gu.assert_parity(st, f"{grid} {tile} head {h}")
+
+
+# heads, grid, tile, sub-tile, window, shifted, heads compared: 129 to 256 items of 128 rows that are not cut, keys in two groups
+# of four waves
+WHOLE_SPLIT_CASES = [
+    (5, (5, 13, 37), (1, 8, 16), None, (3, 1, 3), False, (0, 4)),          # 150 items of up to 9 blocks, idle waves, odd counts
+    (6, (4, 13, 37), (1, 8, 16), None, (9, 9, 9), True, (0, 5)),           # 144 items of 24, all of one length
+    (5, (7, 13, 20), (2, 8, 16), None, (3, 1, 1), False, (0, 4)),          # 160 items, two blocks a tile, one of them cut off
+    (6, (4, 13, 40), (2, 8, 16), None, (1, 3, 3), False, (0, 5)),          # 144 items of 12
+    (6, (4, 13, 40), (2, 8, 16), (1, 8, 16), (1, 3, 3), True, (0, 5)),     # and a scale group each
+]
+
+
+@pytest.mark.parametrize("prec,vscale", [(fps.PREC_FP8, fps.VSCALE_TILE), (fps.PREC_FP8, fps.VSCALE_CHANNEL),
+                                         (fps.PREC_BF16, fps.VSCALE_TILE)])
+@pytest.mark.parametrize("heads,grid,tile,qtile,window,shift,compared", WHOLE_SPLIT_CASES)
+def test_keys_split_over_groups_of_four_waves(prec, vscale, heads, grid, tile, qtile, window, shift, compared):
+    say("split, whole items", prec, vscale, heads, grid, tile, qtile, window, shift)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=heads, n_outlier=3, config_id=29)
+    win = window + ((fps.EDGE_SHIFT,) if shift else ())
+    run = gu.GpuRun(w, qtile=qtile)
+    out, vis = run.attn(prec, window=win, vscale=vscale, visited=True)
+    assert np.array_equal(vis.cpu().numpy().astype(bool), fo.tile_mask(run.g, win))
+    for h in compared:
+        st = gu.compare_head(run, out, h, prec, win, vscale=vscale)
+        gu.assert_parity(st, f"{grid} {tile} head {h}")
+
+
+# heads, grid, tile, sub-tile, window: every kernel of few items of 128-slot tiles
+RASTER_CASES = [
+    (1, (7, 13, 37), (1, 8, 16), None, (3, 3, 3)),           # 42 items
+    (2, (3, 13, 40), (2, 8, 16), None, (3, 3, 3)),           # 48, two blocks a tile
+    (3, (6, 13, 37), (1, 8, 16), None, (3, 3, 3)),           # 108
+    (4, (3, 13, 40), (2, 8, 16), (1, 8, 16), (3, 3, 3)),     # 96, two scale groups a tile
+    (3, (6, 13, 37), (1, 8, 16), None, (5, 3, 3)),           # 108 of up to 30 blocks
+    (2, (7, 13, 37), (2, 8, 16), None, (5, 3, 3)),           # 96 of up to 48
+    (5, (5, 13, 37), (1, 8, 16), None, (3, 1, 3)),           # 150, not cut
+    (6, (4, 13, 40), (2, 8, 16), None, (1, 3, 3)),           # 144
+]
+
+
+@pytest.mark.parametrize("prec,vscale", [(fps.PREC_FP8, fps.VSCALE_TILE), (fps.PREC_FP8, fps.VSCALE_CHANNEL),
+                                         (fps.PREC_BF16, fps.VSCALE_TILE)])
+@pytest.mark.parametrize("heads,grid,tile,qtile,window", RASTER_CASES)
+def test_few_items_in_raster_order_and_shifted_windows(prec, vscale, heads, grid, tile, qtile, window):
+    """The output a caller of the fused entry points gets: fp32 and bf16, every element of a NaN-filled buffer, the same numbers
+    as in tile order; windows shifted at the grid's edges."""
+    import torch
+    say("few items, raster, shifted", prec, vscale, heads, grid, tile, qtile, window)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=heads, n_outlier=3, config_id=30)
+    win = window + (fps.EDGE_SHIFT,)
+    run = gu.GpuRun(w, qtile=qtile)
+    tiled = run.attn(prec, window=win, vscale=vscale)
+    st = gu.compare_head(run, tiled, heads - 1, prec, win, vscale=vscale)
+    gu.assert_parity(st, f"{grid} {tile}")
+    want = fps.tile_unorder(run.shape, tiled)
+    if prec == fps.PREC_FP8:
+        (q, sq), (k, sk), (v, sv) = run.q8
+    else:
+        (q, sq), (k, sk), (v, sv) = run.p16
+    for dtype in (torch.float32, torch.bfloat16):
+        out = torch.full((1, heads) + grid + (128,), float("nan"), dtype=dtype, device="cuda:0")
+        fps.attn_fwd(run.shape, win, prec, q, k, v, sq, sk, sv, vscale=vscale, out=out, raster_out=True)
+        assert torch.equal(out, want.to(dtype))
+
+
+# heads, grid, tile, sub-tile, window: more keys than the L2s hold, so that the last items of an XCD are dealt by length
+TAIL_CASES = [
+    (40, (3, 45, 80), (1, 8, 16), None, (3, 3, 3)),          # one item a tile
+    (36, (4, 30, 52), (2, 8, 16), None, (1, 3, 3)),          # two
+    (28, (6, 30, 52), (6, 8, 8), None, (1, 3, 3)),           # three
+    (42, (3, 30, 52), (3, 4, 4), None, (1, 5, 7)),           # small groups: two waves
+    (18, (8, 30, 52), (2, 8, 16), (1, 8, 8), (1, 3, 3)),     # and four
+    (70, (4, 30, 52), (2, 4, 4), None, (1, 5, 5)),           # one
+]
+
+
+@pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
+@pytest.mark.parametrize("heads,grid,tile,qtile,window", TAIL_CASES)
+def test_the_end_of_a_long_launch_is_dealt_once(prec, heads, grid, tile, qtile, window):
+    """Every head has the same inputs: every slot of a NaN-filled output is written, all heads alike, one against the oracle."""
+    import torch
+    say("tail", prec, heads, grid, tile, qtile, window)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=1, n_outlier=3, config_id=31)
+    run = gu.GpuRun(w, qtile=qtile)
+    run.quantize()
+    shape = fps.make_shape(heads, grid, tile, qtile=qtile)
+    assert 2 * heads * run.g.M * run.tsp * (128 if prec == fps.PREC_FP8 else 256) > 64 << 20
+    packed, scales = [], []
+    for role in range(3):
+        x = run.raster[role].expand((1, heads) + grid + (128,)).contiguous()
+        p, s = (fps.quantize_tiles(shape, x, role, raster=True) if prec == fps.PREC_FP8 else
+                fps.pack_tiles_bf16(shape, x, role, raster=True))
+        packed.append(p)
+        scales.append(s)
+    out = torch.full((1, heads, run.g.M * run.tsp, 128), float("nan"), dtype=torch.float32, device="cuda:0")
+    fps.attn_fwd(shape, window, prec, *packed, *scales, out=out)
+    assert torch.isfinite(out).all()
+    assert torch.equal(out, out[:, :1].expand_as(out))
+    tiles = [u for u in gu.sample_q_tiles(run.g, np.random.default_rng(4)) if u < run.g.M]    # one layer has no interior
+    st = gu.compare_head(run, out[:, :1], 0, prec, window, q_tiles=tiles)
+    # the padding rows of every tile are zero, the sampled tiles within the bars
+    gu.assert_parity(st, f"tail {grid} {tile}")
 
 
 @pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])

@@ -244,9 +244,9 @@ int main() {
         ItemPlan p;
         const int first = plan_tail(g, {rt, rh, rw}, shift, qblocks, waves, row_bytes, blocks, chunk, p);
         std::vector<int> seen(8 * chunk, 0);
-        int bad = 0, rises = 0;
+        int bad = 0, rises = 0, sections = 0;
         for (int xcd = 0; xcd < 8 && first >= 0; ++xcd) {
-            int last = 1 << 30;
+            int longest = 1 << 30;
             for (int slot = 0; slot < chunk; ++slot) {
                 int sec = 0, wi = xcd * chunk + slot;
                 for (int l = 1; l <= kSectionLanes; ++l) sec += (int)(p.section[l] & kSectionStart) <= slot;
@@ -254,21 +254,38 @@ int main() {
                 if (wi < xcd * chunk || wi >= (xcd + 1) * chunk) { ++bad; continue; }
                 ++seen[wi];
                 if (slot < first) continue;
-                // lengths within a layer fall by levels: each at most 1 / 0.72 of the last one's shortest, or an axis' third level
+                // the item is where its section's levels say, and none is much longer than the first
                 const int uh = wi / qblocks / g.nW % g.nH, uw = wi / qblocks % g.nW;
+                auto holds = [&](const AxisLevel& l, int u) {
+                    for (int k = 0; k < AxisLevel::upper(l.skip_count); ++k) if (level_position(l, k) == u) return true;
+                    return false;
+                };
+                bad += !holds(p.level[1][(p.section[sec] >> 28) & 3], uh) || !holds(p.level[2][p.section[sec] >> 30], uw);
                 auto window = [&](int u, int n, int tile, int size, int r) {
                     if (shift) u = n > 2 * r + 1 ? (u < r ? r : u > n - 1 - r ? n - 1 - r : u) : n / 2;
                     const int lo = u > r ? u - r : 0, hi = u + r < n - 1 ? u + r : n - 1;
                     return ((hi + 1) * tile < size ? (hi + 1) * tile : size) - lo * tile;
                 };
                 const int len = window(uh, g.nH, 8, H, rh) * window(uw, g.nW, 16, W, rw);
-                if (slot == first) last = len;
-                rises += len > last * 1.25;                  // the first section holds the longest items
+                if (slot == first) longest = len;
+                rises += len > longest * 1.25;
             }
         }
         for (int s : seen) bad += first >= 0 && s != 1;
+        // the lengths of the sections, those of their levels, never rise
+        long long th[kAxisLevels], tw[kAxisLevels];
+        AxisLevel level[kAxisLevels];
+        plan_axis(g.nH, 8, H, rh, shift, level, th);
+        plan_axis(g.nW, 16, W, rw, shift, level, tw);
+        double last = 1e30;
+        for (int s = 0; first >= 0 && s < kMaxSections && (int)(p.section[s] & kSectionStart) < chunk; ++s) {
+            const double len = (double)th[(p.section[s] >> 28) & 3] * tw[p.section[s] >> 30];
+            rises += len > last;
+            sections += first >= 0;
+            last = len;
+        }
         const int n = first < 0 ? 0 : chunk - first;
-        std::printf("%d %d %d %d %d %d\n", first, bad, rises, chunk, layer, n);
+        std::printf("%d %d %d %d %d %d %d\n", first, bad, rises, chunk, layer, n, sections);
     }
 }
 """
@@ -276,7 +293,8 @@ int main() {
 
 def test_the_tail_dealt_by_length_deals_each_item_once(tmp_path):
     """The sorted end of an XCD's chunk is whole layers' worth of items, wherever in a layer it starts, each dealt once; one
-    round of workgroups or two (FP8); none where everything is resident at once, a layer is longer than that or walks are short."""
+    round of workgroups or two (FP8), the sections in falling order of their length; none where everything is resident at once, a
+    layer is longer than that or walks are short."""
     if not shutil.which(HIPCC):
         pytest.skip("no hipcc")
     src, exe = tmp_path / "tail.hip", tmp_path / "tail"
@@ -294,7 +312,7 @@ def test_the_tail_dealt_by_length_deals_each_item_once(tmp_path):
                          text=True, check=True).stdout.split("\n")
     tails = 0
     for c, line in zip(cases, out):
-        first, bad, rises, chunk, layer, n = map(int, line.split())
+        first, bad, rises, chunk, layer, n, sections = map(int, line.split())
         waves, row, blocks = c[9:]
         assert bad == 0 and rises == 0, (c, line)
         rounds = 32 * (8 // waves)
@@ -303,6 +321,7 @@ def test_the_tail_dealt_by_length_deals_each_item_once(tmp_path):
             assert first == -1, (c, line)
         if first >= 0:
             assert n % layer == 0 and n <= chunk and (wanted <= n < wanted + layer or n > chunk - layer), (c, line)
+            assert sections > 1, (c, line)
             tails += 1
     assert tails > 40
 
@@ -431,7 +450,7 @@ int main() {
         if (sb == 4 && a.waves < 4) groups = fp8 && (a.waves == 1 || narrow_in_four(a)) ? 4 : 2;
         else if ((sb == 4 || g.NS == 1) && split_keys(a, ks)) groups = ks;
         const char* order = a.tail < 0 ? "length" : a.tail < a.chunk ? "tail" : "raster";
-        std::printf("%d %d %d %d %d %s %d %d\n", sb, a.waves, groups, (int)(g.KB > 1), a.total, order, workgroups, a.qblocks);
+        std::printf("%d %d %d %d %d %s %d %d\n", sb, a.waves, groups, (int)(sb == 4 ? g.KB > 1 : g.NS > 1), a.total, order, workgroups, a.qblocks);
     }
 }
 """
@@ -440,7 +459,7 @@ int main() {
 @pytest.fixture(scope="module")
 def routes(tmp_path_factory):
     """(heads, grid, tile, sub-tile, window, shifted, fp8) of calls -> per call (32-key sub-blocks of a key block, waves of an
-    item, wave groups, several blocks a tile, items, order, workgroups of an XCD, items of a tile)."""
+    item, wave groups, several blocks or groups a tile, items, order, workgroups of an XCD, items of a tile)."""
     if not shutil.which(HIPCC):
         pytest.skip("no hipcc")
     d = tmp_path_factory.mktemp("routes")
@@ -459,6 +478,37 @@ def routes(tmp_path_factory):
         assert len(rows) == len(lines)
         return rows
     return run
+
+
+def test_the_gpu_cases_reach_the_kernels_that_they_name(routes):
+    """(sub-blocks of a key block, waves, wave groups, several blocks or groups a tile) of the cases of the GPU tests of few
+    items, FP8 and BF16, and the order of those that are to end by length."""
+    from tests import test_gpu_parity as t
+
+    def kernels(cases, shift=False):
+        rows = [routes([(c[0], c[1], c[2], c[3], c[4], shift or len(c) == 7 and c[5], fp8) for c in cases]) for fp8 in (True, False)]
+        return [tuple(r[i][:4] for r in rows) for i in range(len(cases))]
+
+    one, many = 0, 1
+    assert kernels([c[:3] + (None,) + c[3:4] for c in t.SPLIT_CASES]) == [
+        ((4, 4, 1, one), (4, 4, 1, one)), ((4, 4, 1, one), (4, 4, 1, one)), ((4, 1, 4, one), (4, 2, 2, one)),
+        ((4, 1, 4, one), (4, 2, 2, one)), ((4, 1, 4, one), (4, 2, 2, one)), ((4, 1, 4, many), (4, 2, 2, many)),
+        ((3, 3, 2, one),) * 2, ((2, 2, 4, one),) * 2, ((1, 1, 4, one),) * 2, ((1, 1, 1, one),) * 2, ((2, 2, 1, one),) * 2,
+        ((3, 3, 1, one),) * 2, ((3, 3, 1, one),) * 2]
+    narrow = [((4, 1, 4, one), (4, 2, 2, one)), ((4, 1, 4, many), (4, 2, 2, many)), ((4, 2, 2, one),) * 2,
+              ((4, 2, 2, many),) * 2, ((4, 2, 4, one), (4, 2, 2, one)), ((4, 2, 4, many), (4, 2, 2, many))]
+    whole = [((4, 4, 2, one),) * 2, ((4, 4, 2, many),) * 2]
+    assert kernels(t.NARROW_CASES) == narrow[:1] * 2 + narrow[1:] + [
+        ((4, 2, 2, one), (4, 4, 2, one)), whole[0], ((4, 4, 1, one),) * 2] + [((4, 2, 2, one), (4, 4, 1, one))] * 2
+    assert kernels(t.WHOLE_SPLIT_CASES) == [whole[0]] * 2 + [whole[1]] * 3
+    assert kernels(t.RASTER_CASES, shift=True) == narrow + whole
+    seen = set()
+    for fp8 in (True, False):
+        for case, row in zip(t.TAIL_CASES, routes([c + (False, fp8) for c in t.TAIL_CASES])):
+            assert row[5] == ("raster" if not fp8 and row[7] == 3 else "tail"), (case, row)
+            seen.add((fp8, row[0], row[1], row[7]))
+    # in BF16 the layer of three items a tile is more than a round of workgroups
+    assert {(True, 4, 4, 1), (True, 4, 4, 2), (True, 4, 4, 3), (True, 2, 2, 1), (True, 2, 4, 2), (True, 1, 1, 1)} <= seen
 
 
 def test_narrow_items_are_all_resident_at_once(routes):
