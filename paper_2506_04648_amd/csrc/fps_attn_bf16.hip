@@ -294,8 +294,9 @@ void attn_bf16_kernel(AttnArgs a) {
                     mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[j >> 3][2 * (j & 7)]), s[j >> 3][2 * (j & 7) + 1]);
                     asm volatile("" : "+v"(mx));
                 }
-                // K's copies ride in the first half, so that they have landed when the phase ends: one a step, for blocks
-                // of up to three halves two to four (32-token tiles, window 5x21x21: 354 -> 334 us, one a step against two)
+                // K's copies ride in the first half, so that they have landed when the phase ends: one every other step where a
+                // block has as many halves as a wave has copies, otherwise one a step, or as many a step as it takes, up
+                // to eight (32-token tiles, window 5x21x21: 354 -> 334 us, one a step against two)
                 constexpr int every = NH >= CPT ? 2 : 1, per = (CPT + 2 * NH - 1) / (2 * NH);
                 if (fetch_k && j % every == 0) {
 #pragma unroll

@@ -100,8 +100,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 
 // Work item of this workgroup: query block jq of tile (ut, uh, uw) of head bh.  Workgroups are dealt round-robin to
-// the 8 XCDs by the hardware; giving XCD x the contiguous range [x*chunk, (x+1)*chunk) of items (or that part of every section) keeps
-// the key tiles of neighbouring query tiles of one head in that XCD's L2.
+// the 8 XCDs by the hardware; giving XCD x the contiguous range [x*chunk, (x+1)*chunk) of items (or that part of every
+// section) keeps the key tiles of neighbouring query tiles of one head in that XCD's L2.  (It is the same part of every
+// section: with the sections' odd items on other XCDs in turn, for an even load, an XCD met other heads' keys in every
+// section, and of 10 000 random calls one in 12 was slower by 3 % or more, up to twice.)
 //
 // Within an XCD the hardware deals workgroups in order and round-robin to four shader engines, waiting
 // for the one whose turn it is.  How long an item takes depends on its place in the row of tiles (cut
@@ -410,8 +412,9 @@ struct KeyBlock { int blk, group, n; };
 // index kg (mod KS).  A lane works out the place of one block, so that a wave has the next 64 in two vector
 // registers and a block costs its loop two v_readlane: stepping through the box axis by axis took 25 to 40 scalar
 // instructions a block, and the FP8 kernel of tiles of several 128-slot blocks spilled 228 scalar registers to lanes
-// of vector registers (now 19; kernels of several small groups a tile 0 to 66).  Attention: 64-token sub-tiles of (2,8,16) tiles, 21x30x52 tokens x 24 heads, 1920 -> 1859 us, one-block
-// tiles of that grid x 12 heads 315 -> 311.
+// of vector registers (now 19, with per-channel V 46; of several small groups a tile 0 to 68, with the keys split 20 to 39).
+// Attention: 64-token sub-tiles of (2,8,16) tiles, 21x30x52 tokens x 24 heads, 1920 -> 1859 us, one-block tiles of that grid
+// x 12 heads 315 -> 311.
 template <bool MB, int KS>
 struct BlockList {
     const Geom& G;
@@ -601,7 +604,7 @@ inline bool split_keys(const AttnArgs& a, int ks) {
 //   321-400    40 or more        1.8 or more        0.81-0.85   1.07   0.3 %     (30 to 39 blocks 0.89, 1.10, 7 %: not taken)
 // Where the slow calls are few no property of theirs was found that tells them apart.
 // 225 items of up to 27 blocks, 5x23x37 tokens x 5 heads: 35.6 -> 30.9 us.
-// BF16, 64 rows, up to 128 items, 18 000 calls: none slower; blocks 6-8 0.85, 9-29 0.82, more 0.79; 117 items of up to 21
+// BF16, 64 rows, up to 128 items, 18 000 calls: none slower; blocks 6-8 0.84, 9-29 0.81, more 0.79; 117 items of up to 21
 // blocks 39.0 -> 31.0 us.  (2-3 blocks 0.94, 4-5 0.90, not taken; more than 128 items not measured.)
 // Waves (of 32 rows) of an item; 128-slot blocks only, otherwise query_waves.
 inline int narrow_waves(long long items, int blocks, double longest_over_mean) {

@@ -6,11 +6,11 @@ namespace fps {
 
 // The order in which an XCD deals its work items where its K and V are about the size of its L2 (plan_items), and its
 // last ones where they are not (plan_tail): by falling length.  How long an item takes goes by how much of its window the
-// grid's edges leave, a product over the axes.  Each axis is divided into up to three levels of about equal window length, each the positions between two thresholds
-// on both sides of the axis, and the items into sections of one level per axis, dealt one after the other.  In packed
-// words: a launch's arguments are written and read over the host's bus (1 KB of them, loosely packed, cost a small call
-// 0.7 us).  Not in bytes or halves, which next to words of the same index had the compiler split an address into parts
-// that were no multiples of 4, and scalar loads truncate those.
+// grid's edges leave, a product over the axes.  Each axis is divided into up to three levels of about equal window length,
+// each the positions between two thresholds on both sides of the axis, and the items into sections of one level per axis,
+// dealt one after the other.  In packed words: a launch's arguments are written and read over the host's bus (1 KB of
+// them, loosely packed, cost a small call 0.7 us).  Not in bytes or halves, which next to words of the same index had the
+// compiler split an address into parts that were no multiples of 4, and scalar loads truncate those.
 constexpr int kAxisLevels = 3, kMaxSections = kAxisLevels * kAxisLevels * kAxisLevels;
 constexpr int kSectionLanes = 32;   // lanes that look a slot's section up
 static_assert(kMaxSections <= kSectionLanes, "a lane for the end of each section");
@@ -207,11 +207,11 @@ inline int plan_items(const Geom& g, const int (&radius)[3], bool shift, int qbl
 // so that the launch does not end with long items alone on their CUs; the window of those few layers stays in the L2.  Returns
 // the first slot of an XCD so dealt, or -1: none.  Items of a layer must differ in length and walks be long, as in plan_items.
 // Attention, us, raster order against this (FP8 two rounds, BF16, whose keys take twice the bytes, one):
-//   12 x 21x30x52, window 3x3x3, tile (1,8,16)    FP8 335 -> 309      BF16 506 -> 477
-//   12 x 21x30x52, window 3x5x7, tile (3,4,4)     776 -> 757
-//   40 x 21x45x80, window 5x3x3, tile (1,8,16)    3768 -> 3749
-// 455 random FP8 calls: mean 0.990, slower by 2 % two, the slowest 1.04; 246 BF16 calls: mean 0.992, the slowest 1.01.  One
-// round in FP8 0.991; two in BF16 0.991 but the slowest 1.09, three 1.23.
+//   12 x 21x30x52, window 3x3x3, tile (1,8,16)    FP8 308 -> 296, 308 -> 295      BF16 489 -> 483, 483 -> 476
+//   12 x 21x30x52, window 3x5x7, tile (3,4,4)     765 -> 758, 759 -> 749
+//   40 x 21x45x80, window 5x3x3, tile (1,8,16)    3838 -> 3822, 3794 -> 3771
+// (calls back to back on two boxes; what the whole calls gain is the same).  1736 random calls of both precisions: mean 0.989,
+// 17 slower by 2 %, the slowest 1.04.  One round in FP8 0.991; two in BF16 0.991 but the slowest 1.09, three 1.23.
 inline int plan_tail(const Geom& g, const int (&radius)[3], bool shift, int qblocks, int waves, int row_bytes, int blocks,
                      int chunk, ItemPlan& p) {
     if (blocks < kPlannedBlocks || g.nH > 0xFFFF || g.nW > 0xFFFF) return -1;
