@@ -64,11 +64,12 @@ void attn_bf16_kernel(AttnArgs a) {
     auto k_blk = [&](const KeyBlock& b) FPS_INLINE { return k_head + (size_t)b.blk * BLOCK_BYTES; };
     auto v_blk = [&](const KeyBlock& b) FPS_INLINE { return v_head + (size_t)b.blk * BLOCK_BYTES; };
     auto stage_chunk = [&](int buf, const uint8_t* src, int c) FPS_INLINE {
-        dma_chunk_of(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * BLOCK_BYTES + wave_s * (CPT * 1024));
+        dma_chunk(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * BLOCK_BYTES + wave_s * (CPT * 1024));
     };
     auto stage = [&](int buf, const uint8_t* src) FPS_INLINE {
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) stage_chunk(buf, src, c);
+        for (int c = 0; c < (CPT + 3) / 4; ++c)
+            dma_copy<CPT>(c, src + wave_s * (CPT * 1024), lane * 16, lds_base + buf * BLOCK_BYTES + wave_s * (CPT * 1024));
     };
 
     typedef BlockList<MB, KS> List;
@@ -248,8 +249,9 @@ void attn_bf16_kernel(AttnArgs a) {
             const int n_next = nxt.n;
             const float svv_next = load_uniform(sv_head, nxt.group);
             cur = nxt;
-            const bool fetch_k = i + 2 < nblk;
-            if (fetch_k) {
+            // past the walk's end the last K is copied once more and nobody reads it (with the copies under a condition, which
+            // cuts the steps of PV into pieces, dense 720p took 108.0 ms, now 106.9)
+            if (i + 2 < nblk) {
                 if (((i + 2) & 63) == 0) list.fill(i + 2);
                 nxt = list.block(i + 2);
             }
@@ -298,7 +300,7 @@ void attn_bf16_kernel(AttnArgs a) {
                 // block has as many halves as a wave has copies, otherwise one a step, or as many a step as it takes, up
                 // to eight (32-token tiles, window 5x21x21: 354 -> 334 us, one a step against two)
                 constexpr int every = NH >= CPT ? 2 : 1, per = (CPT + 2 * NH - 1) / (2 * NH);
-                if (fetch_k && j % every == 0) {
+                if (j % every == 0) {
 #pragma unroll
                     for (int c = j / every * per; c < (j / every + 1) * per && c < CPT; ++c) stage_chunk(0, ksrc, c);
                 }

@@ -299,39 +299,50 @@ __device__ __forceinline__ v8i make_v8i(const uint4& lo, const uint4& hi) {
     return v8i{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
 }
 
-// Linear HBM -> LDS copy of one 16-byte chunk per lane, done by the load unit itself: lane i of the
-// wave deposits its chunk at lds_wave_base + 16 i.  Written as inline assembly so that the
-// compiler's wait-count bookkeeping does not serialise it against LDS reads of OTHER buffers; the
-// kernel waits for it explicitly (s_waitcnt vmcnt(0)) before the barrier that publishes the tile.
-// gsrc is a wave-uniform base (kept in scalar registers), lane_off the lane's byte offset from it.
-// OFF (0, 1024, 2048 or 3072) is the instruction's immediate offset: the hardware adds it to the
-// global address AND to the LDS address, so the four 1 KB pieces of a wave's 4 KB share of a tile
-// need one scalar base each side.
-template <int OFF>
-__device__ __forceinline__ void dma_chunk(const void* gsrc, uint32_t lane_off, uint32_t lds_wave_base) {
+// Linear HBM -> LDS copies of the 16-byte chunks FIRST .. FIRST + N - 1 (at most 4) of each lane, done by the load unit itself:
+// lane i of the wave deposits chunk c at lds_wave_base + 1024 c + 16 i.  Written as inline assembly so that the compiler's
+// wait-count bookkeeping does not serialise them against LDS reads of OTHER buffers; the kernel waits for them explicitly
+// (s_waitcnt vmcnt(0)) before the barrier that publishes the tile.  gsrc is a wave-uniform base (kept in scalar registers),
+// lane_off the lane's byte offset from it.  The instruction's immediate offset is added by the hardware to the global address
+// AND to the LDS address, so the pieces of a 4 KB share need one scalar base each side.
+template <int FIRST, int N>
+__device__ __forceinline__ void dma_chunks(const void* gsrc, uint32_t lane_off, uint32_t lds_wave_base) {
+    static_assert(FIRST >= 0 && N >= 1 && FIRST + N <= 4, "immediate offsets of at most 3072");
     // both are wave-uniform by construction; say so where the compiler cannot prove it
     const uint64_t p = reinterpret_cast<uint64_t>(gsrc);
     gsrc = reinterpret_cast<const void*>(
         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) |
         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32));
     lds_wave_base = __builtin_amdgcn_readfirstlane(lds_wave_base);
-    asm volatile("s_mov_b32 m0, %2\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, %1 offset:%3"
-                 :
-                 : "v"(lane_off), "s"(gsrc), "s"(lds_wave_base), "n"(OFF)
-                 : "memory", "m0");
+#define FPS_DMA(more) asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" more : \
+                                   : "v"(lane_off), "s"(gsrc), "s"(lds_wave_base), "n"(1024 * FIRST), "n"(1024 * FIRST + 1024), \
+                                     "n"(2048), "n"(3072) : "memory", "m0")
+#define FPS_DMA_AT(offset) "\n\tglobal_load_lds_dwordx4 %0, %1 offset:%" #offset
+    if constexpr (N == 1)      FPS_DMA("");
+    else if constexpr (N == 2) FPS_DMA(FPS_DMA_AT(4));
+    else if constexpr (N == 3) FPS_DMA(FPS_DMA_AT(4) FPS_DMA_AT(5));
+    else                       FPS_DMA(FPS_DMA_AT(4) FPS_DMA_AT(5) FPS_DMA_AT(6));
+#undef FPS_DMA_AT
+#undef FPS_DMA
 }
-// chunk c of a wave's contiguous share: base moves every four chunks, the rest rides in the offset
-__device__ __forceinline__ void dma_chunk_of(int c, const uint8_t* gsrc_wave, uint32_t lane_off, uint32_t lds_wave) {
-    const uint8_t* gs = gsrc_wave + (c >> 2) * 4096;
-    const uint32_t ld = lds_wave + (c >> 2) * 4096;
+// chunk c of a wave's contiguous share
+__device__ __forceinline__ void dma_chunk(int c, const uint8_t* gsrc_wave, uint32_t lane_off, uint32_t lds_wave) {
+    gsrc_wave += (c >> 2) * 4096;
+    lds_wave += (c >> 2) * 4096;
     switch (c & 3) {
-        case 0: dma_chunk<0>(gs, lane_off, ld); break;
-        case 1: dma_chunk<1024>(gs, lane_off, ld); break;
-        case 2: dma_chunk<2048>(gs, lane_off, ld); break;
-        default: dma_chunk<3072>(gs, lane_off, ld); break;
+        case 0: dma_chunks<0, 1>(gsrc_wave, lane_off, lds_wave); break;
+        case 1: dma_chunks<1, 1>(gsrc_wave, lane_off, lds_wave); break;
+        case 2: dma_chunks<2, 1>(gsrc_wave, lane_off, lds_wave); break;
+        default: dma_chunks<3, 1>(gsrc_wave, lane_off, lds_wave); break;
     }
+}
+// copy b of a wave's contiguous share of CHUNKS chunks: chunks 4b .. 4b + 3, or as many as there are
+template <int CHUNKS>
+__device__ __forceinline__ void dma_copy(int b, const uint8_t* gsrc_wave, uint32_t lane_off, uint32_t lds_wave) {
+    gsrc_wave += b * 4096;
+    lds_wave += b * 4096;
+    if (b < CHUNKS / 4) dma_chunks<0, 4>(gsrc_wave, lane_off, lds_wave);
+    else                dma_chunks<0, CHUNKS % 4 ? CHUNKS % 4 : 4>(gsrc_wave, lane_off, lds_wave);
 }
 
 template <int N> using Count = std::integral_constant<int, N>;

@@ -85,15 +85,18 @@ void attn_fp8_kernel(AttnArgs a) {
         for (int g = 0; g < P; ++g) st.b[g] = list.block(P == 1 ? step : min(P * step + g, count - 1));
         return st;
     };
-    // chunk c of the wave's share of the step's blocks
-    auto stage_chunk = [&](int buf, const uint8_t* head, const Step& st, int c) FPS_INLINE {
-        const int g = c / CPT;
-        dma_chunk_of(c % CPT, head + (size_t)st.b[g].blk * BLOCK_BYTES + wave_s * (CPT * 1024), lane * 16,
-                     lds_base + buf * STEP_BYTES + g * BLOCK_BYTES + wave_s * (CPT * 1024));
+    // copy c of the wave's share of the step's blocks, up to four chunks at once: one chunk a pipeline step takes 0.5 to 1 %
+    // longer (narrow items in two groups, one workgroup a CU, 28.5 against 27.4 us)
+    constexpr int COPIES = P * ((CPT + 3) / 4);
+    auto stage_copy = [&](int buf, const uint8_t* head, const Step& st, int c) FPS_INLINE {
+        const int g = c / (COPIES / P);
+        const uint8_t* const src = head + (size_t)st.b[g].blk * BLOCK_BYTES + wave_s * (CPT * 1024);
+        const uint32_t dst = lds_base + buf * STEP_BYTES + g * BLOCK_BYTES + wave_s * (CPT * 1024);
+        dma_copy<CPT>(c % (COPIES / P), src, lane * 16, dst);
     };
     auto stage = [&](int buf, const uint8_t* head, const Step& st) FPS_INLINE {
 #pragma unroll
-        for (int c = 0; c < P * CPT; ++c) stage_chunk(buf, head, st, c);
+        for (int c = 0; c < COPIES; ++c) stage_copy(buf, head, st, c);
     };
     auto lds_block = [&](int buf) FPS_INLINE { return lds + kg * GROUP_BYTES + buf * STEP_BYTES; };
     auto landed = []() FPS_INLINE { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
@@ -386,8 +389,10 @@ void attn_fp8_kernel(AttnArgs a) {
             float sc_next[P], sv_next[P];
             load_scales(nxt, sc_next, sv_next);
             cur = nxt;
-            const bool fetch_k = i + 2 < steps;
-            if (fetch_k) {
+            // TWO: past the walk's end the last K is copied once more, into the buffer that nobody reads again, while V(i+1) is
+            // on its way too.  With these copies under a condition, which cuts the steps below into pieces, 480p took 303, now
+            // 299 us, and 720p 3.85, now 3.78 ms.
+            if (i + 2 < steps) {
                 // Once in 64 blocks.  Said so only where the compiler put this code in the middle of the loop otherwise: per-channel
                 // V, tiles of several blocks; 2 heads of 9x20x34 tokens, tile (4,16,16), window 5x3x3, 79.7 -> 74.7 us, launches
                 // of 400 items and more 0.992.  Told the same, per-tile V takes up to 1 % more on 480p and 720p, small groups 1 %.
@@ -415,11 +420,16 @@ void attn_fp8_kernel(AttnArgs a) {
                     const int g = t / (2 * NB);
                     weights_half(t >> 1, t & 1, sc[g], cm[g], rs[g]);
                 }
-                constexpr int per = (P * CPT + 2 * NT + 1) / (2 * NT + 2);
+                // wave groups: a copy every other step (225 items of 128 rows in two groups, one chunk a step 30.7 us, a copy in each
+                // of the first two steps 31.0, in steps 2 and 4 30.7; of 120 items 28.8, 27.5 and 28.0)
+                constexpr int first = KS > 1 && COPIES == 2 && NT > 2 ? 2 : 0, left = 2 * NT + 2 - first;
+                constexpr int every = KS > 1 && 2 * COPIES <= left ? 2 : 1, per = (COPIES + left - 1) / left;
+                if (t >= first && (t - first) % every == 0) {
 #pragma unroll
-                for (int c = t * per; c < (t + 1) * per && c < P * CPT; ++c) {
-                    if (!TWO)         stage_chunk(v_buf(0), v_head, v_step, c);          // V(i-1) was consumed
-                    else if (fetch_k) stage_chunk(k_buf(0), k_head, nxt, c);             // K(i) was consumed last iteration
+                    for (int c = (t - first) / every * per; c < ((t - first) / every + 1) * per && c < COPIES; ++c) {
+                        if (TWO) stage_copy(k_buf(0), k_head, nxt, c);         // K(i) was consumed last iteration
+                        else     stage_copy(v_buf(0), v_head, v_step, c);      // V(i-1) was consumed
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -458,11 +468,11 @@ void attn_fp8_kernel(AttnArgs a) {
                 pv_mfma(op[k % 3], k);
 #pragma unroll
                 for (int t = k * HPS; t < (k + 1) * HPS && t < 2 * NT; ++t) max_of_half(mx, t);
-                constexpr int per = (P * CPT + STEPS - 1) / STEPS;
+                constexpr int per = (COPIES + STEPS - 1) / STEPS;
 #pragma unroll
-                for (int c = k * per; c < (k + 1) * per && c < P * CPT; ++c) {
-                    if (TWO)          stage_chunk(v_buf(1), v_head, v_step, c);          // V(i-1) was consumed last iteration
-                    else if (fetch_k) stage_chunk(k_buf(0), k_head, nxt, c);             // K(i+1) was consumed
+                for (int c = k * per; c < (k + 1) * per && c < COPIES; ++c) {
+                    if (TWO) stage_copy(v_buf(1), v_head, v_step, c);          // V(i-1) was consumed last iteration
+                    else if (i + 2 < steps) stage_copy(k_buf(0), k_head, nxt, c);        // K(i+1) was consumed
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
