@@ -203,11 +203,14 @@ struct QueryRows {
         raster0 = (((size_t)bh * G.T + (ut * G.Tt + box.o.t0)) * G.H + (uh * G.Th + box.o.h0)) * G.W +
                   (uw * G.Tw + box.o.w0);
     }
-    // output row of row r (0 <= r < rows)
-    __device__ __forceinline__ size_t out_row(const AttnArgs& a, int r) const {
+    // output row of the group's first token, and that of row r (0 <= r < rows) from there: within a head, 32 bits do
+    __device__ __forceinline__ size_t out_base(const AttnArgs& a) const {
+        return a.out_raster ? raster0 : tile_lin * a.g.TSP + slot_base;
+    }
+    __device__ __forceinline__ int out_offset(const AttnArgs& a, int r) const {
         const Offset d = real_token(box, k0 + r);
-        if (a.out_raster) return raster0 + ((d.t * a.g.H + d.h) * a.g.W + d.w);   // within a head: 32 bits do
-        return tile_lin * a.g.TSP + slot_base + ((d.t * a.g.Qh + d.h) * a.g.Qw + d.w);
+        const int rows_of = a.out_raster ? a.g.H : a.g.Qh, columns = a.out_raster ? a.g.W : a.g.Qw;
+        return (d.t * rows_of + d.h) * columns + d.w;
     }
 };
 
@@ -238,8 +241,10 @@ __device__ __forceinline__ bool any_real_row(const Geom& G, int cls, int jq, int
 // once in bf16, 16 a pass in fp32 (rows n < 16 are held by lanes 0..15 and 32..47) -- and writes whole rows
 // (of all channels 256 or 512 contiguous bytes).  The reads and stores of a pass are unrolled, so that one LDS round trip and
 // one address calculation do not wait for the other: 720p attention 3.84 -> 3.81 ms, dense BF16 12x37x70 x 16 heads
-// 8.27 -> 8.25 ms, one-wave workgroups of 32 tokens 12.4 -> 11.8 us.  The caller guarantees that no wave
-// still reads the LDS buffers.
+// 8.27 -> 8.25 ms, one-wave workgroups of 32 tokens 12.4 -> 11.8 us.  Where a row goes is worked out by the lanes that hold it
+// and fetched from them: worked out by every store for its rows, with two divisions and two branches each, it was half of
+// the epilogue's 800 instructions (480p 299.6 -> 299, 225 items of two groups 30.7 -> 30.6 us).  The caller guarantees that no
+// wave still reads the LDS buffers.
 constexpr int store_region_bytes(int nd) { return 32 * (nd * 64 + 16); }   // a wave's; 16 rows of fp32: less
 template <bool F32, int ND>
 __device__ __forceinline__ void store_rows_as(const AttnArgs& a, const QueryRows& q, int lane, const v16f (&acc)[ND],
@@ -249,7 +254,8 @@ __device__ __forceinline__ void store_rows_as(const AttnArgs& a, const QueryRows
     constexpr int kLanes = kRowBytes / 16, kRowsPerStore = 64 / kLanes;
     static_assert(kRows * kPitch <= store_region_bytes(ND), "the wave's region holds a pass");
     const int h = lane >> 5, n = lane & 31, chunk = lane % kLanes;
-    uint8_t* const out = reinterpret_cast<uint8_t*>(a.out) + c0 * kElem;
+    uint8_t* const out = reinterpret_cast<uint8_t*>(a.out) + q.out_base(a) * (128 * kElem) + c0 * kElem;
+    const int offset = n < q.rows ? q.out_offset(a, n) : -1;       // of row n; the rows of a store ask for theirs
 #pragma unroll
     for (int pass = 0; pass < 32 / kRows; ++pass) {
         if (!F32 || (n >> 4) == pass) {
@@ -275,15 +281,16 @@ __device__ __forceinline__ void store_rows_as(const AttnArgs& a, const QueryRows
         __builtin_amdgcn_wave_barrier();
         // not uint4: the compiler left an array of those in scratch memory in one kernel
         u32x4 val[kRows / kRowsPerStore];
-#pragma unroll
-        for (int i = 0; i < kRows / kRowsPerStore; ++i)
-            val[i] = *reinterpret_cast<const u32x4*>(wave_lds + (i * kRowsPerStore + lane / kLanes) * kPitch + chunk * 16);
+        int at[kRows / kRowsPerStore];
 #pragma unroll
         for (int i = 0; i < kRows / kRowsPerStore; ++i) {
-            const int row = pass * kRows + i * kRowsPerStore + lane / kLanes;
-            if (row < q.rows)
-                reinterpret_cast<u32x4*>(out + q.out_row(a, row) * (128 * kElem))[chunk] = val[i];
+            const int row = i * kRowsPerStore + lane / kLanes;
+            at[i] = __builtin_amdgcn_ds_bpermute(4 * (pass * kRows + row), offset);
+            val[i] = *reinterpret_cast<const u32x4*>(wave_lds + row * kPitch + chunk * 16);
         }
+#pragma unroll
+        for (int i = 0; i < kRows / kRowsPerStore; ++i)
+            if (at[i] >= 0) reinterpret_cast<u32x4*>(out + (size_t)(uint32_t)at[i] * (128 * kElem))[chunk] = val[i];
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }

@@ -381,6 +381,7 @@ void attn_fp8_kernel(AttnArgs a) {
             const uint8_t* vcur = lds_block(v_buf(0));           // V(i)
             if (TWO) __syncthreads();    // every wave is past QK(i) and PV(i-1); staged blocks are visible
             v8i op[3];                   // MFMA operands on their way from LDS, two steps ahead
+            constexpr int PV0 = TWO ? 2 * NT : 0;                // place in the ring of PV's first
             op[0] = load_k(knxt, 0);
             op[1] = load_k(knxt, 1);
 #pragma unroll
@@ -413,6 +414,7 @@ void attn_fp8_kernel(AttnArgs a) {
             for (int t = 0; t < 2 * NT + 2; ++t) {
                 if (t >= 2) {
                     if (t < 2 * NT) op[t % 3] = load_k(knxt, t);       // operand of step t + 2
+                    else if (TWO)   op[t % 3] = load_v(vcur, t - 2 * NT);        // V(i) is there already: PV's first two
                     qk_mfma(op[(t - 2) % 3], t - 2);
                 }
                 if (t < 2) pv_accumulate_half(R - 1, t, w_owed);       // PV(i-1)'s last product
@@ -446,8 +448,10 @@ void attn_fp8_kernel(AttnArgs a) {
                 landed();
                 __syncthreads();         // every wave is past QK(i+1); V(i) is visible
             }
-            op[0] = load_v(vcur, 0);
-            op[1] = load_v(vcur, 1);
+            if (!TWO) {
+                op[0] = load_v(vcur, 0);
+                op[1] = load_v(vcur, 1);
+            }
             mask_blocks(n_cut);
             rescale(0);
 
@@ -458,14 +462,14 @@ void attn_fp8_kernel(AttnArgs a) {
             constexpr int STEPS = R * J, HPS = (2 * NT + STEPS - 1) / STEPS;
 #pragma unroll
             for (int k = 0; k < STEPS; ++k) {
-                if (k + 2 < STEPS) op[(k + 2) % 3] = load_v(vcur, k + 2);
+                if (k + 2 < STEPS) op[(PV0 + k + 2) % 3] = load_v(vcur, k + 2);
                 if (J == 2) {                              // before tq[..] is refilled
                     if (k >= 3) pv_accumulate_half((k - 3) >> 1, (k - 3) & 1, wg[((k - 3) >> 1) % P]);
                 } else if (k >= 2) {
                     pv_accumulate(k - 2, wg[(k - 2) % P]);
                 }
                 if (VCH && k > 0 && k % (4 * J) == 0) rescale(k / (4 * J));
-                pv_mfma(op[k % 3], k);
+                pv_mfma(op[(PV0 + k) % 3], k);
 #pragma unroll
                 for (int t = k * HPS; t < (k + 1) * HPS && t < 2 * NT; ++t) max_of_half(mx, t);
                 constexpr int per = (COPIES + STEPS - 1) / STEPS;
