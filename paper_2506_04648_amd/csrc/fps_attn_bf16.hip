@@ -49,7 +49,7 @@ void attn_bf16_kernel(AttnArgs a) {
     const int row_block = W == 4 || (SB == 4 && W == 2) ? (wave_s + kg + u) & (W - 1) : wave_s;
     const int qs = jq * W + row_block;
     QueryRows rows;
-    rows.init(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
+    rows.init<MB>(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
     zero_padding_rows(a, rows, ucls, lane);
     if (!any_real_row<SB, W, MB>(G, ucls, jq, KBG * SB)) return;
     const size_t tile0 = (size_t)bh * G.M;

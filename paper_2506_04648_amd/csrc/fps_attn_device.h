@@ -192,9 +192,10 @@ struct QueryRows {
     int slot_base;           // first tiled slot of the group within its tile
     size_t tile_lin;         // bh * M + u
     size_t raster0;          // raster token index of the group's first token
-    // sub-block qs of the tile; sbg: sub-blocks per group
+    // sub-block qs of the tile; sbg: sub-blocks per group.  GROUPS: a tile may have several
+    template <bool GROUPS>
     __device__ __forceinline__ void init(const Geom& G, int bh, int u, int cls, int ut, int uh, int uw, int qs, int sbg) {
-        group = qs / sbg;
+        group = GROUPS ? qs / sbg : 0;
         box = real_box(G, cls, group);
         k0 = 32 * (qs - group * sbg);
         rows = box.n - k0;
