@@ -192,10 +192,10 @@ struct QueryRows {
     int slot_base;           // first tiled slot of the group within its tile
     size_t tile_lin;         // bh * M + u
     size_t raster0;          // raster token index of the group's first token
-    // sub-block qs of the tile; sbg: sub-blocks per group.  GROUPS: a tile may have several
+    // sub-block qs of the tile; sbg: sub-blocks per group, QSP / 32.  GROUPS: a tile may have several
     template <bool GROUPS>
     __device__ __forceinline__ void init(const Geom& G, int bh, int u, int cls, int ut, int uh, int uw, int qs, int sbg) {
-        group = GROUPS ? qs / sbg : 0;
+        group = GROUPS ? quotient(qs, sbg, G.rc_sub_blocks) : 0;
         box = real_box(G, cls, group);
         k0 = 32 * (qs - group * sbg);
         rows = box.n - k0;
@@ -230,7 +230,7 @@ template <int SB, int W, bool MB>
 __device__ __forceinline__ bool any_real_row(const Geom& G, int cls, int jq, int sbg) {
     if (!MB && W >= SB) return true;                       // the block is the tile
     for (int w = 0; w < W; ++w) {
-        const int qs = jq * W + w, group = qs / sbg;
+        const int qs = jq * W + w, group = quotient(qs, sbg, G.rc_sub_blocks);
         if (real_tokens(G, cls, sub_tile_origin(G, group)) > 32 * (qs - group * sbg)) return true;
     }
     return false;

@@ -95,6 +95,8 @@ int check_shape(const fps_shape* s, Geom* g) {
     g->KBG = bs == 128 ? kbs : 1;
     g->rc_kbs = reciprocal(kbs); g->rc_ns = reciprocal(ns); g->rc_m = reciprocal((int)m);
     g->rc_layer = reciprocal(nH * nW); g->rc_row = reciprocal(nW);
+    g->rc_sub_layer = reciprocal(g->nsH * g->nsW); g->rc_sub_row = reciprocal(g->nsW);
+    g->rc_sub_blocks = reciprocal(g->QSP / 32);
     for (int nh = 0; nh < 8; ++nh) g->nh_classes[nh] = 0;
     for (int c = 0; c < 8; ++c) {
         const int n = ((c & 4) ? g->cutT : qt) * ((c & 2) ? g->cutH : qh) * ((c & 1) ? g->cutW : qw);

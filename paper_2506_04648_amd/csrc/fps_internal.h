@@ -52,7 +52,8 @@ struct Geom {
     // Bit c of nh_classes[nh - 1]: sub-tiles cut along the axes of c (4: T, 2: H, 1: W) have a key
     // block whose real tokens fill nh 16-key halves.
     uint8_t nh_classes[8];
-    uint32_t rc_kbs, rc_ns, rc_m, rc_layer, rc_row;   // reciprocals of KBS, NS, M, nH*nW, nW
+    uint32_t rc_kbs, rc_ns, rc_m, rc_layer, rc_row;   // reciprocals of KBS, NS, M, nH*nW, nW,
+    uint32_t rc_sub_layer, rc_sub_row, rc_sub_blocks; // nsH*nsW, nsW and QSP/32
 };
 
 // n / d for 0 <= n < 2^21, given inv_d = 1.0f / d correctly rounded.  Exact: (n + 1/2) / d is at
@@ -67,8 +68,8 @@ __host__ __device__ inline int div_by_recip(int n, float inv_d) {
 struct SubTile { int t0, h0, w0; };
 __host__ __device__ inline SubTile sub_tile_origin(const Geom& g, int s) {
     const int layer = g.nsH * g.nsW;
-    const int st = s / layer, srem = s - st * layer;
-    const int sh = srem / g.nsW, sw = srem - sh * g.nsW;
+    const int st = quotient(s, layer, g.rc_sub_layer), srem = s - st * layer;
+    const int sh = quotient(srem, g.nsW, g.rc_sub_row), sw = srem - sh * g.nsW;
     return SubTile{st * g.Qt, sh * g.Qh, sw * g.Qw};
 }
 
