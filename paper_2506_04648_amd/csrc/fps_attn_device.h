@@ -225,15 +225,53 @@ __device__ __forceinline__ void zero_padding_rows(const AttnArgs& a, const Query
         if (!sub_slot_is_token(a.g, cls, q.box.o, q.k0 + (i >> row_shift))) dst[i] = make_uint4(0, 0, 0, 0);
 }
 
-// Some wave of query block jq has a real row.
-template <int SB, int W, bool MB>
-__device__ __forceinline__ bool any_real_row(const Geom& G, int cls, int jq, int sbg) {
-    if (!MB && W >= SB) return true;                       // the block is the tile
-    for (int w = 0; w < W; ++w) {
-        const int qs = jq * W + w, group = quotient(qs, sbg, G.rc_sub_blocks);
-        if (real_tokens(G, cls, sub_tile_origin(G, group)) > 32 * (qs - group * sbg)) return true;
+// Which sub-blocks of a tile of class `cls` hold real tokens: of its scale groups et x eh x ew do, the last ones along an axis
+// with ct, ch, cw tokens.  sbg: sub-blocks per group.
+struct RealSubBlocks {
+    const Geom& g;
+    int sbg, et, eh, ew, ct, ch, cw;
+    __host__ __device__ RealSubBlocks(const Geom& g_, int cls, int sbg_) : g(g_), sbg(sbg_) {
+        const int lt = cls & 4 ? g.lastT : g.Tt, lh = cls & 2 ? g.lastH : g.Th, lw = cls & 1 ? g.lastW : g.Tw;
+        et = quotient_of(lt + g.Qt - 1, g.Qt); eh = quotient_of(lh + g.Qh - 1, g.Qh); ew = quotient_of(lw + g.Qw - 1, g.Qw);
+        ct = lt - (et - 1) * g.Qt; ch = lh - (eh - 1) * g.Qh; cw = lw - (ew - 1) * g.Qw;
     }
-    return false;
+    // n / d for 0 <= n < 2^20, exact: (n + 1/2) / d is at least 1/(2d) away from every integer
+    static __host__ __device__ int quotient_of(int n, int d) { return (int)(((float)n + 0.5f) / (float)d); }
+    // sub-blocks of a row of groups of `th` tokens a column, of a layer of groups of t planes
+    __host__ __device__ int row(int th) const { return (ew - 1) * ((th * g.Qw + 31) >> 5) + ((th * cw + 31) >> 5); }
+    __host__ __device__ int layer(int t) const { return (eh - 1) * row(t * g.Qh) + row(t * ch); }
+    __host__ __device__ int total() const { return (et - 1) * layer(g.Qt) + layer(ct); }
+    // the i-th of them, i < total()
+    __host__ __device__ int sub_block(int i) const {
+        const int full_layer = layer(g.Qt), st = et > 1 ? min_of(quotient_of(i, full_layer), et - 1) : 0;
+        i -= st * full_layer;
+        const int t = st < et - 1 ? g.Qt : ct, full_row = row(t * g.Qh);
+        const int sh = eh > 1 ? min_of(quotient_of(i, full_row), eh - 1) : 0;
+        i -= sh * full_row;
+        const int th = t * (sh < eh - 1 ? g.Qh : ch), full = (th * g.Qw + 31) >> 5;
+        const int sw = ew > 1 ? min_of(quotient_of(i, full), ew - 1) : 0;
+        return ((st * g.nsH + sh) * g.nsW + sw) * sbg + i - sw * full;
+    }
+};
+
+// The sub-block of query rows that a wave takes, the `of_item`-th of work item jq; -1: the tile has no more, -2: for no wave of
+// the item.  The items of a tile of several scale groups take its real sub-blocks one after the other where that saves an item:
+// in the order of all sub-blocks, tiles whose groups are cut or missing had items of few waves with rows, each of them a walk
+// (attention on 21x30x52 tokens x 24 heads, 64-token sub-tiles of (2,8,16) tiles, window 3x3x3, 1715 -> 1630 us, BF16 1870 ->
+// 1817; x 8 heads, 15 planes, 128-token sub-tiles 252 -> 246; 96-token ones of (2,12,16) tiles x 12 815 -> 767).  Elsewhere it
+// only costs the divisions (16-token sub-tiles of (2,4,8) tiles 696 -> 701, tiles of one group 281 -> 282), and as many sub-blocks
+// as an item has are needed for an item without rows.
+template <int SB, int W, bool MB>
+__device__ __forceinline__ int wave_sub_block(const Geom& G, int cls, int jq, int of_item, int sbg) {
+    const int i = jq * W + of_item;
+    if (!MB || G.NS == 1) return i;                        // the rows of the one group lie together
+    const bool cut = ((cls & 4) && G.lastT < G.Tt) || ((cls & 2) && G.lastH < G.Th) || ((cls & 1) && G.lastW < G.Tw);
+    if (!cut && ((G.QS + 31) >> 5) == sbg) return i;       // all of them are real
+    const RealSubBlocks real(G, cls, sbg);
+    const int total = __builtin_amdgcn_readfirstlane(real.total());
+    if (total > G.NS * sbg - W) return i;
+    if (i >= total) return jq * W >= total ? -2 : -1;
+    return __builtin_amdgcn_readfirstlane(real.sub_block(i));
 }
 
 // Epilogue: O = acc * inv (times the per-channel V scale if any), fp32 or bf16, tile or raster order; the ND blocks of 32

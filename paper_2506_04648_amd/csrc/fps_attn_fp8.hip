@@ -60,11 +60,18 @@ void attn_fp8_kernel(AttnArgs a) {
     // the wave's sub-block of query rows; rotated from tile to tile (and wave group to wave group) so that the idle
     // waves of cut tiles fall on different SIMDs
     const int row_block = W == 4 || (SB == 4 && W == 2) ? (wave_s + kg + u) & (W - 1) : wave_s;
-    const int qs = jq * W + row_block;
+    if (MB && !a.out_raster) {                             // all items of a tile clear the padding of its output
+        QueryRows slots;
+        slots.init<MB>(G, bh, u, ucls, ut, uh, uw, jq * W + row_block, KBG * SB);
+        zero_padding_rows(a, slots, ucls, lane);
+    }
+    const int taken = wave_sub_block<SB, W, MB>(G, ucls, jq, row_block, KBG * SB), qs = taken < 0 ? 0 : taken;
+    if (MB && taken == -2) return;
     QueryRows rows;
     rows.init<MB>(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
-    zero_padding_rows(a, rows, ucls, lane);
-    if (!any_real_row<SB, W, MB>(G, ucls, jq, KBG * SB)) return;
+    if (MB && taken < 0) rows.rows = 0;
+    if (!MB) zero_padding_rows(a, rows, ucls, lane);
+    if ((MB || W < SB) && NS == 1 && rows.box.n <= 32 * W * jq) return;        // no wave of the item has a row
     const size_t tile0 = (size_t)bh * G.M;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0]) + kg * GROUP_BYTES;
     KeyBox box;

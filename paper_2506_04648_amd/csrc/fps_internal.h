@@ -63,6 +63,8 @@ __host__ __device__ inline int div_by_recip(int n, float inv_d) {
     return (int)(((float)n + 0.5f) * inv_d);
 }
 
+__host__ __device__ inline int min_of(int a, int b) { return a < b ? a : b; }
+
 // In-tile coordinates of the first token of sub-tile s (decoded once per block: s is the same
 // for all slots of a block).
 struct SubTile { int t0, h0, w0; };

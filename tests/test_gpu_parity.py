@@ -169,6 +169,31 @@ def test_attention_with_quantisation_sub_tiles(prec, grid, tile, qtile):
         gu.assert_parity(st, f"{grid} {tile} {qtile} per-channel V")
 
 
+# tiles of several scale groups that the grid cuts, so that a work item takes sub-blocks of several of its groups
+REAL_ROW_CASES = [
+    ((3, 13, 20), (2, 8, 16), (1, 8, 8)),       # 64 tokens: one sub-block of two in the last column, its other group empty
+    ((3, 13, 20), (2, 8, 16), (1, 8, 16)),      # 128 tokens: one sub-block of four
+    ((2, 30, 30), (1, 12, 24), (1, 12, 8)),     # 96 tokens, items of three sub-blocks: two and one of three
+    ((5, 10, 30), (4, 8, 16), (2, 4, 4)),       # 32 tokens, items of four of 16 groups; cut along every axis
+    ((7, 9, 18), (6, 8, 16), (2, 4, 16)),       # 128 tokens, six groups: layers, rows and columns missing
+]
+
+
+@pytest.mark.parametrize("prec", [fps.PREC_FP8, fps.PREC_BF16])
+@pytest.mark.parametrize("grid,tile,qtile", REAL_ROW_CASES)
+def test_items_take_the_real_rows_of_cut_tiles(prec, grid, tile, qtile):
+    import torch
+    say("real rows", prec, grid, tile, qtile)
+    window = (3, 3, 3)
+    w = dataclasses.replace(synth.TINY, grid=grid, tile=tile, window=window, heads=2, n_outlier=3, config_id=29)
+    run = gu.GpuRun(w, qtile=qtile)
+    out = run.attn(prec)
+    for h in range(2):
+        gu.assert_parity(gu.compare_head(run, out, h, prec, window), f"{grid} {tile} {qtile} head {h}")
+    assert torch.all(out[0][:, run.pad_slots()] == 0)       # tile-ordered output: every padding slot is cleared
+    assert torch.equal(run.attn(prec, raster_out=True), fps.tile_unorder(run.shape, out))
+
+
 def test_quantize_special_values():
     """Ties of the exact quotient, e4m3-representable inputs, all-zero tiles, amax = 448."""
     import torch

@@ -1,6 +1,7 @@
 """CPU checks of host rules of the kernel sources, compiled here without a GPU: which attention launches
 split their keys or deal their items in turns, and division by a stored reciprocal."""
 import os
+import random
 import shutil
 import subprocess
 
@@ -529,3 +530,59 @@ def test_narrow_items_are_all_resident_at_once(routes):
             assert workgroups <= 64, (call, items, workgroups)
             narrow += 1
     assert narrow > 20
+
+
+REAL_PROGRAM = r"""
+#include "fps_attn_device.h"
+#include <cstdio>
+#include <vector>
+using namespace fps;
+int main() {
+    fps_shape s;
+    while (std::scanf("%d %d %d %d %d %d %d %d %d", &s.T, &s.H, &s.W, &s.Tt, &s.Th, &s.Tw, &s.Qt, &s.Qh, &s.Qw) == 9) {
+        s.B = s.heads = 1;
+        s.head_dim = 128;
+        Geom g;
+        if (check_shape(&s, &g) != FPS_OK) return 1;
+        const int sbg = g.QSP / 32;
+        long bad = 0, real = 0;
+        for (int cls = 0; cls < 8; ++cls) {
+            std::vector<int> want;                 // every sub-block with a token, by the definition
+            for (int qs = 0; qs < g.NS * sbg; ++qs)
+                if (real_tokens(g, cls, sub_tile_origin(g, qs / sbg)) > 32 * (qs % sbg)) want.push_back(qs);
+            const RealSubBlocks r(g, cls, sbg);
+            bad += r.total() != (int)want.size();
+            for (int i = 0; i < (int)want.size(); ++i) bad += r.sub_block(i) != want[i];
+            real += (long)want.size();
+        }
+        std::printf("%ld %ld\n", bad, real);
+    }
+}
+"""
+
+
+def test_real_sub_blocks_of_cut_tiles(tmp_path):
+    """The sub-blocks that hold tokens, in order, against their enumeration: groups of 1 to 300 tokens, one or many a tile, the
+    grid's last tiles cut along any of the axes."""
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    src, exe, lib = tmp_path / "real.hip", tmp_path / "real", os.path.join(ROOT, "paper_2506_04648_amd")
+    src.write_text(REAL_PROGRAM)
+    res = subprocess.run([HIPCC, "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                          "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(lib, "csrc"), str(src), "-o", str(exe),
+                          "-L" + lib, "-l:libfps.so", "-Wl,-rpath," + lib], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    rng = random.Random(5)
+    lines = ["1 1 1 1 1 1 1 1 1", "40 50 60 16 16 16 1 1 1"]          # one token; 4096 groups a tile
+    for _ in range(3000):
+        q = [rng.choice((1, 1, 2, 3, 4, 5, 7, 8, 16)) for _ in range(3)]
+        t = [x * rng.choice((1, 1, 2, 3, 5)) for x in q]
+        if q[0] * q[1] * q[2] <= 300 and t[0] * t[1] * t[2] <= 4096:
+            n = [x * rng.randint(1, 3) + rng.randint(0, x) for x in t]
+            lines.append(" ".join(map(str, n + t + q)))
+    out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.split("\n")
+    rows = [tuple(map(int, line.split())) for line in out if line]
+    assert len(rows) == len(lines) > 2000
+    wrong = [(line, row) for line, row in zip(lines, rows) if row[0]]
+    assert not wrong, wrong[:5]
+    assert sum(row[1] for row in rows) > 100000
