@@ -4,6 +4,8 @@
 
 namespace fps {
 
+template <int N> struct Number { static constexpr int value = N; };
+
 // Where a block of BS packed slots sits: its tile, the real box of its SUB-TILE and its first slot
 // within the sub-tile.  Computed once per workgroup (the divisions are by run-time values).
 struct BlockOrigin {
@@ -58,18 +60,29 @@ __device__ __forceinline__ uint32_t amax_of_pairs(uint32_t m2) {        // the l
     const uint32_t lo = m2 & 0xFFFFu, hi = m2 >> 16;
     return lo > hi ? lo : hi;
 }
-// max of m over a wave, and over a workgroup of WAVES waves (red: WAVES words of LDS); every thread gets it
+// the larger of a lane's m and that of lane ^ 16, lane ^ 32
+__device__ __forceinline__ uint32_t max_with_lane_16(uint32_t m) {
+    const auto r = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+    return r[0] > r[1] ? r[0] : r[1];
+}
+__device__ __forceinline__ uint32_t max_with_lane_32(uint32_t m) {
+    const auto r = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    return r[0] > r[1] ? r[0] : r[1];
+}
+// max of m over a wave, and over a workgroup of WAVES waves (red: WAVES words of LDS); every thread gets it.  Lanes exchange
+// through the vector unit: six trips through the LDS, one after the other, are 0.3 us of a small launch.
 __device__ __forceinline__ uint32_t wave_max(uint32_t m) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)m, off);
+    auto rotated = [&](auto n) {                            // that of the lane n further on, in its row of 16
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x120 + decltype(n)::value, 0xf, 0xf, false);
         m = o > m ? o : m;
-    }
-    return m;
+    };
+    rotated(Number<8>{}); rotated(Number<4>{}); rotated(Number<2>{}); rotated(Number<1>{});
+    return max_with_lane_32(max_with_lane_16(m));
 }
 template <int WAVES>
 __device__ __forceinline__ uint32_t workgroup_max(uint32_t m, uint32_t* red) {
     m = wave_max(m);
+    if (WAVES == 1) return m;
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     m = red[0];
