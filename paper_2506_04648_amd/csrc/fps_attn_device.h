@@ -437,6 +437,16 @@ struct KeyBox {
     }
 };
 
+// G.nh_classes as one word: a byte of it at an index known on the device only is a vector load of the arguments, which the
+// waves that have rows wait for at the walk's first barrier (450 items of two groups 30.5 -> 30.2 us, 120 27.6 -> 27.0).  In the
+// kernels of tiles of several blocks the word costs what it saves: 76 blocks of them 13.9 -> 14.1 us.
+__device__ __forceinline__ uint64_t packed_classes(const Geom& G) {
+    uint64_t w = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w |= (uint64_t)G.nh_classes[i] << (8 * i);
+    return w;
+}
+
 // n / d for n >= 0 of a lane and uniform d > 0, given rcp = 1.0f / d to an ulp or two: the estimate is exact
 // below 2^20; beyond it (`large`, uniform) the loops settle it.  The walk waits for these divisions where a list begins:
 // with the loops always there, and groups divided off tiles that are one, calls of few items were 3 to 11 % slower

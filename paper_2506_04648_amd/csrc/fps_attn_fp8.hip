@@ -128,8 +128,9 @@ void attn_fp8_kernel(AttnArgs a) {
 
     if (rows.rows <= 0) {
         // no real row: this wave only copies its share of the K and V blocks, barrier for barrier
+        const uint64_t all_classes = MB ? 0 : packed_classes(G);
         for (int nh = 2 * SB; nh >= 1; --nh) {
-            const uint32_t classes = G.nh_classes[nh - 1] & box.classes;
+            const uint32_t classes = (MB ? G.nh_classes[nh - 1] : (uint32_t)(all_classes >> (8 * (nh - 1)))) & box.classes;
             if (!classes) continue;
             List list(G, box, nh, classes, kg);
             const int count = blocks_of_group(list.total());
