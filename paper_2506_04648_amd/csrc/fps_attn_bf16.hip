@@ -58,7 +58,8 @@ void attn_bf16_kernel(AttnArgs a) {
     rows.init<MB>(G, bh, u, ucls, ut, uh, uw, qs, KBG * SB);
     if (MB && taken < 0) rows.rows = 0;
     if (!MB) zero_padding_rows(a, rows, ucls, lane);
-    if ((MB || W < SB) && NS == 1 && rows.box.n <= 32 * W * jq) return;        // no wave of the item has a row
+    // no wave of the item has a row
+    if ((MB || W < SB) && (W == 1 ? rows.rows <= 0 : NS == 1 && rows.box.n <= 32 * W * jq)) return;
     const size_t tile0 = (size_t)bh * G.M;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(&lds[0]) + kg * GROUP_BYTES;
     KeyBox box;

@@ -176,6 +176,8 @@ REAL_ROW_CASES = [
     ((2, 30, 30), (1, 12, 24), (1, 12, 8)),     # 96 tokens, items of three sub-blocks: two and one of three
     ((5, 10, 30), (4, 8, 16), (2, 4, 4)),       # 32 tokens, items of four of 16 groups; cut along every axis
     ((7, 9, 18), (6, 8, 16), (2, 4, 16)),       # 128 tokens, six groups: layers, rows and columns missing
+    ((10, 9, 12), (2, 8, 16), (1, 8, 16)),      # few items, of one sub-block each: groups of 96 and 12 tokens
+    ((4, 9, 18), (1, 4, 12), (1, 4, 4)),        # 16 tokens, items of one sub-block: one whole, one cut and one empty
 ]
 
 
