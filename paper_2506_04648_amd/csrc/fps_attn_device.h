@@ -362,8 +362,8 @@ __device__ __forceinline__ void dma_chunks(const void* gsrc, uint32_t lane_off, 
         ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32));
     lds_wave_base = __builtin_amdgcn_readfirstlane(lds_wave_base);
 #define FPS_DMA(more) asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" more : \
-                                   : "v"(lane_off), "s"(gsrc), "s"(lds_wave_base), "n"(1024 * FIRST), "n"(1024 * FIRST + 1024), \
-                                     "n"(2048), "n"(3072) : "memory", "m0")
+                                   : "v"(lane_off), "s"(gsrc), "s"(lds_wave_base), "n"(1024 * FIRST), "n"(1024 * (FIRST + 1)), \
+                                     "n"(1024 * (FIRST + 2)), "n"(1024 * (FIRST + 3)) : "memory", "m0")
 #define FPS_DMA_AT(offset) "\n\tglobal_load_lds_dwordx4 %0, %1 offset:%" #offset
     if constexpr (N == 1)      FPS_DMA("");
     else if constexpr (N == 2) FPS_DMA(FPS_DMA_AT(4));

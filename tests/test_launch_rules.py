@@ -2,6 +2,7 @@
 split their keys or deal their items in turns, and division by a stored reciprocal."""
 import os
 import random
+import re
 import shutil
 import subprocess
 
@@ -586,3 +587,43 @@ def test_real_sub_blocks_of_cut_tiles(tmp_path):
     wrong = [(line, row) for line, row in zip(lines, rows) if row[0]]
     assert not wrong, wrong[:5]
     assert sum(row[1] for row in rows) > 100000
+
+
+COPY_PROGRAM = r"""
+#include "fps_attn_device.h"
+namespace fps {
+template <int FIRST, int N>
+__global__ void copies(const uint8_t* p) {
+    __shared__ uint8_t lds[4096];
+    dma_chunks<FIRST, N>(p, 16 * threadIdx.x, (uint32_t)(uintptr_t)&lds[0]);
+}
+#define ONE(f, n) template __global__ void copies<f, n>(const uint8_t*);
+ONE(0, 1) ONE(0, 2) ONE(0, 3) ONE(0, 4) ONE(1, 1) ONE(1, 2) ONE(1, 3) ONE(2, 1) ONE(2, 2) ONE(3, 1)
+}
+"""
+
+
+def device_assembly(tmp_path, name, program):
+    """gfx950 assembly of each kernel of a program, by its mangled name."""
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    src, out = tmp_path / f"{name}.hip", tmp_path / f"{name}.s"
+    src.write_text(program)
+    res = subprocess.run([HIPCC, "--cuda-device-only", "--offload-arch=gfx950", "-O1", "-std=c++17", "-S",
+                          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                          "-I" + os.path.join(ROOT, "include"),
+                          "-I" + os.path.join(ROOT, "paper_2506_04648_amd", "csrc"), str(src), "-o", str(out)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    parts = re.split(r"^(_Z\w+):.*$", out.read_text(), flags=re.M)
+    return {kernel: body.split("s_endpgm")[0] for kernel, body in zip(parts[1::2], parts[2::2])}
+
+
+def test_copies_to_lds_take_consecutive_chunks(tmp_path):
+    """dma_chunks<FIRST, N>: 1 KB pieces FIRST .. FIRST + N - 1, whatever FIRST is."""
+    kernels = device_assembly(tmp_path, "copies", COPY_PROGRAM)
+    seen = {}
+    for kernel, body in kernels.items():
+        key = tuple(map(int, re.search(r"copiesILi(\d)ELi(\d)E", kernel).groups()))
+        seen[key] = [int(x, 0) for x in re.findall(r"global_load_lds_dwordx4 .*offset:(\w+)", body)]
+    assert seen == {(f, n): [1024 * (f + i) for i in range(n)] for f in range(4) for n in range(1, 5 - f)}
