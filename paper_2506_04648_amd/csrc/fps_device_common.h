@@ -69,8 +69,9 @@ __device__ __forceinline__ uint32_t max_with_lane_32(uint32_t m) {
     const auto r = __builtin_amdgcn_permlane32_swap(m, m, false, false);
     return r[0] > r[1] ? r[0] : r[1];
 }
-// max of m over a wave, and over a workgroup of WAVES waves (red: WAVES words of LDS); every thread gets it.  Lanes exchange
-// through the vector unit: six trips through the LDS, one after the other, are 0.3 us of a small launch.
+// max of m over a wave, and over a workgroup of WAVES waves (red: WAVES words of LDS); every thread gets it, and behind
+// workgroup_max what the workgroup has written to its LDS before.  Lanes exchange through the vector unit: six trips through the
+// LDS, one after the other, are 0.3 us of a small launch.
 __device__ __forceinline__ uint32_t wave_max(uint32_t m) {
     auto rotated = [&](auto n) {                            // that of the lane n further on, in its row of 16
         const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x120 + decltype(n)::value, 0xf, 0xf, false);
@@ -82,7 +83,6 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t m) {
 template <int WAVES>
 __device__ __forceinline__ uint32_t workgroup_max(uint32_t m, uint32_t* red) {
     m = wave_max(m);
-    if (WAVES == 1) return m;
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     m = red[0];

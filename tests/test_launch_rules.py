@@ -627,3 +627,29 @@ def test_copies_to_lds_take_consecutive_chunks(tmp_path):
         key = tuple(map(int, re.search(r"copiesILi(\d)ELi(\d)E", kernel).groups()))
         seen[key] = [int(x, 0) for x in re.findall(r"global_load_lds_dwordx4 .*offset:(\w+)", body)]
     assert seen == {(f, n): [1024 * (f + i) for i in range(n)] for f in range(4) for n in range(1, 5 - f)}
+
+
+MAX_PROGRAM = r"""
+#include "fps_device_common.h"
+namespace fps {
+// what a caller has written before is read across lanes behind the maximum
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void maximum(const uint32_t* x, uint32_t* out) {
+    __shared__ uint32_t red[WAVES], held[64 * WAVES];
+    const int i = threadIdx.x;
+    held[i] = x[i];
+    out[64 * WAVES + i] = workgroup_max<WAVES>(x[i], red);
+    out[i] = held[64 * WAVES - 1 - i];
+}
+template __global__ void maximum<1>(const uint32_t*, uint32_t*);
+template __global__ void maximum<2>(const uint32_t*, uint32_t*);
+template __global__ void maximum<4>(const uint32_t*, uint32_t*);
+}
+"""
+
+
+def test_the_maximum_of_a_workgroup_orders_its_lds(tmp_path):
+    """One barrier whatever the number of waves; of a workgroup that is a wave it is the compiler's `wave barrier`."""
+    kernels = device_assembly(tmp_path, "maximum", MAX_PROGRAM)
+    barriers = {k: body.count("s_barrier") + body.count("; wave barrier") for k, body in kernels.items() if "maximum" in k}
+    assert sorted(barriers.values()) == [1, 1, 1], barriers
