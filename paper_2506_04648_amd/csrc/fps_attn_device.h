@@ -259,20 +259,28 @@ struct RealSubBlocks {
 // in the order of all sub-blocks, tiles whose groups are cut or missing had items of few waves with rows, each of them a walk
 // (attention on 21x30x52 tokens x 24 heads, 64-token sub-tiles of (2,8,16) tiles, window 3x3x3, 1715 -> 1630 us, BF16 1870 ->
 // 1817; x 8 heads, 15 planes, 128-token sub-tiles 252 -> 246; 96-token ones of (2,12,16) tiles x 12 815 -> 767).  Elsewhere it
-// only costs the divisions (16-token sub-tiles of (2,4,8) tiles 696 -> 701, tiles of one group 281 -> 282), and as many sub-blocks
-// as an item has are needed for an item without rows.
-template <int SB, int W, bool MB>
-__device__ __forceinline__ int wave_sub_block(const Geom& G, int cls, int jq, int of_item, int sbg) {
+// only costs the divisions (tiles that are one item, 16-token sub-tiles of (2,4,8) and 64-token ones of (2,8,8) tiles, 17
+// calls, 0.5 %, up to 1.4; tiles of one group 281 -> 282), and as many sub-blocks as an item has are needed for an item without
+// rows.
+// uniform(x): x, the same in all lanes, as a scalar.
+template <int SB, int W, typename F>
+__host__ __device__ inline int item_sub_block(const Geom& G, int cls, int jq, int of_item, int sbg, F&& uniform) {
     const int i = jq * W + of_item;
-    if (!MB || G.NS == 1) return i;                        // the rows of the one group lie together
+    if (G.NS == 1) return i;                               // the rows of the one group lie together
     if (W == 1) return i;                                  // an item is a sub-block (36 of them 10.4 us, with the divisions 10.6)
+    if (2 * SB <= W && G.NS * sbg <= W) return i;          // the tile is one item
     const bool cut = ((cls & 4) && G.lastT < G.Tt) || ((cls & 2) && G.lastH < G.Th) || ((cls & 1) && G.lastW < G.Tw);
     if (!cut && ((G.QS + 31) >> 5) == sbg) return i;       // all of them are real
     const RealSubBlocks real(G, cls, sbg);
-    const int total = __builtin_amdgcn_readfirstlane(real.total());
+    const int total = uniform(real.total());
     if (total > G.NS * sbg - W) return i;
     if (i >= total) return jq * W >= total ? -2 : -1;
-    return __builtin_amdgcn_readfirstlane(real.sub_block(i));
+    return uniform(real.sub_block(i));
+}
+template <int SB, int W, bool MB>
+__device__ __forceinline__ int wave_sub_block(const Geom& G, int cls, int jq, int of_item, int sbg) {
+    if (!MB) return jq * W + of_item;
+    return item_sub_block<SB, W>(G, cls, jq, of_item, sbg, [](int x) FPS_INLINE { return __builtin_amdgcn_readfirstlane(x); });
 }
 
 // Epilogue: O = acc * inv (times the per-channel V scale if any), fp32 or bf16, tile or raster order; the ND blocks of 32

@@ -589,6 +589,107 @@ def test_real_sub_blocks_of_cut_tiles(tmp_path):
     assert sum(row[1] for row in rows) > 100000
 
 
+ITEM_PROGRAM = r"""
+#include "fps_attn_device.h"
+#include <cstdio>
+#include <vector>
+using namespace fps;
+typedef int (*Taken)(const Geom&, int cls, int jq, int of_item, int sbg);
+static long calls;                                 // sums of a wave that had to find the order
+template <int SB, int W> int taken(const Geom& g, int cls, int jq, int of_item, int sbg) {
+    return item_sub_block<SB, W>(g, cls, jq, of_item, sbg, [](int x) { ++calls; return x; });
+}
+template <int SB> Taken of_waves(int W) { return W == 1 ? taken<SB, 1> : W == 2 ? taken<SB, 2> : W == 3 ? taken<SB, 3> : taken<SB, 4>; }
+int main() {
+    fps_shape s;
+    int of_rows;                                   // waves of an item; 0: as many as each launch of such a shape may have
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d", &s.T, &s.H, &s.W, &s.Tt, &s.Th, &s.Tw, &s.Qt, &s.Qh, &s.Qw, &of_rows) == 10) {
+        s.B = s.heads = 1;
+        s.head_dim = 128;
+        Geom g;
+        if (check_shape(&s, &g) != FPS_OK) return 1;
+        const int sbg = g.QSP / 32, all = g.NS * sbg, sb = g.BS == 128 ? 4 : g.KBS;
+        long wrong = 0, reordered = 0, without = 0, left_out = 0, needless = 0;
+        for (int W : {1, 2, 3, 4}) {
+            if (of_rows ? W != of_rows : W != query_waves(g) && (g.BS != 128 || W == 3)) continue;
+            const Taken item = sb == 4 ? of_waves<4>(W) : sb == 3 ? of_waves<3>(W) : sb == 2 ? of_waves<2>(W) : of_waves<1>(W);
+            for (int u = 0; u < g.M; ++u) {
+                const int cls = (u / (g.nH * g.nW) == g.nT - 1) << 2 | (u / g.nW % g.nH == g.nH - 1) << 1 | (u % g.nW == g.nW - 1);
+                std::vector<int> times(all);       // that a sub-block is taken
+                calls = 0;
+                bool other = false, saved = false;
+                for (int jq = 0; jq < all / W; ++jq) {
+                    int gone = 0, rows = 0;
+                    for (int w = 0; w < W; ++w) {
+                        const int qs = item(g, cls, jq, w, sbg);
+                        wrong += qs < -2 || qs >= all;
+                        gone += qs == -2;
+                        without += qs == -1;
+                        other |= qs != jq * W + w;
+                        if (qs < 0) continue;
+                        ++times[qs];
+                        rows += real_tokens(g, cls, sub_tile_origin(g, qs / sbg)) > 32 * (qs % sbg);
+                    }
+                    wrong += gone != 0 && gone != W;               // the waves of an item leave together or not at all
+                    // the kernels find out by themselves where the rows are those of one group or of one wave
+                    wrong += g.NS > 1 && W > 1 && gone == 0 && rows == 0;
+                    left_out += gone == W;
+                    saved |= gone == W;
+                }
+                wrong += other && !saved;                          // another order has to save an item
+                for (int qs = 0; qs < all; ++qs) {
+                    const bool real = real_tokens(g, cls, sub_tile_origin(g, qs / sbg)) > 32 * (qs % sbg);
+                    wrong += real ? times[qs] != 1 : times[qs] > 1;
+                }
+                reordered += other;
+                if (all <= W) needless += calls;
+            }
+        }
+        std::printf("%ld %ld %ld %ld %ld\n", wrong, reordered, without, left_out, needless);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def items_of_tiles(tmp_path_factory):
+    """(grid, tile, sub-tile, waves of an item or 0) -> per shape: violations of what an item's waves take, and of all tiles those
+    whose sub-blocks are not taken in their order, waves without a sub-block, items left out, sums for tiles of one item."""
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("items")
+    src, exe, lib = d / "items.hip", d / "items", os.path.join(ROOT, "paper_2506_04648_amd")
+    src.write_text(ITEM_PROGRAM)
+    res = subprocess.run([HIPCC, "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17",
+                          "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(lib, "csrc"), str(src), "-o", str(exe),
+                          "-L" + lib, "-l:libfps.so", "-Wl,-rpath," + lib], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+
+    def run(shapes):
+        lines = [" ".join(map(str, (*grid, *tile, *(qtile or (0, 0, 0)), waves))) for grid, tile, qtile, waves in shapes]
+        out = subprocess.run([str(exe)], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.split("\n")
+        rows = [tuple(map(int, line.split())) for line in out if line]
+        assert len(rows) == len(lines)
+        return rows
+    return run
+
+
+def test_every_real_sub_block_is_taken_by_one_wave(items_of_tiles):
+    """Over all items of every tile of random shapes: each sub-block with a token once, one without at most once, no walked item
+    without rows, and none of the sums that find the order where a tile is one item and nothing can be saved."""
+    rng = random.Random(9)
+    shapes = [((4, 9, 18), (2, 4, 8), (1, 4, 4), 0), ((40, 50, 60), (16, 16, 16), (1, 1, 1), 0)]
+    for _ in range(3000):
+        q = [rng.choice((1, 1, 2, 3, 4, 5, 7, 8, 16)) for _ in range(3)]
+        t = [x * rng.choice((1, 1, 2, 3, 5)) for x in q]
+        if q[0] * q[1] * q[2] <= 300 and t[0] * t[1] * t[2] <= 4096:
+            shapes.append((tuple(x * rng.randint(1, 3) + rng.randint(0, x) for x in t), tuple(t), tuple(q), 0))
+    rows = items_of_tiles(shapes)
+    bad = [(shape, row) for shape, row in zip(shapes, rows) if row[0] or row[4]]
+    assert not bad, bad[:5]
+    assert sum(row[1] > 0 for row in rows) > 100 and sum(row[2] > 0 for row in rows) > 100 and sum(row[3] > 0 for row in rows) > 100
+
+
 COPY_PROGRAM = r"""
 #include "fps_attn_device.h"
 namespace fps {
