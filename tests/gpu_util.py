@@ -77,7 +77,7 @@ class GpuRun:
         return self.p16
 
     def attn(self, prec, window=None, out_dtype=None, visited=False, step=None, raster_out=False,
-             vscale=fps.VSCALE_TILE):
+             vscale=fps.VSCALE_TILE, out=None):
         torch = self.torch
         out_dtype = out_dtype or torch.float32
         vis = torch.zeros((self.g.M, self.g.M), dtype=torch.uint8, device="cuda:0") if visited else None
@@ -91,7 +91,7 @@ class GpuRun:
             (q, _), (k, _), (v, sv) = self.p16
             sq = sk = None
         window = self.w.window if window is None else window
-        out = fps.attn_fwd(self.shape, window, prec, q, k, v, sq, sk, sv, vscale=vscale,
+        out = fps.attn_fwd(self.shape, window, prec, q, k, v, sq, sk, sv, vscale=vscale, out=out,
                            out_dtype=out_dtype, visited=vis, step=step, raster_out=raster_out)
         torch.cuda.synchronize()
         return (out, vis) if visited else out

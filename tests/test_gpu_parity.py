@@ -169,15 +169,22 @@ def test_attention_with_quantisation_sub_tiles(prec, grid, tile, qtile):
         gu.assert_parity(st, f"{grid} {tile} {qtile} per-channel V")
 
 
-# tiles of several scale groups that the grid cuts, so that a work item takes sub-blocks of several of its groups
+# Tiles of several scale groups that the grid cuts.  A work item takes the real sub-blocks of several of its tile's groups one
+# after the other; in items of one sub-block (FP8: the cases so marked) the waves find out that theirs has no row.
 REAL_ROW_CASES = [
     ((3, 13, 20), (2, 8, 16), (1, 8, 8)),       # 64 tokens: one sub-block of two in the last column, its other group empty
-    ((3, 13, 20), (2, 8, 16), (1, 8, 16)),      # 128 tokens: one sub-block of four
+    ((3, 13, 20), (2, 8, 16), (1, 8, 16)),      # 128 tokens: one sub-block of four (FP8: one-wave items)
     ((2, 30, 30), (1, 12, 24), (1, 12, 8)),     # 96 tokens, items of three sub-blocks: two and one of three
     ((5, 10, 30), (4, 8, 16), (2, 4, 4)),       # 32 tokens, items of four of 16 groups; cut along every axis
     ((7, 9, 18), (6, 8, 16), (2, 4, 16)),       # 128 tokens, six groups: layers, rows and columns missing
-    ((10, 9, 12), (2, 8, 16), (1, 8, 16)),      # few items, of one sub-block each: groups of 96 and 12 tokens
-    ((4, 9, 18), (1, 4, 12), (1, 4, 4)),        # 16 tokens, items of one sub-block: one whole, one cut and one empty
+    ((10, 9, 12), (2, 8, 16), (1, 8, 16)),      # few items: groups of 96 and 12 tokens (FP8: one-wave items)
+    ((4, 9, 18), (1, 4, 12), (1, 4, 4)),        # 16 tokens, one-wave items in both: one whole, one cut and one empty
+    ((2, 12, 16), (2, 8, 16), (1, 8, 16)),      # 128 tokens, items of four sub-blocks: two of each group
+    ((5, 5, 16), (5, 8, 16), (1, 8, 16)),       # the same of five groups, three of each, a wave without a sub-block
+    ((3, 13, 68), (2, 8, 16), (1, 8, 16)),      # the same, items of two sub-blocks in two wave groups
+    ((3, 13, 180), (2, 8, 16), (1, 8, 16)),     # and of four in two
+    ((3, 13, 20), (2, 12, 16), (1, 12, 8)),     # 96 tokens, items of four sub-blocks
+    ((4, 13, 12), (3, 8, 8), (1, 8, 8)),        # 64 tokens, items of two
 ]
 
 
@@ -194,6 +201,12 @@ def test_items_take_the_real_rows_of_cut_tiles(prec, grid, tile, qtile):
         gu.assert_parity(gu.compare_head(run, out, h, prec, window), f"{grid} {tile} {qtile} head {h}")
     assert torch.all(out[0][:, run.pad_slots()] == 0)       # tile-ordered output: every padding slot is cleared
     assert torch.equal(run.attn(prec, raster_out=True), fps.tile_unorder(run.shape, out))
+    # every row of the output is written, whoever takes it: into a buffer of NaN, the same again
+    for dtype in (torch.float32, torch.bfloat16):
+        for raster in (False, True):
+            want = (fps.tile_unorder(run.shape, out) if raster else out).to(dtype)
+            got = run.attn(prec, raster_out=raster, out=torch.full_like(want, math.nan))
+            assert torch.equal(got, want), (dtype, raster, int(torch.isnan(got).sum()))
 
 
 def test_quantize_special_values():

@@ -513,6 +513,29 @@ def test_the_gpu_cases_reach_the_kernels_that_they_name(routes):
     assert {(True, 4, 4, 1), (True, 4, 4, 2), (True, 4, 4, 3), (True, 2, 2, 1), (True, 2, 4, 2), (True, 1, 1, 1)} <= seen
 
 
+def test_the_cut_tiles_of_the_gpu_cases_are_taken_as_they_say(routes, items_of_tiles):
+    """Kernels (sub-blocks of a key block, waves, wave groups, several groups a tile) of the GPU test's cut tiles, FP8 and BF16; all
+    cases with more than one wave an item have tiles whose sub-blocks are not taken in their order, and all of them together every
+    kind of wave: with rows, without, and of items left out."""
+    from tests import test_gpu_parity as t
+    window, cases = (3, 3, 3), t.REAL_ROW_CASES
+    kernels, without, reordered = [], 0, set()
+    for grid, tile, qtile in cases:
+        row = routes([(2, grid, tile, qtile, window, False, fp8) for fp8 in (True, False)])
+        kernels.append(tuple(r[:4] for r in row))
+        for r in row:
+            wrong, other, no_block, left_out, needless = items_of_tiles([(grid, tile, qtile, r[1])])[0]
+            assert wrong == needless == 0 and (other > 0) == (left_out > 0) == (r[1] > 1), (grid, tile, qtile, r)
+            without += no_block > 0
+            if other:
+                reordered.add(r[:3])
+    one = ((4, 1, 4, 1), (4, 2, 2, 1))
+    assert kernels == [((2, 4, 1, 1),) * 2, one, ((3, 3, 1, 1),) * 2, ((1, 4, 1, 1),) * 2, ((4, 2, 4, 1), (4, 2, 2, 1)), one,
+                       ((1, 1, 1, 1),) * 2, ((4, 4, 1, 1),) * 2, ((4, 4, 1, 1),) * 2, ((4, 2, 2, 1),) * 2,
+                       ((4, 4, 2, 1), (4, 4, 2, 1)), ((3, 4, 1, 1),) * 2, ((2, 2, 1, 1),) * 2]
+    assert without >= 10 and len(reordered) == 9, (without, reordered)
+
+
 def test_narrow_items_are_all_resident_at_once(routes):
     """Up to 256 items of 128 rows are whole workgroups one on a CU; cut in two they must fit two on a CU, 64 on an XCD, and the
     plan's sections, each rounded up, may take more.  Three calls that did, and the items of others."""
