@@ -34,7 +34,6 @@
 #include "fps_attn_plan.h"
 
 #include <stddef.h>
-#include <type_traits>
 
 namespace fps {
 
@@ -399,8 +398,6 @@ __device__ __forceinline__ void dma_copy(int b, const uint8_t* gsrc_wave, uint32
     if (b < CHUNKS / 4) dma_chunks<0, 4>(gsrc_wave, lane_off, lds_wave);
     else                dma_chunks<0, CHUNKS % 4 ? CHUNKS % 4 : 4>(gsrc_wave, lane_off, lds_wave);
 }
-
-template <int N> using Count = std::integral_constant<int, N>;
 
 // The kernels walk the key-tile box once per number NH = 2*SB .. 1 of 16-key halves: first every key
 // block that fills its slots, then those of fewer halves, each with a main loop compiled for its NH

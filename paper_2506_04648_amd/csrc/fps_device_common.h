@@ -4,8 +4,6 @@
 
 namespace fps {
 
-template <int N> struct Number { static constexpr int value = N; };
-
 // Where a block of BS packed slots sits: its tile, the real box of its SUB-TILE and its first slot
 // within the sub-tile.  Computed once per workgroup (the divisions are by run-time values).
 struct BlockOrigin {
@@ -77,7 +75,7 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t m) {
         const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x120 + decltype(n)::value, 0xf, 0xf, false);
         m = o > m ? o : m;
     };
-    rotated(Number<8>{}); rotated(Number<4>{}); rotated(Number<2>{}); rotated(Number<1>{});
+    rotated(Count<8>{}); rotated(Count<4>{}); rotated(Count<2>{}); rotated(Count<1>{});
     return max_with_lane_32(max_with_lane_16(m));
 }
 template <int WAVES>

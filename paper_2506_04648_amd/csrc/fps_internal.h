@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdarg.h>
+#include <type_traits>
 #include "fps.h"
 
 namespace fps {
@@ -10,6 +11,8 @@ namespace fps {
 constexpr int kHeadDim = 128;
 constexpr int kMaxTileTokens = 32768;                // largest supported tile
 constexpr int kMaxScoreSlots = 4096;                 // largest tile the score debug call accepts
+
+template <int N> using Count = std::integral_constant<int, N>;   // a number as an argument's type
 
 // n / d for any 32-bit n, given m = reciprocal(d): four scalar instructions instead of the ~35 of a division by a
 // run-time value.  m = floor((2^32 - 1) / d) is at least 2^32/d - 1, so n m / 2^32 falls short of n / d by less than

@@ -20,7 +20,6 @@
 //       exact power-of-two scaling per scale group (see pack_bf16_kernel)
 #include "fps_device_common.h"
 
-#include <type_traits>
 
 namespace fps {
 
@@ -110,8 +109,8 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
                 __builtin_amdgcn_sched_barrier(0);         // the next loads follow these stores
             }
         };
-        if (role == FPS_ROLE_Q) copy(std::integral_constant<int, 1>{});
-        else                    copy(std::integral_constant<int, 2>{});
+        if (role == FPS_ROLE_Q) copy(Count<1>{});
+        else                    copy(Count<2>{});
         return;
     }
     uint4 v[U];
