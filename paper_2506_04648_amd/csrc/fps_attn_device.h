@@ -231,24 +231,22 @@ struct RealSubBlocks {
     int sbg, et, eh, ew, ct, ch, cw;
     __host__ __device__ RealSubBlocks(const Geom& g_, int cls, int sbg_) : g(g_), sbg(sbg_) {
         const int lt = cls & 4 ? g.lastT : g.Tt, lh = cls & 2 ? g.lastH : g.Th, lw = cls & 1 ? g.lastW : g.Tw;
-        et = quotient_of(lt + g.Qt - 1, g.Qt); eh = quotient_of(lh + g.Qh - 1, g.Qh); ew = quotient_of(lw + g.Qw - 1, g.Qw);
+        et = divide_small(lt + g.Qt - 1, g.Qt); eh = divide_small(lh + g.Qh - 1, g.Qh); ew = divide_small(lw + g.Qw - 1, g.Qw);
         ct = lt - (et - 1) * g.Qt; ch = lh - (eh - 1) * g.Qh; cw = lw - (ew - 1) * g.Qw;
     }
-    // n / d for 0 <= n < 2^20, exact: (n + 1/2) / d is at least 1/(2d) away from every integer
-    static __host__ __device__ int quotient_of(int n, int d) { return (int)(((float)n + 0.5f) / (float)d); }
     // sub-blocks of a row of groups of `th` tokens a column, of a layer of groups of t planes
     __host__ __device__ int row(int th) const { return (ew - 1) * ((th * g.Qw + 31) >> 5) + ((th * cw + 31) >> 5); }
     __host__ __device__ int layer(int t) const { return (eh - 1) * row(t * g.Qh) + row(t * ch); }
     __host__ __device__ int total() const { return (et - 1) * layer(g.Qt) + layer(ct); }
     // the i-th of them, i < total()
     __host__ __device__ int sub_block(int i) const {
-        const int full_layer = layer(g.Qt), st = et > 1 ? min_of(quotient_of(i, full_layer), et - 1) : 0;
+        const int full_layer = layer(g.Qt), st = et > 1 ? min_of(divide_small(i, full_layer), et - 1) : 0;
         i -= st * full_layer;
         const int t = st < et - 1 ? g.Qt : ct, full_row = row(t * g.Qh);
-        const int sh = eh > 1 ? min_of(quotient_of(i, full_row), eh - 1) : 0;
+        const int sh = eh > 1 ? min_of(divide_small(i, full_row), eh - 1) : 0;
         i -= sh * full_row;
         const int th = t * (sh < eh - 1 ? g.Qh : ch), full = (th * g.Qw + 31) >> 5;
-        const int sw = ew > 1 ? min_of(quotient_of(i, full), ew - 1) : 0;
+        const int sw = ew > 1 ? min_of(divide_small(i, full), ew - 1) : 0;
         return ((st * g.nsH + sh) * g.nsW + sw) * sbg + i - sw * full;
     }
 };

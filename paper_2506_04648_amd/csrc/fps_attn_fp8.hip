@@ -483,7 +483,10 @@ void attn_fp8_kernel(AttnArgs a) {
 #pragma unroll
                 for (int c = k * per; c < (k + 1) * per && c < COPIES; ++c) {
                     if (TWO) stage_copy(v_buf(1), v_head, v_step, c);          // V(i-1) was consumed last iteration
-                    else if (i + 2 < steps) stage_copy(k_buf(0), k_head, nxt, c);        // K(i+1) was consumed
+                    // K(i+1) was consumed.  With one buffer each the condition stays: without it 30 calls of tiles of 32 and 48 tokens
+                    // and of one-wave items took 1.005 of the time (0.98 to 1.04; tile (3,4,4), window 3x5x7, 760 -> 750 us, window
+                    // 3x3x3 257 -> 260, 63 items of 128 rows 26.2 -> 27.3)
+                    else if (i + 2 < steps) stage_copy(k_buf(0), k_head, nxt, c);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
