@@ -483,7 +483,7 @@ struct KeyBlock { int blk, group, n; };
 // index kg (mod KS).  A lane works out the place of one block, so that a wave has the next 64 in two vector
 // registers and a block costs its loop two v_readlane: stepping through the box axis by axis took 25 to 40 scalar
 // instructions a block, and the FP8 kernel of tiles of several 128-slot blocks spilled 228 scalar registers to lanes
-// of vector registers (now 20, with per-channel V 29; of several small groups a tile 0 to 59, with the keys split 22 to 50).
+// of vector registers (now 20, with per-channel V 29; of several small groups a tile 0 to 59, with the keys split 10 to 36).
 // Attention: 64-token sub-tiles of (2,8,16) tiles, 21x30x52 tokens x 24 heads, 1920 -> 1859 us, one-block tiles of that grid
 // x 12 heads 315 -> 311.
 template <bool MB, int KS>
